@@ -78,6 +78,18 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
 }
 
+// 16-byte buffer store with a scalar offset.  The store reads its four data registers over several cycles, and a vector
+// instruction that overwrites one of them right behind it can reach the register first.  The compiler separates the two
+// by wait states only when the store has NO scalar offset register; with one it assumes that none are needed, which is
+// not so on gfx950: k_src_times_block stored `v_add_u32 v0, ...` of the following instruction in the place of the first
+// of four ranks, in the last four of every sixteen lanes, about once in a thousand tiles.  The data are therefore
+// kept live past two wait states.
+template <int AUX>
+__device__ __forceinline__ void store_b128(u32x4 x, rsrc_t r, uint32_t voff, uint32_t soff) {
+  __builtin_amdgcn_raw_buffer_store_b128(x, r, voff, soff, AUX);
+  asm volatile("s_nop 1" ::"v"(x) : "memory");
+}
+
 // Direct global-to-LDS load of one 1 KiB operand fragment: lane i's 16 bytes land at
 // lds_dst_wave_base + i (checked on the hardware); the LDS address must be uniform over the wave.
 #define LDS_AS __attribute__((address_space(3)))
@@ -822,7 +834,7 @@ template <> struct WAcc<false> {
     return f32x4{__uint_as_float(w.x), __uint_as_float(w.y), __uint_as_float(w.z), __uint_as_float(w.w)};
   }
   static __device__ __forceinline__ void store(f32x4 x, rsrc_t r, uint32_t voff, uint32_t soff) {
-    __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(x.x), __float_as_uint(x.y), __float_as_uint(x.z), __float_as_uint(x.w)}, r, voff, soff, STREAM);
+    store_b128<STREAM>(u32x4{__float_as_uint(x.x), __float_as_uint(x.y), __float_as_uint(x.z), __float_as_uint(x.w)}, r, voff, soff);
   }
 };
 template <> struct WAcc<true> {
@@ -1235,15 +1247,15 @@ __global__ __launch_bounds__(64 * NW) void k_proj_up_dma(DevCtx d, const ProjTil
             step[e] = ua.nesterov ? fmaf(ua.mu, bn[e], x[e]) : bn[e];
           }
           u32x4 bs = {__float_as_uint(bn.x), __float_as_uint(bn.y), __float_as_uint(bn.z), __float_as_uint(bn.w)};
-          __builtin_amdgcn_raw_buffer_store_b128(bs, rmom, voff, w_soff(a, j), STREAM);
+          store_b128<STREAM>(bs, rmom, voff, w_soff(a, j));
         }
         o.x = __float_as_uint(fmaf(-lr, step.x, wf.x));
         o.y = __float_as_uint(fmaf(-lr, step.y, wf.y));
         o.z = __float_as_uint(fmaf(-lr, step.z, wf.z));
         o.w = __float_as_uint(fmaf(-lr, step.w, wf.w));
-        __builtin_amdgcn_raw_buffer_store_b128(o, ranchor, voff, w_soff(a, j), STREAM);
+        store_b128<STREAM>(o, ranchor, voff, w_soff(a, j));
       }
-      __builtin_amdgcn_raw_buffer_store_b128(o, rw_out, voff, w_soff(a, j), STREAM);
+      store_b128<STREAM>(o, rw_out, voff, w_soff(a, j));
     }
   }
 }
@@ -1528,7 +1540,7 @@ __device__ __forceinline__ void store_y_tile(const DevCtx& d, const MatDev& m, c
         const int row = row0 + 8 * j;                       // first of the eight rows this access covers
         const uint32_t soff = row < p ? (uint32_t)row * yrow_bytes : (uint32_t)p * yrow_bytes;
         u32x4 o = {__float_as_uint(x.x), __float_as_uint(x.y), __float_as_uint(x.z), __float_as_uint(x.w)};
-        __builtin_amdgcn_raw_buffer_store_b128(o, ry, voff, soff, 0);
+        store_b128<0>(o, ry, voff, soff);
       }
     }
 }
