@@ -30,7 +30,7 @@
  *   - Stream capture: the compute calls enqueue kernels only (no allocation, no memset, no
  *     host synchronisation), so they can be recorded into a HIP graph.  The step count and
  *     the bias corrections 1 - beta^t derived from it live in device memory and are advanced
- *     by a kernel at the head of every local step, so a recorded lordo_local_step counts its
+ *     by the last kernel of every local step, so a recorded lordo_local_step counts its
  *     REPLAYS: replaying it k times is k local steps (on whatever the gradient buffers hold
  *     at each replay).  The learning rate and the gradient scale travel as kernel arguments:
  *     a replay uses the values of the recording.  lordo_get_step returns the number of

@@ -25,6 +25,8 @@ enum ExtTable : int32_t {       // per-call tables of caller pointers, one entry
   EXT_NONE = -1, EXT_W = 0, EXT_G = 1, EXT_SRC = 2, EXT_OMEGA = 3, EXT_DIN = 4, EXT_DOUT = 5, EXT_COUNT = 6
 };
 
+struct StepDev;                 // step count and bias corrections in device memory (below)
+
 // Per-matrix record in device memory.  Offsets are in BYTES from the arena base unless noted.
 struct MatDev {
   int32_t p, q, r, pp, qp, rp;
@@ -131,6 +133,7 @@ struct UpArgs {
   int32_t outer, nesterov, has_mom;
   float mu;
   int32_t w_bf16;         // the caller's W is bf16 storage (target W only; the plain update)
+  StepDev* advance;       // last launch of a local step: its first workgroup moves the step count on and does nothing else (else null)
 };
 hipError_t launch_proj_up(const DevCtx& d, const ProjTile* tiles, int ntiles, bool vec, const uint16_t* b_hi,
                           const uint16_t* b_lo, const UpArgs& ua, hipStream_t s);
@@ -143,19 +146,48 @@ hipError_t launch_gemm32(const DevCtx& d, const GemmDesc* descs, const GemmTile*
 hipError_t launch_gemm_reduce(const DevCtx& d, const GemmDesc* descs, int ndescs, hipStream_t s);
 // elementwise.hip
 // Elements at flat position >= grp_start[i] are the sum of grp_nsplit[i] split-K slices of g.
-// Step count and the bias corrections 1 - beta^t derived from it (Sec. 2), kept in device memory and advanced by a
-// kernel at the head of every local step: a local step recorded into a HIP graph then counts its REPLAYS, which
-// values passed as kernel arguments could not.
+// Step count and the bias corrections 1 - beta^t derived from it (Sec. 2), kept in device memory and advanced on the
+// device by every local step: a local step recorded into a HIP graph then counts its REPLAYS, which values passed as
+// kernel arguments could not.  The corrections of the NEXT step are kept ready beside those of the current one: the
+// moment update of a step in flight reads them, and the step's last launch, whose kernels do not, advances the count in
+// one extra workgroup.  A one-thread kernel at the head of the step did this before, 4.9 us in front of everything else.
 struct StepDev {
   int64_t t;
   float inv_c1, inv_c2;   // 1 / (1 - beta1^t), 1 / (1 - beta2^t); 1 without bias correction
   float c1, c2;
+  float next_inv_c1, next_inv_c2;   // the same for t + 1
+  int32_t bias_correction, pad_;
+  double beta1, beta2;
 };
-hipError_t launch_step(StepDev* sd, double beta1, double beta2, int bias_correction, int64_t set_to, hipStream_t s);
+hipError_t launch_step_set(StepDev* sd, double beta1, double beta2, int bias_correction, int64_t t, hipStream_t s);
+
+// beta^t by squaring (relative error of the order of t 2^-53, far below the fp32 the corrections are rounded to)
+__device__ inline double int_pow(double b, int64_t t) {
+  double r = 1.0;
+  for (; t > 0; t >>= 1) {
+    if (t & 1) r *= b;
+    b *= b;
+  }
+  return r;
+}
+// t <- t and every value derived from it, formed in double and rounded to fp32 once (one thread)
+__device__ inline void step_write(StepDev* sd, int64_t t) {
+  double c1 = 1.0, c2 = 1.0, n1 = 1.0, n2 = 1.0;
+  if (sd->bias_correction) {
+    const double p1 = int_pow(sd->beta1, t), p2 = int_pow(sd->beta2, t);
+    if (t > 0) { c1 = 1.0 - p1; c2 = 1.0 - p2; }
+    n1 = 1.0 - p1 * sd->beta1;
+    n2 = 1.0 - p2 * sd->beta2;
+  }
+  sd->t = t;
+  sd->c1 = (float)c1; sd->c2 = (float)c2;
+  sd->inv_c1 = (float)(1.0 / c1); sd->inv_c2 = (float)(1.0 / c2);
+  sd->next_inv_c1 = (float)(1.0 / n1); sd->next_inv_c2 = (float)(1.0 / n2);
+}
 
 struct AdamArgs {
   float b1, omb1, b2, omb2, eps;
-  const StepDev* step;    // bias corrections of the current step
+  const StepDev* step;    // bias corrections: those of the step in flight are its `next` fields
   int32_t grp_nsplit[4];
   int64_t grp_start[4];
   int64_t split_stride;

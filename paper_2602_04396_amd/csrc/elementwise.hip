@@ -11,7 +11,7 @@
 //   k_jacobi_svd      singular vectors of the Cholesky factor of the r x r Ritz matrix (Rayleigh-Ritz step: basis ordered as in Sec. 2's SVD projection)
 //   k_frob2_chunks / k_frob2_sum / k_stable_rank   squared Frobenius norm of the refresh source and its stable rank (Sec. 5.1)
 //   k_rot_pre / k_rot_post, k_mssv   elementwise parts of the moment rotation (Alg. 1 rotation lines); similarity diagnostic (Sec. 5.1)
-//   k_step            step count and bias corrections 1 - beta^t (Sec. 2) in device memory, advanced once per local step
+//   k_step_set        step count and bias corrections 1 - beta^t (Sec. 2) in device memory
 //   k_gauss_block     Gaussian start blocks of the range finder and of the random initial projection (Alg. 1 Require)
 //   k_gram_diag_part / k_gram_diag_sum   exact diagonal of the Gram matrices of CholeskyQR
 //   k_bf16_to_f32 / k_f32_to_bf16   a bf16-stored residual through the fp32 state interface
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(256) void k_adam4(const float* __restrict__ glow, f
   if (!COLSUM && !live) return;
   const int64_t base = a.first + qidx * 4;
   float dsum = 0.f;
-  const float inv_c1 = a.step->inv_c1, inv_c2 = a.step->inv_c2;      // uniform: scalar loads
+  const float inv_c1 = a.step->next_inv_c1, inv_c2 = a.step->next_inv_c2;      // uniform: scalar loads
   if (live) {
   f32x4n g = __builtin_nontemporal_load(reinterpret_cast<const f32x4n*>(glow + base));
   int nsplit = a.grp_nsplit[0];
@@ -167,22 +167,14 @@ hipError_t launch_adam(const float* glow, float* u, float* v, uint16_t* n_hi, ui
 }
 
 // ---------------------------------------------------------------------------------------
-// step counter on the device: t <- t + 1 (set_to < 0) or t <- set_to, and the bias corrections of the new t
-// (Sec. 2: u_hat = u / (1 - beta1^t), v_hat = v / (1 - beta2^t)), formed in double and rounded to fp32 once
+// step counter on the device: set to a count (at the start, and after lordo_set_step); a local step moves it on itself
 // ---------------------------------------------------------------------------------------
-__global__ void k_step(StepDev* sd, double beta1, double beta2, int bias_correction, int64_t set_to) {
-  const int64_t t = set_to < 0 ? sd->t + 1 : set_to;
-  double c1 = 1.0, c2 = 1.0;
-  if (bias_correction && t > 0) {
-    c1 = 1.0 - pow(beta1, (double)t);
-    c2 = 1.0 - pow(beta2, (double)t);
-  }
-  sd->t = t;
-  sd->c1 = (float)c1; sd->c2 = (float)c2;
-  sd->inv_c1 = (float)(1.0 / c1); sd->inv_c2 = (float)(1.0 / c2);
+__global__ void k_step_set(StepDev* sd, double beta1, double beta2, int bias_correction, int64_t t) {
+  sd->beta1 = beta1; sd->beta2 = beta2; sd->bias_correction = bias_correction;
+  step_write(sd, t);
 }
-hipError_t launch_step(StepDev* sd, double beta1, double beta2, int bias_correction, int64_t set_to, hipStream_t s) {
-  hipLaunchKernelGGL(k_step, dim3(1), dim3(1), 0, s, sd, beta1, beta2, bias_correction, set_to);
+hipError_t launch_step_set(StepDev* sd, double beta1, double beta2, int bias_correction, int64_t t, hipStream_t s) {
+  hipLaunchKernelGGL(k_step_set, dim3(1), dim3(1), 0, s, sd, beta1, beta2, bias_correction, t);
   return hipGetLastError();
 }
 

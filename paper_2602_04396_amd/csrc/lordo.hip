@@ -961,7 +961,7 @@ struct lordo_ctx {
   bool step_dirty = false;       // the step count on the device has to be set from `t` (after lordo_set_step)
   int sync_step(hipStream_t s) {
     if (!step_dirty) return LORDO_OK;
-    if (launch_step(at<StepDev>(plan.step), hp.beta1, hp.beta2, hp.bias_correction, t, s) != hipSuccess) return LORDO_EHIP;
+    if (launch_step_set(at<StepDev>(plan.step), hp.beta1, hp.beta2, hp.bias_correction, t, s) != hipSuccess) return LORDO_EHIP;
     step_dirty = false;
     return LORDO_OK;
   }
@@ -1100,7 +1100,7 @@ static int init_context(lordo_ctx** out, const lordo_shape* shapes, int32_t n, c
   INITCHK(launch_fill_zero(c->at<void>(P.flag), 256, s));
   INITCHK(launch_fill_zero(c->at<void>(P.ext), ((sizeof(void*) * EXT_COUNT * EXT_SLOTS * n + 255) & ~size_t(255)), s));
   INITCHK(launch_fill_zero(c->at<void>(P.glow), (int64_t)(P.down_tiles - P.glow), s));
-  INITCHK(launch_step(c->at<StepDev>(P.step), hp->beta1, hp->beta2, hp->bias_correction, 0, s));      // t = 0
+  INITCHK(launch_step_set(c->at<StepDev>(P.step), hp->beta1, hp->beta2, hp->bias_correction, 0, s));      // t = 0
   c->step_dirty = false;
   INITCHK(launch_identity_q(c->dev, s));
   INITCHK(launch_pack_q(c->dev, 0, n, s));
@@ -1173,7 +1173,7 @@ int lordo_local_step(lordo_ctx* c, void* const* W, const void* const* G, double 
   AdamArgs a;
   a.b1 = (float)c->hp.beta1; a.omb1 = (float)(1.0 - c->hp.beta1);
   a.b2 = (float)c->hp.beta2; a.omb2 = (float)(1.0 - c->hp.beta2);
-  a.step = c->at<StepDev>(P.step);        // the step count and 1 - beta^t live on the device: advanced below, by a kernel
+  a.step = c->at<StepDev>(P.step);        // the step count and 1 - beta^t live on the device: advanced by the last launch of the step
   a.eps = (float)c->hp.eps;
   for (int i = 0; i < 4; ++i) { a.grp_nsplit[i] = P.grp_nsplit[i]; a.grp_start[i] = P.grp_start[i]; }
   a.split_stride = P.lr_total;
@@ -1205,7 +1205,6 @@ int lordo_local_step(lordo_ctx* c, void* const* W, const void* const* G, double 
   // every argument and state check has passed: from here on kernels are enqueued
   int rc = c->sync_step(s);
   if (rc != LORDO_OK) return rc;
-  HIPCHK(launch_step(c->at<StepDev>(P.step), c->hp.beta1, c->hp.beta2, c->hp.bias_correction, -1, s));      // t <- t + 1
   c->step_dirty = true;         // until the whole step is enqueued: a call that fails below leaves the device count to be set back from `t`
   rc = c->set_ext(EXT_W, W, s);
   if (rc != LORDO_OK) return rc;
@@ -1283,6 +1282,8 @@ int lordo_local_step(lordo_ctx* c, void* const* W, const void* const* G, double 
   } else {
     ua.coef_acc = (float)-lr; ua.coef_g = 0.f; ua.colscale = 0; ua.colpart = nullptr;
   }
+  StepDev* const advance = c->at<StepDev>(P.step);             // t <- t + 1, with the last launch
+  if (!P.any_tr) ua.advance = advance;
   if (!P.up_wide_h.empty() && w_vec && !(qhm_full && g_f32))   // (the wide kernel's gradient-term epilogue reads bf16 gradients)
     HIPCHK(launch_proj_up_wide(c->dev, c->at<ProjTile>(P.up_wide_tiles), (int)P.up_wide_h.size(), c->at<uint16_t>(P.n_hi),
                                c->at<uint16_t>(P.n_lo), ua, s));
@@ -1296,6 +1297,7 @@ int lordo_local_step(lordo_ctx* c, void* const* W, const void* const* G, double 
     DevCtx du = c->dev;
     du.mats = c->at<MatDev>(P.mats_up);
     UpArgs ut = ua;
+    ut.advance = advance;
     if (qhm_full) ut.colscale = 2;      // the scale of the gradient term runs over the rows of W: the columns of the low-rank state
     HIPCHK(launch_proj_up(du, c->at<ProjTile>(P.up_tr_tiles), (int)P.up_tr_h.size(), w_vec_tr, reinterpret_cast<uint16_t*>(c->dev.arena),
                           reinterpret_cast<uint16_t*>(c->dev.arena + P.tr_plane_gap), ut, s));

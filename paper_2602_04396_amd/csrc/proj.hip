@@ -231,7 +231,7 @@ struct FusedAdam {
   uint16_t* n_hi;
   uint16_t* n_lo;
   float b1, omb1, b2, omb2, eps;
-  const StepDev* step;        // bias corrections of the current step (device memory: a replayed graph sees its own step)
+  const StepDev* step;        // bias corrections in device memory (a replayed graph sees its own step): the `next` fields
   float qw, qg;               // update bracket (qw u_hat + qg g) / den: 1, 0 for "No QHM"; omega, 1 - omega for low-rank QHM
   // 256-rank tiles only (the 128-rank kernel has no registers to spare):
   uint16_t* g_hi;             // error feedback: the bf16 hi / lo operand planes of g for the residual update (else null)
@@ -244,7 +244,7 @@ template <bool EXTRA>
 __device__ __forceinline__ float adam4(const FusedAdam& f, int64_t at, f32x4 g, f32x4 uu, f32x4 vv) {
   float nn[4];
   float dsum = 0.f;
-  const float inv_c1 = f.step->inv_c1, inv_c2 = f.step->inv_c2;
+  const float inv_c1 = f.step->next_inv_c1, inv_c2 = f.step->next_inv_c2;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const float un = fmaf(f.b1, uu[e], f.omb1 * g[e]);
@@ -823,6 +823,18 @@ hipError_t launch_proj_down(const DevCtx& d, const ProjTile* tiles, int ntiles, 
   return hipErrorInvalidValue;
 }
 
+// The last launch of a local step has one workgroup more than tiles, the first, which moves the step count on.  The test
+// stands behind the loads of a kernel's tables: with the store in front of them the compiler gives up reading the tables
+// through the scalar unit, and buffer descriptors in vector registers cost a loop per access.
+__device__ __forceinline__ int tile_index(const StepDev* advance) {
+  return advance != nullptr && blockIdx.x > 0 ? (int)blockIdx.x - 1 : (int)blockIdx.x;
+}
+__device__ __forceinline__ bool advance_step(StepDev* advance) {
+  if (advance == nullptr || blockIdx.x != 0) return false;
+  if (threadIdx.x == 0) step_write(advance, advance->t + 1);
+  return true;
+}
+
 // Element type of the caller's weights: fp32, or bf16 storage (the update is formed in fp32 from the stored value and
 // rounded to nearest-even once when it is written back).  Four consecutive columns of a row per lane.
 template <bool WBF> struct WAcc;
@@ -859,9 +871,10 @@ template <> struct WAcc<true> {
 // ---------------------------------------------------------------------------------------
 template <bool WBF>       // WBF: the caller's W is bf16 (never together with to_mom: the momentum is fp32)
 __global__ __launch_bounds__(256) void k_proj_up(DevCtx d, const ProjTile* __restrict__ tiles,
-                                                 const uint16_t* __restrict__ n_hi, const uint16_t* __restrict__ n_lo, float lr, int to_mom) {
+                                                 const uint16_t* __restrict__ n_hi, const uint16_t* __restrict__ n_lo, float lr, int to_mom,
+                                                 StepDev* advance) {
   constexpr uint32_t ES = WBF ? 2u : 4u;
-  const ProjTile t = tiles[blockIdx.x];
+  const ProjTile t = tiles[tile_index(advance)];
   if (t.mat < 0 || mat_skipped(d, t.mat)) return;
   const MatDev m = d.mats[t.mat];
   const GAS u32x4* qa_hi = TO_GLOBAL(const u32x4, d.arena + m.qa_hi);
@@ -874,7 +887,6 @@ __global__ __launch_bounds__(256) void k_proj_up(DevCtx d, const ProjTile* __res
   const int mb0 = t.m0 / 32 + 2 * (wave & 1);
   const int nb0 = t.n0 / 32 + 2 * (wave >> 1);
   const int mblocks = m.pp / 32, nblocks = m.qp / 32;
-  if (mb0 >= mblocks || nb0 >= nblocks) return;
   const int p = m.p, q = m.q;
   const int64_t rgroups = m.rp / 8;
 
@@ -894,6 +906,7 @@ __global__ __launch_bounds__(256) void k_proj_up(DevCtx d, const ProjTile* __res
     const int row = 32 * (mb0 + a) + 8 * (v >> 2) + (v & 3);
     return row < p ? (uint32_t)row * row_bytes + (uint32_t)(32 * (nb0 + b)) * ES : (uint32_t)p * row_bytes;
   };
+  if (advance_step(advance) || mb0 >= mblocks || nb0 >= nblocks) return;
   float wv[2][2][16];
 #pragma unroll
   for (int a = 0; a < 2; ++a)
@@ -1011,7 +1024,7 @@ __global__ __launch_bounds__(64 * NW) void k_proj_up_dma(DevCtx d, const ProjTil
   const float lr = -ua.coef_acc;
   constexpr int AM = NW == 4 ? 2 : 1;                      // row blocks per wave
   constexpr int WM = 4 / AM;                               // wave rows
-  const ProjTile t = tiles[blockIdx.x];
+  const ProjTile t = tiles[tile_index(ua.advance)];
   if (t.mat < 0 || mat_skipped(d, t.mat)) return;
   const MatDev m = d.mats[t.mat];
   const GAS u32x4* qa_hi = TO_GLOBAL(const u32x4, d.arena + m.qa_hi);
@@ -1075,6 +1088,8 @@ __global__ __launch_bounds__(64 * NW) void k_proj_up_dma(DevCtx d, const ProjTil
     return row < p ? (uint32_t)row * row_bytes + (uint32_t)(32 * nb0) * WES : (uint32_t)p * row_bytes;
   };
 
+  const rsrc_t rg = WITH_G ? make_rsrc(ext_ptr(d, EXT_G, t.mat), (uint32_t)p * ((uint32_t)q * (ua.g_is_f32 ? 4u : 2u))) : rw;
+  if (advance_step(ua.advance)) return;
   issue_chunk(0, 0);
   typename WA::raw_t wv[AM][8];
 #pragma unroll
@@ -1085,7 +1100,6 @@ __global__ __launch_bounds__(64 * NW) void k_proj_up_dma(DevCtx d, const ProjTil
   // requested here, with the W tile, so that it arrives during the contraction
   const uint32_t ges = ua.g_is_f32 ? 4u : 2u;
   const uint32_t grow_bytes = (uint32_t)q * ges;
-  const rsrc_t rg = WITH_G ? make_rsrc(ext_ptr(d, EXT_G, t.mat), (uint32_t)p * grow_bytes) : rw;
   auto g_soff = [&](int a, int j) -> uint32_t {
     const int row = 32 * (mb0 + a) + 4 * j;
     return row < p ? (uint32_t)row * grow_bytes + (uint32_t)(32 * nb0) * ges : (uint32_t)p * grow_bytes;
@@ -1280,7 +1294,7 @@ __global__ __launch_bounds__(256) void k_proj_up_wide(DevCtx d, const ProjTile* 
   typedef WAcc<WBF> WA;
   constexpr uint32_t WES = WA::ES;
   const float lr = -ua.coef_acc;
-  const ProjTile t = tiles[blockIdx.x];
+  const ProjTile t = tiles[tile_index(ua.advance)];
   if (t.mat < 0) return;
   const MatDev m = d.mats[t.mat];
   const GAS u32x4* qa_hi = TO_GLOBAL(const u32x4, d.arena + m.qa_hi);
@@ -1342,6 +1356,8 @@ __global__ __launch_bounds__(256) void k_proj_up_wide(DevCtx d, const ProjTile* 
     return row < p ? (uint32_t)row * row_bytes + (uint32_t)(32 * nb0) * WES : (uint32_t)p * row_bytes;
   };
 
+  const rsrc_t rg = WITH_G ? make_rsrc(ext_ptr(d, EXT_G, t.mat), (uint32_t)p * ((uint32_t)q * 2u)) : rw;
+  if (advance_step(ua.advance)) return;
   issue_chunk(0, 0);
   issue_chunk(1, 1);
 
@@ -1404,7 +1420,6 @@ __global__ __launch_bounds__(256) void k_proj_up_wide(DevCtx d, const ProjTile* 
   // gradient term: coef_g * G * c_j on the lane's four columns, c_j the column scale of the full-rank QHM update
   // (1 / mean over the rank of sqrt(v_hat) + eps, from the sums the Adam kernel left) or 1
   const uint32_t grow_bytes = (uint32_t)q * 2u;
-  const rsrc_t rg = WITH_G ? make_rsrc(ext_ptr(d, EXT_G, t.mat), (uint32_t)p * grow_bytes) : rw;
   const uint32_t gvoff = lcol < q ? (uint32_t)rr * grow_bytes + (uint32_t)c16 * 8u : OOB;
   auto g_soff = [&](int a, int j) -> uint32_t {
     const int row = 32 * (mb0 + a) + 4 * j;
@@ -1503,7 +1518,7 @@ hipError_t launch_proj_up_wide(const DevCtx& d, const ProjTile* tiles, int ntile
   const bool with_g = ua.coef_g != 0.f || ua.target_err == 1;
   if (with_g && ua.g_is_f32) return hipErrorInvalidValue;      // the gradient-term epilogue here reads bf16 gradients
   if (ua.target_err == 2 || ua.outer || ua.colscale == 2) return hipErrorInvalidValue;
-#define LORDO_WIDE(WBFV, GV) hipLaunchKernelGGL((k_proj_up_wide<WBFV, GV>), dim3(ntiles), dim3(256), LDS_BYTES, s, d, tiles, b_hi, b_lo, ua)
+#define LORDO_WIDE(WBFV, GV) hipLaunchKernelGGL((k_proj_up_wide<WBFV, GV>), dim3(ntiles + (ua.advance ? 1 : 0)), dim3(256), LDS_BYTES, s, d, tiles, b_hi, b_lo, ua)
   if (ua.w_bf16) { if (with_g) LORDO_WIDE(true, true); else LORDO_WIDE(true, false); }
   else { if (with_g) LORDO_WIDE(false, true); else LORDO_WIDE(false, false); }
 #undef LORDO_WIDE
@@ -1661,7 +1676,7 @@ hipError_t launch_src_times_block(const DevCtx& d, const ProjTile* tiles, int nt
 hipError_t launch_proj_up(const DevCtx& d, const ProjTile* tiles, int ntiles, bool vec, const uint16_t* b_hi,
                           const uint16_t* b_lo, const UpArgs& ua, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
-  dim3 grid(ntiles), block(256);
+  dim3 grid(ntiles + (ua.advance ? 1 : 0)), block(256);
   const bool with_g = ua.coef_g != 0.f || ua.target_err == 1;
   const bool w_bf16 = ua.w_bf16 != 0 && ua.target_err != 2;     // element type of the target as the caller of this launch states it (the momentum is always fp32)
   if (ua.outer) {
@@ -1675,8 +1690,8 @@ hipError_t launch_proj_up(const DevCtx& d, const ProjTile* tiles, int ntiles, bo
     if (w_bf16) hipLaunchKernelGGL((k_proj_up_dma<4, 0, true>), grid, block, 0, s, d, tiles, b_hi, b_lo, ua);
     else hipLaunchKernelGGL((k_proj_up_dma<4, 0, false>), grid, block, 0, s, d, tiles, b_hi, b_lo, ua);
   } else {
-    if (w_bf16) hipLaunchKernelGGL(k_proj_up<true>, grid, block, 0, s, d, tiles, b_hi, b_lo, -ua.coef_acc, 0);
-    else hipLaunchKernelGGL(k_proj_up<false>, grid, block, 0, s, d, tiles, b_hi, b_lo, -ua.coef_acc, ua.target_err == 2 ? 1 : 0);
+    if (w_bf16) hipLaunchKernelGGL(k_proj_up<true>, grid, block, 0, s, d, tiles, b_hi, b_lo, -ua.coef_acc, 0, ua.advance);
+    else hipLaunchKernelGGL(k_proj_up<false>, grid, block, 0, s, d, tiles, b_hi, b_lo, -ua.coef_acc, ua.target_err == 2 ? 1 : 0, ua.advance);
   }
   return hipGetLastError();
 }
