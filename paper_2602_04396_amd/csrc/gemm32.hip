@@ -333,7 +333,7 @@ __device__ __forceinline__ void gemm_loop_bf(f32x16 (&acc)[WB][WB], const Operan
 // is fetched into registers while the matrix cores work on the one in LDS.
 template <int WB>
 __global__ __launch_bounds__(256) void k_gemm32(DevCtx d, const GemmDesc* __restrict__ descs,
-                                                const GemmTile* __restrict__ tiles, int src_is_bf16, float alpha_mul) {
+                                                const GemmTile* __restrict__ tiles, int src_is_bf16, float alpha_mul, int sub_m, int sub_n) {
   constexpr int TM = 64 * WB, TN = 64 * WB;
   constexpr int PITCH = TM + 4;
   constexpr int NV = TM * TK / 4 / 256;
@@ -343,7 +343,9 @@ __global__ __launch_bounds__(256) void k_gemm32(DevCtx d, const GemmDesc* __rest
   const int M = g.M, N = g.N;
   const int kbeg = g.ksplit > 1 ? t.ks * g.klen : 0;
   int K = g.ksplit > 1 ? (kbeg + g.klen < g.K ? kbeg + g.klen : g.K) : g.K;           // end of this slice
-  const int m0 = t.tm * TM, n0 = t.tn * TN;
+  // a table entry covers sub_m x sub_n tiles of this kernel (1 x 1 but where the table was made for k_gemm_planes)
+  const int m0 = (t.tm * sub_m + (int)blockIdx.y) * TM, n0 = (t.tn * sub_n + (int)blockIdx.z) * TN;
+  if (sub_m + sub_n > 2 && (m0 >= M || n0 >= N)) return;
   if (g.tri && n0 + TN < K) K = n0 + TN;            // B is zero below this tile's last column
   const int a_bf16 = g.a_bf16 == 2 ? src_is_bf16 : g.a_bf16;
   float* C = reinterpret_cast<float*>(const_cast<char*>(resolve(d, g.C, g.mat)));
@@ -440,11 +442,218 @@ hipError_t launch_gemm_reduce(const DevCtx& d, const GemmDesc* descs, int ndescs
   return hipGetLastError();
 }
 
-hipError_t launch_gemm32(const DevCtx& d, const GemmDesc* descs, const GemmTile* tiles, int ntiles, int tile, int src_is_bf16,
-                         hipStream_t s, float alpha_mul) {
+// ---------------------------------------------------------------------------------------
+// C = A B with a tall fp32 A (rows contiguous in k) and a narrow B that many row tiles share: the products of an fp32
+// refresh source with a block (Sec. 2 range finder), the application of the factor's inverse, X M^T, and the moment
+// rotation.  Same arithmetic, in the same order, as the split loop above (three bf16 terms per operand, six products),
+// so the results are the same bits; what differs is who does the splitting.  There, every 128 x 128 tile splits its
+// share of B again and stages one K step at a time between two barriers; here B is split once (k_pack_planes) into
+// operand fragments that travel from global memory to LDS without passing through registers, and A is split once per
+// 128 rows x up to 256 columns.  Four waves in a 2 x 2 grid, wave tile 64 rows x 32 NBW columns; two LDS buffers of
+// one k-step of 16 each (72 KiB at NBW = 4: two workgroups per compute unit, one splits while the other multiplies);
+// the rows of A are requested two to three k-steps ahead of their use.  The loads into LDS are issued from inline
+// assembly with explicit waits: in an even step they precede the loads of A, so "at most the four loads of A
+// outstanding" implies that they have landed.
+// Measured (24 x 7 matrices, 2048 x 2048 .. 5632, r = 256, fp32 source): Y = Src B 4.6 -> 3.65 ms (3.8 TFLOP of bf16
+// products; the matrix cores are busy 67 % of the time at a clock that this load holds at 1.56 GHz: power is the bound,
+// and skipping the zero half of M^T gains nothing), X M^T 0.51 -> 0.37 ms, rotation product 0.51 -> 0.43 ms; 28 matrices of
+// 4096 .. 11008 at r = 512: X M^T 0.48 -> 0.35 and 0.58 -> 0.43 ms; 72 matrices of 768 .. 3072 at r = 128, fp32 source:
+// three products 0.29 -> 0.25 ms each.
+// ---------------------------------------------------------------------------------------
+#define LDS_AS __attribute__((address_space(3)))
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+// lane i's 16 bytes land at lds_dst_wave_base + 16 i; M0 carries the LDS address, one wait state before its use
+__device__ __forceinline__ void plane_to_lds(const GAS u32x4* src, u32x4* lds_dst_wave_base) {
+  const uint32_t lds_addr = (uint32_t)(uintptr_t)(LDS_AS void*)lds_dst_wave_base;
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_addr) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+#define WAIT_VM_BARRIER(N) asm volatile("s_waitcnt vmcnt(" #N ") lgkmcnt(0)\n\ts_barrier" ::: "memory")
+
+template <int NBW, bool ONCE>      // ONCE: A is read by one column tile only (streaming loads)
+__global__ __launch_bounds__(256, 2) void k_gemm_planes(DevCtx d, const GemmDesc* __restrict__ descs, const GemmTile* __restrict__ tiles,
+                                                        int ntiles, const uint16_t* __restrict__ p0, const uint16_t* __restrict__ p1,
+                                                        const uint16_t* __restrict__ p2) {
+  constexpr int TN = 64 * NBW;
+  constexpr int ASLOTS = 12, BSLOTS = 6 * NBW, SLOTS = ASLOTS + BSLOTS;     // 1 KiB fragments of a k-step: three planes each
+  constexpr int BLOADS = (BSLOTS + 3) / 4;                                  // fragments of B a wave brings in per k-step
+  // Runs of sixteen consecutive tiles share an XCD and so its L2: sixteen row tiles read the same planes of B
+  // (workgroups go to the eight XCDs round-robin by index; whole runs keep uneven matrices spread over all of them).
+  const int b = (int)blockIdx.x;
+  const int tile = ((b >> 7) * 8 + (b & 7)) * 16 + ((b >> 3) & 15);
+  if (tile >= ntiles) return;
+  const GemmTile t = tiles[tile];
+  const GemmDesc g = descs[t.desc];
+  if (mat_skipped(d, g.mat)) return;
+  const int M = g.M, N = g.N, m0 = t.tm * 128, n0 = t.tn * TN;
+  const int kend = g.tri && n0 + TN < g.K ? n0 + TN : g.K;                   // (tri: B is zero below this tile's last column)
+  const int nsteps = (kend + 31) / 32 * 2;
+  const int64_t kgroups = pad32(g.K) / 8;
+  const int nblocks = (int)pad32(N) / 32;
+
+  extern __shared__ u32x4 lds_planes[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave & 1, wn = wave >> 1;
+
+  // B fragments: slot (plane, block of 32 columns); a block past the last repeats the last (its columns are not stored)
+  const int64_t lr_off = d.mats[g.mat].lr_off;
+  const GAS u32x4* bsrc[BLOADS];
+  int bslot[BLOADS];
+#pragma unroll
+  for (int j = 0; j < BLOADS; ++j) {
+    const int i = wave + 4 * j < BSLOTS ? wave + 4 * j : BSLOTS - 1;
+    const int c = i / (2 * NBW), nb = n0 / 32 + i % (2 * NBW);
+    const uint16_t* pl = c == 0 ? p0 : c == 1 ? p1 : p2;
+    bsrc[j] = (const GAS u32x4*)(pl + lr_off) + (int64_t)(nb < nblocks ? nb : nblocks - 1) * kgroups * 32 + lane;
+    bslot[j] = ASLOTS + i;
+  }
+  auto issue_b = [&](int s, int buf) {
+    s = s < nsteps ? s : nsteps - 1;               // past the end the last step again: the same number of loads in every step
+#pragma unroll
+    for (int j = 0; j < BLOADS; ++j) plane_to_lds(bsrc[j] + (int64_t)s * 64, lds_planes + (buf * SLOTS + bslot[j]) * 64);
+  };
+  // A: thread = (row, k octet of a step); a chunk is two steps.  Rows past M repeat row M - 1 and are not stored.
+  const int arow = tid >> 1, koct = (tid & 1) * 8;
+  const GAS char* abase = (const GAS char*)resolve(d, g.A, g.mat) + (int64_t)(m0 + arow < M ? m0 + arow : M - 1) * g.sAm * 4;
+  const int aslot = ((arow >> 5) * 2 + (tid & 1)) * 32 + (arow & 31);        // 16-byte unit inside a plane of the tile
+  auto load_a = [&](u32x4 (&x)[4], int chunk) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int k = chunk * 32 + (v >> 1) * 16 + koct + (v & 1) * 4;
+      const GAS u32x4* at = (const GAS u32x4*)(abase + (k < kend ? k : 0) * 4);
+      if constexpr (ONCE) x[v] = __builtin_nontemporal_load(at);
+      else x[v] = *at;
+    }
+  };
+  auto stash_a = [&](u32x4& x, u32x4& y, int k, int buf) {                    // eight consecutive k of a row: one unit per plane
+    asm volatile("" : "+v"(x), "+v"(y));          // nothing of this moves ahead of the step it stands in, where it would wait for the loads
+    const bool okx = k < kend, oky = k + 4 < kend;                            // (K is a multiple of 4: whole vectors)
+    uint32_t t0[3], t1[3], t2[3], t3[3];
+    OperandBF<128>::split3(okx ? x.x : 0u, okx ? x.y : 0u, t0);
+    OperandBF<128>::split3(okx ? x.z : 0u, okx ? x.w : 0u, t1);
+    OperandBF<128>::split3(oky ? y.x : 0u, oky ? y.y : 0u, t2);
+    OperandBF<128>::split3(oky ? y.z : 0u, oky ? y.w : 0u, t3);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) lds_planes[(buf * SLOTS + 4 * c) * 64 + aslot] = u32x4{t0[c], t1[c], t2[c], t3[c]};
+  };
+
+  f32x16 acc[2][NBW];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int n = 0; n < NBW; ++n)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[a][n][i] = 0.f;
+  auto compute = [&](int buf) {
+    const u32x4* base = lds_planes + buf * SLOTS * 64 + lane;
+    bf16x8 fa[3][2];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) fa[c][a] = __builtin_bit_cast(bf16x8, base[(4 * c + 2 * wm + a) * 64]);
+#pragma unroll
+    for (int n = 0; n < NBW; ++n) {
+      bf16x8 fb[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) fb[c] = __builtin_bit_cast(bf16x8, base[(ASLOTS + c * 2 * NBW + wn * NBW + n) * 64]);
+#pragma unroll
+      for (int ca = 0; ca < 3; ++ca)
+#pragma unroll
+        for (int cb = 0; cb + ca < 3; ++cb)
+#pragma unroll
+          for (int a = 0; a < 2; ++a) acc[a][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ca][a], fb[cb], acc[a][n], 0, 0, 0);
+    }
+  };
+
+  u32x4 xa[4], xb[4];
+  issue_b(0, 0);
+  load_a(xa, 0);
+  stash_a(xa[0], xa[1], koct, 0);
+  WAIT_VM_BARRIER(0);
+  for (int s = 0; s < nsteps; s += 2) {
+    issue_b(s + 1, 1);
+    load_a(xb, s / 2 + 1);                          // (past the end: element 0 of the row, replaced by zeros or not used)
+    asm volatile("" ::: "memory");
+    compute(0);
+    stash_a(xa[2], xa[3], 16 * (s + 1) + koct, 1);
+    WAIT_VM_BARRIER(4);
+    issue_b(s + 2, 0);
+    compute(1);
+    stash_a(xb[0], xb[1], 16 * (s + 2) + koct, 0);
+    WAIT_VM_BARRIER(0);
+    xa[2] = xb[2];
+    xa[3] = xb[3];
+  }
+
+  // accumulator register v of lane l is row 8*(v/4) + 4*(l/32) + v%4, column l%32 of the block
+  float* C = reinterpret_cast<float*>(const_cast<char*>(resolve(d, g.C, g.mat)));
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int n = 0; n < NBW; ++n) {
+      const int col = n0 + 32 * (wn * NBW + n) + (lane & 31);
+      if (col >= N) continue;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int row = m0 + 32 * (2 * wm + a) + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+        if (row < M) *((GAS float*)C + (int64_t)row * g.ldc + col) = g.alpha * acc[a][n][v];
+      }
+    }
+}
+
+// B of the descriptors as three bf16 planes in operand layout (m = column n of B, k), zero outside K x N, at the
+// matrix's place in three flat arrays.
+__global__ __launch_bounds__(256) void k_pack_planes(DevCtx d, const GemmDesc* __restrict__ descs, uint16_t* __restrict__ p0,
+                                                     uint16_t* __restrict__ p1, uint16_t* __restrict__ p2) {
+  const GemmDesc g = descs[blockIdx.y];
+  if (mat_skipped(d, g.mat)) return;
+  const int64_t off = d.mats[g.mat].lr_off;
+  const GAS float* B = (const GAS float*)resolve(d, g.B, g.mat);
+  const int kgroups = (int)pad32(g.K) / 8, total = kgroups * (int)pad32(g.N);
+  for (int i = (int)blockIdx.x * 256 + threadIdx.x; i < total; i += (int)gridDim.x * 256) {
+    const int blk = i / (kgroups * 32), rem = i % (kgroups * 32);
+    const int n = blk * 32 + (rem & 31), k = (rem >> 5) * 8;      // n fastest over the threads: a row of B is read contiguously
+    uint32_t x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = n < g.N && k + e < g.K ? __float_as_uint(B[(int64_t)(k + e) * g.sBk + n * g.sBn]) : 0u;
+    uint32_t t[4][3];
+#pragma unroll
+    for (int h = 0; h < 4; ++h) OperandBF<128>::split3(x[2 * h], x[2 * h + 1], t[h]);
+    *((GAS u32x4*)(p0 + off) + i) = u32x4{t[0][0], t[1][0], t[2][0], t[3][0]};
+    *((GAS u32x4*)(p1 + off) + i) = u32x4{t[0][1], t[1][1], t[2][1], t[3][1]};
+    *((GAS u32x4*)(p2 + off) + i) = u32x4{t[0][2], t[1][2], t[2][2], t[3][2]};
+  }
+}
+
+hipError_t launch_gemm_planes(const DevCtx& d, const GemmDesc* descs, int desc_first, int ndescs, const GemmTile* tiles, int ntiles, int tn_edge, bool a_once,
+                              int64_t max_groups, uint16_t* p0, uint16_t* p1, uint16_t* p2, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
-  if (tile == 128) hipLaunchKernelGGL((k_gemm32<2>), dim3(ntiles), dim3(256), 0, s, d, descs, tiles, src_is_bf16, alpha_mul);
-  else hipLaunchKernelGGL((k_gemm32<1>), dim3(ntiles), dim3(256), 0, s, d, descs, tiles, src_is_bf16, alpha_mul);
+  const int64_t pack_blocks = (max_groups + 255) / 256;
+  hipLaunchKernelGGL(k_pack_planes, dim3((unsigned)(pack_blocks < 1024 ? pack_blocks : 1024), ndescs), dim3(256), 0, s, d, descs + desc_first, p0, p1, p2);
+  const dim3 grid((ntiles + 127) / 128 * 128), block(256);
+#define LORDO_PLANES(NBWV, OV)                                                                                        \
+  {                                                                                                                   \
+    constexpr int LDS_BYTES = 2 * (12 + 6 * NBWV) * 1024;                                                             \
+    static LdsRaised raised;                                                                                          \
+    if (hipError_t e = raise_lds(reinterpret_cast<const void*>(k_gemm_planes<NBWV, OV>), LDS_BYTES, raised); e != hipSuccess) return e; \
+    hipLaunchKernelGGL((k_gemm_planes<NBWV, OV>), grid, block, LDS_BYTES, s, d, descs, tiles, ntiles, p0, p1, p2);    \
+  }
+  if (tn_edge == 256) { if (a_once) LORDO_PLANES(4, true) else LORDO_PLANES(4, false) }
+  else if (tn_edge == 128) { if (a_once) LORDO_PLANES(2, true) else LORDO_PLANES(2, false) }
+  else if (tn_edge == 64) { if (a_once) LORDO_PLANES(1, true) else LORDO_PLANES(1, false) }
+  else return hipErrorInvalidValue;
+#undef LORDO_PLANES
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm32(const DevCtx& d, const GemmDesc* descs, const GemmTile* tiles, int ntiles, int tile, int src_is_bf16,
+                         hipStream_t s, float alpha_mul, int sub_m, int sub_n) {
+  if (ntiles <= 0) return hipSuccess;
+  const dim3 grid(ntiles, sub_m, sub_n);
+  if (tile == 128) hipLaunchKernelGGL((k_gemm32<2>), grid, dim3(256), 0, s, d, descs, tiles, src_is_bf16, alpha_mul, sub_m, sub_n);
+  else hipLaunchKernelGGL((k_gemm32<1>), grid, dim3(256), 0, s, d, descs, tiles, src_is_bf16, alpha_mul, sub_m, sub_n);
   return hipGetLastError();
 }
 

@@ -39,6 +39,9 @@ struct Op {
   bool rot_only = false;            // part of the moment rotation (skipped while t == 0)
   int fast = 0;                     // OP_GEMM: 1 = the product Z = Src^T Y, which the down-projection kernel can take over (iarg: y buffer);
                                     // 2 = a product Y = Src B for the source-streaming kernel (iarg: z buffer of B, -1 = Omega)
+  int planes = 0;                   // OP_GEMM: column edge (64, 128, 256) of the 128-row tiles of k_gemm_planes its table is made for; 0: square tiles
+  bool a_once = false;              // ... with one column tile per matrix
+  int64_t max_groups = 0;           // ... largest plane of B, in groups of 8 elements
 };
 
 struct Plan {
@@ -140,12 +143,14 @@ std::vector<ProjTile> xcd_order(const std::vector<ProjTile>& logical) {
 struct ProgramBuilder {
   Plan& P;
   int n;
+  bool shared_b = false;            // the program may use the planes of N and the array g as scratch (a refresh; see k_gemm_planes)
   explicit ProgramBuilder(Plan& p, int n_) : P(p), n(n_) {}
 
   // One grouped GEMM launch.  `small_out` marks r x r products with a long contraction (Gram matrix,
   // rotation matrix): with few output tiles they are split along K so that the chip is filled.
+  // `shared_b` marks products of a tall A with a narrow B (see k_gemm_planes).
   template <class F>
-  void gemm(F make, bool rot_only = false, bool small_out = false, bool lower_only = false) {   // make(i, desc) -> false to skip matrix i
+  void gemm(F make, bool rot_only = false, bool small_out = false, bool lower_only = false, bool shared_b = false) {   // make(i, desc) -> false to skip matrix i
     Op op;
     op.kind = OP_GEMM;
     op.tile_first = (int)P.gtile_h.size();
@@ -173,6 +178,7 @@ struct ProgramBuilder {
       made.push_back(g);
     }
     op.tile = (big_ok && (tiles128 >= 512 || small_out)) ? 128 : 64;
+    if (shared_b) op.planes = planes_edge(made);
     const int64_t tiles = op.tile == 128 ? tiles128 : tiles64;
     int ksplit = 1;
     if (small_out && tiles > 0 && tiles < 1024)
@@ -190,6 +196,13 @@ struct ProgramBuilder {
       }
       int di = (int)P.desc_h.size();
       P.desc_h.push_back(g);
+      if (op.planes) {
+        op.max_groups = std::max(op.max_groups, pad32(g.N) * (pad32(g.K) / 8));
+        for (int tm = 0; tm < (g.M + 127) / 128; ++tm)
+          for (int tn = 0; tn < (g.N + op.planes - 1) / op.planes; ++tn)
+            P.gtile_h.push_back(GemmTile{di, (int16_t)tm, (int16_t)tn, 0, 0});
+        continue;
+      }
       for (int sl = 0; sl < g.ksplit; ++sl)
         for (int tm = 0; tm < (g.M + op.tile - 1) / op.tile; ++tm)
           for (int tn = 0; tn < (g.N + op.tile - 1) / op.tile; ++tn) {
@@ -199,7 +212,42 @@ struct ProgramBuilder {
     }
     op.ndescs = (int)P.desc_h.size() - op.desc_first;
     op.ntiles = (int)P.gtile_h.size() - op.tile_first;
+    if (op.planes) {
+      op.tile = op.planes == 64 ? 64 : 128;          // (what an unaligned source falls back to, several tiles per table entry)
+      op.a_once = true;
+      for (const GemmDesc& g : made) op.a_once = op.a_once && g.N <= op.planes;
+    }
     P.ops.push_back(op);
+  }
+  // Column edge of the tiles k_gemm_planes takes these products on, or 0 if it cannot: A is read in 16-byte vectors along
+  // k, and the planes of B have to fit where the matrix's operand planes of N live between steps.
+  int planes_edge(const std::vector<GemmDesc>& made) const {
+    if (made.empty()) return 0;
+    int64_t rows128 = 0;
+    double cost[3] = {0.0, 0.0, 0.0};
+    constexpr int edges[3] = {64, 128, 256};
+    // relative time of a tile per column: a narrow tile splits its rows of A for fewer products
+    constexpr double per_column[3] = {1.6, 1.2, 1.0};
+    int64_t tiles[3] = {0, 0, 0};
+    for (const GemmDesc& g : made) {
+      const MatDev& m = P.mat[g.mat];
+      if (g.sAk != 1 || (g.sAm & 3) != 0 || (g.K & 3) != 0 || g.a_bf16 == 1 || g.C2.off >= 0 || g.beta != 0.f) return 0;
+      if (pad32(g.N) * pad32(g.K) > (int64_t)m.qp * m.rp) return 0;
+      // a short contraction does not pay for the launch that packs B (X M^T of 72 matrices at r = 128: 42 us on the
+      // general kernel, 32 + 7 us and one more launch here; at r = 256: 510 us against 370 + 40 us)
+      if (g.K < 192) return 0;
+      const int64_t tm = (g.M + 127) / 128;
+      rows128 += tm;
+      for (int e = 0; e < 3; ++e) {
+        const int64_t tn = (g.N + edges[e] - 1) / edges[e];
+        tiles[e] += tm * tn;
+        cost[e] += (double)(tm * tn) * edges[e] * g.K * per_column[e];
+      }
+    }
+    int best = 0;
+    for (int e = 1; e < 3; ++e)
+      if (cost[e] < cost[best] && (tiles[e] >= 512 || tiles[e] == tiles[best])) best = e;
+    return tiles[best] >= 128 ? edges[best] : 0;
   }
   // A operand = the source (transposed: its transpose).  The source of a right-projected matrix is the caller's
   // row-major array read as its transpose: element (i, j) of the p x q matrix at j * p + i.
@@ -317,7 +365,7 @@ struct ProgramBuilder {
         g.M = rows_of(i); g.N = m.r; g.K = m.r;
         g.tri = 1;
         return true;
-      });
+      }, false, false, false, shared_b);
       cur = dst;
     }
     return cur;
@@ -459,6 +507,7 @@ struct ProgramBuilder {
   // of the source then does not compound from product to product) and shifted, shifted, plain at the end.
   void build(int power_iters, int passes, bool rayleigh_ritz) {
     const int inner = passes >= 3 ? 2 : 1, nshift = passes >= 3 ? 2 : 1;
+    shared_b = true;
     // Y = Src Omega
     gemm([&](int i, GemmDesc& g) {
       const MatDev& m = P.mat[i];
@@ -467,7 +516,7 @@ struct ProgramBuilder {
       g.C = ref_arena(m.y[0]); g.ldc = m.r;
       g.M = m.p; g.N = m.r; g.K = m.q;
       return true;
-    });
+    }, false, false, false, shared_b);
     P.ops.back().fast = 2;
     P.ops.back().iarg = -1;
     // Inside the power iteration the blocks only have to stay well conditioned (any basis of the
@@ -495,7 +544,7 @@ struct ProgramBuilder {
         g.C = ref_arena(m.y[0]); g.ldc = m.r;
         g.M = m.p; g.N = m.r; g.K = m.q;
         return true;
-      });
+      }, false, false, false, shared_b);
       P.ops.back().fast = 2;
       P.ops.back().iarg = zcur;
       ycur = it + 1 < power_iters ? orth(true, 0, inner, inner) : orth(true, 0, passes, nshift);
@@ -559,10 +608,11 @@ struct ProgramBuilder {
         g.C = ref_arena(m.zw[which]); g.ldc = m.r;
         g.M = m.q; g.N = m.r; g.K = m.r;
         return true;
-      }, true);
+      }, true, false, false, shared_b);
     simple(OP_ROT_POST, 0, 0.f, true);
     simple(OP_Q_FROM_Y, ycur);
     simple(OP_PACK);
+    shared_b = false;
   }
 };
 
@@ -1311,12 +1361,13 @@ int lordo_local_step(lordo_ctx* c, void* const* W, const void* const* G, double 
 }
 
 static int run_ops(lordo_ctx* c, const std::vector<Op>& ops, int32_t src_dtype, hipStream_t s, bool rotate, double c1, double c2,
-                   bool proj_kernels, bool stream_kernel, bool proj_tr = false);
+                   bool proj_kernels, bool stream_kernel, bool proj_tr = false, bool planes_src = false);
 
 // Runs the refresh program on the source table currently selected in EXT_SRC; with `fold` the error
 // buffer first takes E <- fold_scale * G + E (Alg. 2, argument of ComputeProjection).
 static int run_refresh(lordo_ctx* c, int32_t src_dtype, hipStream_t s, bool fold = false, double fold_scale = 0.0,
-                       bool proj_kernels = false, bool stream_kernel = false, bool proj_tr = false) {
+                       bool proj_kernels = false, bool stream_kernel = false, bool proj_tr = false,
+                       bool planes_src = false) {
   Plan& P = c->plan;
   const bool rotate = c->t > 0;
   const double c1 = 1.0, c2 = 1.0;       // (the rotation passes read the bias corrections of the current step from the device)
@@ -1325,7 +1376,7 @@ static int run_refresh(lordo_ctx* c, int32_t src_dtype, hipStream_t s, bool fold
   c->prof.begin(LORDO_K_REFRESH, s);
   if (fold && launch_fold_grad(c->dev, c->at<int64_t>(P.chunk_start), P.nchunks, (float)fold_scale, c->hp.grad_dtype == LORDO_F32, s) != hipSuccess)
     rc = LORDO_EHIP;
-  if (rc == LORDO_OK) rc = run_ops(c, P.ops, src_dtype, s, rotate, c1, c2, proj_kernels, stream_kernel, proj_tr);
+  if (rc == LORDO_OK) rc = run_ops(c, P.ops, src_dtype, s, rotate, c1, c2, proj_kernels, stream_kernel, proj_tr, planes_src);
   if (rc != LORDO_OK) { c->prof.abandon(LORDO_K_REFRESH); return rc; }
   c->prof.end(LORDO_K_REFRESH, s);
   c->refreshed = true;
@@ -1334,7 +1385,7 @@ static int run_refresh(lordo_ctx* c, int32_t src_dtype, hipStream_t s, bool fold
 
 // Enqueues one static program (the refresh, or the initial projection).
 static int run_ops(lordo_ctx* c, const std::vector<Op>& ops, int32_t src_dtype, hipStream_t s, bool rotate, double c1, double c2,
-                   bool proj_kernels, bool stream_kernel, bool proj_tr) {
+                   bool proj_kernels, bool stream_kernel, bool proj_tr, bool planes_src) {
   Plan& P = c->plan;
   const GemmDesc* descs = c->at<GemmDesc>(P.descs);
   const GemmTile* tiles = c->at<GemmTile>(P.gtiles);
@@ -1362,7 +1413,14 @@ static int run_ops(lordo_ctx* c, const std::vector<Op>& ops, int32_t src_dtype, 
                                         c->at<uint16_t>(P.n_lo), s));
           break;
         }
-        HIPCHK(launch_gemm32(c->dev, descs, tiles + op.tile_first, op.ntiles, op.tile, src_dtype == LORDO_BF16, s));
+        if (op.planes && (op.fast == 0 || planes_src)) {
+          // the third plane of B goes where the array g lives between steps (half of it; g is scratch of a refresh, as N is)
+          HIPCHK(launch_gemm_planes(c->dev, descs, op.desc_first, op.ndescs, tiles + op.tile_first, op.ntiles, op.planes, op.a_once, op.max_groups,
+                                    c->at<uint16_t>(P.n_hi), c->at<uint16_t>(P.n_lo), c->at<uint16_t>(P.glow), s));
+          break;
+        }
+        HIPCHK(launch_gemm32(c->dev, descs, tiles + op.tile_first, op.ntiles, op.tile, src_dtype == LORDO_BF16, s, 1.f,
+                             op.planes ? 128 / op.tile : 1, op.planes ? op.planes / op.tile : 1));
         if (op.split) HIPCHK(launch_gemm_reduce(c->dev, descs + op.desc_first, op.ndescs, s));
         break;
       case OP_SHIFT: HIPCHK(launch_gram_shift(c->dev, op.farg, op.iarg != 0, s)); break;
@@ -1395,7 +1453,7 @@ static int run_ops(lordo_ctx* c, const std::vector<Op>& ops, int32_t src_dtype, 
 }
 
 // Which of the projection-type kernels can take the products of a program whose source is Src.
-struct SrcPaths { bool proj_kernels, stream_kernel, proj_tr; };
+struct SrcPaths { bool proj_kernels, stream_kernel, proj_tr, planes_src; };
 static int source_paths(lordo_ctx* c, const void* const* Src, int32_t src_dtype, hipStream_t s, SrcPaths& out) {
   // a bf16 source with the alignment the pipelined down-projection kernel reads gradients with lets that
   // kernel take the products of the power iteration that have its shape
@@ -1419,7 +1477,11 @@ static int source_paths(lordo_ctx* c, const void* const* Src, int32_t src_dtype,
   bool proj_tr = proj_kernels && src_dtype == LORDO_BF16;
   for (int i = 0; i < c->n && proj_tr; ++i)
     if ((c->plan.mat[i].q & 7) != 0 || (reinterpret_cast<uintptr_t>(Src[i]) & 15) != 0) proj_tr = false;
-  out = SrcPaths{proj_kernels, stream_kernel, proj_tr};
+  // k_gemm_planes reads the rows of an fp32 source in 16-byte vectors
+  bool planes_src = src_dtype == LORDO_F32;
+  for (int i = 0; i < c->n && planes_src; ++i)
+    if ((reinterpret_cast<uintptr_t>(Src[i]) & 15) != 0) planes_src = false;
+  out = SrcPaths{proj_kernels, stream_kernel, proj_tr, planes_src};
   return LORDO_OK;
 }
 
@@ -1454,7 +1516,7 @@ int lordo_refresh_subspace(lordo_ctx* c, const void* const* Src, int32_t src_dty
   rc = select_omega(c, Omega, s);
   SrcPaths sp{};
   if (rc == LORDO_OK) rc = source_paths(c, Src, src_dtype, s, sp);
-  if (rc == LORDO_OK) rc = run_refresh(c, src_dtype, s, false, 0.0, sp.proj_kernels, sp.stream_kernel, sp.proj_tr);
+  if (rc == LORDO_OK) rc = run_refresh(c, src_dtype, s, false, 0.0, sp.proj_kernels, sp.stream_kernel, sp.proj_tr, sp.planes_src);
   c->dev.skip_null = 0;
   return rc;
 }
@@ -1500,7 +1562,7 @@ int lordo_refresh_subspace_local(lordo_ctx* c, const void* const* G, double grad
   bool proj_kernels = P.down_pipe != 0 && !P.any_tr;   // the residual is 256-byte aligned; pairs of columns need an even q
   for (int i = 0; i < c->n && proj_kernels; ++i)
     if ((P.mat[i].q & 1) != 0) proj_kernels = false;
-  rc = run_refresh(c, LORDO_F32, s, true, grad_scale, proj_kernels, false);
+  rc = run_refresh(c, LORDO_F32, s, true, grad_scale, proj_kernels, false, false, true);
   if (rc != LORDO_OK) return rc;
   // only a refresh that was enqueued in full commits the context to the step that consumes the folded buffer
   c->grad_folded = true;
