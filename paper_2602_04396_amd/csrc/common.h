@@ -41,7 +41,6 @@ struct MatDev {
   int64_t y[2];           // fp32 p x r, ping-pong of the orthonormalisation
   int64_t zw[4];          // fp32 q x r; zw[0], zw[1] ping-pong of the q-side block, all four rotation temporaries
   int64_t gram, lfac;     // fp32 r x r : Gram matrix (consumed by the factorisation) and its Cholesky factor
-  int64_t dinv;           // fp32 ceil(r/NB) blocks of NB x NB : inverses of the diagonal blocks of the factor
   int64_t minv;           // fp32 r x r : inverse of the whole factor, lower triangular (zeros above the diagonal are never written)
   int64_t rot, rot2;      // fp32 r x r : R = Q_new^T Q_old and its elementwise square
   int64_t part;           // fp32 split-K partial sums of the r x r products (Gram, R): slices x r x r
@@ -110,7 +109,7 @@ __device__ __forceinline__ bool mat_skipped(const DevCtx& d, int mat) {
 }
 
 constexpr int CHUNK = 2048;       // elements per workgroup of the p x q elementwise kernels
-constexpr int NB = 64;            // Cholesky / triangular-solve block size
+constexpr int NB = 128;           // Cholesky block size
 
 // ---------------------------------------------------------------------------------------
 // launchers (each defined in one .hip file)
@@ -232,12 +231,11 @@ hipError_t launch_gram_shift(const DevCtx& d, float coef, bool store, hipStream_
 // exact diagonal of the Gram matrix of block `which` (0, 1: Y pair; 2, 3: zw[0], zw[1]) written over the one the GEMM left
 hipError_t launch_gram_diag(const DevCtx& d, int which, int rmax, int part_slices, hipStream_t s);
 hipError_t launch_mssv(const DevCtx& d, float* out, hipStream_t s);
-hipError_t launch_potf2(const DevCtx& d, int jb, hipStream_t s);
+hipError_t launch_factor_diag(const DevCtx& d, int jb, hipStream_t s);
 hipError_t launch_frob2(const DevCtx& d, const int64_t* chunk_start, int64_t nchunks, float* partial, bool src_f32, hipStream_t s);
 hipError_t launch_stable_rank(const DevCtx& d, float* out, int which, hipStream_t s);
 hipError_t launch_jacobi_svd(const DevCtx& d, int rmax, bool top_value_only, hipStream_t s);
 hipError_t launch_jacobi_svd_blocked(const DevCtx& d, int rmax, int64_t rank_sq_sum, bool top_value_only, int* flags, hipStream_t s);
-hipError_t launch_diag_inverses(const DevCtx& d, hipStream_t s);
 hipError_t launch_rot_pre(const DevCtx& d, const float* u, const float* v, const StepDev* step, hipStream_t s);
 hipError_t launch_rot_post(const DevCtx& d, float* u, float* v, const StepDev* step, hipStream_t s);
 hipError_t launch_q_from_y(const DevCtx& d, int ybuf, hipStream_t s);

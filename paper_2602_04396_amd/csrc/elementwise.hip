@@ -7,7 +7,7 @@
 //   k_fold_grad       E <- E + s G, the projection source of the local variant (Alg. 2)
 //   k_pack_q / k_pack_y / k_pack_block / k_split_planes   fp32 -> bf16 hi/lo operand planes in matrix-core order
 //   k_glow_to_z, k_lr_to_plain, k_plain_to_lr, k_lr_exchange, k_tr_exchange   between the operand layout of the low-rank state and plain buffers
-//   k_gram_shift, k_potf2, k_diag_inverses   CholeskyQR: diagonal shift, Cholesky of a diagonal block and its inverse
+//   k_gram_shift, k_factor_diag   CholeskyQR: diagonal shift, Cholesky of a diagonal block and its inverse
 //   k_jacobi_svd      singular vectors of the Cholesky factor of the r x r Ritz matrix (Rayleigh-Ritz step: basis ordered as in Sec. 2's SVD projection)
 //   k_frob2_chunks / k_frob2_sum / k_stable_rank   squared Frobenius norm of the refresh source and its stable rank (Sec. 5.1)
 //   k_rot_pre / k_rot_post, k_mssv   elementwise parts of the moment rotation (Alg. 1 rotation lines); similarity diagnostic (Sec. 5.1)
@@ -835,138 +835,242 @@ hipError_t launch_gram_shift(const DevCtx& d, float coef, bool store, hipStream_
   return hipGetLastError();
 }
 
-// Diagonal block jb of the Gram matrix: L = chol(S_jj) (lower), X = L^{-1}; writes L into the
-// factor and X into the block-inverse array.  One workgroup per matrix.
-__device__ __forceinline__ float lane_value(float x, int lane) {      // value of x in lane `lane` (a constant), as a scalar
+// value of x in lane `lane` (uniform over the wave), as a scalar
+__device__ __forceinline__ float lane_value(float x, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
 }
 
-// One wave per matrix; lane i keeps row i of the 64 x 64 block in 64 registers, so the 64 column
-// steps of the factorisation and of the inversion need no barrier and no LDS round trip: a column
-// is broadcast lane by lane through scalar registers (v_readlane) and applied with one FMA per
-// element.  Everything is unrolled, every register index is a constant.
-__global__ __launch_bounds__(256) void k_potf2(DevCtx d, int jb) {
-  if (mat_skipped(d, blockIdx.x)) return;
-  const MatDev& m = d.mats[blockIdx.x];
-  const int o = jb * NB;
-  int nbk = m.r - o;
-  if (nbk <= 0) return;
-  if (nbk > NB) nbk = NB;
-  const float* S = reinterpret_cast<const float*>(d.arena + m.gram);
-  float* L = reinterpret_cast<float*>(d.arena + m.lfac);
-  float* X = reinterpret_cast<float*>(d.arena + m.dinv) + (int64_t)jb * NB * NB;
-  static_assert(NB == 64, "four waves of sixteen columns each");
-  __shared__ float tile[NB][NB + 1];
-  __shared__ __align__(16) float lrow[NB][NB];       // the factor, rows 16-byte aligned: operand of the inversion
-  __shared__ __align__(16) float ccol[2][NB];        // column k of the factor with entries <= k zeroed (multipliers of step k)
-  __shared__ float crow[2][NB];                      // column k of the factor (every row's own factor)
-  __shared__ float red[4];
-  __shared__ int bad_s;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // rows are read coalesced and handed to their lanes through LDS; identity outside the block
-  for (int rr = w; rr < NB; rr += 4) {
-    float val;
-    if (rr < nbk && lane < nbk) val = lane <= rr ? S[(int64_t)(o + rr) * m.r + (o + lane)] : 0.f;
-    else val = rr == lane ? 1.f : 0.f;
-    tile[rr][lane] = val;
-  }
-  if (tid == 0) bad_s = 0;
-  __syncthreads();
-  // lane = row, wave w holds columns 16 w .. 16 w + 15 of it
+// Diagonal block jb (up to 128 x 128) of the Gram matrix: L = chol(S_jj) (lower) into the factor and X = L^{-1} onto the
+// diagonal of the inverse.  One workgroup of four waves per matrix, everything in LDS, two 64 x 64 halves:
+//     L_11 = chol(S_11),  L_21 = S_21 X_11^T,  L_22 = chol(S_22 - L_21 L_21^T),  X_21 = -X_22 (L_21 X_11).
+// A chain of dependent operations on one compute unit: latency is the bound, so the aim is few and short links.
+//   - 64 x 64 factor: lane = row, wave w keeps columns 16 w .. 16 w + 15 in registers.  A wave factors its sixteen columns
+//     alone, without a barrier (pivot and multipliers go round through v_readlane), and leaves them in LDS; the waves
+//     to its right subtract all sixteen at once.  Four barriers and not sixty-four.
+//   - Square root and quotients start from v_rsq_f32 with a Newton step and a residual correction each, which are
+//     within an ulp of the correctly rounded ones: six dependent instructions in place of about forty.
+//   - Products and the inverse below the 16 x 16 diagonal blocks run on the fp32 matrix cores (16 x 16 x 4).
+//   - The loops over halves and column blocks stay rolled: an unrolled chain is tens of KiB of code, fetched anew by every
+//     launch.
+// 72 matrices, r = 128: 48 us.  It replaces two launches of a 64-wide kernel with a barrier per column (41.7 us each), two
+// panel and two inverse products (9 us each) and the copy of the inverses to their places (9.4 us), 129 us in all.
+typedef float f32x4m __attribute__((ext_vector_type(4)));
+constexpr int HB = 64;                // edge of a half
+constexpr int FPITCH = HB + 4;        // LDS pitch: 16-byte rows, a column of sixteen lanes spread over all banks
+typedef float (*LdsTile)[FPITCH];
+// compiler-level order of a wave's own LDS accesses (the hardware keeps it anyway)
+#define LDS_ORDER() asm volatile("" ::: "memory")
+
+// A (lower triangle of S, identity outside the block) -> L, zeros above the diagonal; X <- L^{-1}, zeros above.
+__device__ __forceinline__ void factor_half(LdsTile A, LdsTile X, int nbk, int w, int lane, int* bad) {
   float a[16];
 #pragma unroll
-  for (int jc = 0; jc < 16; ++jc) a[jc] = tile[lane][16 * w + jc];
-  float dmax = lane < nbk ? tile[lane][lane] : 0.f;
+  for (int g4 = 0; g4 < 4; ++g4) {
+    const f32x4m t = *reinterpret_cast<const f32x4m*>(&A[lane][16 * w + 4 * g4]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) a[4 * g4 + e] = t[e];
+    *reinterpret_cast<f32x4m*>(&X[lane][16 * w + 4 * g4]) = f32x4m{0.f, 0.f, 0.f, 0.f};
+  }
+  float dmax = lane < nbk ? A[lane][lane] : 0.f;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) dmax = fmaxf(dmax, __shfl_xor(dmax, off));
   const float floor_piv = 1e-12f * dmax + 1e-37f;
-  // right-looking Cholesky, one barrier per column: the wave that holds column k scales it and leaves it in LDS (two
-  // buffers alternate, so the next column can be written while this one is still being read); every wave then updates
-  // its sixteen columns, a[j] -= L[i][k] L[j][k], with the multipliers L[j][k] read as broadcasts (zero for j <= k, which
-  // leaves the finished columns alone)
-#pragma clang loop unroll(full)
-  for (int k = 0; k < NB; ++k) {
-    const int buf = k & 1;
-    if (w == k / 16) {
-      float piv = lane_value(a[k % 16], k);
-      if (!(piv > floor_piv)) {
-        if (lane == 0) bad_s = 1;
-        piv = floor_piv;
+  __syncthreads();                                   // every wave has its columns and the diagonal
+#pragma clang loop unroll(disable)
+  for (int b = 0; b < 4; ++b) {
+    if (w == b) {
+      bool low = false;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        float piv = lane_value(a[k], 16 * b + k);
+        const bool ok = piv > floor_piv;
+        low |= !ok;
+        piv = ok ? piv : floor_piv;
+        float y = __builtin_amdgcn_rsqf(piv);
+        y = fmaf(0.5f * y, fmaf(-piv * y, y, 1.f), y);
+        float dd = piv * y;
+        dd = fmaf(0.5f * y, fmaf(-dd, dd, piv), dd);
+        float q = a[k] * y;
+        q = fmaf(fmaf(-q, dd, a[k]), y, q);
+        const float lk = lane == 16 * b + k ? dd : (lane > 16 * b + k ? q : 0.f);
+        a[k] = lk;
+#pragma unroll
+        for (int j = k + 1; j < 16; ++j) a[j] = fmaf(-lk, lane_value(lk, 16 * b + j), a[j]);
       }
-      const float dd = sqrtf(piv);
-      const float lk = lane == k ? dd : (lane > k ? a[k % 16] / dd : 0.f);
-      a[k % 16] = lk;
-      crow[buf][lane] = lk;
-      ccol[buf][lane] = lane > k ? lk : 0.f;
+      if (low && lane == 0) *bad = 1;
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4)
+        *reinterpret_cast<f32x4m*>(&A[lane][16 * b + 4 * g4]) = f32x4m{a[4 * g4], a[4 * g4 + 1], a[4 * g4 + 2], a[4 * g4 + 3]};
     }
     __syncthreads();
-    if (16 * w + 15 > k) {                           // this wave still has columns to the right of k
-      const float mine = crow[buf][lane];
-      const f32x4n* cp = reinterpret_cast<const f32x4n*>(&ccol[buf][16 * w]);
-#pragma unroll
+    if (w > b) {
+#pragma clang loop unroll(disable)
       for (int g4 = 0; g4 < 4; ++g4) {
-        const f32x4n cv = cp[g4];
+        const f32x4m mine = *reinterpret_cast<const f32x4m*>(&A[lane][16 * b + 4 * g4]);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) a[4 * g4 + e] = fmaf(-mine, cv[e], a[4 * g4 + e]);
-      }
-    }
-  }
-  // the factor to LDS (zeros above the diagonal): for the inversion and for the coalesced store
+        for (int jc = 0; jc < 16; ++jc) {
+          const f32x4m cv = *reinterpret_cast<const f32x4m*>(&A[16 * w + jc][16 * b + 4 * g4]);      // a broadcast
 #pragma unroll
-  for (int jc = 0; jc < 16; ++jc) {
-    const int j = 16 * w + jc;
-    const float v = j <= lane ? a[jc] : 0.f;
-    lrow[lane][j] = v;
-    tile[lane][j] = v;
-  }
-  __syncthreads();
-  if (w == 0) {
-    // X = L^{-1} by forward substitution: lane j builds column j, x[i] = X[i][j]; row i of L is read as broadcasts
-    float x[NB];
-#pragma clang loop unroll(full)
-    for (int i = 0; i < NB; ++i) {
-      // four partial sums: the FMA chain of a row is split so that consecutive terms overlap
-      float acc[4] = {lane == i ? 1.f : 0.f, 0.f, 0.f, 0.f};
-      const f32x4n* lp = reinterpret_cast<const f32x4n*>(&lrow[i][0]);
-#pragma clang loop unroll(full)
-      for (int g4 = 0; g4 < NB / 4; ++g4) {
-        if (4 * g4 < i) {
-          const f32x4n lv = lp[g4];
-#pragma clang loop unroll(full)
-          for (int e = 0; e < 4; ++e)
-            if (4 * g4 + e < i) acc[e] = fmaf(-lv[e], x[4 * g4 + e], acc[e]);
+          for (int e = 0; e < 4; ++e) a[jc] = fmaf(-mine[e], cv[e], a[jc]);
         }
       }
-      x[i] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) / lrow[i][i];
+    }
+  }
+  // X = L^{-1}.  Wave w: the 16 x 16 inverse on the diagonal by forward substitution (lane % 16 = column, the four groups of
+  // sixteen lanes do the same), ...
+  const int c = lane & 15, h = lane >> 4;
+  {
+    const float dg = A[16 * w + c][16 * w + c];
+    float rc = __builtin_amdgcn_rcpf(dg);
+    rc = fmaf(rc, fmaf(-dg, rc, 1.f), rc);
+    float x[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      float acc[2] = {c == i ? 1.f : 0.f, 0.f};
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        if (4 * g4 < i) {
+          const f32x4m lv = *reinterpret_cast<const f32x4m*>(&A[16 * w + i][16 * w + 4 * g4]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (4 * g4 + e < i) acc[e & 1] = fmaf(-lv[e], x[4 * g4 + e], acc[e & 1]);
+        }
+      }
+      const float s = acc[0] + acc[1], di = lane_value(dg, i), ri = lane_value(rc, i);
+      const float q = s * ri;
+      x[i] = fmaf(fmaf(-q, di, s), ri, q);
+    }
+    if (h == 0) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) X[16 * w + i][16 * w + c] = x[i];
+    }
+  }
+  __syncthreads();
+  // ... then column block w downwards: X_iw = -X_ii sum_k L_ik X_kw (one wave, so LDS order is program order)
+#pragma clang loop unroll(disable)
+  for (int i = w + 1; i < 4; ++i) {
+    f32x4m t = {0.f, 0.f, 0.f, 0.f}, o = {0.f, 0.f, 0.f, 0.f};
+#pragma clang loop unroll(disable)
+    for (int kb = w; kb < i; ++kb) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        t = __builtin_amdgcn_mfma_f32_16x16x4f32(A[16 * i + c][16 * kb + 4 * s + h], X[16 * kb + 4 * s + h][16 * w + c], t, 0, 0, 0);
     }
 #pragma unroll
-    for (int i = 0; i < NB; ++i) X[i * NB + lane] = lane <= i ? x[i] : 0.f;
+    for (int v = 0; v < 4; ++v) X[16 * i + 4 * h + v][16 * w + c] = t[v];
+    LDS_ORDER();
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      o = __builtin_amdgcn_mfma_f32_16x16x4f32(X[16 * i + c][16 * i + 4 * s + h], X[16 * i + 4 * s + h][16 * w + c], o, 0, 0, 0);
+    LDS_ORDER();
+#pragma unroll
+    for (int v = 0; v < 4; ++v) X[16 * i + 4 * h + v][16 * w + c] = -o[v];
+    LDS_ORDER();
   }
-  if (tid == 0 && bad_s) *d.flag = 1;
-  for (int rr = w; rr < nbk; rr += 4)
-    if (lane < nbk) L[(int64_t)(o + rr) * m.r + (o + lane)] = tile[rr][lane];
+  __syncthreads();
 }
-// The inverses of the diagonal blocks, copied to their places on the diagonal of the r x r inverse of the
-// whole factor (the rows below are then built from them by products).
-__global__ __launch_bounds__(256) void k_diag_inverses(DevCtx d) {
+
+// acc[n] = rows 16 w .. of A times B (BT: times B^T), columns 16 n ..; element 16 w + 4 (lane / 16) + v, 16 n + lane % 16
+template <bool BT>
+__device__ __forceinline__ void mul_half(f32x4m (&acc)[4], LdsTile A, LdsTile B, int w, int lane) {
+  const int c = lane & 15, h = lane >> 4;
+#pragma unroll
+  for (int n = 0; n < 4; ++n) acc[n] = f32x4m{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int s = 0; s < 16; ++s) {
+    const float av = A[16 * w + c][4 * s + h];
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+      acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, BT ? B[16 * n + c][4 * s + h] : B[4 * s + h][16 * n + c], acc[n], 0, 0, 0);
+  }
+}
+
+constexpr int FACTOR_LDS = 6 * HB * FPITCH * 4;
+__global__ __launch_bounds__(256) void k_factor_diag(DevCtx d, int jb) {
   if (mat_skipped(d, blockIdx.x)) return;
   const MatDev& m = d.mats[blockIdx.x];
-  const float* X = reinterpret_cast<const float*>(d.arena + m.dinv);
-  float* M = reinterpret_cast<float*>(d.arena + m.minv);
-  const int nblocks = (m.r + NB - 1) / NB;
-  for (int t = threadIdx.x; t < nblocks * NB * NB; t += 256) {
-    const int jb = t / (NB * NB), i = (t / NB) % NB, j = t % NB;
-    const int row = jb * NB + i, col = jb * NB + j;
-    if (row < m.r && col < m.r) M[(int64_t)row * m.r + col] = X[t];
+  const int o = jb * NB, r = m.r;
+  int nbk = r - o;
+  if (nbk <= 0) return;
+  if (nbk > NB) nbk = NB;
+  static_assert(NB == 2 * HB && HB == 64, "two halves of one row per lane");
+  const float* S = reinterpret_cast<const float*>(d.arena + m.gram) + (int64_t)o * r + o;
+  float* L = reinterpret_cast<float*>(d.arena + m.lfac) + (int64_t)o * r + o;
+  float* M = reinterpret_cast<float*>(d.arena + m.minv) + (int64_t)o * r + o;
+  extern __shared__ __align__(16) float fsm[];
+  auto tile_at = [&](int i) { return reinterpret_cast<LdsTile>(fsm + i * HB * FPITCH); };
+  const LdsTile A1 = tile_at(0), X1 = tile_at(1), A2 = tile_at(2), X2 = tile_at(3), P = tile_at(4), T = tile_at(5);
+  __shared__ int bad_s;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 15, h = lane >> 4;
+  const int n1 = nbk < HB ? nbk : HB, n2 = nbk - n1;
+  if (tid == 0) bad_s = 0;
+  // rows are read coalesced; identity outside the block
+#pragma unroll 4
+  for (int rr = w; rr < HB; rr += 4) A1[rr][lane] = rr < n1 && lane <= rr ? S[(int64_t)rr * r + lane] : (rr == lane ? 1.f : 0.f);
+  if (n2 > 0) {
+#pragma unroll 4
+    for (int rr = w; rr < HB; rr += 4) {
+      const float* row = S + (int64_t)(HB + rr) * r;
+      P[rr][lane] = rr < n2 ? row[lane] : 0.f;
+      A2[rr][lane] = rr < n2 && lane <= rr ? row[HB + lane] : (rr == lane ? 1.f : 0.f);
+    }
+  }
+  __syncthreads();
+  f32x4m acc[4];
+  auto put = [&](LdsTile C, float sign) {
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) C[16 * w + 4 * h + v][16 * n + c] = sign * acc[n][v];
+  };
+#pragma clang loop unroll(disable)
+  for (int half = 0;; half = 1) {                    // one copy of the code for both halves
+    factor_half(half ? A2 : A1, half ? X2 : X1, half ? n2 : n1, w, lane, &bad_s);
+    if (half || n2 == 0) break;
+    mul_half<true>(acc, P, X1, w, lane);             // L_21 = S_21 X_11^T, over S_21: a wave reads and writes its own sixteen rows only
+    LDS_ORDER();
+    put(P, 1.f);
+    __syncthreads();
+    mul_half<true>(acc, P, P, w, lane);              // S_22 - L_21 L_21^T
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (16 * n + c <= 16 * w + 4 * h + v) A2[16 * w + 4 * h + v][16 * n + c] -= acc[n][v];
+    __syncthreads();
+  }
+  if (n2 > 0) {
+    mul_half<false>(acc, P, X1, w, lane);            // X_21 = -X_22 (L_21 X_11)
+    put(T, 1.f);
+    __syncthreads();
+    mul_half<false>(acc, X2, T, w, lane);
+    __syncthreads();
+    put(T, -1.f);
+    __syncthreads();
+  }
+  if (tid == 0 && bad_s) *d.flag = 1;
+  for (int rr = w; rr < n1; rr += 4)
+    if (lane < n1) {
+      L[(int64_t)rr * r + lane] = A1[rr][lane];
+      M[(int64_t)rr * r + lane] = X1[rr][lane];
+    }
+  for (int rr = w; rr < n2; rr += 4) {
+    const int64_t row = (int64_t)(HB + rr) * r;
+    L[row + lane] = P[rr][lane];
+    M[row + lane] = T[rr][lane];
+    if (lane < n2) {
+      L[row + HB + lane] = A2[rr][lane];
+      M[row + HB + lane] = X2[rr][lane];
+    }
   }
 }
-hipError_t launch_diag_inverses(const DevCtx& d, hipStream_t s) {
-  hipLaunchKernelGGL(k_diag_inverses, dim3(d.n), dim3(256), 0, s, d);
-  return hipGetLastError();
-}
-hipError_t launch_potf2(const DevCtx& d, int jb, hipStream_t s) {
-  hipLaunchKernelGGL(k_potf2, dim3(d.n), dim3(256), 0, s, d, jb);
+hipError_t launch_factor_diag(const DevCtx& d, int jb, hipStream_t s) {
+  static LdsRaised raised;
+  const hipError_t e = raise_lds(reinterpret_cast<const void*>(k_factor_diag), FACTOR_LDS, raised);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_factor_diag, dim3(d.n), dim3(256), FACTOR_LDS, s, d, jb);
   return hipGetLastError();
 }
 
