@@ -428,8 +428,18 @@ __global__ __launch_bounds__(256) void k_gemm_reduce(DevCtx d, const GemmDesc* _
   const int64_t total = (int64_t)g.M * g.N;
   for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
     float acc = 0.f;
-    for (int sl = 0; sl < g.ksplit; ++sl) acc += Pp[(int64_t)sl * total + e];
-    int64_t o = (e / g.N) * g.ldc + e % g.N;
+    // eight loads in flight, added in slice order (one at a time, each waited for: 18 us at r = 128, 72 matrices, 15 slices)
+    int sl = 0;
+    for (; sl + 8 <= g.ksplit; sl += 8) {
+      float x[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[i] = Pp[(int64_t)(sl + i) * total + e];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc += x[i];
+    }
+    for (; sl < g.ksplit; ++sl) acc += Pp[(int64_t)sl * total + e];
+    const uint32_t row = (uint32_t)e / (uint32_t)g.N, col = (uint32_t)e - row * (uint32_t)g.N;      // (M N < 2^32: r x r products)
+    int64_t o = (int64_t)row * g.ldc + col;
     float val = g.alpha * acc;
     if (g.beta != 0.f) val = fmaf(g.beta, C[o], val);
     C[o] = val;
