@@ -212,7 +212,7 @@ struct DownFuse {
 hipError_t launch_adam(const float* glow, float* u, float* v, uint16_t* n_hi, uint16_t* n_lo, int64_t nelem,
                        const AdamArgs& a, hipStream_t s);
 hipError_t launch_store_ptrs(void** dst, void* const* host_src, int count, hipStream_t s);
-hipError_t launch_pack_q(const DevCtx& d, int mat_first, int mat_count, hipStream_t s);
+hipError_t launch_pack_q(const DevCtx& d, int mat_first, int mat_count, hipStream_t s, int ybuf = -1);      // ybuf >= 0: Q <- that Y buffer first
 hipError_t launch_identity_q(const DevCtx& d, hipStream_t s);
 hipError_t launch_fill_zero(void* dst, int64_t bytes, hipStream_t s);
 hipError_t launch_bf16_to_f32(float* dst, const uint16_t* src, int64_t n, hipStream_t s);      // exact widening
@@ -238,7 +238,6 @@ hipError_t launch_jacobi_svd(const DevCtx& d, int rmax, bool top_value_only, hip
 hipError_t launch_jacobi_svd_blocked(const DevCtx& d, int rmax, int64_t rank_sq_sum, bool top_value_only, int* flags, hipStream_t s);
 hipError_t launch_rot_pre(const DevCtx& d, const float* u, const float* v, const StepDev* step, hipStream_t s);
 hipError_t launch_rot_post(const DevCtx& d, float* u, float* v, const StepDev* step, hipStream_t s);
-hipError_t launch_q_from_y(const DevCtx& d, int ybuf, hipStream_t s);
 hipError_t launch_y_from_ext(const DevCtx& d, hipStream_t s);
 hipError_t launch_pack_y(const DevCtx& d, int ybuf, hipStream_t s);
 hipError_t launch_pack_block(const DevCtx& d, int zbuf, uint16_t* p_hi, uint16_t* p_lo, hipStream_t s);

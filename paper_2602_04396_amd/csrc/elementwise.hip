@@ -5,7 +5,7 @@
 //   k_pq<MODE>        p x q family: outer step (Alg. 1 OuterOpt; App. A.2, D.4), pseudo-gradient anchor - W
 //                     (App. A.1), anchor copy, and the part of the outer step that does not depend on Delta
 //   k_fold_grad       E <- E + s G, the projection source of the local variant (Alg. 2)
-//   k_pack_q / k_pack_y / k_pack_block / k_split_planes   fp32 -> bf16 hi/lo operand planes in matrix-core order
+//   k_pack_q / k_pack_block / k_split_planes   fp32 -> bf16 hi/lo operand planes in matrix-core order
 //   k_glow_to_z, k_lr_to_plain, k_plain_to_lr, k_lr_exchange, k_tr_exchange   between the operand layout of the low-rank state and plain buffers
 //   k_gram_shift, k_factor_diag   CholeskyQR: diagonal shift, Cholesky of a diagonal block and its inverse
 //   k_jacobi_svd      singular vectors of the Cholesky factor of the r x r Ritz matrix (Rayleigh-Ritz step: basis ordered as in Sec. 2's SVD projection)
@@ -271,96 +271,120 @@ hipError_t launch_identity_q(const DevCtx& d, hipStream_t s) {
   return hipGetLastError();
 }
 
-// One thread writes one 8-element group of the up-projection planes and one of the
-// down-projection planes (both have pp*rp/8 groups).
-__global__ __launch_bounds__(256) void k_pack_q(DevCtx d, int mat_first) {
+// The projection (plain p x r) as bf16 hi / lo planes in operand layout, one 32 x 32 block per wave: read once, 16 bytes per
+// lane, split once, turned through LDS (hi and lo of an element in one word) and written in runs of 512 bytes in both
+// orientations.  HBM-bound.  Before, a thread gathered the eight elements of a group of each orientation for itself: the block
+// was read twice in 4-byte accesses and split twice, with four 64-bit divisions per group.  168 matrices of the 1B
+// set, r = 256: 336 us (5.2 TB/s) for Q and its planes, 596 us and another 203 us for the copy of Y to Q before; 173 us for the
+// planes of Y (269).
+//   PACK_Q          from Q, the planes of both projections
+//   PACK_Q_FROM_Y   Q <- Y (buffer ybuf) on the way.  While a numerical breakdown is latched -- a refresh (or an initial
+//                   projection) whose factorisation met a non-positive pivot -- the projection stays as it was
+//   PACK_Y          range-finder product Z = Src^T Y on the down-projection kernel (it has the shape of g = Q^T G with Y in
+//                   the place of Q): Y into the down-projection planes only; the refresh repacks them when it ends
+enum PackMode { PACK_Q, PACK_Q_FROM_Y, PACK_Y };
+template <int MODE>
+__global__ __launch_bounds__(256) void k_pack_q(DevCtx d, int mat_first, int ybuf) {
   if (mat_skipped(d, mat_first + blockIdx.y)) return;
   const MatDev& m = d.mats[mat_first + blockIdx.y];
-  const float* q32 = reinterpret_cast<const float*>(d.arena + m.q32);
+  const bool renew = MODE == PACK_Q_FROM_Y && *d.flag == 0;
+  float* q32 = reinterpret_cast<float*>(d.arena + m.q32);
+  const float* src = MODE == PACK_Y || renew ? reinterpret_cast<const float*>(d.arena + m.y[ybuf]) : q32;
   uint16_t* qa_hi = reinterpret_cast<uint16_t*>(d.arena + m.qa_hi);
   uint16_t* qa_lo = reinterpret_cast<uint16_t*>(d.arena + m.qa_lo);
   uint16_t* qt_hi = reinterpret_cast<uint16_t*>(d.arena + m.qt_hi);
   uint16_t* qt_lo = reinterpret_cast<uint16_t*>(d.arena + m.qt_lo);
-  int64_t ngroups = (int64_t)m.pp * m.rp / 8;
-  for (int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x; g < ngroups; g += (int64_t)gridDim.x * 256) {
-    uint32_t hi[8], lo[8];
-    {   // up-projection plane: group = (row block, rank octet, row in block)
-      int64_t per_mb = (int64_t)(m.rp / 8) * 32;
-      int64_t mb = g / per_mb, rem = g % per_mb;
-      int64_t k8 = rem / 32, m32 = rem % 32;
-      int64_t row = mb * 32 + m32;
-      for (int e = 0; e < 8; ++e) {
-        int64_t k = k8 * 8 + e;
-        float x = (row < m.p && k < m.r) ? q32[row * m.r + k] : 0.0f;
-        split_bf(x, hi[e], lo[e]);
+  __shared__ __align__(16) uint32_t block[4][32][36];          // hi | lo << 16; one block per wave, no barrier
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t (*blk)[36] = block[w];
+  const uint32_t rt = m.rp / 32, ntiles = (m.pp / 32) * rt;
+  const bool vec = (m.r & 3) == 0;
+  for (uint32_t t = blockIdx.x * 4 + w; t < ntiles; t += gridDim.x * 4) {
+    const int mb = t / rt, ib = t - mb * rt;
+    f32x4n x[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = mb * 32 + 8 * i + (lane >> 3), col = ib * 32 + 4 * (lane & 7);
+      const int64_t at = (int64_t)row * m.r + col;
+      x[i] = f32x4n{0.f, 0.f, 0.f, 0.f};
+      if (row >= m.p || col >= m.r) continue;
+      if (vec) {
+        x[i] = *reinterpret_cast<const f32x4n*>(src + at);
+        if (renew) *reinterpret_cast<f32x4n*>(q32 + at) = x[i];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (col + e < m.r) {
+            x[i][e] = src[at + e];
+            if (renew) q32[at + e] = x[i][e];
+          }
       }
-      uint4 ph = make_uint4(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16), hi[4] | (hi[5] << 16), hi[6] | (hi[7] << 16));
-      uint4 pl = make_uint4(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16), lo[4] | (lo[5] << 16), lo[6] | (lo[7] << 16));
-      *reinterpret_cast<uint4*>(qa_hi + g * 8) = ph;
-      *reinterpret_cast<uint4*>(qa_lo + g * 8) = pl;
     }
-    {   // down-projection plane: group = (rank block, row octet, rank in block)
-      int64_t per_ib = (int64_t)(m.pp / 8) * 32;
-      int64_t ib = g / per_ib, rem = g % per_ib;
-      int64_t k8 = rem / 32, i32 = rem % 32;
-      int64_t i = ib * 32 + i32;
-      for (int e = 0; e < 8; ++e) {
-        int64_t row = k8 * 8 + e;
-        float x = (row < m.p && i < m.r) ? q32[row * m.r + i] : 0.0f;
-        split_bf(x, hi[e], lo[e]);
+    asm volatile("" ::: "memory");                             // a wave's own LDS accesses stay in order
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      u32x4n v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        uint32_t hi, lo;
+        split_bf(x[i][e], hi, lo);
+        v[e] = hi | (lo << 16);
       }
-      uint4 ph = make_uint4(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16), hi[4] | (hi[5] << 16), hi[6] | (hi[7] << 16));
-      uint4 pl = make_uint4(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16), lo[4] | (lo[5] << 16), lo[6] | (lo[7] << 16));
-      *reinterpret_cast<uint4*>(qt_hi + g * 8) = ph;
-      *reinterpret_cast<uint4*>(qt_lo + g * 8) = pl;
+      *reinterpret_cast<u32x4n*>(&blk[8 * i + (lane >> 3)][4 * (lane & 7)]) = v;
+    }
+    asm volatile("" ::: "memory");
+    auto store = [&](uint16_t* p_hi, uint16_t* p_lo, int64_t at, const uint32_t (&v)[8]) {
+      u32x4n ph, pl;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        ph[e] = (v[2 * e] & 0xffffu) | (v[2 * e + 1] << 16);
+        pl[e] = (v[2 * e] >> 16) | (v[2 * e + 1] & 0xffff0000u);
+      }
+      *reinterpret_cast<u32x4n*>(p_hi + at) = ph;
+      *reinterpret_cast<u32x4n*>(p_lo + at) = pl;
+    };
+    const int i32 = lane & 31;
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+      const int k8 = 2 * hf + (lane >> 5);
+      uint32_t v[8];
+      if constexpr (MODE != PACK_Y) {                          // up-projection planes: (row block, rank octet, row in block)
+        const u32x4n v0 = *reinterpret_cast<const u32x4n*>(&blk[i32][8 * k8]), v1 = *reinterpret_cast<const u32x4n*>(&blk[i32][8 * k8 + 4]);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = e < 4 ? v0[e] : v1[e - 4];
+        store(qa_hi, qa_lo, (((int64_t)mb * (m.rp / 8) + ib * 4 + k8) * 32 + i32) * 8, v);
+      }
+#pragma unroll                                                 // down-projection planes: (rank block, row octet, rank in block)
+      for (int e = 0; e < 8; ++e) v[e] = blk[8 * k8 + e][i32];
+      store(qt_hi, qt_lo, (((int64_t)ib * (m.pp / 8) + mb * 4 + k8) * 32 + i32) * 8, v);
     }
   }
 }
-hipError_t launch_pack_q(const DevCtx& d, int mat_first, int mat_count, hipStream_t s) {
+hipError_t launch_pack_q(const DevCtx& d, int mat_first, int mat_count, hipStream_t s, int ybuf) {
   if (mat_count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_pack_q, dim3(128, mat_count), dim3(256), 0, s, d, mat_first);
+  if (ybuf >= 0) hipLaunchKernelGGL(k_pack_q<PACK_Q_FROM_Y>, dim3(128, mat_count), dim3(256), 0, s, d, mat_first, ybuf);
+  else hipLaunchKernelGGL(k_pack_q<PACK_Q>, dim3(128, mat_count), dim3(256), 0, s, d, mat_first, 0);
+  return hipGetLastError();
+}
+hipError_t launch_pack_y(const DevCtx& d, int ybuf, hipStream_t s) {
+  hipLaunchKernelGGL(k_pack_q<PACK_Y>, dim3(128, d.n), dim3(256), 0, s, d, 0, ybuf);
   return hipGetLastError();
 }
 
-// Does nothing while a numerical breakdown is latched: a refresh (or an initial projection) whose factorisation met a
-// non-positive pivot leaves the projection as it was.
-__global__ __launch_bounds__(256) void k_q_from_y(DevCtx d, int ybuf) {
-  if (*d.flag != 0 || mat_skipped(d, blockIdx.y)) return;
-  const MatDev& m = d.mats[blockIdx.y];
-  float* q32 = reinterpret_cast<float*>(d.arena + m.q32);
-  const float* y = reinterpret_cast<const float*>(d.arena + m.y[ybuf]);
-  int64_t total = (int64_t)m.p * m.r;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) q32[i] = y[i];
-}
-// Range-finder product Z = Src^T Y on the down-projection kernel (Alg. 2 of the refresh: the product has the
-// shape of g = Q^T G with Y in the place of Q): Y (plain p x r, buffer ybuf) -> the down-projection operand
-// planes.  The planes hold Q between refreshes; the refresh repacks them from the new Q when it ends.
-__global__ __launch_bounds__(256) void k_pack_y(DevCtx d, int ybuf) {
-  if (mat_skipped(d, blockIdx.y)) return;
-  const MatDev& m = d.mats[blockIdx.y];
-  const float* y = reinterpret_cast<const float*>(d.arena + m.y[ybuf]);
-  uint16_t* qt_hi = reinterpret_cast<uint16_t*>(d.arena + m.qt_hi);
-  uint16_t* qt_lo = reinterpret_cast<uint16_t*>(d.arena + m.qt_lo);
-  const int64_t ngroups = (int64_t)m.pp * m.rp / 8;
-  const int64_t per_ib = (int64_t)(m.pp / 8) * 32;
-  // thread -> (rank block, row octet, rank in block) with the rank fastest: reads of one row are contiguous
-  for (int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x; g < ngroups; g += (int64_t)gridDim.x * 256) {
-    const int64_t ib = g / per_ib, rem = g % per_ib;
-    const int64_t k8 = rem / 32, i = ib * 32 + rem % 32;
-    uint32_t hi[8], lo[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int64_t row = k8 * 8 + e;
-      const float x = (row < m.p && i < m.r) ? y[row * m.r + i] : 0.0f;
-      split_bf(x, hi[e], lo[e]);
-    }
-    *reinterpret_cast<uint4*>(qt_hi + g * 8) = make_uint4(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16), hi[4] | (hi[5] << 16), hi[6] | (hi[7] << 16));
-    *reinterpret_cast<uint4*>(qt_lo + g * 8) = make_uint4(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16), lo[4] | (lo[5] << 16), lo[6] | (lo[7] << 16));
-  }
-}
-hipError_t launch_pack_y(const DevCtx& d, int ybuf, hipStream_t s) {
-  hipLaunchKernelGGL(k_pack_y, dim3(128, d.n), dim3(256), 0, s, d, ybuf);
-  return hipGetLastError();
+// Octet t of a matrix's low-rank state between the blocked layout and plain rows of r: sixteen columns x four octets to a
+// wave, so that the wave touches runs of 512 bytes of the one and of 128 bytes of the other.  1B set: k_glow_to_z 435 -> 222 us
+// (it went element by element), k_rot_pre 457 -> 433 us and k_rot_post 483 -> 452 us (32 x 1 and 1 x 64 octets to a wave).
+struct LowRankOctet {
+  uint32_t j, i8;         // column, rank octet
+  int64_t flat;           // element offset in the blocked array of the matrix
+};
+__device__ __forceinline__ LowRankOctet low_rank_octet(uint32_t t, uint32_t rp) {
+  const uint32_t quads = rp / 32, blk = t >> 7, jb = blk / quads, jj = (t & 127) >> 2;
+  LowRankOctet o;
+  o.j = jb * 32 + jj;
+  o.i8 = (blk - jb * quads) * 4 + (t & 3);
+  o.flat = ((int64_t)(jb * (rp / 8) + o.i8) * 32 + jj) * 8;
+  return o;
 }
 // The result of that product, left by the down-projection kernel in the layout of g (split-K slices
 // included), as the plain q x r block Z: Z[j][i] = sum over slices of g(i, j), slices added in order.
@@ -372,17 +396,29 @@ __global__ __launch_bounds__(256) void k_glow_to_z(DevCtx d, const float* __rest
 #pragma unroll
   for (int i = 1; i < 4; ++i)
     if (m.lr_off >= a.grp_start[i]) nsplit = a.grp_nsplit[i];
-  const int64_t total = (int64_t)m.q * m.r;
-  for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
-    const int64_t j = t / m.r, i = t % m.r;
-    const int64_t src = m.lr_off + bl_index(j, i, m.rp);
-    float acc = glow[src];
-    for (int sp = 1; sp < nsplit; ++sp) acc += glow[src + sp * a.split_stride];
-    z[t] = acc;
+  const uint32_t ngroups = (uint32_t)((int64_t)m.qp * m.rp / 8);
+  const bool vec = (m.r & 3) == 0;
+  for (uint32_t t = blockIdx.x * 256 + threadIdx.x; t < ngroups; t += gridDim.x * 256) {
+    const LowRankOctet o = low_rank_octet(t, m.rp);
+    const int i0 = (int)o.i8 * 8;
+    if ((int)o.j >= m.q || i0 >= m.r) continue;
+    const float* src = glow + m.lr_off + o.flat;
+    f32x4n a0 = *reinterpret_cast<const f32x4n*>(src), a1 = *reinterpret_cast<const f32x4n*>(src + 4);
+    for (int sp = 1; sp < nsplit; ++sp) {
+      a0 += *reinterpret_cast<const f32x4n*>(src + sp * a.split_stride);
+      a1 += *reinterpret_cast<const f32x4n*>(src + sp * a.split_stride + 4);
+    }
+    float* dst = z + (int64_t)o.j * m.r + i0;
+    if (vec && i0 + 8 <= m.r) {
+      *reinterpret_cast<f32x4n*>(dst) = a0;
+      *reinterpret_cast<f32x4n*>(dst + 4) = a1;
+    } else {
+      for (int e = 0; e < 8 && i0 + e < m.r; ++e) dst[e] = e < 4 ? a0[e] : a1[e - 4];
+    }
   }
 }
 hipError_t launch_glow_to_z(const DevCtx& d, const float* glow, int zbuf, const AdamArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_glow_to_z, dim3(64, d.n), dim3(256), 0, s, d, glow, zbuf, a);
+  hipLaunchKernelGGL(k_glow_to_z, dim3(256, d.n), dim3(256), 0, s, d, glow, zbuf, a);
   return hipGetLastError();
 }
 // The q x r block of the products Y = Src B (B = Omega from the caller's table when zbuf < 0, else the
@@ -425,10 +461,6 @@ __global__ __launch_bounds__(256) void k_y_from_ext(DevCtx d) {
 }
 hipError_t launch_y_from_ext(const DevCtx& d, hipStream_t s) {
   hipLaunchKernelGGL(k_y_from_ext, dim3(128, d.n), dim3(256), 0, s, d);
-  return hipGetLastError();
-}
-hipError_t launch_q_from_y(const DevCtx& d, int ybuf, hipStream_t s) {
-  hipLaunchKernelGGL(k_q_from_y, dim3(128, d.n), dim3(256), 0, s, d, ybuf);
   return hipGetLastError();
 }
 
@@ -1483,14 +1515,13 @@ __global__ __launch_bounds__(256) void k_rot_pre(DevCtx d, const float* __restri
   const MatDev& m = d.mats[blockIdx.y];
   float* uh = reinterpret_cast<float*>(d.arena + m.zw[2]);
   float* var = reinterpret_cast<float*>(d.arena + m.zw[3]);
-  const int64_t octets = m.rp / 8;                     // rank octets per column; a multiple of 4
-  const int64_t ngroups = (int64_t)m.qp * octets;
+  const uint32_t ngroups = (uint32_t)((int64_t)m.qp * m.rp / 8);
   const bool vec = (m.r & 3) == 0;
-  for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < ngroups; t += (int64_t)gridDim.x * 256) {
-    // t = (column * octets/4 + octet quad) * 4 + octet in quad: four neighbours share a column
-    const int64_t j = t / octets, i8 = t % octets;
+  for (uint32_t t = blockIdx.x * 256 + threadIdx.x; t < ngroups; t += gridDim.x * 256) {
+    const LowRankOctet o = low_rank_octet(t, m.rp);
+    const int64_t j = o.j, i8 = o.i8;
     if (j >= m.q || i8 * 8 >= m.r) continue;
-    const int64_t src = m.lr_off + (((j >> 5) * octets + i8) * 32 + (j & 31)) * 8;
+    const int64_t src = m.lr_off + o.flat;
     const f32x4n u0 = *reinterpret_cast<const f32x4n*>(u + src), u1 = *reinterpret_cast<const f32x4n*>(u + src + 4);
     const f32x4n v0 = *reinterpret_cast<const f32x4n*>(v + src), v1 = *reinterpret_cast<const f32x4n*>(v + src + 4);
     const f32x4n a0 = u0 * inv_c1, a1 = u1 * inv_c1;
@@ -1517,12 +1548,11 @@ __global__ __launch_bounds__(256) void k_rot_post(DevCtx d, float* __restrict__ 
   const MatDev& m = d.mats[blockIdx.y];
   const float* a1 = reinterpret_cast<const float*>(d.arena + m.zw[0]);
   const float* a2 = reinterpret_cast<const float*>(d.arena + m.zw[1]);
-  int64_t ngroups = (int64_t)m.qp * m.rp / 8;
-  int64_t per_jb = (int64_t)(m.rp / 8) * 32;
+  const uint32_t ngroups = (uint32_t)((int64_t)m.qp * m.rp / 8);
   const bool vec = (m.r & 3) == 0;
-  for (int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x; g < ngroups; g += (int64_t)gridDim.x * 256) {
-    int64_t jb = g / per_jb, rem = g % per_jb;
-    int64_t i8 = rem / 32, j = jb * 32 + rem % 32;
+  for (uint32_t t = blockIdx.x * 256 + threadIdx.x; t < ngroups; t += gridDim.x * 256) {
+    const LowRankOctet o = low_rank_octet(t, m.rp);
+    const int64_t j = o.j, i8 = o.i8;
     f32x4n ru[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}}, rv[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
     if (j < m.q && i8 * 8 < m.r) {
       const int64_t src = j * m.r + i8 * 8;
@@ -1539,8 +1569,8 @@ __global__ __launch_bounds__(256) void k_rot_post(DevCtx d, float* __restrict__ 
       f32x4n un = ru[h] * c1, vn;
 #pragma unroll
       for (int e = 0; e < 4; ++e) vn[e] = c2 * fabsf(rv[h][e] + ru[h][e] * ru[h][e]);
-      *reinterpret_cast<f32x4n*>(u + m.lr_off + g * 8 + 4 * h) = un;
-      *reinterpret_cast<f32x4n*>(v + m.lr_off + g * 8 + 4 * h) = vn;
+      *reinterpret_cast<f32x4n*>(u + m.lr_off + o.flat + 4 * h) = un;
+      *reinterpret_cast<f32x4n*>(v + m.lr_off + o.flat + 4 * h) = vn;
     }
   }
 }

@@ -26,7 +26,7 @@ namespace {
     }                                                                                             \
   } while (0)
 
-enum OpKind : int { OP_GEMM, OP_SHIFT, OP_FACTOR_DIAG, OP_ROT_PRE, OP_ROT_POST, OP_Q_FROM_Y, OP_PACK, OP_Y_FROM_EXT, OP_JSVD, OP_FROB, OP_GRAM_DIAG };
+enum OpKind : int { OP_GEMM, OP_SHIFT, OP_FACTOR_DIAG, OP_ROT_PRE, OP_ROT_POST, OP_PACK, OP_Y_FROM_EXT, OP_JSVD, OP_FROB, OP_GRAM_DIAG };
 
 struct Op {
   int kind;
@@ -34,7 +34,7 @@ struct Op {
   int tile = 64;                    // OP_GEMM: workgroup tile edge (64 or 128)
   int desc_first = 0, ndescs = 0;   // OP_GEMM: descriptors of this launch
   bool split = false;               // OP_GEMM: split-K launch, followed by the slice reduction
-  int iarg = 0;                     // OP_FACTOR_DIAG: block index; OP_Q_FROM_Y: y buffer
+  int iarg = 0;                     // OP_FACTOR_DIAG: block index; OP_PACK: y buffer that becomes Q, -1: Q stays
   float farg = 0.f;                 // OP_SHIFT: coefficient
   bool rot_only = false;            // part of the moment rotation (skipped while t == 0)
   int fast = 0;                     // OP_GEMM: 1 = the product Z = Src^T Y, which the down-projection kernel can take over (iarg: y buffer);
@@ -377,8 +377,7 @@ struct ProgramBuilder {
     saved.swap(P.ops);
     simple(OP_Y_FROM_EXT);
     const int ycur = orth(true, 0, passes, passes >= 3 ? 2 : 1);
-    simple(OP_Q_FROM_Y, ycur);
-    simple(OP_PACK);
+    simple(OP_PACK, ycur);
     P.init_ops.swap(P.ops);
     P.ops.swap(saved);
   }
@@ -457,7 +456,7 @@ struct ProgramBuilder {
     simple(OP_SHIFT, 1, 32.f * 5.9604645e-8f);
     factor(max_blocks_all());
     simple(OP_JSVD, 1);                 // largest singular value only
-    simple(OP_PACK);                    // the Z products borrowed the operand planes of Q
+    simple(OP_PACK, -1);                // the Z products borrowed the operand planes of Q
     P.gap_ops.swap(P.ops);
     P.ops.swap(saved);
   }
@@ -610,8 +609,7 @@ struct ProgramBuilder {
         return true;
       }, true, false, false, shared_b);
     simple(OP_ROT_POST, 0, 0.f, true);
-    simple(OP_Q_FROM_Y, ycur);
-    simple(OP_PACK);
+    simple(OP_PACK, ycur);
     shared_b = false;
   }
 };
@@ -1438,8 +1436,7 @@ static int run_ops(lordo_ctx* c, const std::vector<Op>& ops, int32_t src_dtype, 
       case OP_ROT_POST:
         HIPCHK(launch_rot_post(c->dev, c->at<float>(P.u), c->at<float>(P.v), c->at<StepDev>(P.step), s));
         break;
-      case OP_Q_FROM_Y: HIPCHK(launch_q_from_y(c->dev, op.iarg, s)); break;
-      case OP_PACK: HIPCHK(launch_pack_q(c->dev, 0, c->n, s)); break;
+      case OP_PACK: HIPCHK(launch_pack_q(c->dev, 0, c->n, s, op.iarg)); break;
       case OP_Y_FROM_EXT:
         if (c->gauss_init) HIPCHK(launch_gauss_block(c->dev, 0, c->hp.seed, c->draws, s));
         else HIPCHK(launch_y_from_ext(c->dev, s));
