@@ -151,12 +151,16 @@ __device__ __forceinline__ void gemm_loop(f32x16 (&acc)[WB][WB], const Operand<T
 // of the range finder's block sit in the noise of the source, where gaps between singular values are
 // of the order of a percent, and a 2^-16 perturbation moved the subspace by up to 9e-4 in Frobenius
 // norm of the projector, against 3e-5 for fp32 arithmetic.
-// Plane element (i, k) of a TMN x 32 tile: ((i/32)*4 + k/8) * 264 + (i%32)*8 + k%8 (eight elements
-// of padding per 32 x 8 group spread the groups over the LDS banks).
+// Plane element (i, k) of a TMN x 32 tile: (i/32) * FRAG_BLOCK + (k/8) * 264 + (i%32)*8 + k%8 (eight elements
+// of padding per 32 x 8 group and eight more per 32 x 32 block).  The 8-byte writes of a wave then meet at most twice in a bank,
+// the least there is: the lanes of a transposed patch lie four rows (64 bytes) apart, eight to a block, so the blocks have to be
+// 16 bytes off (they met eight times without), and rows contiguous in k are dealt out four apart (four times).  28 matrices,
+// r = 512, 4096 .. 11008 rows: Gram matrices 674 -> 476 us, R = Q_new^T Q 862 -> 611 us; 72 matrices of 768 .. 3072, r = 128: 48 -> 41 us.
 // ---------------------------------------------------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-__device__ __forceinline__ int frag_index(int i, int k) { return ((i >> 5) * 4 + (k >> 3)) * 264 + (i & 31) * 8 + (k & 7); }
+constexpr int FRAG_BLOCK = 4 * 264 + 8;      // elements per 32 x 32 block
+__device__ __forceinline__ int frag_index(int i, int k) { return (i >> 5) * FRAG_BLOCK + (k >> 3) * 264 + (i & 31) * 8 + (k & 7); }
 
 // Operand tile of the split-bf16 loop; whole-vector access only (the caller falls back to the fp32
 // loop otherwise).  A thread owns up to four vectors of four elements; along k they pack directly,
@@ -177,8 +181,8 @@ struct OperandBF {
   __device__ __forceinline__ bool coords(int tid, int n, int& ii, int& kk) const {
     if (kfast) {
       if (n >= NVK) return false;
-      const int v = tid + n * 256;
-      kk = (v & 7) * 4; ii = v >> 3;
+      kk = (tid & 7) * 4;
+      ii = n * 32 + ((tid >> 1) & 28) + (tid >> 6);          // the eight rows of a wave lie four apart
       return true;
     }
     if (tid >= TMN * 2) return false;           // TMN/4 i-quads x 8 k-quads patches
@@ -280,7 +284,7 @@ struct OperandBF {
 template <int WB, bool A_BF16, int TM>
 __device__ __forceinline__ void gemm_loop_bf(f32x16 (&acc)[WB][WB], const OperandBF<TM>& opA, const OperandBF<TM>& opB,
                                              uint16_t* lds, int kbeg, int K, int tid, int lane, int wm, int wn, bool same_ab) {
-  constexpr int PLANE = (TM / 32) * 4 * 264;                   // elements
+  constexpr int PLANE = (TM / 32) * FRAG_BLOCK;                   // elements
   constexpr int NA = A_BF16 ? 1 : 3;                           // planes of A; B always has three
   uint16_t* PA = lds;
   uint16_t* PB = (!A_BF16 && same_ab) ? lds : lds + NA * PLANE;
@@ -352,11 +356,11 @@ __global__ __launch_bounds__(256) void k_gemm32(DevCtx d, const GemmDesc* __rest
   float* C2 = g.C2.off >= 0 ? reinterpret_cast<float*>(const_cast<char*>(resolve(d, g.C2, g.mat))) : nullptr;
 
   // As | Bs of the fp32 loop, or up to six bf16 planes of the split loop
-  constexpr int LDS_FLOATS = 2 * TK * PITCH > 3 * (TM / 32) * 4 * 264 ? 2 * TK * PITCH : 3 * (TM / 32) * 4 * 264;
+  constexpr int LDS_FLOATS = 2 * TK * PITCH > 3 * (TM / 32) * FRAG_BLOCK ? 2 * TK * PITCH : 3 * (TM / 32) * FRAG_BLOCK;
   __shared__ __attribute__((aligned(16))) float lds_raw[LDS_FLOATS];
   float (*As)[PITCH] = reinterpret_cast<float (*)[PITCH]>(lds_raw);
   float (*Bs)[PITCH] = reinterpret_cast<float (*)[PITCH]>(lds_raw + TK * PITCH);
-  static_assert(sizeof(lds_raw) >= sizeof(uint16_t) * 6 * (TM / 32) * 4 * 264, "six bf16 planes must fit");
+  static_assert(sizeof(lds_raw) >= sizeof(uint16_t) * 6 * (TM / 32) * FRAG_BLOCK, "six bf16 planes must fit");
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
