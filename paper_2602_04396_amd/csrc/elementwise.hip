@@ -893,7 +893,8 @@ __device__ __forceinline__ float lane_value(float x, int lane) {
 //   - Products and the inverse below the 16 x 16 diagonal blocks run on the fp32 matrix cores (16 x 16 x 4).
 //   - The loops over halves and column blocks stay rolled: an unrolled chain is tens of KiB of code, fetched anew by every
 //     launch.
-// 72 matrices, r = 128: 48 us.  It replaces two launches of a 64-wide kernel with a barrier per column (41.7 us each), two
+// 72 matrices, r = 128: 40 us (of 97 thousand cycles: loads 7, four panels and their updates 24 in each half, inverse of a half 7,
+// the products between and behind the halves 20, stores 5).  It replaces two launches of a 64-wide kernel with a barrier per column (41.7 us each), two
 // panel and two inverse products (9 us each) and the copy of the inverses to their places (9.4 us), 129 us in all.
 typedef float f32x4m __attribute__((ext_vector_type(4)));
 constexpr int HB = 64;                // edge of a half
@@ -1017,7 +1018,7 @@ __device__ __forceinline__ void mul_half(f32x4m (&acc)[4], LdsTile A, LdsTile B,
   const int c = lane & 15, h = lane >> 4;
 #pragma unroll
   for (int n = 0; n < 4; ++n) acc[n] = f32x4m{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
+#pragma unroll 8
   for (int s = 0; s < 16; ++s) {
     const float av = A[16 * w + c][4 * s + h];
 #pragma unroll
@@ -1047,15 +1048,26 @@ __global__ __launch_bounds__(256) void k_factor_diag(DevCtx d, int jb) {
   const int c = lane & 15, h = lane >> 4;
   const int n1 = nbk < HB ? nbk : HB, n2 = nbk - n1;
   if (tid == 0) bad_s = 0;
-  // rows are read coalesced; identity outside the block
-#pragma unroll 4
-  for (int rr = w; rr < HB; rr += 4) A1[rr][lane] = rr < n1 && lane <= rr ? S[(int64_t)rr * r + lane] : (rr == lane ? 1.f : 0.f);
-  if (n2 > 0) {
-#pragma unroll 4
-    for (int rr = w; rr < HB; rr += 4) {
-      const float* row = S + (int64_t)(HB + rr) * r;
-      P[rr][lane] = rr < n2 ? row[lane] : 0.f;
-      A2[rr][lane] = rr < n2 && lane <= rr ? row[HB + lane] : (rr == lane ? 1.f : 0.f);
+  // Rows are read coalesced, identity outside the block.  All loads are requested before the first is used (element 0 in the
+  // place of what is not read): row by row, each waited for, they took 11 of the launch's 49 us.
+  {
+    float s11[HB / 4], s21[HB / 4], s22[HB / 4];
+#pragma unroll
+    for (int i = 0; i < HB / 4; ++i) {
+      const int rr = w + 4 * i;
+      s11[i] = S[rr < n1 && lane <= rr ? (int64_t)rr * r + lane : 0];
+      const int64_t row = rr < n2 ? (int64_t)(HB + rr) * r : 0;
+      s21[i] = S[row + (rr < n2 ? lane : 0)];
+      s22[i] = S[row + (rr < n2 && lane <= rr ? HB + lane : 0)];
+    }
+    asm volatile("" ::: "memory");                   // the loads stay ahead of the first use
+#pragma unroll
+    for (int i = 0; i < HB / 4; ++i) {
+      const int rr = w + 4 * i;
+      const float diag = rr == lane ? 1.f : 0.f;
+      A1[rr][lane] = rr < n1 && lane <= rr ? s11[i] : diag;
+      P[rr][lane] = rr < n2 ? s21[i] : 0.f;
+      A2[rr][lane] = rr < n2 && lane <= rr ? s22[i] : diag;
     }
   }
   __syncthreads();
@@ -1092,18 +1104,22 @@ __global__ __launch_bounds__(256) void k_factor_diag(DevCtx d, int jb) {
     __syncthreads();
   }
   if (tid == 0 && bad_s) *d.flag = 1;
-  for (int rr = w; rr < n1; rr += 4)
-    if (lane < n1) {
-      L[(int64_t)rr * r + lane] = A1[rr][lane];
-      M[(int64_t)rr * r + lane] = X1[rr][lane];
+#pragma unroll 4
+  for (int i = 0; i < HB / 4; ++i) {
+    const int rr = w + 4 * i;
+    const int64_t row1 = (int64_t)rr * r, row2 = (int64_t)(HB + rr) * r;
+    const float l11 = A1[rr][lane], x11 = X1[rr][lane];
+    if (rr < n1 && lane < n1) {
+      L[row1 + lane] = l11;
+      M[row1 + lane] = x11;
     }
-  for (int rr = w; rr < n2; rr += 4) {
-    const int64_t row = (int64_t)(HB + rr) * r;
-    L[row + lane] = P[rr][lane];
-    M[row + lane] = T[rr][lane];
-    if (lane < n2) {
-      L[row + HB + lane] = A2[rr][lane];
-      M[row + HB + lane] = X2[rr][lane];
+    if (rr < n2) {
+      L[row2 + lane] = P[rr][lane];
+      M[row2 + lane] = T[rr][lane];
+      if (lane < n2) {
+        L[row2 + HB + lane] = A2[rr][lane];
+        M[row2 + HB + lane] = X2[rr][lane];
+      }
     }
   }
 }
