@@ -41,6 +41,7 @@ struct MatDev {
   int64_t y[2];           // fp32 p x r, ping-pong of the orthonormalisation
   int64_t zw[4];          // fp32 q x r; zw[0], zw[1] ping-pong of the q-side block, all four rotation temporaries
   int64_t gram, lfac;     // fp32 r x r : Gram matrix (consumed by the factorisation) and its Cholesky factor
+  int64_t dinv;           // fp32 ceil(r/NB_INIT) blocks of NB_INIT x NB_INIT : inverses of the diagonal blocks (initial projection)
   int64_t minv;           // fp32 r x r : inverse of the whole factor, lower triangular (zeros above the diagonal are never written)
   int64_t rot, rot2;      // fp32 r x r : R = Q_new^T Q_old and its elementwise square
   int64_t part;           // fp32 split-K partial sums of the r x r products (Gram, R): slices x r x r
@@ -109,7 +110,8 @@ __device__ __forceinline__ bool mat_skipped(const DevCtx& d, int mat) {
 }
 
 constexpr int CHUNK = 2048;       // elements per workgroup of the p x q elementwise kernels
-constexpr int NB = 128;           // Cholesky block size
+constexpr int NB = 128;           // Cholesky block size of the refresh programs
+constexpr int NB_INIT = 64;       // ... of the initial projection
 
 // ---------------------------------------------------------------------------------------
 // launchers (each defined in one .hip file)
@@ -232,6 +234,8 @@ hipError_t launch_gram_shift(const DevCtx& d, float coef, bool store, hipStream_
 hipError_t launch_gram_diag(const DevCtx& d, int which, int rmax, int part_slices, hipStream_t s);
 hipError_t launch_mssv(const DevCtx& d, float* out, hipStream_t s);
 hipError_t launch_factor_diag(const DevCtx& d, int jb, hipStream_t s);
+hipError_t launch_potf2(const DevCtx& d, int jb, hipStream_t s);
+hipError_t launch_diag_inverses(const DevCtx& d, hipStream_t s);
 hipError_t launch_frob2(const DevCtx& d, const int64_t* chunk_start, int64_t nchunks, float* partial, bool src_f32, hipStream_t s);
 hipError_t launch_stable_rank(const DevCtx& d, float* out, int which, hipStream_t s);
 hipError_t launch_jacobi_svd(const DevCtx& d, int rmax, bool top_value_only, hipStream_t s);

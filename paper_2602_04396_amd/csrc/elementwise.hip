@@ -7,7 +7,7 @@
 //   k_fold_grad       E <- E + s G, the projection source of the local variant (Alg. 2)
 //   k_pack_q / k_pack_block / k_split_planes   fp32 -> bf16 hi/lo operand planes in matrix-core order
 //   k_glow_to_z, k_lr_to_plain, k_plain_to_lr, k_lr_exchange, k_tr_exchange   between the operand layout of the low-rank state and plain buffers
-//   k_gram_shift, k_factor_diag   CholeskyQR: diagonal shift, Cholesky of a diagonal block and its inverse
+//   k_gram_shift, k_factor_diag   CholeskyQR: diagonal shift, Cholesky of a diagonal block and its inverse (k_potf2, k_diag_inverses: of the initial projection)
 //   k_jacobi_svd      singular vectors of the Cholesky factor of the r x r Ritz matrix (Rayleigh-Ritz step: basis ordered as in Sec. 2's SVD projection)
 //   k_frob2_chunks / k_frob2_sum / k_stable_rank   squared Frobenius norm of the refresh source and its stable rank (Sec. 5.1)
 //   k_rot_pre / k_rot_post, k_mssv   elementwise parts of the moment rotation (Alg. 1 rotation lines); similarity diagnostic (Sec. 5.1)
@@ -879,6 +879,137 @@ hipError_t launch_gram_shift(const DevCtx& d, float coef, bool store, hipStream_
 // value of x in lane `lane` (uniform over the wave), as a scalar
 __device__ __forceinline__ float lane_value(float x, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
+}
+
+// The initial projection is drawn from a seed and every later state of a run follows from it, so its bits are kept: it is
+// factored 64 columns at a time by this kernel, in the order of operations it always had (a last-bit change of Q_0 moves the
+// weights by 6e-6 relative after three steps, where the normalised update of a nearly cancelled gradient element turns over).
+// It runs once per run, 42 us per block of 64; the refreshes, hundreds per run, take k_factor_diag.
+// Diagonal block jb: L = chol(S_jj) (lower), X = L^{-1}; one workgroup per matrix, lane = row, wave w holds columns
+// 16 w .. 16 w + 15 in registers, one barrier per column; the inverse by forward substitution in one wave.
+__global__ __launch_bounds__(256) void k_potf2(DevCtx d, int jb) {
+  if (mat_skipped(d, blockIdx.x)) return;
+  const MatDev& m = d.mats[blockIdx.x];
+  const int o = jb * NB_INIT;
+  int nbk = m.r - o;
+  if (nbk <= 0) return;
+  if (nbk > NB_INIT) nbk = NB_INIT;
+  const float* S = reinterpret_cast<const float*>(d.arena + m.gram);
+  float* L = reinterpret_cast<float*>(d.arena + m.lfac);
+  float* X = reinterpret_cast<float*>(d.arena + m.dinv) + (int64_t)jb * NB_INIT * NB_INIT;
+  static_assert(NB_INIT == 64, "four waves of sixteen columns each");
+  __shared__ float tile[NB_INIT][NB_INIT + 1];
+  __shared__ __align__(16) float lrow[NB_INIT][NB_INIT];       // the factor, rows 16-byte aligned: operand of the inversion
+  __shared__ __align__(16) float ccol[2][NB_INIT];        // column k of the factor with entries <= k zeroed (multipliers of step k)
+  __shared__ float crow[2][NB_INIT];                      // column k of the factor (every row's own factor)
+  __shared__ float red[4];
+  __shared__ int bad_s;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // rows are read coalesced and handed to their lanes through LDS; identity outside the block
+  for (int rr = w; rr < NB_INIT; rr += 4) {
+    float val;
+    if (rr < nbk && lane < nbk) val = lane <= rr ? S[(int64_t)(o + rr) * m.r + (o + lane)] : 0.f;
+    else val = rr == lane ? 1.f : 0.f;
+    tile[rr][lane] = val;
+  }
+  if (tid == 0) bad_s = 0;
+  __syncthreads();
+  // lane = row, wave w holds columns 16 w .. 16 w + 15 of it
+  float a[16];
+#pragma unroll
+  for (int jc = 0; jc < 16; ++jc) a[jc] = tile[lane][16 * w + jc];
+  float dmax = lane < nbk ? tile[lane][lane] : 0.f;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) dmax = fmaxf(dmax, __shfl_xor(dmax, off));
+  const float floor_piv = 1e-12f * dmax + 1e-37f;
+  // right-looking Cholesky, one barrier per column: the wave that holds column k scales it and leaves it in LDS (two
+  // buffers alternate, so the next column can be written while this one is still being read); every wave then updates
+  // its sixteen columns, a[j] -= L[i][k] L[j][k], with the multipliers L[j][k] read as broadcasts (zero for j <= k, which
+  // leaves the finished columns alone)
+#pragma clang loop unroll(full)
+  for (int k = 0; k < NB_INIT; ++k) {
+    const int buf = k & 1;
+    if (w == k / 16) {
+      float piv = lane_value(a[k % 16], k);
+      if (!(piv > floor_piv)) {
+        if (lane == 0) bad_s = 1;
+        piv = floor_piv;
+      }
+      const float dd = sqrtf(piv);
+      const float lk = lane == k ? dd : (lane > k ? a[k % 16] / dd : 0.f);
+      a[k % 16] = lk;
+      crow[buf][lane] = lk;
+      ccol[buf][lane] = lane > k ? lk : 0.f;
+    }
+    __syncthreads();
+    if (16 * w + 15 > k) {                           // this wave still has columns to the right of k
+      const float mine = crow[buf][lane];
+      const f32x4n* cp = reinterpret_cast<const f32x4n*>(&ccol[buf][16 * w]);
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        const f32x4n cv = cp[g4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[4 * g4 + e] = fmaf(-mine, cv[e], a[4 * g4 + e]);
+      }
+    }
+  }
+  // the factor to LDS (zeros above the diagonal): for the inversion and for the coalesced store
+#pragma unroll
+  for (int jc = 0; jc < 16; ++jc) {
+    const int j = 16 * w + jc;
+    const float v = j <= lane ? a[jc] : 0.f;
+    lrow[lane][j] = v;
+    tile[lane][j] = v;
+  }
+  __syncthreads();
+  if (w == 0) {
+    // X = L^{-1} by forward substitution: lane j builds column j, x[i] = X[i][j]; row i of L is read as broadcasts
+    float x[NB_INIT];
+#pragma clang loop unroll(full)
+    for (int i = 0; i < NB_INIT; ++i) {
+      // four partial sums: the FMA chain of a row is split so that consecutive terms overlap
+      float acc[4] = {lane == i ? 1.f : 0.f, 0.f, 0.f, 0.f};
+      const f32x4n* lp = reinterpret_cast<const f32x4n*>(&lrow[i][0]);
+#pragma clang loop unroll(full)
+      for (int g4 = 0; g4 < NB_INIT / 4; ++g4) {
+        if (4 * g4 < i) {
+          const f32x4n lv = lp[g4];
+#pragma clang loop unroll(full)
+          for (int e = 0; e < 4; ++e)
+            if (4 * g4 + e < i) acc[e] = fmaf(-lv[e], x[4 * g4 + e], acc[e]);
+        }
+      }
+      x[i] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) / lrow[i][i];
+    }
+#pragma unroll
+    for (int i = 0; i < NB_INIT; ++i) X[i * NB_INIT + lane] = lane <= i ? x[i] : 0.f;
+  }
+  if (tid == 0 && bad_s) *d.flag = 1;
+  for (int rr = w; rr < nbk; rr += 4)
+    if (lane < nbk) L[(int64_t)(o + rr) * m.r + (o + lane)] = tile[rr][lane];
+}
+// The inverses of the diagonal blocks, copied to their places on the diagonal of the r x r inverse of the
+// whole factor (the rows below are then built from them by products).
+__global__ __launch_bounds__(256) void k_diag_inverses(DevCtx d) {
+  if (mat_skipped(d, blockIdx.x)) return;
+  const MatDev& m = d.mats[blockIdx.x];
+  const float* X = reinterpret_cast<const float*>(d.arena + m.dinv);
+  float* M = reinterpret_cast<float*>(d.arena + m.minv);
+  const int nblocks = (m.r + NB_INIT - 1) / NB_INIT;
+  for (int t = threadIdx.x; t < nblocks * NB_INIT * NB_INIT; t += 256) {
+    const int jb = t / (NB_INIT * NB_INIT), i = (t / NB_INIT) % NB_INIT, j = t % NB_INIT;
+    const int row = jb * NB_INIT + i, col = jb * NB_INIT + j;
+    if (row < m.r && col < m.r) M[(int64_t)row * m.r + col] = X[t];
+  }
+}
+hipError_t launch_diag_inverses(const DevCtx& d, hipStream_t s) {
+  hipLaunchKernelGGL(k_diag_inverses, dim3(d.n), dim3(256), 0, s, d);
+  return hipGetLastError();
+}
+hipError_t launch_potf2(const DevCtx& d, int jb, hipStream_t s) {
+  hipLaunchKernelGGL(k_potf2, dim3(d.n), dim3(256), 0, s, d, jb);
+  return hipGetLastError();
 }
 
 // Diagonal block jb (up to 128 x 128) of the Gram matrix: L = chol(S_jj) (lower) into the factor and X = L^{-1} onto the

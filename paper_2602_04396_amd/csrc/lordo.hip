@@ -26,7 +26,7 @@ namespace {
     }                                                                                             \
   } while (0)
 
-enum OpKind : int { OP_GEMM, OP_SHIFT, OP_FACTOR_DIAG, OP_ROT_PRE, OP_ROT_POST, OP_PACK, OP_Y_FROM_EXT, OP_JSVD, OP_FROB, OP_GRAM_DIAG };
+enum OpKind : int { OP_GEMM, OP_SHIFT, OP_FACTOR_DIAG, OP_POTF2, OP_DIAG_INV, OP_ROT_PRE, OP_ROT_POST, OP_PACK, OP_Y_FROM_EXT, OP_JSVD, OP_FROB, OP_GRAM_DIAG };
 
 struct Op {
   int kind;
@@ -34,7 +34,7 @@ struct Op {
   int tile = 64;                    // OP_GEMM: workgroup tile edge (64 or 128)
   int desc_first = 0, ndescs = 0;   // OP_GEMM: descriptors of this launch
   bool split = false;               // OP_GEMM: split-K launch, followed by the slice reduction
-  int iarg = 0;                     // OP_FACTOR_DIAG: block index; OP_PACK: y buffer that becomes Q, -1: Q stays
+  int iarg = 0;                     // OP_FACTOR_DIAG, OP_POTF2: block index; OP_PACK: y buffer that becomes Q, -1: Q stays
   float farg = 0.f;                 // OP_SHIFT: coefficient
   bool rot_only = false;            // part of the moment rotation (skipped while t == 0)
   int fast = 0;                     // OP_GEMM: 1 = the product Z = Src^T Y, which the down-projection kernel can take over (iarg: y buffer);
@@ -269,14 +269,17 @@ struct ProgramBuilder {
   // Cholesky factor of the Gram matrix of every matrix, block column by block column (NB-wide: diagonal block by
   // k_factor_diag, two grouped GEMMs for the panel and the trailing update); the Gram buffer is consumed, the factor
   // goes to its own buffer, the inverses of the diagonal blocks to their places in that of the whole factor.
+  bool initial = false;             // the program of the initial projection: factored in blocks of 64 by the kernels that keep its bits
+  int nb() const { return initial ? NB_INIT : NB; }
   int max_blocks_all() const {
     int mb = 0;
-    for (int i = 0; i < n; ++i) mb = std::max(mb, (P.mat[i].r + NB - 1) / NB);
+    for (int i = 0; i < n; ++i) mb = std::max(mb, (P.mat[i].r + nb() - 1) / nb());
     return mb;
   }
   void factor(int max_blocks) {
+    const int NB = nb();
     for (int jb = 0; jb < max_blocks; ++jb) {
-      simple(OP_FACTOR_DIAG, jb);
+      simple(initial ? OP_POTF2 : OP_FACTOR_DIAG, jb);
       // L_21 = S_21 L_11^{-T}
       gemm([&](int i, GemmDesc& g) {
         const MatDev& m = P.mat[i];
@@ -284,10 +287,11 @@ struct ProgramBuilder {
         if (rest <= 0) return false;
         int64_t o = ((int64_t)(jb + 1) * NB * m.r + (int64_t)jb * NB) * 4;
         g.A = ref_arena(m.gram + o); g.sAm = m.r; g.sAk = 1;
-        g.B = ref_arena(m.minv + ((int64_t)jb * NB * m.r + (int64_t)jb * NB) * 4); g.sBk = 1; g.sBn = m.r;
+        if (initial) { g.B = ref_arena(m.dinv + (int64_t)jb * NB * NB * 4); g.sBk = 1; g.sBn = NB; }
+        else { g.B = ref_arena(m.minv + ((int64_t)jb * NB * m.r + (int64_t)jb * NB) * 4); g.sBk = 1; g.sBn = m.r; }
         g.C = ref_arena(m.lfac + o); g.ldc = m.r;
         g.M = rest; g.N = NB; g.K = NB;
-        g.tri = 1;
+        g.tri = initial ? 0 : 1;
         return true;
       });
       // S_22 -= L_21 L_21^T
@@ -313,8 +317,7 @@ struct ProgramBuilder {
   int orth(bool y_side, int cur, int passes, int nshift = 1) {
     auto buf_of = [&](int i, int which) { return y_side ? P.mat[i].y[which] : P.mat[i].zw[which]; };
     auto rows_of = [&](int i) { return y_side ? P.mat[i].p : P.mat[i].q; };
-    int max_blocks = 0;
-    for (int i = 0; i < n; ++i) max_blocks = std::max(max_blocks, (P.mat[i].r + NB - 1) / NB);
+    const int NB = nb(), max_blocks = max_blocks_all();
     for (int pass = 0; pass < passes; ++pass) {
       // S = X^T X
       gemm([&](int i, GemmDesc& g) {
@@ -328,6 +331,7 @@ struct ProgramBuilder {
       simple(OP_GRAM_DIAG, (y_side ? 0 : 2) + cur);      // the diagonal (the column norms) exactly
       if (pass < nshift) simple(OP_SHIFT, 0, 32.f * 5.9604645e-8f);
       factor(max_blocks);
+      if (initial) simple(OP_DIAG_INV);
       // M = L^{-1}, row block by row block from the inverses of the diagonal blocks, which are in place:
       // M[i, <i] = -M_ii (L[i, <i] M[<i, <i]); the Gram buffer, consumed by the factorisation, holds the inner product
       for (int ib = 1; ib < max_blocks; ++ib) {
@@ -376,7 +380,9 @@ struct ProgramBuilder {
     std::vector<Op> saved;
     saved.swap(P.ops);
     simple(OP_Y_FROM_EXT);
+    initial = true;
     const int ycur = orth(true, 0, passes, passes >= 3 ? 2 : 1);
+    initial = false;
     simple(OP_PACK, ycur);
     P.init_ops.swap(P.ops);
     P.ops.swap(saved);
@@ -786,6 +792,7 @@ void build_plan(const lordo_shape* shapes, int n, const lordo_hparams& hp, Plan&
     m.y[0] = A.take(pr * 4); m.y[1] = A.take(pr * 4);
     for (int k = 0; k < 4; ++k) m.zw[k] = A.take(qr * 4);
     m.gram = A.take(rr * 4); m.lfac = A.take(rr * 4);
+    m.dinv = A.take((size_t)((m.r + NB_INIT - 1) / NB_INIT) * NB_INIT * NB_INIT * 4);
     m.minv = A.take(rr * 4);
     m.rot = A.take(rr * 4); m.rot2 = A.take(rr * 4);
     m.part = A.take(rr * 4 * P.part_slices);
@@ -1423,6 +1430,8 @@ static int run_ops(lordo_ctx* c, const std::vector<Op>& ops, int32_t src_dtype, 
       case OP_SHIFT: HIPCHK(launch_gram_shift(c->dev, op.farg, op.iarg != 0, s)); break;
       case OP_GRAM_DIAG: HIPCHK(launch_gram_diag(c->dev, op.iarg, P.r_max, P.part_slices, s)); break;
       case OP_FACTOR_DIAG: HIPCHK(launch_factor_diag(c->dev, op.iarg, s)); break;
+      case OP_POTF2: HIPCHK(launch_potf2(c->dev, op.iarg, s)); break;
+      case OP_DIAG_INV: HIPCHK(launch_diag_inverses(c->dev, s)); break;
       case OP_JSVD:
         if (P.r_max <= 128) HIPCHK(launch_jacobi_svd(c->dev, P.r_max, op.iarg != 0, s));
         else HIPCHK(launch_jacobi_svd_blocked(c->dev, P.r_max, P.rank_sq_sum, op.iarg != 0, c->at<int>(P.jflags), s));
