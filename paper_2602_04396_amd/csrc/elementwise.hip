@@ -932,7 +932,7 @@ __global__ __launch_bounds__(256) void k_potf2(DevCtx d, int jb) {
     const int buf = k & 1;
     if (w == k / 16) {
       float piv = lane_value(a[k % 16], k);
-      if (!(piv > floor_piv)) {
+      if (k < nbk && !(piv > floor_piv)) {           // (the floor is in the scale of the Gram matrix, the padding is not)
         if (lane == 0) bad_s = 1;
         piv = floor_piv;
       }
@@ -1056,7 +1056,7 @@ __device__ __forceinline__ void factor_half(LdsTile A, LdsTile X, int nbk, int w
 #pragma unroll
       for (int k = 0; k < 16; ++k) {
         float piv = lane_value(a[k], 16 * b + k);
-        const bool ok = piv > floor_piv;
+        const bool ok = piv > floor_piv || 16 * b + k >= nbk;      // (the floor is in the scale of the Gram matrix, the padding is not)
         low |= !ok;
         piv = ok ? piv : floor_piv;
         float y = __builtin_amdgcn_rsqf(piv);

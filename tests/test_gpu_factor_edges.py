@@ -31,3 +31,30 @@ def test_refresh_orthonormalises_at_every_edge_of_the_factor(r):
         assert float((got.T @ got - torch.eye(k, device="cuda", dtype=torch.float64)).norm()) <= 6e-8 * 8 * k + 1e-6, i
         # rounding of the source and of the products with it, about 1e-7 sqrt(q) of the norm per direction
         assert float((got - u @ (u.T @ got)).norm()) / k ** 0.5 <= 2e-5, i
+
+
+@pytest.mark.parametrize("r", [1, 16, 63, 64, 65, 72, 100, 128, 130, 200])
+@pytest.mark.parametrize("exponent", [-20, 20, 26])
+def test_scale_of_the_source_does_not_change_the_factorisation(r, exponent):
+    """Every sum, root and quotient of the orthonormalisation scales exactly with a power of two, so the projection of 2^k Src
+    (and the initial projection of a block 2^k B) has the same bits as that of Src.  The identity that pads a block of
+    the factor does not scale: a column norm of 1e6 made the pivot floor of the block exceed it."""
+    import torch
+    from paper_2602_04396_amd import lordo
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(r)
+    p, q = 640, 576
+    W = [torch.zeros(p, q, device="cuda")]
+    src = 0.1 * torch.randn(p, q, generator=gen, device="cuda")
+    block = torch.randn(p, r, generator=gen, device="cuda")
+    refreshed, initial = [], []
+    for scale in (1.0, 2.0 ** exponent):
+        opt = lordo.Lordo([(p, q, r)], lordo.hparams(power_iters=1, seed=1, grad_dtype=lordo.F32), W, torch)
+        opt.init_projection([block * scale])
+        opt.poll_status()
+        initial.append(opt.get_state(0, lordo.STATE_Q))
+        opt.refresh_subspace([src * scale])
+        opt.poll_status()
+        refreshed.append(opt.get_state(0, lordo.STATE_Q))
+    assert torch.equal(initial[0], initial[1])
+    assert torch.equal(refreshed[0], refreshed[1])
