@@ -881,6 +881,11 @@ __device__ __forceinline__ float lane_value(float x, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
 }
 
+// Diagonal of the columns that pad a Cholesky block.  The pivot floor of a block is 1e-12 of its largest real diagonal entry,
+// whatever the scale of the source; the padding has to lie above it for every finite one (with 1, a column norm of 1e6
+// latched a breakdown), and its root and reciprocal have to be ordinary numbers.
+constexpr float PAD_PIVOT = 1e38f;
+
 // The initial projection is drawn from a seed and every later state of a run follows from it, so its bits are kept: it is
 // factored 64 columns at a time by this kernel, in the order of operations it always had (a last-bit change of Q_0 moves the
 // weights by 6e-6 relative after three steps, where the normalised update of a nearly cancelled gradient element turns over).
@@ -906,11 +911,11 @@ __global__ __launch_bounds__(256) void k_potf2(DevCtx d, int jb) {
   __shared__ int bad_s;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // rows are read coalesced and handed to their lanes through LDS; identity outside the block
+  // rows are read coalesced and handed to their lanes through LDS; PAD_PIVOT on the diagonal outside the block
   for (int rr = w; rr < NB_INIT; rr += 4) {
     float val;
     if (rr < nbk && lane < nbk) val = lane <= rr ? S[(int64_t)(o + rr) * m.r + (o + lane)] : 0.f;
-    else val = rr == lane ? 1.f : 0.f;
+    else val = rr == lane ? PAD_PIVOT : 0.f;
     tile[rr][lane] = val;
   }
   if (tid == 0) bad_s = 0;
@@ -932,7 +937,7 @@ __global__ __launch_bounds__(256) void k_potf2(DevCtx d, int jb) {
     const int buf = k & 1;
     if (w == k / 16) {
       float piv = lane_value(a[k % 16], k);
-      if (k < nbk && !(piv > floor_piv)) {           // (the floor is in the scale of the Gram matrix, the padding is not)
+      if (!(piv > floor_piv)) {
         if (lane == 0) bad_s = 1;
         piv = floor_piv;
       }
@@ -1034,7 +1039,7 @@ typedef float (*LdsTile)[FPITCH];
 // compiler-level order of a wave's own LDS accesses (the hardware keeps it anyway)
 #define LDS_ORDER() asm volatile("" ::: "memory")
 
-// A (lower triangle of S, identity outside the block) -> L, zeros above the diagonal; X <- L^{-1}, zeros above.
+// A (lower triangle of S, PAD_PIVOT on the diagonal outside the block) -> L, zeros above the diagonal; X <- L^{-1}, zeros above.
 __device__ __forceinline__ void factor_half(LdsTile A, LdsTile X, int nbk, int w, int lane, int* bad) {
   float a[16];
 #pragma unroll
@@ -1056,7 +1061,7 @@ __device__ __forceinline__ void factor_half(LdsTile A, LdsTile X, int nbk, int w
 #pragma unroll
       for (int k = 0; k < 16; ++k) {
         float piv = lane_value(a[k], 16 * b + k);
-        const bool ok = piv > floor_piv || 16 * b + k >= nbk;      // (the floor is in the scale of the Gram matrix, the padding is not)
+        const bool ok = piv > floor_piv;
         low |= !ok;
         piv = ok ? piv : floor_piv;
         float y = __builtin_amdgcn_rsqf(piv);
@@ -1179,7 +1184,7 @@ __global__ __launch_bounds__(256) void k_factor_diag(DevCtx d, int jb) {
   const int c = lane & 15, h = lane >> 4;
   const int n1 = nbk < HB ? nbk : HB, n2 = nbk - n1;
   if (tid == 0) bad_s = 0;
-  // Rows are read coalesced, identity outside the block.  All loads are requested before the first is used (element 0 in the
+  // Rows are read coalesced, PAD_PIVOT on the diagonal outside the block.  All loads are requested before the first is used (element 0 in the
   // place of what is not read): row by row, each waited for, they took 11 of the launch's 49 us.
   {
     float s11[HB / 4], s21[HB / 4], s22[HB / 4];
@@ -1195,7 +1200,7 @@ __global__ __launch_bounds__(256) void k_factor_diag(DevCtx d, int jb) {
 #pragma unroll
     for (int i = 0; i < HB / 4; ++i) {
       const int rr = w + 4 * i;
-      const float diag = rr == lane ? 1.f : 0.f;
+      const float diag = rr == lane ? PAD_PIVOT : 0.f;
       A1[rr][lane] = rr < n1 && lane <= rr ? s11[i] : diag;
       P[rr][lane] = rr < n2 ? s21[i] : 0.f;
       A2[rr][lane] = rr < n2 && lane <= rr ? s22[i] : diag;
