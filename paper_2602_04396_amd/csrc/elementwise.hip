@@ -1163,7 +1163,10 @@ __device__ __forceinline__ void mul_half(f32x4m (&acc)[4], LdsTile A, LdsTile B,
   }
 }
 
-constexpr int FACTOR_LDS = 6 * HB * FPITCH * 4;
+// A block without a second half touches the first two of the six tiles only; where no matrix of the launch has one, it asks for
+// no more: 34 KiB let four workgroups share a compute unit where 102 KiB let one, which sets of more matrices than units need
+// (whole refresh of 1024 matrices of 256 x 256 at r = 16: 1536 -> 1419 us; of 2048 of 128 x 128 at r = 8: 2482 -> 2212 us).
+constexpr int FACTOR_LDS = 6 * HB * FPITCH * 4, FACTOR_LDS_HALF = 2 * HB * FPITCH * 4;
 __global__ __launch_bounds__(256) void k_factor_diag(DevCtx d, int jb) {
   if (mat_skipped(d, blockIdx.x)) return;
   const MatDev& m = d.mats[blockIdx.x];
@@ -1202,8 +1205,10 @@ __global__ __launch_bounds__(256) void k_factor_diag(DevCtx d, int jb) {
       const int rr = w + 4 * i;
       const float diag = rr == lane ? PAD_PIVOT : 0.f;
       A1[rr][lane] = rr < n1 && lane <= rr ? s11[i] : diag;
-      P[rr][lane] = rr < n2 ? s21[i] : 0.f;
-      A2[rr][lane] = rr < n2 && lane <= rr ? s22[i] : diag;
+      if (n2 > 0) {
+        P[rr][lane] = rr < n2 ? s21[i] : 0.f;
+        A2[rr][lane] = rr < n2 && lane <= rr ? s22[i] : diag;
+      }
     }
   }
   __syncthreads();
@@ -1259,11 +1264,11 @@ __global__ __launch_bounds__(256) void k_factor_diag(DevCtx d, int jb) {
     }
   }
 }
-hipError_t launch_factor_diag(const DevCtx& d, int jb, hipStream_t s) {
+hipError_t launch_factor_diag(const DevCtx& d, int jb, int rmax, hipStream_t s) {
   static LdsRaised raised;
   const hipError_t e = raise_lds(reinterpret_cast<const void*>(k_factor_diag), FACTOR_LDS, raised);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_factor_diag, dim3(d.n), dim3(256), FACTOR_LDS, s, d, jb);
+  hipLaunchKernelGGL(k_factor_diag, dim3(d.n), dim3(256), rmax - jb * NB > HB ? FACTOR_LDS : FACTOR_LDS_HALF, s, d, jb);
   return hipGetLastError();
 }
 

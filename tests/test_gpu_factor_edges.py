@@ -58,3 +58,24 @@ def test_scale_of_the_source_does_not_change_the_factorisation(r, exponent):
         refreshed.append(opt.get_state(0, lordo.STATE_Q))
     assert torch.equal(initial[0], initial[1])
     assert torch.equal(refreshed[0], refreshed[1])
+
+
+@pytest.mark.parametrize("r", [8, 64, 65])
+def test_refresh_of_more_matrices_than_compute_units(r):
+    """Several workgroups of the factorisation share a compute unit where no block has a second half (r <= 64), one where it has.
+    Without power iterations Q is an orthonormal basis of Src Omega."""
+    import torch
+    from paper_2602_04396_amd import lordo
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(r)
+    n, p, q = 700, 96, 80
+    src = torch.randn(n, p, q, generator=gen, device="cuda")
+    omega = torch.randn(n, q, r, generator=gen, device="cuda")
+    opt = lordo.Lordo([(p, q, r)] * n, lordo.hparams(power_iters=0), [torch.zeros(p, q, device="cuda") for _ in range(n)], torch)
+    opt.refresh_subspace(list(src.unbind()), list(omega.unbind()))
+    opt.poll_status()
+    for i in range(n):
+        Q, Y = opt.get_state(i, lordo.STATE_Q).double(), src[i].double() @ omega[i].double()
+        assert float((Q.T @ Q - torch.eye(r, device="cuda", dtype=torch.float64)).norm()) <= 6e-8 * 8 * r + 1e-6, i
+        # fp32 sums over q and the passes of CholeskyQR2: 1e-7 sqrt(r) of a column's norm
+        assert float(((Y - Q @ (Q.T @ Y)).norm(dim=0) / Y.norm(dim=0)).max()) <= 2e-5, i
