@@ -213,7 +213,12 @@ struct ProgramBuilder {
     op.ndescs = (int)P.desc_h.size() - op.desc_first;
     op.ntiles = (int)P.gtile_h.size() - op.tile_first;
     if (op.planes) {
-      op.tile = op.planes == 64 ? 64 : 128;          // (what an unaligned source falls back to, several tiles per table entry)
+      // What a source falls back to that k_gemm_planes cannot read (bf16, or fp32 rows that are not 16-byte aligned): k_gemm32 on
+      // the same table, several tiles to an entry.  At edge 64 these are the 64 x 64 tiles the product would have had
+      // anyway.  From edge 128 on (512 entries at least) 128 x 128 tiles are as good or better also where N < 128 would
+      // have meant 64 x 64: bf16, 64 x (1028 x 516) at r = 100 89 -> 83 us, 96 x (1028 x 516) at r = 72 121 -> 93, 16 x (16384 x 516)
+      // at r = 100 345 -> 202; fp32 off by 4 bytes 178 -> 202, 260 -> 257, 657 -> 554.
+      op.tile = op.planes == 64 ? 64 : 128;
       op.a_once = true;
       for (const GemmDesc& g : made) op.a_once = op.a_once && g.N <= op.planes;
     }
@@ -1429,7 +1434,7 @@ static int run_ops(lordo_ctx* c, const std::vector<Op>& ops, int32_t src_dtype, 
         break;
       case OP_SHIFT: HIPCHK(launch_gram_shift(c->dev, op.farg, op.iarg != 0, s)); break;
       case OP_GRAM_DIAG: HIPCHK(launch_gram_diag(c->dev, op.iarg, P.r_max, P.part_slices, s)); break;
-      case OP_FACTOR_DIAG: HIPCHK(launch_factor_diag(c->dev, op.iarg, s)); break;
+      case OP_FACTOR_DIAG: HIPCHK(launch_factor_diag(c->dev, op.iarg, P.r_max, s)); break;
       case OP_POTF2: HIPCHK(launch_potf2(c->dev, op.iarg, s)); break;
       case OP_DIAG_INV: HIPCHK(launch_diag_inverses(c->dev, s)); break;
       case OP_JSVD:
