@@ -214,9 +214,10 @@ struct ProgramBuilder {
     op.ntiles = (int)P.gtile_h.size() - op.tile_first;
     if (op.planes) {
       // What a source falls back to that k_gemm_planes cannot read (bf16, or fp32 rows that are not 16-byte aligned): k_gemm32 on
-      // the same table, several tiles to an entry.  At edge 64 these are the 64 x 64 tiles the product would have had
-      // anyway.  From edge 128 on (512 entries at least) 128 x 128 tiles are as good or better also where N < 128 would
-      // have meant 64 x 64: bf16, 64 x (1028 x 516) at r = 100 89 -> 83 us, 96 x (1028 x 516) at r = 72 121 -> 93, 16 x (16384 x 516)
+      // the same table, several tiles to an entry.  At edge 64 64 x 64 tiles, as a table of its own would mostly have (whole refresh of
+      // 64 x (2048 x 1028) at r = 192, which would have 128 x 128: bf16 2607 -> 2619 us; 32 of them, fp32 off by 4 bytes,
+      // 2787 -> 2646).  From edge 128 on (512 entries at least) 128 x 128 tiles, also where N < 128 would have meant 64 x 64;
+      // the product alone: bf16, 64 x (1028 x 516) at r = 100 89 -> 83 us, 96 x (1028 x 516) at r = 72 121 -> 93, 16 x (16384 x 516)
       // at r = 100 345 -> 202; fp32 off by 4 bytes 178 -> 202, 260 -> 257, 657 -> 554.
       op.tile = op.planes == 64 ? 64 : 128;
       op.a_once = true;
@@ -224,35 +225,44 @@ struct ProgramBuilder {
     }
     P.ops.push_back(op);
   }
-  // Column edge of the tiles k_gemm_planes takes these products on, or 0 if it cannot: A is read in 16-byte vectors along
-  // k, and the planes of B have to fit where the matrix's operand planes of N live between steps.
+  // Column edge of the tiles k_gemm_planes takes these products on, or 0 if it cannot or k_gemm32 is the faster one: A is read
+  // in 16-byte vectors along k, and the planes of B have to fit where the matrix's operand planes of N live between steps.
+  // Measured as whole refreshes without power iterations, fp32 source, on k_gemm32 / edge 64 / 128 / 256 (us):
+  //   N <= 64    16 x (1024 x 1024) 208 / 226, 24 x (2048 x 2048) 342 / 394, 72 x (3072 x 768) 580 / 656, 1 x (65536 x 1024) 692 / 713
+  //   N = 128    24 x (2048 x 2048) 618 / 548 / 597, 125M set 758 / 695 / 737 / 832, 1 x (16384 x 4096) 589 / 533 / 611,
+  //              64 x (2048 x 1024) 819 / 833 / 841
+  //   N = 192    24 x (4096 x 1024) 1142 / 1033 / 1072 / 1123, 350M set 2759 / 2506 / 2593 / 2855
+  //   N = 256    350M set 3294 / 3220 / 2991 / 3266, 1B set 7730 / 7837 / 7084 / 7390, 4 x (4096 x 1024), of few tiles, 553 / 533 / 541 / 620
+  //   N = 512    four blocks of 7B 9293 / 8934 / 8236 / 8131, 64 x (2048 x 1024) 4904 / 4792 / 4588 / 4539, 4 x (4096 x 1024) 1185 / 1186 / 1173 / 1222
+  // So: not where 64 columns are all there is; else the narrowest tile until a wider one leaves 512 workgroups, then 128 columns, and
+  // 256 where N has at least two such tiles and pads no worse.  128 workgroups at least: 1 x (6144 x 8192) at r = 192 (144 of them)
+  // 825 -> 735, 1 x (4096 x 28672) at r = 192 (96) would be 1708 -> 1781.
   int planes_edge(const std::vector<GemmDesc>& made) const {
     if (made.empty()) return 0;
-    int64_t rows128 = 0;
-    double cost[3] = {0.0, 0.0, 0.0};
     constexpr int edges[3] = {64, 128, 256};
-    // relative time of a tile per column: a narrow tile splits its rows of A for fewer products
-    constexpr double per_column[3] = {1.6, 1.2, 1.0};
+    double cost[3] = {0.0, 0.0, 0.0}, narrow = 0.0, wide = 0.0;
     int64_t tiles[3] = {0, 0, 0};
     for (const GemmDesc& g : made) {
       const MatDev& m = P.mat[g.mat];
       if (g.sAk != 1 || (g.sAm & 3) != 0 || (g.K & 3) != 0 || g.a_bf16 == 1 || g.C2.off >= 0 || g.beta != 0.f) return 0;
       if (pad32(g.N) * pad32(g.K) > (int64_t)m.qp * m.rp) return 0;
-      // a short contraction does not pay for the launch that packs B (X M^T of 72 matrices at r = 128: 42 us on the
-      // general kernel, 32 + 7 us and one more launch here; at r = 256: 510 us against 370 + 40 us)
+      // a short contraction does not pay for the launch that packs B (products X M^T, K = r, bf16 source; 72 x (768 x 768): r = 128
+      // 533 -> 537, 160 819 -> 791, 192 911 -> 886, 256 1147 -> 1170; 4 x (4096 x 4096): 329 -> 337, 493 -> 499, 511 -> 520, 627 -> 617;
+      // 350M set at r = 256 2570 -> 2534, 1B set 5139 -> 5017, four blocks of 7B at r = 512 5738 -> 5552)
       if (g.K < 192) return 0;
       const int64_t tm = (g.M + 127) / 128;
-      rows128 += tm;
+      const double per_column[3] = {1.3, 1.0, g.N > 256 ? 0.98 : 1.05};
       for (int e = 0; e < 3; ++e) {
         const int64_t tn = (g.N + edges[e] - 1) / edges[e];
         tiles[e] += tm * tn;
         cost[e] += (double)(tm * tn) * edges[e] * g.K * per_column[e];
       }
+      (g.N <= 64 ? narrow : wide) += (double)tm * g.N * g.K;
     }
     int best = 0;
     for (int e = 1; e < 3; ++e)
-      if (cost[e] < cost[best] && (tiles[e] >= 512 || tiles[e] == tiles[best])) best = e;
-    return tiles[best] >= 128 ? edges[best] : 0;
+      if (cost[e] < cost[best] && tiles[e] >= 512) best = e;
+    return tiles[best] >= 128 && narrow <= wide ? edges[best] : 0;
   }
   // A operand = the source (transposed: its transpose).  The source of a right-projected matrix is the caller's
   // row-major array read as its transpose: element (i, j) of the p x q matrix at j * p + i.

@@ -5,11 +5,12 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-# (p, q, r), number of matrices: enough row tiles for the kernel to be taken (128), a lone tall matrix, ranks on both
-# sides of each column edge, columns that end inside a 32-column chunk, rows that end inside a row tile, and the shapes
-# that stay with the general kernel (q % 4 != 0; few tiles)
+# (p, q, r), number of matrices: column tiles of 64, then of 128 and of 256 (512 tiles of that width), a lone tall matrix, columns
+# that end inside a 32-column chunk, rows that end inside a row tile, and the shapes that stay with the general kernel
+# (r <= 64; q % 4 != 0; few tiles)
 @pytest.mark.parametrize("shape, n", [((640, 516, 64), 28), ((520, 1000, 72), 28), ((776, 192, 192), 20), ((2048, 512, 128), 9), ((1100, 260, 132), 16),
-                                      ((16500, 384, 256), 1), ((1030, 1028, 260), 16), ((516, 2052, 300), 32), ((640, 518, 64), 28), ((256, 320, 16), 2)])
+                                      ((16500, 384, 256), 1), ((1030, 1028, 260), 16), ((516, 2052, 300), 32), ((1100, 1028, 256), 32), ((1030, 640, 500), 32),
+                                      ((640, 518, 100), 28), ((256, 320, 16), 2)])
 def test_refresh_from_fp32_source_spans_the_dominant_directions(shape, n):
     """k_gemm_planes in the products Y = Src B, X M^T and the moment rotation.  The source is 100 A B^T with orthonormal A and B of
     r columns: exactly rank r up to fp32 rounding, all r singular values equal, so the refreshed subspace is the column space
@@ -72,8 +73,9 @@ def test_refresh_from_fp32_source_spans_the_dominant_directions(shape, n):
         assert float((W[i].double() + dW).abs().max() / dW.square().mean().sqrt()) <= 1e-3, i
 
 
-# row and column tiles beyond the first of a table entry, at each column edge (64, 128, 256) that the table can be made for
-@pytest.mark.parametrize("shape, n", [((640, 516, 64), 28), ((1028, 516, 100), 64), ((516, 516, 132), 128)])
+# every way the fallback reads the tile table: entries of 128 x 64 as two 64 x 64 tiles, of 128 x 128 as one tile, of 128 x 256 as two
+# 128 x 128 tiles; and a set that takes k_gemm32 in the first place
+@pytest.mark.parametrize("shape, n", [((640, 516, 100), 28), ((1028, 516, 100), 64), ((516, 516, 200), 52), ((516, 516, 500), 52), ((640, 516, 64), 28)])
 @pytest.mark.parametrize("source", ["fp32", "fp32 off by 4 bytes", "bf16"])
 def test_source_product_spans_src_times_start_block(shape, n, source):
     """Y = Src Omega where the source is read by k_gemm_planes (aligned fp32) and where it falls back to k_gemm32 on the
