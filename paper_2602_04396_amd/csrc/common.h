@@ -142,12 +142,13 @@ hipError_t launch_proj_up(const DevCtx& d, const ProjTile* tiles, int ntiles, bo
 hipError_t launch_proj_up_wide(const DevCtx& d, const ProjTile* tiles, int ntiles, const uint16_t* b_hi, const uint16_t* b_lo,
                                const UpArgs& ua, hipStream_t s);
 // gemm32.hip
+// alpha_mul scales every product of the launch (per-call coefficients); an entry of the table covers sub_m x sub_n tiles
 hipError_t launch_gemm32(const DevCtx& d, const GemmDesc* descs, const GemmTile* tiles, int ntiles, int tile, int src_is_bf16,
                          hipStream_t s, float alpha_mul = 1.f, int sub_m = 1, int sub_n = 1);
 // The same products with B split once into three bf16 planes (p0, p1, p2: flat arrays addressed by lr_off) and tiles of
-// 128 x tn_edge; max_groups: largest number of 8-element groups of a plane; a_once: one column tile, A is read once;
+// 128 x tn_edge; max_groups: largest number of 8-element groups of a plane; a_once: one column tile, A is read once
 hipError_t launch_gemm_planes(const DevCtx& d, const GemmDesc* descs, int desc_first, int ndescs, const GemmTile* tiles, int ntiles, int tn_edge,
-                              bool a_once, int64_t max_groups, uint16_t* p0, uint16_t* p1, uint16_t* p2, hipStream_t s);   // alpha_mul scales every product of the launch (per-call coefficients)
+                              bool a_once, int64_t max_groups, uint16_t* p0, uint16_t* p1, uint16_t* p2, hipStream_t s);
 hipError_t launch_gemm_reduce(const DevCtx& d, const GemmDesc* descs, int ndescs, hipStream_t s);
 // elementwise.hip
 // Elements at flat position >= grp_start[i] are the sum of grp_nsplit[i] split-K slices of g.

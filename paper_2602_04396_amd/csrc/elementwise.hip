@@ -886,10 +886,11 @@ __device__ __forceinline__ float lane_value(float x, int lane) {
 // latched a breakdown), and its root and reciprocal have to be ordinary numbers.
 constexpr float PAD_PIVOT = 1e38f;
 
-// The initial projection is drawn from a seed and every later state of a run follows from it, so its bits are kept: it is
-// factored 64 columns at a time by this kernel, in the order of operations it always had (a last-bit change of Q_0 moves the
-// weights by 6e-6 relative after three steps, where the normalised update of a nearly cancelled gradient element turns over).
-// It runs once per run, 42 us per block of 64; the refreshes, hundreds per run, take k_factor_diag.
+// The initial projection keeps the bits it always had for a seed: it is factored 64 columns at a time by this kernel, in
+// the order of operations it always had.  Until the first refresh the run follows from those bits alone, and a last-bit change
+// of Q_0 moves the weights by 6e-6 relative after three steps (the normalised update of a nearly cancelled gradient element
+// turns over).  It runs once per run, 42 us per block of 64; the refreshes, hundreds per run, take k_factor_diag, whose last
+// bits differ.
 // Diagonal block jb: L = chol(S_jj) (lower), X = L^{-1}; one workgroup per matrix, lane = row, wave w holds columns
 // 16 w .. 16 w + 15 in registers, one barrier per column; the inverse by forward substitution in one wave.
 __global__ __launch_bounds__(256) void k_potf2(DevCtx d, int jb) {
@@ -1660,11 +1661,8 @@ hipError_t launch_jacobi_svd_blocked(const DevCtx& d, int rmax, int64_t rank_sq_
 // the paper's r x q arrays): zw[2] = u_hat^T, zw[3] = (v_hat - u_hat^2)^T; the two GEMMs leave
 // zw[0] = (R u_hat)^T and zw[1] = ((R o R)(v_hat - u_hat^2))^T.
 // ---------------------------------------------------------------------------------------
-// Both kernels move eight consecutive rank indices of one column per thread, as two 16-byte accesses
-// where r % 4 == 0.  k_rot_pre numbers its threads so that eight neighbours hold eight consecutive
-// octets of one column: their writes to the plain temporaries form one 256-byte run (the blocked
-// side is then read in 32-byte pieces, which costs far less than scattered partial-line writes).
-// k_rot_post keeps the flat numbering: its writes go to the blocked arrays, contiguous over threads.
+// Both kernels move eight consecutive rank indices of one column per thread, as two 16-byte accesses where r % 4 == 0, sixteen
+// columns x four octets to a wave (low_rank_octet): runs of 512 bytes of the blocked arrays, of 128 bytes of the plain ones.
 __global__ __launch_bounds__(256) void k_rot_pre(DevCtx d, const float* __restrict__ u, const float* __restrict__ v,
                                                  const StepDev* __restrict__ step) {
   if (mat_skipped(d, blockIdx.y)) return;

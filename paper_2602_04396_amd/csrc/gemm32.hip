@@ -5,7 +5,8 @@
 // and the bf16 gradient type are handled by the loader; accumulation is fp32.  Arithmetic: operands that
 // can be read with 16-byte accesses are split into bf16 terms (three per fp32 operand: as exact as fp32)
 // and multiplied on v_mfma_f32_32x32x16_bf16; anything else runs on the fp32 matrix cores
-// (v_mfma_f32_32x32x2_f32).
+// (v_mfma_f32_32x32x2_f32).  k_gemm_planes is the kernel for products of a tall fp32 matrix with a block that many row tiles
+// share: the same arithmetic with the block split once (k_pack_planes).
 #include "common.h"
 
 namespace lordo {

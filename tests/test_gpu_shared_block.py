@@ -111,13 +111,13 @@ def test_source_product_spans_src_times_start_block(shape, n, source):
         assert float((out.norm(dim=0) / Y.norm(dim=0)).max()) <= 2e-5, i
 
 
-def test_split_planes_give_the_bits_of_the_general_kernel():
+@pytest.mark.parametrize("n, p, q, r", [(64, 640, 516, 512), (256, 260, 260, 256), (256, 260, 260, 192)])      # edges 256, 128, 64
+def test_split_planes_give_the_bits_of_the_general_kernel(n, p, q, r):
     """The same matrices and inputs in two sets: alone, where Y = Src B, X M^T and the rotation products run on k_gemm_planes, and
     with one more matrix whose columns and rank are no multiples of four, which sends those products of the whole
-    set to k_gemm32.  (64 matrices of sixteen 128 x 128 tiles of the Gram product: no K slices in either set.)"""
+    set to k_gemm32.  (At least 1024 tiles of 128 x 128 in the Gram product: no K slices in either set.)"""
     import torch
     from paper_2602_04396_amd import lordo
-    n, p, q, r = 64, 640, 516, 512
     gen = torch.Generator(device="cuda")
     gen.manual_seed(11)
     src = [torch.randn(p, q, generator=gen, device="cuda") for _ in range(n)]
@@ -125,7 +125,7 @@ def test_split_planes_give_the_bits_of_the_general_kernel():
     u0 = torch.randn(r, q, generator=gen, device="cuda")
     v0 = u0 * u0 + torch.rand(r, q, generator=gen, device="cuda")
     results = []
-    for extra in ([], [(640, 518, 510)]):
+    for extra in ([], [(p, q + 2, r - 2)]):
         shapes = [(p, q, r)] * n + extra
         opt = lordo.Lordo(shapes, lordo.hparams(power_iters=0, seed=3), [torch.zeros(s[0], s[1], device="cuda") for s in shapes], torch)
         for i in range(n):
