@@ -152,7 +152,7 @@ typedef struct {
 /* Bytes of arena lordo_init needs for these shapes and hyper-parameters (host call). */
 int lordo_workspace_bytes(const lordo_shape* shapes, int32_t n, const lordo_hparams* hp, size_t* out_bytes);
 
-/* Create a context (the north-star call "lordo_init": matrix shapes, rank, hyper-parameters).
+/* Create a context from matrix shapes, ranks and hyper-parameters.
  *   arena        device, caller-allocated, 256-byte aligned, >= lordo_workspace_bytes; the library
  *                keeps Q, u, v, the anchor, the outer momentum and all scratch in it until destroy.
  *   W            host array of n device pointers to p x q weights of hp.param_dtype; read once: anchor <- W.

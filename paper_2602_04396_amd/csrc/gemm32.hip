@@ -469,11 +469,11 @@ hipError_t launch_gemm_reduce(const DevCtx& d, const GemmDesc* descs, int ndescs
 // the rows of A are requested two to three k-steps ahead of their use.  The loads into LDS are issued from inline
 // assembly with explicit waits: in an even step they precede the loads of A, so "at most the four loads of A
 // outstanding" implies that they have landed.
-// Measured (24 x 7 matrices, 2048 x 2048 .. 5632, r = 256, fp32 source): Y = Src B 4.6 -> 3.65 ms (3.8 TFLOP of bf16
-// products; the matrix cores are busy 67 % of the time at a clock that this load holds at 1.56 GHz: power is the bound,
-// and skipping the zero half of M^T gains nothing), X M^T 0.51 -> 0.37 ms, rotation product 0.51 -> 0.43 ms; 28 matrices of
-// 4096 .. 11008 at r = 512: X M^T 0.48 -> 0.35 and 0.58 -> 0.43 ms; 72 matrices of 768 .. 3072 at r = 128, fp32 source:
-// three products 0.29 -> 0.25 ms each.
+// Measured (24 x 7 matrices, 2048 x 2048 .. 5632, r = 256, fp32 source): Y = Src B 4.6 -> 3.54 ms at edge 128, 3.65 at 256 (3.8 TFLOP of
+// bf16 products, 1.07 PFLOP/s; the matrix cores are busy 64 % of the cycles at a clock that this load holds at 1.59 GHz: power is the
+// bound, and skipping the zero half of M^T gains nothing), X M^T 0.51 -> 0.33 ms, rotation product 0.51 -> 0.40 ms (both on edge 128;
+// profiles/1b_synchronisation_*.txt); 28 matrices of 4096 .. 11008 at r = 512: X M^T 0.48 -> 0.35 and 0.58 -> 0.43 ms; 72 matrices
+// of 768 .. 3072 at r = 128, fp32 source: three products 0.29 -> 0.25 ms each.
 // ---------------------------------------------------------------------------------------
 #define LDS_AS __attribute__((address_space(3)))
 #pragma clang diagnostic push
