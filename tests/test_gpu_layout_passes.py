@@ -7,8 +7,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("p, q, r", [(64, 64, 32), (65, 96, 33), (31, 40, 8), (33, 64, 30), (200, 136, 100), (257, 320, 36), (640, 512, 128), (515, 1000, 130)])
 @pytest.mark.parametrize("source", ["bf16", "fp32"])
 def test_refresh_and_step_keep_projection_planes_and_moments_consistent(p, q, r, source):
-    """After a refresh from an equal-valued low-rank source: Q spans it, u is R u of before, and the next step's moments and
-    weights follow from the Q that get_state returns, i.e. the operand planes hold the same Q in both orientations."""
+    """After a refresh from an equal-valued low-rank source: Q spans it, u and v are those of before, rotated, and the next step's
+    moments and weights follow from the Q that get_state returns, i.e. the operand planes hold the same Q in both orientations."""
     import torch
     from paper_2602_04396_amd import lordo
     gen = torch.Generator(device="cuda")
@@ -20,8 +20,11 @@ def test_refresh_and_step_keep_projection_planes_and_moments_consistent(p, q, r,
     opt.init_projection()
     G = [torch.randn(p, q, generator=gen, device="cuda").bfloat16() for _ in range(n)]
     opt.local_step(W, G, lr)
+    opt.local_step(W, [torch.randn(p, q, generator=gen, device="cuda").bfloat16() for _ in range(n)], lr)      # (so that v - u^2 is a variance)
     q_old = [opt.get_state(i, lordo.STATE_Q).double() for i in range(n)]
     u_old = [opt.get_state(i, lordo.STATE_U).double() for i in range(n)]
+    v_old = [opt.get_state(i, lordo.STATE_V).double() for i in range(n)]
+    c1, c2 = 1 - beta1 ** 2, 1 - opt.hp.beta2 ** 2
     src, U = [], []
     for i in range(n):
         k = min(p, q, r)
@@ -41,6 +44,10 @@ def test_refresh_and_step_keep_projection_planes_and_moments_consistent(p, q, r,
         want = (Q[i].T @ q_old[i]) @ u_old[i]
         got = opt.get_state(i, lordo.STATE_U).double()
         assert float((got - want).norm() / want.norm()) <= 1e-5, i              # fp32 sums over p and r
+        R = Q[i].T @ q_old[i]
+        want = c2 * ((R * R) @ (v_old[i] / c2 - (u_old[i] / c1) ** 2) + (R @ u_old[i] / c1) ** 2).abs()
+        got = opt.get_state(i, lordo.STATE_V).double()
+        assert float((got - want).norm() / want.norm()) <= 1e-5, i              # the same, on terms of one size
     u1 = [opt.get_state(i, lordo.STATE_U).double() for i in range(n)]
     before = [w.double() for w in W]
     opt.local_step(W, G, lr)

@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 # (r <= 64; q % 4 != 0; few tiles)
 @pytest.mark.parametrize("shape, n", [((640, 516, 64), 28), ((520, 1000, 72), 28), ((776, 192, 192), 20), ((2048, 512, 128), 9), ((1100, 260, 132), 16),
                                       ((16500, 384, 256), 1), ((1030, 1028, 260), 16), ((516, 2052, 300), 32), ((1100, 1028, 256), 32), ((1030, 640, 500), 32),
-                                      ((640, 518, 100), 28), ((256, 320, 16), 2)])
+                                      ((640, 518, 64), 28), ((640, 518, 100), 28), ((256, 320, 16), 2)])
 def test_refresh_from_fp32_source_spans_the_dominant_directions(shape, n):
     """k_gemm_planes in the products Y = Src B, X M^T and the moment rotation.  The source is 100 A B^T with orthonormal A and B of
     r columns: exactly rank r up to fp32 rounding, all r singular values equal, so the refreshed subspace is the column space
