@@ -80,7 +80,7 @@ struct Plan {
   std::vector<Op> init_ops;         // Q_0 from a caller-supplied block: copy, orthonormalise, pack
   std::vector<Op> gap_ops;          // estimate of sigma_{r+1} of a source (Rayleigh-Ritz option)
   bool any_tr = false;              // some matrix is projected on the right
-  bool down_generic = false;        // fp32 gradients: the down-projection of EVERY matrix runs in the grouped GEMM (three-term operands)
+  bool down_generic = false;        // fp32 gradients, or a matrix of one column: the down-projection of EVERY matrix runs in the grouped GEMM (three-term operands)
   std::vector<Op> tr_down_ops;      // their product g^T = G Q by the generic GEMM (fp32 gradients, shapes the streaming kernel does not take)
   // Right-projected matrices in the kernels of the left projection: the products of the step are those of the caller's
   // p x q matrix with the operand planes in exchanged roles (see build_plan), described by two shadow tables of MatDev.
@@ -713,11 +713,14 @@ void build_plan(const lordo_shape* shapes, int n, const lordo_hparams& hp, Plan&
   if (hp.rayleigh_ritz) { P.frob_part = A.take(sizeof(float) * (size_t)chunks); P.jflags = A.take(256); }
   // rank blocks of 32 per down-projection tile: the pipelined kernel (bf16 G) always takes four and
   // leaves the waves of absent blocks idle; the plain kernel is instantiated for 1, 2 and 4
+  // (the pipelined kernel reads columns in pairs: a matrix of one column sends the set to the grouped GEMM, as fp32 gradients do)
   P.down_generic = hp.grad_dtype == LORDO_F32;
+  for (int i = 0; i < n; ++i)
+    if (!P.mat[i].tr && P.mat[i].q < 2) P.down_generic = true;
   P.mb = 4;
   // Down-projection launch shape: the pipelined kernel (rank tiles of 128, bf16 G, 256-column
   // tiles) where it applies, else the plain kernel with 128-column tiles.
-  P.down_pipe = (P.mb == 4 && hp.grad_dtype == LORDO_BF16) ? (rp_max >= 256 ? 2 : 1) : 0;
+  P.down_pipe = (P.mb == 4 && !P.down_generic) ? (rp_max >= 256 ? 2 : 1) : 0;
   P.rank_tile = P.down_pipe ? 128 * P.down_pipe : 32 * P.mb;
   P.g_once = rp_max <= P.rank_tile;
   const int down_bn = P.down_pipe ? 256 : 128;
@@ -1328,7 +1331,7 @@ int lordo_local_step(lordo_ctx* c, void* const* W, const void* const* G, double 
     ua.coef_acc = -1.f; ua.coef_g = (float)proj_scale; ua.target_err = 1; ua.colscale = 0; ua.colpart = nullptr;
     ua.w_bf16 = e_bf16 ? 1 : 0;         // element type of this launch's target: the residual
     if (!P.up_wide_h.empty() && w_vec && !g_f32)
-      HIPCHK(launch_proj_up_wide(c->dev, c->at<ProjTile>(P.up_wide_tiles), (int)P.up_wide_h.size(), c->at<uint16_t>(P.g_hi),
+      HIPCHK(launch_proj_up_wide(c->dev, c->at<ProjTile>(P.up_wide_tiles), (int)P.up_wide_h.size(), w_vec, c->at<uint16_t>(P.g_hi),
                                  c->at<uint16_t>(P.g_lo), ua, s));
     else if (!P.up_h.empty())
       HIPCHK(launch_proj_up(c->dev, c->at<ProjTile>(P.up_tiles), (int)P.up_h.size(), w_vec, c->at<uint16_t>(P.g_hi),
@@ -1353,8 +1356,8 @@ int lordo_local_step(lordo_ctx* c, void* const* W, const void* const* G, double 
   }
   StepDev* const advance = c->at<StepDev>(P.step);             // t <- t + 1, with the last launch
   if (!P.any_tr) ua.advance = advance;
-  if (!P.up_wide_h.empty() && w_vec && !(qhm_full && g_f32))   // (the wide kernel's gradient-term epilogue reads bf16 gradients)
-    HIPCHK(launch_proj_up_wide(c->dev, c->at<ProjTile>(P.up_wide_tiles), (int)P.up_wide_h.size(), c->at<uint16_t>(P.n_hi),
+  if (!P.up_wide_h.empty() && !(qhm_full && g_f32))   // (the wide kernel's gradient-term epilogue reads bf16 gradients)
+    HIPCHK(launch_proj_up_wide(c->dev, c->at<ProjTile>(P.up_wide_tiles), (int)P.up_wide_h.size(), w_vec, c->at<uint16_t>(P.n_hi),
                                c->at<uint16_t>(P.n_lo), ua, s));
   else if (!P.up_h.empty())
     HIPCHK(launch_proj_up(c->dev, c->at<ProjTile>(P.up_tiles), (int)P.up_h.size(), w_vec, c->at<uint16_t>(P.n_hi),
@@ -1731,7 +1734,7 @@ int lordo_outer_step_lowrank(lordo_ctx* c, void* const* W, const void* const* Av
     return LORDO_OK;
   }
   // any q, any alignment of W: b' = mu b + Delta, W' = anchor - eta_s (Delta + mu b') or anchor - eta_s b' in
-  // separate passes -- the part without Delta elementwise, then Delta through the fallback up-projection
+  // separate passes -- the part without Delta elementwise, then Delta through the up-projection
   // kernel into W and into b, then anchor <- W
   HIPCHK(launch_outer_base(c->dev, chunks, P.nchunks, a, s));
   ua.coef_acc = (float)(-c->hp.outer_lr * ((a.has_mom && a.nesterov) ? 1.0 + c->hp.outer_momentum : 1.0));

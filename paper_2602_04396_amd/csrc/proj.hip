@@ -17,8 +17,8 @@
 // Caller matrices (G, W) are reached through buffer resources: the hardware range check returns
 // zero for reads past the end (rows beyond the matrix or beyond this workgroup's slice of the
 // contraction) and drops such writes, and a lane whose column is outside the matrix is given an
-// offset beyond the range.  No access is guarded by a branch.  Pointers into the arena are cast
-// to the global address space so that no access is a flat one.
+// offset beyond the range.  No access is guarded by a branch, but where rows start at any element (see Ragged, load_gstage).
+// Pointers into the arena are cast to the global address space so that no access is a flat one.
 #include "common.h"
 
 namespace lordo {
@@ -40,14 +40,6 @@ __device__ __forceinline__ u32x4 mk4(uint32_t a, uint32_t b, uint32_t c, uint32_
   r.x = a; r.y = b; r.z = c; r.w = d;
   return r;
 }
-
-__device__ __forceinline__ uint32_t f2bf_rne(float x) {
-  uint32_t u = __float_as_uint(x);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return 0x7fc0u;
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return u >> 16;
-}
-
 
 __device__ __forceinline__ uint32_t pack_bf16_rne(float lo, float hi) {       // the hardware's packed round-to-nearest-even conversion
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -107,44 +99,61 @@ struct GStage {
   uint32_t x[GF32 ? 16 : 8];   // bf16: row i -> two columns packed; fp32: row i -> two floats
 };
 
-// Column handling of one lane, fixed for the whole kernel: byte offsets of its two columns
-// inside a row (OOB if the column is outside the matrix).
+// Column handling of one lane, fixed for the whole kernel.  VEC: byte offset of its two columns inside a row (OOB if they
+// lie outside the matrix; q is even then).  Else rows start at any element: the pair is read at element alignment, and a lane whose
+// second column does not exist reads the pair one column further left, so that no access leaves the row; `shift` and `mask` put
+// its values in place when the stage goes to LDS.
 struct GCol {
-  uint32_t off0, off1;
-  bool vec;           // both columns with one aligned access
+  uint32_t off0;
+  uint32_t shift, mask;       // !VEC: of a packed bf16 pair
+  bool edge;                  // !VEC: this wave's columns reach past the last one (uniform)
 };
+template <bool VEC>
+__device__ __forceinline__ GCol g_columns(int col, int wave_col0, int q, uint32_t es) {
+  GCol gc;
+  gc.off0 = col < q ? (uint32_t)col * es : OOB;
+  gc.shift = 0u; gc.mask = 0xffffffffu;
+  gc.edge = false;
+  if constexpr (!VEC) {
+    gc.edge = wave_col0 + 128 > q;
+    if (col == q - 1) { gc.off0 -= es; gc.shift = 16u; gc.mask = 0xffffu; }
+    if (col >= q) gc.mask = 0u;
+  }
+  return gc;
+}
 
 // Rows krow .. krow+7 (krow uniform over the wave) of the lane's two columns.  The resource ends
 // after row `rows`; a row at or beyond it is clamped to `rows`, which puts the scalar offset exactly
 // at the end of the resource, so every lane of that access is out of range and reads zero.
-template <bool GF32, int AUX>     // AUX: cache policy of the loads (STREAM where G is read once, 0 where rank tiles re-read it)
-__device__ __forceinline__ void load_gstage(GStage<GF32>& st, rsrc_t rs, uint32_t row_bytes, int krow, int rows, const GCol& gc) {
-  if (gc.vec) {                     // uniform branch, taken once per stage
+// A bf16 matrix with rows at odd elements is read with 4-byte global accesses at 2-byte alignment, rows clamped to the last one,
+// lanes outside the matrix to its first column: fix_gstage() turns what they fetch into zeros.  (Sixteen 2-byte accesses per
+// stage before: the set above, 166 -> 113 us; 103 for 1024 and 2732 columns in aligned pairs.)
+template <bool GF32, int AUX, bool VEC>     // AUX: cache policy of the loads (STREAM where G is read once, 0 where rank tiles re-read it)
+__device__ __forceinline__ void load_gstage(GStage<GF32>& st, rsrc_t rs, const GAS char* base, uint32_t row_bytes, int krow, int rows, const GCol& gc) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const uint32_t soff = (uint32_t)(krow + i < rows ? krow + i : rows) * row_bytes;       // scalar
-      if constexpr (!GF32) {
-        st.x[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, gc.off0, soff, AUX);
-      } else {
-        u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(rs, gc.off0, soff, AUX);
-        st.x[2 * i] = t.x;
-        st.x[2 * i + 1] = t.y;
-      }
+  for (int i = 0; i < 8; ++i) {
+    if constexpr (!VEC && !GF32) {
+      typedef uint32_t pair_t __attribute__((aligned(2)));
+      const uint32_t soff = (uint32_t)(krow + i < rows ? krow + i : rows - 1) * row_bytes;   // scalar
+      const GAS pair_t* at = (const GAS pair_t*)(base + soff + (gc.off0 == OOB ? 0u : gc.off0));
+      st.x[i] = *at;                       // (cacheable: a row's cache lines are shared with the tiles beside it)
+      continue;
     }
-  } else {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const uint32_t soff = (uint32_t)(krow + i < rows ? krow + i : rows) * row_bytes;
-      if constexpr (!GF32) {
-        uint32_t lo = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, gc.off0, soff, AUX);
-        uint32_t hi = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, gc.off1, soff, AUX);
-        st.x[i] = lo | (hi << 16);
-      } else {
-        st.x[2 * i] = __builtin_amdgcn_raw_buffer_load_b32(rs, gc.off0, soff, AUX);
-        st.x[2 * i + 1] = __builtin_amdgcn_raw_buffer_load_b32(rs, gc.off1, soff, AUX);
-      }
+    const uint32_t soff = (uint32_t)(krow + i < rows ? krow + i : rows) * row_bytes;         // scalar
+    if constexpr (!GF32) {
+      st.x[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, gc.off0, soff, AUX);
+    } else {
+      u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(rs, gc.off0, soff, AUX);
+      st.x[2 * i] = t.x;
+      st.x[2 * i + 1] = t.y;
     }
   }
+}
+// Values of the lanes and rows outside the matrix, and the pair read one column too far left, put right (!VEC; a uniform branch).
+__device__ __forceinline__ void fix_gstage(GStage<false>& st, int krow, int rows, const GCol& gc) {
+  if (!gc.edge && krow + 8 <= rows) return;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) st.x[i] = krow + i < rows ? (st.x[i] >> gc.shift) & gc.mask : 0u;
 }
 
 // 8 rows x 2 columns -> two 16-byte vectors (one per column, 8 consecutive k each)
@@ -288,7 +297,7 @@ __device__ __forceinline__ void store_colpart(const FusedAdam& f, const MatDev& 
 // w % 4 + 4*rb: the tile spans 128*RB rank indices.  RB = 2 (ranks from 256 up) halves the number of
 // passes over G and the LDS reads per MFMA (each G fragment feeds two rank blocks); its 96 KiB of
 // LDS admit one workgroup per compute unit.
-// VEC: every G row is read with aligned 4-byte accesses (8 loads per stage, else 16).
+// VEC: q is even and every pair of columns 4-byte aligned; else pairs are read at the alignment of an element (q >= 2).
 // GONCE: one rank tile per column block, G is read once (streaming loads).
 // A tile marked `fuse` holds the whole contraction (no split-K): its epilogue applies Adam to its
 // elements of the low-rank state instead of leaving that to a separate pass over g.
@@ -336,22 +345,18 @@ __global__ __launch_bounds__(512) void k_proj_down_pipe(DevCtx d, const ProjTile
 
   const int klim = t.k1 < m.p ? t.k1 : m.p;
   const void* Gbase = ext_ptr(d, EXT_G, t.mat);
+  const GAS char* gbytes = TO_GLOBAL(const char, Gbase);
   const uint32_t row_bytes = (uint32_t)m.q * 2u;
   const rsrc_t rs = make_rsrc(Gbase, (uint32_t)klim * row_bytes);
   const int col = t.n0 + 128 * half + 2 * lane;
-  GCol gc;
-  gc.vec = VEC;
-  gc.off0 = col < m.q ? (uint32_t)col * 2u : OOB;
-  gc.off1 = col + 1 < m.q ? (uint32_t)(col + 1) * 2u : OOB;
+  const GCol gc = g_columns<VEC>(col, t.n0 + 128 * half, m.q, 2u);
+  static_assert(VEC || EFM == 0, "fp32 operands are read in aligned pairs");
   const int wslot = ((4 * half + (lane >> 4)) * 4 + kgrp) * 32 + 2 * (lane & 15);
-  // residual E: fp32 p x q in the arena, same rows and columns (8-byte accesses need an even q: VEC)
+  // residual E: fp32 p x q in the arena, same rows and columns (8-byte accesses)
   const uint32_t erow_bytes = (uint32_t)m.q * EES;
   const rsrc_t re = SRC32 ? make_rsrc(ext_ptr(d, EXT_SRC, t.mat), (uint32_t)klim * erow_bytes)
                           : (EF ? make_rsrc(d.arena + m.err, (uint32_t)klim * erow_bytes) : rs);
-  GCol ge;
-  ge.vec = VEC;
-  ge.off0 = col < m.q ? (uint32_t)col * EES : OOB;
-  ge.off1 = col + 1 < m.q ? (uint32_t)(col + 1) * EES : OOB;
+  const GCol ge = g_columns<true>(col, t.n0 + 128 * half, m.q, EES);
 
   // Q fragments of a stage: (mblk, kstep) pairs, both planes each; 8*RB pairs, RB per wave
   const int64_t kgroups = m.pp / 8;
@@ -437,14 +442,14 @@ __global__ __launch_bounds__(512) void k_proj_down_pipe(DevCtx d, const ProjTile
   GStage<false> st0, st1;
   GStage<E32> se0, se1;                                        // EF: rows of E of the same stages
   constexpr int GAUX = GONCE ? STREAM : 0;
-  // outstanding loads of one stage: 8 (or 16 two-byte ones) of G, as many again of E
-  constexpr int NLOADS = ((SRC32 ? 0 : 1) + (EF ? 1 : 0)) * (VEC ? 8 : 16);
+  // outstanding loads of one stage: 8 of G, as many again of E
+  constexpr int NLOADS = ((SRC32 ? 0 : 1) + (EF ? 1 : 0)) * 8;
   auto wait_one_stage = [&]() {
     if constexpr (NLOADS == 8) WAIT_VM_BARRIER(8);
-    else if constexpr (NLOADS == 16) WAIT_VM_BARRIER(16);
-    else WAIT_VM_BARRIER(32);
+    else WAIT_VM_BARRIER(16);
   };
-  auto stage_out = [&](const GStage<false>& g, const GStage<E32>& e, int sbuf) {
+  auto stage_out = [&](GStage<false>& g, const GStage<E32>& e, int krow, int sbuf) {
+    if constexpr (!VEC) fix_gstage(g, krow, klim, gc);
     if constexpr (SRC32) {
       store_gstage<true>(e, gfrag + sbuf * GSLOTS, glo + sbuf * GSLOTS, wslot);
     } else if constexpr (EF) {
@@ -456,11 +461,11 @@ __global__ __launch_bounds__(512) void k_proj_down_pipe(DevCtx d, const ProjTile
     }
   };
   issue_a(t.k0, 0);
-  if constexpr (!SRC32) load_gstage<false, GAUX>(st0, rs, row_bytes, krow0, klim, gc);                  // stage 0
-  if constexpr (EF) load_gstage<E32, GAUX>(se0, re, erow_bytes, krow0, klim, ge);
-  if constexpr (!SRC32) load_gstage<false, GAUX>(st1, rs, row_bytes, krow0 + BK, klim, gc);             // stage 1
-  if constexpr (EF) load_gstage<E32, GAUX>(se1, re, erow_bytes, krow0 + BK, klim, ge);
-  stage_out(st0, se0, 0);
+  if constexpr (!SRC32) load_gstage<false, GAUX, VEC>(st0, rs, gbytes, row_bytes, krow0, klim, gc);                  // stage 0
+  if constexpr (EF) load_gstage<E32, GAUX, true>(se0, re, nullptr, erow_bytes, krow0, klim, ge);
+  if constexpr (!SRC32) load_gstage<false, GAUX, VEC>(st1, rs, gbytes, row_bytes, krow0 + BK, klim, gc);             // stage 1
+  if constexpr (EF) load_gstage<E32, GAUX, true>(se1, re, nullptr, erow_bytes, krow0 + BK, klim, ge);
+  stage_out(st0, se0, krow0, 0);
   wait_one_stage();
 
   // one iteration; NEXT holds stage s+1 (read one iteration ago), LOAD receives stage s+2
@@ -468,12 +473,12 @@ __global__ __launch_bounds__(512) void k_proj_down_pipe(DevCtx d, const ProjTile
   {                                                                                               \
     const int kr = t.k0 + (S) * BK;                                                               \
     if ((S) + 1 < nstages) issue_a(kr + BK, ((S) + 1) & 1);                                       \
-    if constexpr (!SRC32) load_gstage<false, GAUX>(LOAD, rs, row_bytes, krow0 + ((S) + 2) * BK, klim, gc); \
-    if constexpr (EF) load_gstage<E32, GAUX>(LOADE, re, erow_bytes, krow0 + ((S) + 2) * BK, klim, ge); \
+    if constexpr (!SRC32) load_gstage<false, GAUX, VEC>(LOAD, rs, gbytes, row_bytes, krow0 + ((S) + 2) * BK, klim, gc); \
+    if constexpr (EF) load_gstage<E32, GAUX, true>(LOADE, re, nullptr, erow_bytes, krow0 + ((S) + 2) * BK, klim, ge); \
     ISSUE_FENCE();                                                                                \
     compute((S) & 1);                                                                             \
     ISSUE_FENCE();                                                                                \
-    stage_out(NEXT, NEXTE, ((S) + 1) & 1);                                                        \
+    stage_out(NEXT, NEXTE, krow0 + ((S) + 1) * BK, ((S) + 1) & 1);                                \
     wait_one_stage();                                                                             \
   }
   // two stages per trip so that the two register sets alternate statically; the odd last stage is
@@ -781,10 +786,13 @@ static hipError_t launch_pipe(dim3 grid, const DevCtx& d, const ProjTile* tiles,
 template <int RB, int EF>
 static hipError_t launch_pipe_vo(bool g_vec, bool g_once, dim3 grid, const DevCtx& d, const ProjTile* tiles, float* glow,
                                  int64_t split_stride, float grad_scale, const FusedAdam& fa, hipStream_t s) {
-  if (g_once) return g_vec ? launch_pipe<RB, true, true, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s)
-                           : launch_pipe<RB, false, true, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s);
-  return g_vec ? launch_pipe<RB, true, false, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s)
-               : launch_pipe<RB, false, false, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+  if constexpr (EF == 0) {
+    if (!g_vec) return g_once ? launch_pipe<RB, false, true, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s)
+                              : launch_pipe<RB, false, false, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+  }
+  if (!g_vec) return hipErrorInvalidValue;                       // (error feedback and fp32 sources come with aligned pairs only)
+  return g_once ? launch_pipe<RB, true, true, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s)
+                : launch_pipe<RB, true, false, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s);
 }
 static hipError_t launch_pipe_select(int rb, bool g_vec, bool g_once, int ef, dim3 grid, const DevCtx& d, const ProjTile* tiles,
                                      float* glow, int64_t split_stride, float grad_scale, const FusedAdam& fa, hipStream_t s) {
@@ -861,133 +869,66 @@ template <> struct WAcc<true> {
   }
 };
 
-// ---------------------------------------------------------------------------------------
-// Up-projection with the weight update fused, fallback for any q and any alignment of W (the main
-// path below needs q % 4 == 0 and 16-byte aligned W).  Workgroup tile 128 x 128 of W, 4 waves in a
-// 2 x 2 grid, each wave 64 x 64 = 2 x 2 accumulator blocks.  Operand fragments come straight from
-// the packed planes (one coalesced 1 KiB read per wave and fragment), double-buffered in registers;
-// the W tile is fetched through a buffer resource, one dword per access, before the contraction so
-// that its latency hides behind it.
-// ---------------------------------------------------------------------------------------
-template <bool WBF>       // WBF: the caller's W is bf16 (never together with to_mom: the momentum is fp32)
-__global__ __launch_bounds__(256) void k_proj_up(DevCtx d, const ProjTile* __restrict__ tiles,
-                                                 const uint16_t* __restrict__ n_hi, const uint16_t* __restrict__ n_lo, float lr, int to_mom,
-                                                 StepDev* advance) {
-  constexpr uint32_t ES = WBF ? 2u : 4u;
-  const ProjTile t = tiles[tile_index(advance)];
-  if (t.mat < 0 || mat_skipped(d, t.mat)) return;
-  const MatDev m = d.mats[t.mat];
-  const GAS u32x4* qa_hi = TO_GLOBAL(const u32x4, d.arena + m.qa_hi);
-  const GAS u32x4* qa_lo = TO_GLOBAL(const u32x4, d.arena + m.qa_lo);
-  const GAS u32x4* nh = TO_GLOBAL(const u32x4, n_hi + m.lr_off);
-  const GAS u32x4* nl = TO_GLOBAL(const u32x4, n_lo + m.lr_off);
-
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: keeps row offsets scalar
-  const int mb0 = t.m0 / 32 + 2 * (wave & 1);
-  const int nb0 = t.n0 / 32 + 2 * (wave >> 1);
-  const int mblocks = m.pp / 32, nblocks = m.qp / 32;
-  const int p = m.p, q = m.q;
-  const int64_t rgroups = m.rp / 8;
-
-  // W is a buffer of p*q floats: a lane whose column or row is outside the matrix gets an offset
-  // outside the buffer (reads give 0, writes are dropped).  Register v of block (a, b) is row
-  // 8*(v/4) + 4*(lane/32) + v%4, column lane%32: the lane supplies its part of the offset, the
-  // block / register part is scalar, and a row at or past p gets the size of the resource.
-  const uint32_t row_bytes = (uint32_t)q * ES;
-  const rsrc_t rw = make_rsrc(to_mom ? static_cast<void*>(d.arena + m.mom) : ext_ptr(d, EXT_W, t.mat), (uint32_t)p * row_bytes);
-  uint32_t voff[2];
-#pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    int col = 32 * (nb0 + b) + (lane & 31);
-    voff[b] = col < q ? (uint32_t)(4 * (lane >> 5)) * row_bytes + (uint32_t)(lane & 31) * ES : OOB;
+// Four consecutive columns per lane of a target whose rows start at any element (q % 4 != 0, or a pointer that is not aligned to
+// four elements).  fp32: the same 16-byte buffer accesses, which need no more than dword alignment.  bf16: 8-byte global accesses
+// at 2-byte alignment under a range check of their own.  A wave whose 64 columns reach past the last column (`edge`,
+// uniform) takes one element at a time: its four columns could otherwise run over into the next row.
+// Cacheable, not streaming: the rows' cache lines are shared with the wave and the tile beside, and a streaming line is fetched
+// again.  12 x (4 x 1023 x 1023, 1023 x 2731, 2731 x 1023), r = 100, fp32: 286 us with a kernel of 4-byte accesses, 268 with these
+// and streaming, 239 with streaming stores alone, 230 so (1.08 GB); 193 for 1024 and 2732 columns in whole vectors.
+template <bool WBF>
+struct Ragged {
+  static constexpr uint32_t ES = WAcc<WBF>::ES;
+  typedef typename WAcc<WBF>::raw_t raw_t;
+  typedef raw_t unaligned_t __attribute__((aligned(2)));
+  rsrc_t r;
+  GAS char* base;
+  uint32_t bytes, voff;      // size of the target; the lane's offset (OOB where its first column is outside)
+  uint32_t ncol;             // edge: how many of the lane's four columns exist
+  bool edge;
+  __device__ __forceinline__ void setup(rsrc_t r_, const void* b, uint32_t n, uint32_t v, int lcol, int q, bool edge_) {
+    r = r_; base = TO_GLOBAL(char, const_cast<void*>(b)); bytes = n; voff = v;
+    ncol = lcol + 4 <= q ? 4u : lcol < q ? (uint32_t)(q - lcol) : 0u;
+    edge = edge_;
   }
-  auto w_soff = [&](int a, int b, int v) -> uint32_t {
-    const int row = 32 * (mb0 + a) + 8 * (v >> 2) + (v & 3);
-    return row < p ? (uint32_t)row * row_bytes + (uint32_t)(32 * (nb0 + b)) * ES : (uint32_t)p * row_bytes;
-  };
-  if (advance_step(advance) || mb0 >= mblocks || nb0 >= nblocks) return;
-  float wv[2][2][16];
+  __device__ __forceinline__ uint32_t element(uint32_t i) const { return i < ncol ? voff + i * ES : OOB; }
+  __device__ __forceinline__ raw_t load(uint32_t soff) const {
+    if (edge) {
+      uint32_t e[4];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        if constexpr (WBF) wv[a][b][v] = __uint_as_float((uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, voff[b], w_soff(a, b, v), STREAM) << 16);
-        else wv[a][b][v] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rw, voff[b], w_soff(a, b, v), STREAM));
+      for (uint32_t i = 0; i < 4; ++i) {
+        if constexpr (WBF) e[i] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, element(i), soff, 0);
+        else e[i] = __builtin_amdgcn_raw_buffer_load_b32(r, element(i), soff, 0);
       }
-  ISSUE_FENCE();
-
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
-
-  const int ksteps = m.rp / 16;                    // even: rp is a multiple of 32
-  // uniform plane pointers of the row blocks and column blocks (clamped into the planes: loads of
-  // blocks past the edge stay inside, their stores fall outside the buffer); the lane adds its index
-  const GAS u32x4* pqh[2]; const GAS u32x4* pql[2];
-  const GAS u32x4* pnh[2]; const GAS u32x4* pnl[2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a) {
-    int mbc = mb0 + a < mblocks ? mb0 + a : mblocks - 1;
-    pqh[a] = qa_hi + (int64_t)mbc * rgroups * 32;
-    pql[a] = qa_lo + (int64_t)mbc * rgroups * 32;
+      if constexpr (WBF) return u32x2{e[0] | (e[1] << 16), e[2] | (e[3] << 16)};
+      else return mk4(e[0], e[1], e[2], e[3]);
+    }
+    if constexpr (WBF) {       // (no overflow: no lane of the wave holds OOB here)
+      raw_t x = {0u, 0u};
+      if (voff + soff < bytes) x = *(const GAS unaligned_t*)(base + soff + voff);
+      return x;
+    } else {
+      return __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
+    }
   }
+  __device__ __forceinline__ void store(f32x4 x, uint32_t soff) const {
+    if (edge) {
 #pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    int nbc = nb0 + b < nblocks ? nb0 + b : nblocks - 1;
-    pnh[b] = nh + (int64_t)nbc * rgroups * 32;
-    pnl[b] = nl + (int64_t)nbc * rgroups * 32;
-  }
-  struct Frags { u32x4 qh[2], ql[2], nh[2], nl[2]; };
-  auto load_frags = [&](Frags& f, int ks) {
-    const uint32_t o = (uint32_t)ks * 64u + (uint32_t)lane;
-#pragma unroll
-    for (int a = 0; a < 2; ++a) { f.qh[a] = pqh[a][o]; f.ql[a] = pql[a][o]; }
-#pragma unroll
-    for (int b = 0; b < 2; ++b) { f.nh[b] = pnh[b][o]; f.nl[b] = pnl[b][o]; }
-  };
-  auto compute = [&](const Frags& f) {
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf(f.qh[a]), as_bf(f.nh[b]), acc[a][b], 0, 0, 0);
-        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf(f.qh[a]), as_bf(f.nl[b]), acc[a][b], 0, 0, 0);
-        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf(f.ql[a]), as_bf(f.nh[b]), acc[a][b], 0, 0, 0);
+      for (uint32_t i = 0; i < 4; ++i) {
+        if constexpr (WBF) __builtin_amdgcn_raw_buffer_store_b16((short)pack_bf16_rne(x[i], 0.f), r, element(i), soff, 0);
+        else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[i]), r, element(i), soff, 0);
       }
-  };
-  Frags f0, f1;
-  load_frags(f0, 0);
-  for (int ks = 0; ks < ksteps; ks += 2) {
-    load_frags(f1, ks + 1);
-    ISSUE_FENCE();
-    compute(f0);
-    if (ks + 2 < ksteps) load_frags(f0, ks + 2);
-    ISSUE_FENCE();
-    compute(f1);
+    } else if constexpr (WBF) {
+      if (voff + soff < bytes) *(GAS unaligned_t*)(base + soff + voff) = u32x2{pack_bf16_rne(x.x, x.y), pack_bf16_rne(x.z, x.w)};
+    } else {
+      store_b128<0>(mk4(__float_as_uint(x.x), __float_as_uint(x.y), __float_as_uint(x.z), __float_as_uint(x.w)), r, voff, soff);
+    }
   }
-  ISSUE_FENCE();
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int v = 0; v < 16; ++v)
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const float val = fmaf(-lr, acc[a][b][v], wv[a][b][v]);
-        if constexpr (WBF) __builtin_amdgcn_raw_buffer_store_b16((short)f2bf_rne(val), rw, voff[b], w_soff(a, b, v), STREAM);
-        else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(val), rw, voff[b], w_soff(a, b, v), STREAM);
-      }
-}
+};
 
 // ---------------------------------------------------------------------------------------
-// Up-projection, main path (q % 4 == 0, W 16-byte aligned).  Same tile and wave layout as the
-// fallback above.
+// Up-projection with the weight update fused.  Workgroup tile 128 x 128 of W, 4 waves in a 2 x 2 grid, each wave
+// 64 x 64 = 2 x 2 accumulator blocks.
 // W access.  The vector-memory front end costs about 16 cycles per instruction whatever its width
 // and one tag look-up per cache line touched, so W is moved with 16-byte accesses that cover whole
 // 128-byte lines: the matrix core computes the transposed block (Q N)^T = N^T Q^T, which puts four
@@ -995,6 +936,7 @@ __global__ __launch_bounds__(256) void k_proj_up(DevCtx d, const ProjTile* __res
 // block then goes through a per-wave LDS buffer (16-byte writes, 16-byte reads) into row order,
 // where 8 lanes cover one 128-byte line of a row, and is combined with the W values that were
 // fetched in that same order.
+// (rows at any element: see Ragged.)
 // Operands.  The fragments are brought in ONCE per workgroup by direct global-to-LDS loads (each
 // 1 KiB fragment is one 16-byte-per-lane load that lands in lane order, so no registers and no
 // transposition are involved) and every wave then reads its fragments from LDS.  This halves the
@@ -1012,13 +954,14 @@ __global__ __launch_bounds__(256) void k_proj_up(DevCtx d, const ProjTile* __res
 //   Delta = Q B stays in the accumulators, the tile that is read is the anchor, and the epilogue does
 //   b <- mu b + Delta;  x <- anchor - eta_s (Delta + mu b) (Nesterov), anchor - eta_s b (heavy ball) or anchor - eta_s Delta
 //   (no momentum);  W <- x, anchor <- x.
-template <int NW, int EPI, bool WBF>   // NW waves per workgroup: 4 (wave tile 64 x 64) or 8 (wave tile 32 x 64); EPI 0 plain, 1 gradient term, 2 outer step;
-                                       // WBF: the target (the caller's W, or the residual E) is stored in bf16
+template <int NW, int EPI, bool WBF, bool RAG = false>   // NW waves per workgroup: 4 (wave tile 64 x 64) or 8 (wave tile 32 x 64); EPI 0 plain, 1 gradient term, 2 outer step;
+                                       // WBF: the target (the caller's W, or the residual E) is stored in bf16; RAG: rows at any alignment (plain update)
 __global__ __launch_bounds__(64 * NW) void k_proj_up_dma(DevCtx d, const ProjTile* __restrict__ tiles,
                                                          const uint16_t* __restrict__ n_hi, const uint16_t* __restrict__ n_lo, UpArgs ua) {
   constexpr bool WITH_G = EPI == 1;
   constexpr bool OUTER = EPI == 2;
   static_assert(!WBF || EPI != 2, "bf16 targets: plain update and gradient-term epilogue");
+  static_assert(!RAG || EPI == 0, "the other epilogues need rows of whole quads");
   typedef WAcc<WBF> WA;
   constexpr uint32_t WES = WA::ES;
   const float lr = -ua.coef_acc;
@@ -1089,13 +1032,18 @@ __global__ __launch_bounds__(64 * NW) void k_proj_up_dma(DevCtx d, const ProjTil
   };
 
   const rsrc_t rg = WITH_G ? make_rsrc(ext_ptr(d, EXT_G, t.mat), (uint32_t)p * ((uint32_t)q * (ua.g_is_f32 ? 4u : 2u))) : rw;
+  Ragged<WBF> rag;
+  if constexpr (RAG) rag.setup(rw, target, (uint32_t)p * row_bytes, voff, lcol, q, 32 * nb0 + 64 > q);
   if (advance_step(ua.advance)) return;
   issue_chunk(0, 0);
   typename WA::raw_t wv[AM][8];
 #pragma unroll
   for (int a = 0; a < AM; ++a)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) wv[a][j] = WA::load(rw, voff, w_soff(a, j));
+    for (int j = 0; j < 8; ++j) {
+      if constexpr (RAG) wv[a][j] = rag.load(w_soff(a, j));
+      else wv[a][j] = WA::load(rw, voff, w_soff(a, j));
+    }
   // gradient term (WITH_G): four consecutive columns per lane, same rows as the W accesses; a bf16 G tile is
   // requested here, with the W tile, so that it arrives during the contraction
   const uint32_t ges = ua.g_is_f32 ? 4u : 2u;
@@ -1235,6 +1183,10 @@ __global__ __launch_bounds__(64 * NW) void k_proj_up_dma(DevCtx d, const ProjTil
     for (int j = 0; j < 8; ++j) {
       f32x4 x = *reinterpret_cast<const f32x4*>(T + (rr + 4 * j) * TP + 4 * c16);
       const f32x4 wf = WA::unpack(wv[a][j]);
+      if constexpr (RAG) {
+        rag.store(f32x4{fmaf(-lr, x.x, wf.x), fmaf(-lr, x.y, wf.y), fmaf(-lr, x.z, wf.z), fmaf(-lr, x.w, wf.w)}, w_soff(a, j));
+        continue;
+      }
       if constexpr (WBF) {       // bf16 target: the new value is formed in fp32 and rounded once
         f32x4 val = {fmaf(-lr, x.x, wf.x), fmaf(-lr, x.y, wf.y), fmaf(-lr, x.z, wf.z), fmaf(-lr, x.w, wf.w)};
         if constexpr (WITH_G) val += gt[j];
@@ -1288,7 +1240,7 @@ __global__ __launch_bounds__(64 * NW) void k_proj_up_dma(DevCtx d, const ProjTil
 // the contraction: its row blocks are requested when the contraction ends, three in flight (two when the epilogue
 // also reads a gradient tile: the full-rank QHM update, the residual of the error feedback).
 // ---------------------------------------------------------------------------------------
-template <bool WBF, bool WITH_G>     // WITH_G: gradient-term epilogue (bf16 G): the full-rank QHM update, or the residual E as target
+template <bool WBF, bool WITH_G, bool RAG = false>     // WITH_G: gradient-term epilogue (bf16 G): the full-rank QHM update, or the residual E as target; RAG: rows of the target at any alignment (plain update)
 __global__ __launch_bounds__(256) void k_proj_up_wide(DevCtx d, const ProjTile* __restrict__ tiles,
                                                       const uint16_t* __restrict__ n_hi, const uint16_t* __restrict__ n_lo, UpArgs ua) {
   typedef WAcc<WBF> WA;
@@ -1357,6 +1309,9 @@ __global__ __launch_bounds__(256) void k_proj_up_wide(DevCtx d, const ProjTile* 
   };
 
   const rsrc_t rg = WITH_G ? make_rsrc(ext_ptr(d, EXT_G, t.mat), (uint32_t)p * ((uint32_t)q * 2u)) : rw;
+  static_assert(!RAG || !WITH_G, "the gradient-term epilogue needs rows of whole quads");
+  Ragged<WBF> rag;
+  if constexpr (RAG) rag.setup(rw, target, (uint32_t)p * row_bytes, voff, lcol, q, 32 * nb0 + 64 > q);
   if (advance_step(ua.advance)) return;
   issue_chunk(0, 0);
   issue_chunk(1, 1);
@@ -1465,12 +1420,16 @@ __global__ __launch_bounds__(256) void k_proj_up_wide(DevCtx d, const ProjTile* 
         val.x = fmaf(cscale.x, __uint_as_float(w.x << 16), val.x); val.y = fmaf(cscale.y, __uint_as_float(w.x & 0xffff0000u), val.y);
         val.z = fmaf(cscale.z, __uint_as_float(w.y << 16), val.z); val.w = fmaf(cscale.w, __uint_as_float(w.y & 0xffff0000u), val.w);
       }
-      WA::store(val, rw, voff, w_soff(a, j));
+      if constexpr (RAG) rag.store(val, w_soff(a, j));
+      else WA::store(val, rw, voff, w_soff(a, j));
     }
   };
   auto fetch = [&](int a, typename WA::raw_t (&wv)[8], GRows& gr) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) wv[j] = WA::load(rw, voff, w_soff(a, j));
+    for (int j = 0; j < 8; ++j) {
+      if constexpr (RAG) wv[j] = rag.load(w_soff(a, j));
+      else wv[j] = WA::load(rw, voff, w_soff(a, j));
+    }
     if constexpr (WITH_G) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) gr.g[j] = __builtin_amdgcn_raw_buffer_load_b64(rg, gvoff, g_soff(a, j), STREAM);
@@ -1506,20 +1465,22 @@ __global__ __launch_bounds__(256) void k_proj_up_wide(DevCtx d, const ProjTile* 
   }
 }
 
-hipError_t launch_proj_up_wide(const DevCtx& d, const ProjTile* tiles, int ntiles, const uint16_t* b_hi, const uint16_t* b_lo,
+hipError_t launch_proj_up_wide(const DevCtx& d, const ProjTile* tiles, int ntiles, bool vec, const uint16_t* b_hi, const uint16_t* b_lo,
                                const UpArgs& ua, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
   constexpr int LDS_BYTES = 3 * 24 * 1024;
-  static LdsRaised raised[4];
-  const void* kernels[4] = {reinterpret_cast<const void*>(k_proj_up_wide<false, false>), reinterpret_cast<const void*>(k_proj_up_wide<true, false>),
-                            reinterpret_cast<const void*>(k_proj_up_wide<false, true>), reinterpret_cast<const void*>(k_proj_up_wide<true, true>)};
-  for (int k = 0; k < 4; ++k)
+  static LdsRaised raised[6];
+  const void* kernels[6] = {reinterpret_cast<const void*>(k_proj_up_wide<false, false>), reinterpret_cast<const void*>(k_proj_up_wide<true, false>),
+                            reinterpret_cast<const void*>(k_proj_up_wide<false, true>), reinterpret_cast<const void*>(k_proj_up_wide<true, true>),
+                            reinterpret_cast<const void*>(k_proj_up_wide<false, false, true>), reinterpret_cast<const void*>(k_proj_up_wide<true, false, true>)};
+  for (int k = 0; k < 6; ++k)
     if (hipError_t e = raise_lds(kernels[k], LDS_BYTES, raised[k]); e != hipSuccess) return e;
   const bool with_g = ua.coef_g != 0.f || ua.target_err == 1;
-  if (with_g && ua.g_is_f32) return hipErrorInvalidValue;      // the gradient-term epilogue here reads bf16 gradients
+  if (with_g && (ua.g_is_f32 || !vec)) return hipErrorInvalidValue;      // the gradient-term epilogue here reads bf16 gradients, four columns at a time
   if (ua.target_err == 2 || ua.outer || ua.colscale == 2) return hipErrorInvalidValue;
-#define LORDO_WIDE(WBFV, GV) hipLaunchKernelGGL((k_proj_up_wide<WBFV, GV>), dim3(ntiles + (ua.advance ? 1 : 0)), dim3(256), LDS_BYTES, s, d, tiles, b_hi, b_lo, ua)
-  if (ua.w_bf16) { if (with_g) LORDO_WIDE(true, true); else LORDO_WIDE(true, false); }
+#define LORDO_WIDE(...) hipLaunchKernelGGL((k_proj_up_wide<__VA_ARGS__>), dim3(ntiles + (ua.advance ? 1 : 0)), dim3(256), LDS_BYTES, s, d, tiles, b_hi, b_lo, ua)
+  if (!vec) { if (ua.w_bf16) LORDO_WIDE(true, false, true); else LORDO_WIDE(false, false, true); }
+  else if (ua.w_bf16) { if (with_g) LORDO_WIDE(true, true); else LORDO_WIDE(true, false); }
   else { if (with_g) LORDO_WIDE(false, true); else LORDO_WIDE(false, false); }
 #undef LORDO_WIDE
   return hipGetLastError();
@@ -1690,8 +1651,8 @@ hipError_t launch_proj_up(const DevCtx& d, const ProjTile* tiles, int ntiles, bo
     if (w_bf16) hipLaunchKernelGGL((k_proj_up_dma<4, 0, true>), grid, block, 0, s, d, tiles, b_hi, b_lo, ua);
     else hipLaunchKernelGGL((k_proj_up_dma<4, 0, false>), grid, block, 0, s, d, tiles, b_hi, b_lo, ua);
   } else {
-    if (w_bf16) hipLaunchKernelGGL(k_proj_up<true>, grid, block, 0, s, d, tiles, b_hi, b_lo, -ua.coef_acc, 0, ua.advance);
-    else hipLaunchKernelGGL(k_proj_up<false>, grid, block, 0, s, d, tiles, b_hi, b_lo, -ua.coef_acc, ua.target_err == 2 ? 1 : 0, ua.advance);
+    if (w_bf16) hipLaunchKernelGGL((k_proj_up_dma<4, 0, true, true>), grid, block, 0, s, d, tiles, b_hi, b_lo, ua);
+    else hipLaunchKernelGGL((k_proj_up_dma<4, 0, false, true>), grid, block, 0, s, d, tiles, b_hi, b_lo, ua);
   }
   return hipGetLastError();
 }
