@@ -75,7 +75,7 @@ struct GemmDesc {
   int32_t M, N, K, mat;
   int64_t sAm, sAk, sBk, sBn;
   int32_t ldc, a_bf16, b_bf16;        // a_bf16: 0 fp32, 1 bf16, 2 = element type given at launch (refresh source)
-  int32_t prec;                       // 0: fp32 matrix cores; 1: operands split into bf16 hi + lo (range-finder products)
+  int32_t pad0;
   float alpha, beta;
   // split-K (ksplit > 1): slice s covers k in [s*klen, (s+1)*klen) and writes its raw M x N sum to
   // P + s*M*N; a reduction kernel then adds the slices in order and applies alpha, beta, C2
@@ -83,6 +83,12 @@ struct GemmDesc {
   OpRef P;
   int32_t tri, pad_;      // tri = 1: B(k, n) = 0 for k > n (transposed lower-triangular factor): the contraction of a column tile ends at its last column
 };
+
+// How the operands of every problem of a launch can be read along their unit-stride direction:
+//   ALIGNED  whole 16-byte vectors (8-byte ones of a bf16 source): split into bf16 terms (see gemm32.hip);
+//   RAGGED   rows, ends or pointers at any element, at least four elements long: split into bf16 terms too;
+//   ANY      neither: such problems run on the fp32 matrix cores element by element, the aligned ones of the launch as in ALIGNED
+enum GemmMode : int32_t { GEMM_ALIGNED = 0, GEMM_RAGGED = 1, GEMM_ANY = 2 };
 
 struct GemmTile { int32_t desc; int16_t tm, tn; int16_t ks, pad; };
 
@@ -143,7 +149,7 @@ hipError_t launch_proj_up_wide(const DevCtx& d, const ProjTile* tiles, int ntile
                                const UpArgs& ua, hipStream_t s);
 // gemm32.hip
 // alpha_mul scales every product of the launch (per-call coefficients); an entry of the table covers sub_m x sub_n tiles
-hipError_t launch_gemm32(const DevCtx& d, const GemmDesc* descs, const GemmTile* tiles, int ntiles, int tile, int src_is_bf16,
+hipError_t launch_gemm32(const DevCtx& d, const GemmDesc* descs, const GemmTile* tiles, int ntiles, int tile, int mode, bool a_bf16,
                          hipStream_t s, float alpha_mul = 1.f, int sub_m = 1, int sub_n = 1);
 // The same products with B split once into three bf16 planes (p0, p1, p2: flat arrays addressed by lr_off) and tiles of
 // 128 x tn_edge; max_groups: largest number of 8-element groups of a plane; a_once: one column tile, A is read once

@@ -2,9 +2,9 @@
 // blocked Cholesky panels, the inverse of the factor and its application, and the moment rotation.
 // One launch runs a list of independent problems (one per weight matrix); a tile table maps each
 // workgroup to (problem, tile, K slice).  Operands are addressed by element strides, so any transpose
-// and the bf16 gradient type are handled by the loader; accumulation is fp32.  Arithmetic: operands that
-// can be read with 16-byte accesses are split into bf16 terms (three per fp32 operand: as exact as fp32)
-// and multiplied on v_mfma_f32_32x32x16_bf16; anything else runs on the fp32 matrix cores
+// and the bf16 gradient type are handled by the loader; accumulation is fp32.  Arithmetic: operands are read in vectors of four
+// elements, aligned or not (GemmMode), split into bf16 terms (three per fp32 operand: as exact as fp32) and multiplied on
+// v_mfma_f32_32x32x16_bf16; operands too short for a vector, and unaligned ones of the initial projection, run on the fp32 matrix cores
 // (v_mfma_f32_32x32x2_f32).  k_gemm_planes is the kernel for products of a tall fp32 matrix with a block that many row tiles
 // share: the same arithmetic with the block split once (k_pack_planes).
 #include "common.h"
@@ -52,7 +52,7 @@ struct Operand {
   // Branch-free: an element outside the operand is read from element 0 (always valid) and replaced
   // by zero when the tile is written to LDS.  fetch_raw only issues the loads and leaves the loaded
   // bits untouched, so nothing waits for them until stash() runs one K step later.
-  template <bool BF16, bool VEC>
+  template <bool BF16>
   __device__ __forceinline__ void fetch_raw(u32x4 (&raw)[NV], int k0, int tid) const {
     const int64_t e_step = kfast ? s_k : s_i;                        // from one element of a vector to the next
     const int d_i = kfast ? 0 : 1, d_k = kfast ? 1 : 0;
@@ -62,27 +62,17 @@ struct Operand {
       coords(tid + n * 256, ii, kk);
       const int gi = i0 + ii, gk = k0 + kk;
       const int64_t idx = (int64_t)gi * s_i + (int64_t)gk * s_k;
-      if constexpr (VEC) {
-        const int64_t at = (gi < lim && gk < kend) ? idx : 0;
-        if constexpr (BF16) {
-          u32x2 w = *reinterpret_cast<const GAS u32x2*>((const GAS char*)base + at * 2);
-          raw[n].x = w.x; raw[n].y = w.y;
-        } else {
-          raw[n] = *reinterpret_cast<const GAS u32x4*>((const GAS char*)base + at * 4);
-        }
-      } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const bool ok = gi + e * d_i < lim && gk + e * d_k < kend;
-          const int64_t at = ok ? idx + e * e_step : 0;
-          if constexpr (BF16) raw[n][e] = *reinterpret_cast<const GAS uint16_t*>((const GAS char*)base + at * 2);
-          else raw[n][e] = *reinterpret_cast<const GAS uint32_t*>((const GAS char*)base + at * 4);
-        }
+      for (int e = 0; e < 4; ++e) {
+        const bool ok = gi + e * d_i < lim && gk + e * d_k < kend;
+        const int64_t at = ok ? idx + e * e_step : 0;
+        if constexpr (BF16) raw[n][e] = *reinterpret_cast<const GAS uint16_t*>((const GAS char*)base + at * 2);
+        else raw[n][e] = *reinterpret_cast<const GAS uint32_t*>((const GAS char*)base + at * 4);
       }
     }
   }
   // Converts the raw bits of the tile starting at k0, zeroes what lies outside the operand and writes S[k][i].
-  template <bool BF16, bool VEC>
+  template <bool BF16>
   __device__ __forceinline__ void stash(const u32x4 (&raw)[NV], float (*S)[TMN + 4], int k0, int tid) const {
     const int d_i = kfast ? 0 : 1, d_k = kfast ? 1 : 0;
 #pragma unroll
@@ -91,13 +81,8 @@ struct Operand {
       coords(tid + n * 256, ii, kk);
       const int gi = i0 + ii, gk = k0 + kk;
       f32x4 r;
-      if constexpr (VEC && BF16) {
-        r.x = __uint_as_float(raw[n].x << 16); r.y = __uint_as_float(raw[n].x & 0xffff0000u);
-        r.z = __uint_as_float(raw[n].y << 16); r.w = __uint_as_float(raw[n].y & 0xffff0000u);
-      } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) r[e] = __uint_as_float(BF16 ? raw[n][e] << 16 : raw[n][e]);
-      }
+      for (int e = 0; e < 4; ++e) r[e] = __uint_as_float(BF16 ? raw[n][e] << 16 : raw[n][e]);
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         if (!(gi + e * d_i < lim && gk + e * d_k < kend)) r[e] = 0.f;
@@ -111,21 +96,21 @@ struct Operand {
   }
 };
 
-// K loop of one workgroup tile, specialised on the element type of A and on whole-vector access.
-template <int WB, bool A_BF16, bool VEC, int TM, int NV>
+// K loop of one workgroup tile on the fp32 matrix cores, specialised on the element type of A.
+template <int WB, bool A_BF16, int TM, int NV>
 __device__ __forceinline__ void gemm_loop(f32x16 (&acc)[WB][WB], const Operand<TM, NV>& opA, const Operand<TM, NV>& opB,
                                           float (*As)[TM + 4], float (*Bs)[TM + 4], int kbeg, int K, int tid, int lane, int wm, int wn) {
   u32x4 ra[NV], rb[NV];
-  opA.template fetch_raw<A_BF16, VEC>(ra, kbeg, tid);
-  opB.template fetch_raw<false, VEC>(rb, kbeg, tid);
+  opA.template fetch_raw<A_BF16>(ra, kbeg, tid);
+  opB.template fetch_raw<false>(rb, kbeg, tid);
   for (int k0 = kbeg; k0 < K; k0 += TK) {
     __syncthreads();                           // previous tile fully consumed
-    opA.template stash<A_BF16, VEC>(ra, As, k0, tid);
-    opB.template stash<false, VEC>(rb, Bs, k0, tid);
+    opA.template stash<A_BF16>(ra, As, k0, tid);
+    opB.template stash<false>(rb, Bs, k0, tid);
     __syncthreads();
     if (k0 + TK < K) {
-      opA.template fetch_raw<A_BF16, VEC>(ra, k0 + TK, tid);
-      opB.template fetch_raw<false, VEC>(rb, k0 + TK, tid);
+      opA.template fetch_raw<A_BF16>(ra, k0 + TK, tid);
+      opB.template fetch_raw<false>(rb, k0 + TK, tid);
     }
     asm volatile("" ::: "memory");             // keep the loads above the arithmetic: they must be in flight during it
 #pragma unroll
@@ -163,15 +148,37 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 constexpr int FRAG_BLOCK = 4 * 264 + 8;      // elements per 32 x 32 block
 __device__ __forceinline__ int frag_index(int i, int k) { return (i >> 5) * FRAG_BLOCK + (k >> 3) * 264 + (i & 31) * 8 + (k & 7); }
 
-// Operand tile of the split-bf16 loop; whole-vector access only (the caller falls back to the fp32
-// loop otherwise).  A thread owns up to four vectors of four elements; along k they pack directly,
+// Operand tile of the split-bf16 loop, read in vectors of four elements along the unit-stride direction.  UA = false: every
+// vector is aligned and lies entirely inside or outside the operand.  UA = true (rows of an odd number of elements, pointers into
+// the middle of a vector, ranks that are no multiple of four): vectors are read at the alignment of an element, and one that would run
+// over the end of the operand is read further back, ending with its last element; shift_in() then moves the elements to their
+// places and zeros in behind them (a uniform branch: only tiles at the end have such vectors).  On the fp32 matrix cores with
+// element accesses, which such operands took before, a refresh of 21 matrices (2047 x 2047 .. 5001, r = 171) took 6.25 ms from bf16 and
+// 6.23 ms from fp32, so 3.11 and 3.68 ms.
+// A thread owns up to four vectors of four elements; along k they pack directly,
 // along i the thread owns a 4 x 4 patch (four i, four consecutive k) and transposes it in registers.
-template <int TMN>
+template <int TMN, bool UA = false>
 struct OperandBF {
   const char* base;
   int64_t s_i, s_k;
   int lim, kend, i0;
   bool kfast;
+  // how many of the vector's elements lie past the end (1 .. 3) if it starts inside and ends outside, else 0
+  __device__ __forceinline__ int overrun(int gi, int gk) const {
+    const int over = kfast ? gk + 4 - kend : gi + 4 - lim;
+    return over > 0 && over < 4 ? over : 0;
+  }
+  template <bool BF16>
+  static __device__ __forceinline__ u32x4 shift_in(u32x4 x, int n) {
+    if constexpr (BF16) {
+      const uint64_t v = (((uint64_t)x.y << 32) | x.x) >> (16 * n);
+      x.x = (uint32_t)v; x.y = (uint32_t)(v >> 32);
+    } else {
+      if (n & 1) x = u32x4{x.y, x.z, x.w, 0u};
+      if (n & 2) x = u32x4{x.z, x.w, 0u, 0u};
+    }
+    return x;
+  }
   static constexpr int NVK = TMN / 32;          // vectors per thread when k is the unit-stride direction
 
   __device__ __forceinline__ void setup(const char* b, int64_t si, int64_t sk, int lim_, int kend_, int i0_) {
@@ -198,8 +205,18 @@ struct OperandBF {
       int ii = 0, kk = 0;
       const bool have = coords(tid, n, ii, kk);
       const int gi = i0 + ii, gk = k0 + kk;
-      const int64_t at = (have && gi < lim && gk < kend) ? (int64_t)gi * s_i + (int64_t)gk * s_k : 0;
-      if constexpr (BF16) {
+      int64_t at = (have && gi < lim && gk < kend) ? (int64_t)gi * s_i + (int64_t)gk * s_k : 0;
+      if constexpr (UA) {
+        if (at != 0) at -= overrun(gi, gk);         // (a vector that starts at element 0 ends inside: there are four elements at least)
+        typedef u32x2 half_t __attribute__((aligned(2)));
+        typedef u32x4 full_t __attribute__((aligned(4)));
+        if constexpr (BF16) {
+          u32x2 w = *reinterpret_cast<const GAS half_t*>((const GAS char*)base + at * 2);
+          raw[n].x = w.x; raw[n].y = w.y;
+        } else {
+          raw[n] = *reinterpret_cast<const GAS full_t*>((const GAS char*)base + at * 4);
+        }
+      } else if constexpr (BF16) {
         u32x2 w = *reinterpret_cast<const GAS u32x2*>((const GAS char*)base + at * 2);
         raw[n].x = w.x; raw[n].y = w.y;
       } else {
@@ -233,7 +250,17 @@ struct OperandBF {
   }
   // P: the operand's planes (one for an exact bf16 operand, three for an fp32 one), PLANE elements apart
   template <bool BF16>
-  __device__ __forceinline__ void stash(const u32x4 (&raw)[4], uint16_t* P, int plane, int k0, int tid) const {
+  __device__ __forceinline__ void stash(u32x4 (&raw)[4], uint16_t* P, int plane, int k0, int tid) const {
+    if constexpr (UA) {
+      if (kfast ? k0 + TK > kend : i0 + TMN > lim) {
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+          int ii = 0, kk = 0;
+          coords(tid, n, ii, kk);
+          raw[n] = shift_in<BF16>(raw[n], overrun(i0 + ii, k0 + kk));
+        }
+      }
+    }
     if (kfast) {
 #pragma unroll
       for (int n = 0; n < NVK; ++n) {
@@ -282,8 +309,8 @@ struct OperandBF {
 
 // same_ab (uniform): the tile of B is the tile of A (a diagonal tile of a Gram matrix X^T X): it is fetched and
 // split once and the B fragments are read from the planes of A.
-template <int WB, bool A_BF16, int TM>
-__device__ __forceinline__ void gemm_loop_bf(f32x16 (&acc)[WB][WB], const OperandBF<TM>& opA, const OperandBF<TM>& opB,
+template <int WB, bool A_BF16, int TM, bool UA>
+__device__ __forceinline__ void gemm_loop_bf(f32x16 (&acc)[WB][WB], const OperandBF<TM, UA>& opA, const OperandBF<TM, UA>& opB,
                                              uint16_t* lds, int kbeg, int K, int tid, int lane, int wm, int wn, bool same_ab) {
   constexpr int PLANE = (TM / 32) * FRAG_BLOCK;                   // elements
   constexpr int NA = A_BF16 ? 1 : 3;                           // planes of A; B always has three
@@ -336,8 +363,10 @@ __device__ __forceinline__ void gemm_loop_bf(f32x16 (&acc)[WB][WB], const Operan
 // 256 threads = 4 waves in a 2 x 2 grid; each wave WB x WB accumulator blocks of 32 x 32, so the
 // workgroup tile is 64*WB square (64 for small problems, 128 for large launches).  The next K tile
 // is fetched into registers while the matrix cores work on the one in LDS.
-template <int WB>
-__global__ __launch_bounds__(256) void k_gemm32(DevCtx d, const GemmDesc* __restrict__ descs,
+// MODE (GemmMode; known on the host for a whole launch): how the operands of all its problems can be read.  One kernel that chose per tile
+// held six loops in the registers of the largest.  A_BF16 matters in the first two modes, src_is_bf16 in the third.
+template <int WB, int MODE, bool A_BF16>
+__global__ __launch_bounds__(256, MODE == GEMM_RAGGED ? 2 : 1) void k_gemm32(DevCtx d, const GemmDesc* __restrict__ descs,
                                                 const GemmTile* __restrict__ tiles, int src_is_bf16, float alpha_mul, int sub_m, int sub_n) {
   constexpr int TM = 64 * WB, TN = 64 * WB;
   constexpr int PITCH = TM + 4;
@@ -352,24 +381,17 @@ __global__ __launch_bounds__(256) void k_gemm32(DevCtx d, const GemmDesc* __rest
   const int m0 = (t.tm * sub_m + (int)blockIdx.y) * TM, n0 = (t.tn * sub_n + (int)blockIdx.z) * TN;
   if (sub_m + sub_n > 2 && (m0 >= M || n0 >= N)) return;
   if (g.tri && n0 + TN < K) K = n0 + TN;            // B is zero below this tile's last column
-  const int a_bf16 = g.a_bf16 == 2 ? src_is_bf16 : g.a_bf16;
   float* C = reinterpret_cast<float*>(const_cast<char*>(resolve(d, g.C, g.mat)));
   float* C2 = g.C2.off >= 0 ? reinterpret_cast<float*>(const_cast<char*>(resolve(d, g.C2, g.mat))) : nullptr;
 
   // As | Bs of the fp32 loop, or up to six bf16 planes of the split loop
-  constexpr int LDS_FLOATS = 2 * TK * PITCH > 3 * (TM / 32) * FRAG_BLOCK ? 2 * TK * PITCH : 3 * (TM / 32) * FRAG_BLOCK;
+  constexpr int PLANE_FLOATS = (MODE != GEMM_ANY && A_BF16 ? 4 : 6) * (TM / 32) * FRAG_BLOCK / 2;
+  constexpr int LDS_FLOATS = MODE == GEMM_ANY && 2 * TK * PITCH > PLANE_FLOATS ? 2 * TK * PITCH : PLANE_FLOATS;
   __shared__ __attribute__((aligned(16))) float lds_raw[LDS_FLOATS];
-  float (*As)[PITCH] = reinterpret_cast<float (*)[PITCH]>(lds_raw);
-  float (*Bs)[PITCH] = reinterpret_cast<float (*)[PITCH]>(lds_raw + TK * PITCH);
-  static_assert(sizeof(lds_raw) >= sizeof(uint16_t) * 6 * (TM / 32) * FRAG_BLOCK, "six bf16 planes must fit");
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int wm = (wave & 1) * 32 * WB, wn = (wave >> 1) * 32 * WB;
-
-  Operand<TM, NV> opA, opB;
-  opA.setup(resolve(d, g.A, g.mat), g.sAm, g.sAk, a_bf16, M, K, m0, kbeg);
-  opB.setup(resolve(d, g.B, g.mat), g.sBn, g.sBk, 0, N, K, n0, kbeg);
 
   f32x16 acc[WB][WB];
 #pragma unroll
@@ -379,23 +401,35 @@ __global__ __launch_bounds__(256) void k_gemm32(DevCtx d, const GemmDesc* __rest
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
 
-  if (kbeg < K && g.prec == 1 && opA.vec_ok && opB.vec_ok) {
-    OperandBF<TM> pa, pb;
-    pa.setup(opA.base, g.sAm, g.sAk, M, K, m0);
-    pb.setup(opB.base, g.sBn, g.sBk, N, K, n0);
-    uint16_t* planes = reinterpret_cast<uint16_t*>(lds_raw);
-    // same matrix, same strides with the roles of the two indices swapped, same tile: A(m, k) = B(k, n = m)
-    const bool same_ab = g.A.off == g.B.off && g.A.ext == g.B.ext && g.sAm == g.sBn && g.sAk == g.sBk && m0 == n0 && M == N;
-    if (a_bf16) gemm_loop_bf<WB, true>(acc, pa, pb, planes, kbeg, K, tid, lane, wm, wn, false);
-    else gemm_loop_bf<WB, false>(acc, pa, pb, planes, kbeg, K, tid, lane, wm, wn, same_ab);
-  } else if (kbeg < K) {
+  const char* baseA = resolve(d, g.A, g.mat);
+  const char* baseB = resolve(d, g.B, g.mat);
+  // same matrix, same strides with the roles of the two indices swapped, same tile: A(m, k) = B(k, n = m)
+  const bool same_ab = g.A.off == g.B.off && g.A.ext == g.B.ext && g.sAm == g.sBn && g.sAk == g.sBk && m0 == n0 && M == N;
+  uint16_t* planes = reinterpret_cast<uint16_t*>(lds_raw);
+  if constexpr (MODE != GEMM_ANY) {
+    OperandBF<TM, MODE == GEMM_RAGGED> pa, pb;
+    pa.setup(baseA, g.sAm, g.sAk, M, K, m0);
+    pb.setup(baseB, g.sBn, g.sBk, N, K, n0);
+    if (kbeg < K) gemm_loop_bf<WB, A_BF16>(acc, pa, pb, planes, kbeg, K, tid, lane, wm, wn, !A_BF16 && same_ab);
+  } else {
+    const int a_bf16 = g.a_bf16 == 2 ? src_is_bf16 : g.a_bf16;
+    float (*As)[PITCH] = reinterpret_cast<float (*)[PITCH]>(lds_raw);
+    float (*Bs)[PITCH] = reinterpret_cast<float (*)[PITCH]>(lds_raw + TK * PITCH);
+    Operand<TM, NV> opA, opB;
+    opA.setup(baseA, g.sAm, g.sAk, a_bf16, M, K, m0, kbeg);
+    opB.setup(baseB, g.sBn, g.sBk, 0, N, K, n0, kbeg);
     const bool vec = opA.vec_ok && opB.vec_ok;
-    if (a_bf16) {
-      if (vec) gemm_loop<WB, true, true>(acc, opA, opB, As, Bs, kbeg, K, tid, lane, wm, wn);
-      else gemm_loop<WB, true, false>(acc, opA, opB, As, Bs, kbeg, K, tid, lane, wm, wn);
+    if (kbeg >= K) {
+    } else if (vec) {
+      OperandBF<TM> pa, pb;
+      pa.setup(baseA, g.sAm, g.sAk, M, K, m0);
+      pb.setup(baseB, g.sBn, g.sBk, N, K, n0);
+      if (a_bf16) gemm_loop_bf<WB, true>(acc, pa, pb, planes, kbeg, K, tid, lane, wm, wn, false);
+      else gemm_loop_bf<WB, false>(acc, pa, pb, planes, kbeg, K, tid, lane, wm, wn, same_ab);
+    } else if (a_bf16) {
+      gemm_loop<WB, true>(acc, opA, opB, As, Bs, kbeg, K, tid, lane, wm, wn);
     } else {
-      if (vec) gemm_loop<WB, false, true>(acc, opA, opB, As, Bs, kbeg, K, tid, lane, wm, wn);
-      else gemm_loop<WB, false, false>(acc, opA, opB, As, Bs, kbeg, K, tid, lane, wm, wn);
+      gemm_loop<WB, false>(acc, opA, opB, As, Bs, kbeg, K, tid, lane, wm, wn);
     }
   }
 
@@ -663,12 +697,19 @@ hipError_t launch_gemm_planes(const DevCtx& d, const GemmDesc* descs, int desc_f
   return hipGetLastError();
 }
 
-hipError_t launch_gemm32(const DevCtx& d, const GemmDesc* descs, const GemmTile* tiles, int ntiles, int tile, int src_is_bf16,
+hipError_t launch_gemm32(const DevCtx& d, const GemmDesc* descs, const GemmTile* tiles, int ntiles, int tile, int mode, bool a_bf16,
                          hipStream_t s, float alpha_mul, int sub_m, int sub_n) {
   if (ntiles <= 0) return hipSuccess;
   const dim3 grid(ntiles, sub_m, sub_n);
-  if (tile == 128) hipLaunchKernelGGL((k_gemm32<2>), grid, dim3(256), 0, s, d, descs, tiles, src_is_bf16, alpha_mul, sub_m, sub_n);
-  else hipLaunchKernelGGL((k_gemm32<1>), grid, dim3(256), 0, s, d, descs, tiles, src_is_bf16, alpha_mul, sub_m, sub_n);
+#define LORDO_GEMM(MODEV, BFV)                                                                                                        \
+  {                                                                                                                                   \
+    if (tile == 128) hipLaunchKernelGGL((k_gemm32<2, MODEV, BFV>), grid, dim3(256), 0, s, d, descs, tiles, a_bf16, alpha_mul, sub_m, sub_n); \
+    else hipLaunchKernelGGL((k_gemm32<1, MODEV, BFV>), grid, dim3(256), 0, s, d, descs, tiles, a_bf16, alpha_mul, sub_m, sub_n);       \
+  }
+  if (mode == GEMM_ANY) LORDO_GEMM(GEMM_ANY, false)
+  else if (mode == GEMM_RAGGED) { if (a_bf16) LORDO_GEMM(GEMM_RAGGED, true) else LORDO_GEMM(GEMM_RAGGED, false) }
+  else { if (a_bf16) LORDO_GEMM(GEMM_ALIGNED, true) else LORDO_GEMM(GEMM_ALIGNED, false) }
+#undef LORDO_GEMM
   return hipGetLastError();
 }
 

@@ -34,6 +34,9 @@ struct Op {
   int tile = 64;                    // OP_GEMM: workgroup tile edge (64 or 128)
   int desc_first = 0, ndescs = 0;   // OP_GEMM: descriptors of this launch
   bool split = false;               // OP_GEMM: split-K launch, followed by the slice reduction
+  int mode = GEMM_ALIGNED;          // OP_GEMM: the most general access any of its operands needs, caller's pointers taken as aligned
+  int a_bf16 = 0;                   // OP_GEMM: element type of A (as in GemmDesc)
+  bool reads_src = false, reads_grad = false, reads_omega = false;      // OP_GEMM: caller's arrays among its operands
   int iarg = 0;                     // OP_FACTOR_DIAG, OP_POTF2: block index; OP_PACK: y buffer that becomes Q, -1: Q stays
   float farg = 0.f;                 // OP_SHIFT: coefficient
   bool rot_only = false;            // part of the moment rotation (skipped while t == 0)
@@ -166,12 +169,17 @@ struct ProgramBuilder {
       g.beta = 0.f;
       g.mat = i;
       g.ksplit = 1;
-      // every product of the program runs on the bf16 matrix cores with operands split into three terms
-      // (as exact as fp32, and faster than the fp32 matrix-core path from r = 256 up); the kernel falls back
-      // to fp32 matrix cores for operands it cannot read with 16-byte accesses
-      g.prec = 1;
       if (!make(i, g)) continue;
       if (g.M <= 0 || g.N <= 0 || g.K <= 0) continue;
+      // every product of the program runs on the bf16 matrix cores with operands split into three terms (as exact as fp32);
+      // operands off the 16-byte grid too, but not in the initial projection, whose bits stay those of the fp32 matrix cores there
+      int mode = std::max(operand_mode(g.A, g.sAm, g.sAk, g.M, g.K, g.a_bf16 != 0), operand_mode(g.B, g.sBn, g.sBk, g.N, g.K, false));
+      if (initial && mode == GEMM_RAGGED) mode = GEMM_ANY;
+      op.mode = std::max(op.mode, mode);
+      op.a_bf16 = g.a_bf16;
+      if (g.B.ext == EXT_OMEGA) op.reads_omega = true;
+      if (g.A.ext == EXT_SRC) op.reads_src = true;
+      if (g.A.ext == EXT_G) op.reads_grad = true;
       if (g.M < 128 || g.N < 128) big_ok = false;
       tiles128 += (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128);
       tiles64 += (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64);
@@ -225,6 +233,14 @@ struct ProgramBuilder {
     }
     P.ops.push_back(op);
   }
+  // How one operand can be read (caller's arrays as if their pointers were aligned: see run_gemm)
+  static int operand_mode(const OpRef& ref, int64_t s_i, int64_t s_k, int n_i, int n_k, bool bf16) {
+    const bool kfast = s_k == 1 && s_i != 1;
+    const int64_t s_fast = kfast ? s_k : s_i, s_slow = kfast ? s_i : s_k;
+    const int n_fast = kfast ? n_k : n_i;
+    if (s_fast != 1 || n_fast < 4) return GEMM_ANY;
+    return (s_slow & 3) != 0 || (n_fast & 3) != 0 || (ref.off & (bf16 ? 7 : 15)) != 0 ? GEMM_RAGGED : GEMM_ALIGNED;
+  }
   // Column edge of the tiles k_gemm_planes takes these products on, or 0 if it cannot or k_gemm32 is the faster one: A is read
   // in 16-byte vectors along k, and the planes of B have to fit where the matrix's operand planes of N live between steps.
   // Measured as whole refreshes without power iterations, fp32 source, on k_gemm32 / edge 64 / 128 / 256 (us):
@@ -267,7 +283,7 @@ struct ProgramBuilder {
   // A operand = the source (transposed: its transpose).  The source of a right-projected matrix is the caller's
   // row-major array read as its transpose: element (i, j) of the p x q matrix at j * p + i.
   static void src_operand(GemmDesc& g, const MatDev& m, bool transposed) {
-    g.A = ref_ext(EXT_SRC); g.a_bf16 = 2; g.prec = 1;
+    g.A = ref_ext(EXT_SRC); g.a_bf16 = 2;
     const int64_t s_row = m.tr ? 1 : m.q, s_col = m.tr ? m.p : 1;
     g.sAm = transposed ? s_col : s_row;
     g.sAk = transposed ? s_row : s_col;
@@ -1083,6 +1099,12 @@ struct lordo_ctx {
     dev.slot[table] = table * EXT_SLOTS + k;
     return LORDO_OK;
   }
+  // every pointer of the table in use is a multiple of mask + 1
+  bool ext_aligned(int table, uintptr_t mask) const {
+    for (const void* p : shadow[table][dev.slot[table] - table * EXT_SLOTS])
+      if ((reinterpret_cast<uintptr_t>(p) & mask) != 0) return false;
+    return true;
+  }
 };
 
 extern "C" {
@@ -1228,6 +1250,20 @@ int lordo_init_static(lordo_ctx** out, const lordo_shape* shapes, int32_t n, con
   return LORDO_OK;
 }
 
+// One launch of the grouped GEMM.  Pointers of the caller that are off the grid of 16-byte vectors (8-byte ones of bf16) send it to the
+// kernel for operands at any alignment.
+static hipError_t run_gemm(lordo_ctx* c, const Op& op, int32_t src_dtype, hipStream_t s, float alpha_mul = 1.f) {
+  Plan& P = c->plan;
+  const bool a_bf16 = op.a_bf16 == 2 ? src_dtype == LORDO_BF16 : op.a_bf16 != 0;
+  int mode = op.mode;
+  const uintptr_t mask = a_bf16 ? 7 : 15;
+  if (mode == GEMM_ALIGNED && ((op.reads_src && !c->ext_aligned(EXT_SRC, mask)) || (op.reads_grad && !c->ext_aligned(EXT_G, mask)) ||
+                               (op.reads_omega && !c->ext_aligned(EXT_OMEGA, 15))))
+    mode = GEMM_RAGGED;
+  return launch_gemm32(c->dev, c->at<GemmDesc>(P.descs), c->at<GemmTile>(P.gtiles) + op.tile_first, op.ntiles, op.tile, mode, a_bf16, s, alpha_mul,
+                       op.planes ? 128 / op.tile : 1, op.planes ? op.planes / op.tile : 1);
+}
+
 int lordo_local_step(lordo_ctx* c, void* const* W, const void* const* G, double lr, double grad_scale, void* stream) {
   if (!c || !W || !G || !std::isfinite(lr) || !std::isfinite(grad_scale)) return LORDO_EINVAL;
   if (!c->on_its_device()) return LORDO_ESTATE;
@@ -1299,7 +1335,7 @@ int lordo_local_step(lordo_ctx* c, void* const* W, const void* const* G, double 
       if (!folded)
         HIPCHK(launch_fold_grad(c->dev, c->at<int64_t>(P.chunk_start), P.nchunks, (float)grad_scale, g_f32, s, !generic));
       for (const Op& op : P.tr_down_ef_ops)
-        HIPCHK(launch_gemm32(c->dev, c->at<GemmDesc>(P.descs), c->at<GemmTile>(P.gtiles) + op.tile_first, op.ntiles, op.tile, 0, s, 1.f));
+        HIPCHK(run_gemm(c, op, 0, s));
     }
     for (int i = 0; i < c->n && stream; ++i)
       if (P.mat[i].tr && (reinterpret_cast<uintptr_t>(G[i]) & 15) != 0) stream = false;
@@ -1312,7 +1348,7 @@ int lordo_local_step(lordo_ctx* c, void* const* W, const void* const* G, double 
       HIPCHK(launch_src_times_block(dv, c->at<ProjTile>(P.ytile_tr), (int)P.ytile_tr_h.size(), planes_hi, planes_lo, s));
     } else if (!ef) {
       for (const Op& op : P.tr_down_ops)
-        HIPCHK(launch_gemm32(c->dev, c->at<GemmDesc>(P.descs), c->at<GemmTile>(P.gtiles) + op.tile_first, op.ntiles, op.tile, 0, s, (float)grad_scale));
+        HIPCHK(run_gemm(c, op, 0, s, (float)grad_scale));
     }
     HIPCHK(launch_tr_exchange(c->dev, c->at<float>(P.glow), stream ? (float)grad_scale : 1.f, generic, s));
   }
@@ -1441,8 +1477,7 @@ static int run_ops(lordo_ctx* c, const std::vector<Op>& ops, int32_t src_dtype, 
                                     c->at<uint16_t>(P.n_hi), c->at<uint16_t>(P.n_lo), c->at<uint16_t>(P.glow), s));
           break;
         }
-        HIPCHK(launch_gemm32(c->dev, descs, tiles + op.tile_first, op.ntiles, op.tile, src_dtype == LORDO_BF16, s, 1.f,
-                             op.planes ? 128 / op.tile : 1, op.planes ? op.planes / op.tile : 1));
+        HIPCHK(run_gemm(c, op, src_dtype, s));
         if (op.split) HIPCHK(launch_gemm_reduce(c->dev, descs + op.desc_first, op.ndescs, s));
         break;
       case OP_SHIFT: HIPCHK(launch_gram_shift(c->dev, op.farg, op.iarg != 0, s)); break;

@@ -57,3 +57,92 @@ def test_step_on_rows_at_any_element(p, q, r, store, offset):
             assert float(((W[i].double() - want).abs() - 2.0 ** -8 * want.abs()).max()) <= 3e-5 * float(want.abs().max()), i
         got[start:start + a * b] = flat0[start:start + a * b]
         assert torch.equal(got, flat0), i
+
+
+# ranks and sides around the edges of tiles (32, 64, 128) and of vectors (remainders 1 to 3), and sides too short for a vector
+@pytest.mark.parametrize("p, q, r", [(5, 3, 2), (3, 9, 3), (37, 70, 5), (67, 41, 4), (65, 129, 39), (131, 258, 63), (130, 97, 66), (200, 301, 127), (389, 514, 130), (257, 515, 171)])
+@pytest.mark.parametrize("source", ["bf16", "fp32"])
+@pytest.mark.parametrize("offset", [0, 1, 2])
+def test_refresh_at_any_element(p, q, r, source, offset):
+    """Refresh from a source of r equal singular values, source and start block at any element of a buffer: Q is orthonormal and
+    spans the source's columns, and u and v are those of before, rotated."""
+    import torch
+    from paper_2602_04396_amd import lordo
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7 * p + q + r)
+    n = 2
+    W = [torch.randn(p, q, generator=gen, device="cuda") for _ in range(n)]
+    beta1 = 0.9
+    opt = lordo.Lordo([(p, q, r)] * n, lordo.hparams(beta1=beta1, power_iters=1, seed=3), W, torch)
+    opt.init_projection()
+    for _ in range(2):
+        opt.local_step(W, [torch.randn(p, q, generator=gen, device="cuda").bfloat16() for _ in range(n)], 0.5)
+    q_old = [opt.get_state(i, lordo.STATE_Q).double() for i in range(n)]
+    u_old = [opt.get_state(i, lordo.STATE_U).double() for i in range(n)]
+    v_old = [opt.get_state(i, lordo.STATE_V).double() for i in range(n)]
+    dt = torch.bfloat16 if source == "bf16" else torch.float32
+    src, om, U = [], [], []
+    for i in range(n):
+        a, _ = torch.linalg.qr(torch.randn(p, r, generator=gen, device="cuda", dtype=torch.float64))
+        b, _ = torch.linalg.qr(torch.randn(q, r, generator=gen, device="cuda", dtype=torch.float64))
+        s = _window(torch, p, q, dt, offset, gen)[1]
+        s.copy_(100.0 * a @ b.T)
+        o = _window(torch, q, r, torch.float32, offset, gen)[1]
+        src.append(s)
+        om.append(o)
+        U.append(a)
+    opt.refresh_subspace(src, om)
+    opt.poll_status()
+    c1, c2 = 1 - beta1 ** 2, 1 - opt.hp.beta2 ** 2
+    for i in range(n):
+        Q = opt.get_state(i, lordo.STATE_Q).double()
+        assert float((Q.T @ Q - torch.eye(r, device="cuda", dtype=torch.float64)).norm()) <= 1e-4, i      # CholeskyQR2 in fp32
+        if source == "fp32":      # (a bf16 source has rounding noise: its trailing directions depend on the start block)
+            assert float((U[i] - Q @ (Q.T @ U[i])).norm()) / r ** 0.5 <= 5e-5, i
+        R = Q.T @ q_old[i]
+        want = R @ u_old[i]
+        assert float((opt.get_state(i, lordo.STATE_U).double() - want).norm() / want.norm()) <= 1e-5, i   # fp32 sums over p and r
+        want = c2 * ((R * R) @ (v_old[i] / c2 - (u_old[i] / c1) ** 2) + (R @ u_old[i] / c1) ** 2).abs()
+        assert float((opt.get_state(i, lordo.STATE_V).double() - want).norm() / want.norm()) <= 1e-5, i
+
+
+@pytest.mark.parametrize("p, q, r", [(256, 320, 64), (384, 256, 128), (512, 384, 192)])
+def test_aligned_source_at_an_odd_address_gives_the_same_bits(p, q, r):
+    """An fp32 source whose rows are whole vectors, once on the grid of 16-byte vectors and once 4 bytes off it: the kernel for
+    operands at any element sums the same values in the same order."""
+    import torch
+    from paper_2602_04396_amd import lordo
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(p + q + r)
+    data = torch.randn(p, q, generator=gen, device="cuda")
+    om = torch.randn(q, r, generator=gen, device="cuda")
+    got = []
+    for offset in (0, 1):
+        W = [torch.zeros(p, q, device="cuda")]
+        opt = lordo.Lordo([(p, q, r)], lordo.hparams(power_iters=0, seed=3), W, torch)
+        s = _window(torch, p, q, torch.float32, offset, gen)[1]
+        s.copy_(data)
+        opt.refresh_subspace([s], [om])
+        got.append(opt.get_state(0, lordo.STATE_Q))
+    assert torch.equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("p, q, r", [(33, 65, 7), (130, 259, 37), (301, 77, 66)])
+@pytest.mark.parametrize("side", [0, 1])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_fp32_gradients_at_any_element(p, q, r, side, offset):
+    """fp32 gradients run in the grouped GEMM, on either side: u of one step against float64 at the library's own Q."""
+    import torch
+    from paper_2602_04396_amd import lordo
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(p + 3 * q + r)
+    W = [torch.randn(p, q, generator=gen, device="cuda")]
+    G = [_window(torch, p, q, torch.float32, offset, gen)[1]]
+    opt = lordo.Lordo([(p, q, r, side)], lordo.hparams(seed=2, grad_dtype=lordo.F32), W, torch)
+    opt.init_projection()
+    opt.local_step(W, G, 0.1)
+    opt.poll_status()
+    Q = opt.get_state(0, lordo.STATE_Q).double()
+    g = Q.T @ (G[0].double().T if side else G[0].double())
+    u = (1 - opt.hp.beta1) * g
+    assert float((opt.get_state(0, lordo.STATE_U).double() - u).norm() / u.norm()) <= 2e-6       # fp32 products and sums over 300 terms
