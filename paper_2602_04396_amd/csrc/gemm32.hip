@@ -155,20 +155,66 @@ __device__ __forceinline__ int frag_index(int i, int k) { return (i >> 5) * FRAG
 // places and zeros in behind them (a uniform branch: only tiles at the end have such vectors).  On the fp32 matrix cores with
 // element accesses, which such operands took before, a refresh of 21 matrices (2047 x 2047 .. 5001, r = 171) took 6.25 ms from bf16 and
 // 6.23 ms from fp32, so 3.11 and 3.68 ms.
-// A thread owns up to four vectors of four elements; along k they pack directly,
-// along i the thread owns a 4 x 4 patch (four i, four consecutive k) and transposes it in registers.
-template <int TMN, bool UA = false>
+// A thread owns NV vectors of four elements.  KF (k is the unit-stride direction): they pack directly; else they are a patch of
+// four i and NV consecutive k, which the thread transposes in registers.
+// Addresses: a uniform base that moves on with k and one 32-bit byte offset per vector, fixed over the loop (every array is below
+// 4 GiB); only the last K tile works its offsets out again, so that nothing past the end is read.
+template <int TMN, bool UA, bool BF16, bool KF>
 struct OperandBF {
-  const char* base;
-  int64_t s_i, s_k;
-  int lim, kend, i0;
-  bool kfast;
-  // how many of the vector's elements lie past the end (1 .. 3) if it starts inside and ends outside, else 0
-  __device__ __forceinline__ int overrun(int gi, int gk) const {
-    const int over = kfast ? gk + 4 - kend : gi + 4 - lim;
-    return over > 0 && over < 4 ? over : 0;
+  static constexpr int ES = BF16 ? 2 : 4;
+  static constexpr int NV = TMN / 32;
+  const GAS char* base;
+  int64_t k_bytes;                              // from one k to the next
+  int lim, kend, i0, kk0;                       // kk0: k of the thread's first vector inside a K tile
+  uint32_t off[NV];                             // vector n at K tile 0
+
+  __device__ __forceinline__ void setup(const char* b, int64_t s_i, int64_t s_k, int lim_, int kend_, int i0_, int tid) {
+    base = (const GAS char*)b; lim = lim_; kend = kend_; i0 = i0_;
+    k_bytes = s_k * ES;
+    kk0 = KF ? (tid & 7) * 4 : tid / (TMN / 4) * NV;
+#pragma unroll
+    for (int n = 0; n < NV; ++n) {
+      int gi = i0 + row(n, tid);                // rows past the end are read from the last one, vectors across it further back
+      const int last = KF ? lim - 1 : lim - 4;
+      gi = gi < last ? gi : last;
+      off[n] = (uint32_t)gi * (uint32_t)(s_i * ES) + (uint32_t)(kk0 + (KF ? 0 : n)) * (uint32_t)k_bytes;
+    }
   }
-  template <bool BF16>
+  // first i of vector n inside the tile (along i: of the whole patch)
+  static __device__ __forceinline__ int row(int n, int tid) {
+    return KF ? n * 32 + ((tid >> 1) & 28) + (tid >> 6)                    // the eight rows of a wave lie four apart
+              : tid % (TMN / 4) * 4;
+  }
+  __device__ __forceinline__ void fetch(u32x4 (&raw)[NV], int k0) const {
+    const bool whole = k0 + TK <= kend;
+    const GAS char* at = whole ? base + (int64_t)k0 * k_bytes : base;
+    uint32_t o[NV];
+#pragma unroll
+    for (int n = 0; n < NV; ++n) o[n] = off[n];
+    if (!whole) {
+#pragma unroll
+      for (int n = 0; n < NV; ++n) {
+        const int kk = kk0 + (KF ? 0 : n), last = kend - (KF ? 4 : 1);
+        const int k = k0 + kk < last ? k0 + kk : last;
+        o[n] += (uint32_t)(k - kk) * (uint32_t)k_bytes;
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < NV; ++n) {
+      typedef u32x2 half_t __attribute__((aligned(2)));
+      typedef u32x4 full_t __attribute__((aligned(4)));
+      if constexpr (BF16) {
+        u32x2 w;
+        if constexpr (UA) w = *(const GAS half_t*)(at + o[n]);
+        else w = *(const GAS u32x2*)(at + o[n]);
+        raw[n].x = w.x; raw[n].y = w.y;
+      } else if constexpr (UA) {
+        raw[n] = *(const GAS full_t*)(at + o[n]);
+      } else {
+        raw[n] = *(const GAS u32x4*)(at + o[n]);
+      }
+    }
+  }
   static __device__ __forceinline__ u32x4 shift_in(u32x4 x, int n) {
     if constexpr (BF16) {
       const uint64_t v = (((uint64_t)x.y << 32) | x.x) >> (16 * n);
@@ -178,51 +224,6 @@ struct OperandBF {
       if (n & 2) x = u32x4{x.z, x.w, 0u, 0u};
     }
     return x;
-  }
-  static constexpr int NVK = TMN / 32;          // vectors per thread when k is the unit-stride direction
-
-  __device__ __forceinline__ void setup(const char* b, int64_t si, int64_t sk, int lim_, int kend_, int i0_) {
-    base = b; s_i = si; s_k = sk; lim = lim_; kend = kend_; i0 = i0_;
-    kfast = sk == 1 && si != 1;
-  }
-  // vector n of thread tid: first element (ii, kk); false if the thread has no such vector
-  __device__ __forceinline__ bool coords(int tid, int n, int& ii, int& kk) const {
-    if (kfast) {
-      if (n >= NVK) return false;
-      kk = (tid & 7) * 4;
-      ii = n * 32 + ((tid >> 1) & 28) + (tid >> 6);          // the eight rows of a wave lie four apart
-      return true;
-    }
-    if (tid >= TMN * 2) return false;           // TMN/4 i-quads x 8 k-quads patches
-    ii = (tid % (TMN / 4)) * 4;
-    kk = (tid / (TMN / 4)) * 4 + n;
-    return true;
-  }
-  template <bool BF16>
-  __device__ __forceinline__ void fetch_raw(u32x4 (&raw)[4], int k0, int tid) const {
-#pragma unroll
-    for (int n = 0; n < 4; ++n) {
-      int ii = 0, kk = 0;
-      const bool have = coords(tid, n, ii, kk);
-      const int gi = i0 + ii, gk = k0 + kk;
-      int64_t at = (have && gi < lim && gk < kend) ? (int64_t)gi * s_i + (int64_t)gk * s_k : 0;
-      if constexpr (UA) {
-        if (at != 0) at -= overrun(gi, gk);         // (a vector that starts at element 0 ends inside: there are four elements at least)
-        typedef u32x2 half_t __attribute__((aligned(2)));
-        typedef u32x4 full_t __attribute__((aligned(4)));
-        if constexpr (BF16) {
-          u32x2 w = *reinterpret_cast<const GAS half_t*>((const GAS char*)base + at * 2);
-          raw[n].x = w.x; raw[n].y = w.y;
-        } else {
-          raw[n] = *reinterpret_cast<const GAS full_t*>((const GAS char*)base + at * 4);
-        }
-      } else if constexpr (BF16) {
-        u32x2 w = *reinterpret_cast<const GAS u32x2*>((const GAS char*)base + at * 2);
-        raw[n].x = w.x; raw[n].y = w.y;
-      } else {
-        raw[n] = *reinterpret_cast<const GAS u32x4*>((const GAS char*)base + at * 4);
-      }
-    }
   }
   // Two fp32 values -> three packed bf16 pairs whose sum is the values to 2^-26: hi is the value rounded to nearest,
   // mid the (exactly representable) remainder rounded to nearest, lo the rounded rest; the conversion is the
@@ -248,59 +249,52 @@ struct OperandBF {
     const float s1 = r1 - __uint_as_float(t[1] & 0xffff0000u);
     t[2] = pack_rne(s0, s1);
   }
-  // P: the operand's planes (one for an exact bf16 operand, three for an fp32 one), PLANE elements apart
-  template <bool BF16>
-  __device__ __forceinline__ void stash(u32x4 (&raw)[4], uint16_t* P, int plane, int k0, int tid) const {
-    if constexpr (UA) {
-      if (kfast ? k0 + TK > kend : i0 + TMN > lim) {
+  // P: the operand's planes (one for an exact bf16 operand, three for an fp32 one), `plane` elements apart
+  __device__ __forceinline__ void stash(u32x4 (&raw)[NV], uint16_t* P, int plane, int k0, int tid) const {
+    if (i0 + TMN > lim || k0 + TK > kend) {           // (uniform) what lies outside becomes zero
 #pragma unroll
-        for (int n = 0; n < 4; ++n) {
-          int ii = 0, kk = 0;
-          coords(tid, n, ii, kk);
-          raw[n] = shift_in<BF16>(raw[n], overrun(i0 + ii, k0 + kk));
+      for (int n = 0; n < NV; ++n) {
+        const int gi = i0 + row(n, tid), gk = k0 + kk0 + (KF ? 0 : n);
+        if constexpr (UA) {                           // how many elements of a vector that starts inside lie past the end
+          const int over = KF ? gk + 4 - kend : gi + 4 - lim;
+          if (over > 0 && over < 4) raw[n] = shift_in(raw[n], over);
         }
+        if (!(gi < lim && gk < kend)) raw[n] = u32x4{0u, 0u, 0u, 0u};
       }
     }
-    if (kfast) {
+    if constexpr (KF) {
 #pragma unroll
-      for (int n = 0; n < NVK; ++n) {
-        int ii = 0, kk = 0;
-        coords(tid, n, ii, kk);
-        const bool ok = i0 + ii < lim && k0 + kk < kend;
-        const int at = frag_index(ii, kk);                    // four consecutive k: 8 contiguous bytes
+      for (int n = 0; n < NV; ++n) {
+        const int at = frag_index(row(n, tid), kk0);          // four consecutive k: 8 contiguous bytes
         if constexpr (BF16) {
-          *reinterpret_cast<u32x2*>(P + at) = ok ? u32x2{raw[n].x, raw[n].y} : u32x2{0u, 0u};
+          *reinterpret_cast<u32x2*>(P + at) = u32x2{raw[n].x, raw[n].y};
         } else {
           uint32_t ta[3], tb[3];
           split3(raw[n].x, raw[n].y, ta);
           split3(raw[n].z, raw[n].w, tb);
 #pragma unroll
-          for (int c = 0; c < 3; ++c) *reinterpret_cast<u32x2*>(P + c * plane + at) = ok ? u32x2{ta[c], tb[c]} : u32x2{0u, 0u};
+          for (int c = 0; c < 3; ++c) *reinterpret_cast<u32x2*>(P + c * plane + at) = u32x2{ta[c], tb[c]};
         }
       }
-    } else if (tid < TMN * 2) {
-      // 4 x 4 patch: vector n holds i = ii .. ii+3 at k = kfirst + n; row ii + e of the plane gets k = kfirst .. kfirst+3
-      int ii = 0, kfirst = 0;
-      coords(tid, 0, ii, kfirst);
-      const bool i_ok = i0 + ii < lim;
-      u32x4 r[4];
-#pragma unroll
-      for (int n = 0; n < 4; ++n) r[n] = (i_ok && k0 + kfirst + n < kend) ? raw[n] : u32x4{0u, 0u, 0u, 0u};
+    } else {
+      // vector n holds i = ii .. ii+3 at k = kk0 + n; row ii + e of the plane gets k = kk0 .. kk0 + NV - 1
+      const int ii = row(0, tid);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int at = frag_index(ii + e, kfirst);
-        if constexpr (BF16) {                                 // element e of vector n: half (e & 1) of word e / 2
-          const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
-          u32x2 h;
-          h.x = __builtin_amdgcn_perm(r[1][e >> 1], r[0][e >> 1], sel);
-          h.y = __builtin_amdgcn_perm(r[3][e >> 1], r[2][e >> 1], sel);
-          *reinterpret_cast<u32x2*>(P + at) = h;
-        } else {
-          uint32_t ta[3], tb[3];
-          split3(r[0][e], r[1][e], ta);
-          split3(r[2][e], r[3][e], tb);
+        const int at = frag_index(ii + e, kk0);
+        uint32_t t[NV / 2][3];
 #pragma unroll
-          for (int c = 0; c < 3; ++c) *reinterpret_cast<u32x2*>(P + c * plane + at) = u32x2{ta[c], tb[c]};
+        for (int h = 0; h < NV / 2; ++h) {
+          if constexpr (BF16) {                               // element e of vector n: half (e & 1) of word e / 2
+            t[h][0] = __builtin_amdgcn_perm(raw[2 * h + 1][e >> 1], raw[2 * h][e >> 1], (e & 1) ? 0x07060302u : 0x05040100u);
+          } else {
+            split3(raw[2 * h][e], raw[2 * h + 1][e], t[h]);
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < (BF16 ? 1 : 3); ++c) {
+          if constexpr (NV == 4) *reinterpret_cast<u32x2*>(P + c * plane + at) = u32x2{t[0][c], t[1][c]};
+          else *reinterpret_cast<uint32_t*>(P + c * plane + at) = t[0][c];
         }
       }
     }
@@ -309,26 +303,28 @@ struct OperandBF {
 
 // same_ab (uniform): the tile of B is the tile of A (a diagonal tile of a Gram matrix X^T X): it is fetched and
 // split once and the B fragments are read from the planes of A.
-template <int WB, bool A_BF16, int TM, bool UA>
-__device__ __forceinline__ void gemm_loop_bf(f32x16 (&acc)[WB][WB], const OperandBF<TM, UA>& opA, const OperandBF<TM, UA>& opB,
-                                             uint16_t* lds, int kbeg, int K, int tid, int lane, int wm, int wn, bool same_ab) {
+template <int WB, bool UA, bool A_BF16, bool A_KF, bool B_KF>
+__device__ __forceinline__ void gemm_loop_bf(f32x16 (&acc)[WB][WB], const GemmDesc& g, const char* baseA, const char* baseB,
+                                             uint16_t* lds, int m0, int n0, int kbeg, int K, int tid, int lane, int wm, int wn, bool same_ab) {
+  constexpr int TM = 64 * WB;
+  typedef OperandBF<TM, UA, A_BF16, A_KF> OpA;
+  typedef OperandBF<TM, UA, false, B_KF> OpB;
+  OpA opA;
+  OpB opB;
+  opA.setup(baseA, g.sAm, g.sAk, g.M, K, m0, tid);
+  opB.setup(baseB, g.sBn, g.sBk, g.N, K, n0, tid);
   constexpr int PLANE = (TM / 32) * FRAG_BLOCK;                   // elements
   constexpr int NA = A_BF16 ? 1 : 3;                           // planes of A; B always has three
   uint16_t* PA = lds;
   uint16_t* PB = (!A_BF16 && same_ab) ? lds : lds + NA * PLANE;
   const bool own_b = A_BF16 || !same_ab;
-  u32x4 ra[4], rb[4];
-  opA.template fetch_raw<A_BF16>(ra, kbeg, tid);
-  if (own_b) opB.template fetch_raw<false>(rb, kbeg, tid);
-  for (int k0 = kbeg; k0 < K; k0 += TK) {
+  auto step = [&](u32x4 (&ra)[OpA::NV], u32x4 (&rb)[OpB::NV], int k0) {
     __syncthreads();                           // previous tile fully consumed
-    opA.template stash<A_BF16>(ra, PA, PLANE, k0, tid);
-    if (own_b) opB.template stash<false>(rb, PB, PLANE, k0, tid);
+    opA.stash(ra, PA, PLANE, k0, tid);
+    if (own_b) opB.stash(rb, PB, PLANE, k0, tid);
     __syncthreads();
-    if (k0 + TK < K) {
-      opA.template fetch_raw<A_BF16>(ra, k0 + TK, tid);
-      if (own_b) opB.template fetch_raw<false>(rb, k0 + TK, tid);
-    }
+    opA.fetch(ra, k0 + 2 * TK);                // (past the end: the last vectors once more, so that every step has the same loads in flight)
+    if (own_b) opB.fetch(rb, k0 + 2 * TK);
     asm volatile("" ::: "memory");             // keep the loads above the arithmetic: they must be in flight during it
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
@@ -357,7 +353,33 @@ __device__ __forceinline__ void gemm_loop_bf(f32x16 (&acc)[WB][WB], const Operan
             for (int b = 0; b < WB; ++b)
               acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ca][a], fb[cb][b], acc[a][b], 0, 0, 0);
     }
+  };
+  // Two K tiles in flight, in register sets that alternate statically: the load of a K tile has a whole step more to arrive.  With one in
+  // flight and 64-bit addresses of every vector in every step a tile's K step was a memory latency: one 256 x 256 matrix with fp32
+  // gradients (4 tiles, 8 steps) 16.1 -> 11.7 us, 18 matrices 957 x 957 .. 2201, r = 39, Y = Src B 126 -> 62 us, 6 of 2304 x 2304 .. 6400,
+  // r = 384, fp32 gradients 606 -> 466 us; full launches of 128-wide tiles are as fast as before.
+  u32x4 ra0[OpA::NV], rb0[OpB::NV], ra1[OpA::NV], rb1[OpB::NV];
+  opA.fetch(ra0, kbeg);
+  if (own_b) opB.fetch(rb0, kbeg);
+  opA.fetch(ra1, kbeg + TK);
+  if (own_b) opB.fetch(rb1, kbeg + TK);
+  int k0 = kbeg;
+  for (; k0 + TK < K; k0 += 2 * TK) {
+    step(ra0, rb0, k0);
+    step(ra1, rb1, k0 + TK);
   }
+  if (k0 < K) step(ra0, rb0, k0);
+}
+
+// The loop for the unit-stride directions of a problem's operands (uniform)
+template <int WB, bool UA, bool A_BF16>
+__device__ __forceinline__ void gemm_loops_bf(f32x16 (&acc)[WB][WB], const GemmDesc& g, const char* baseA, const char* baseB, uint16_t* lds,
+                                              int m0, int n0, int kbeg, int K, int tid, int lane, int wm, int wn, bool same_ab) {
+  const bool akf = g.sAk == 1 && g.sAm != 1, bkf = g.sBk == 1 && g.sBn != 1;
+  if (akf && bkf) gemm_loop_bf<WB, UA, A_BF16, true, true>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab);
+  else if (akf) gemm_loop_bf<WB, UA, A_BF16, true, false>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab);
+  else if (bkf) gemm_loop_bf<WB, UA, A_BF16, false, true>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab);
+  else gemm_loop_bf<WB, UA, A_BF16, false, false>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab);
 }
 
 // 256 threads = 4 waves in a 2 x 2 grid; each wave WB x WB accumulator blocks of 32 x 32, so the
@@ -407,10 +429,7 @@ __global__ __launch_bounds__(256, MODE == GEMM_RAGGED ? 2 : 1) void k_gemm32(Dev
   const bool same_ab = g.A.off == g.B.off && g.A.ext == g.B.ext && g.sAm == g.sBn && g.sAk == g.sBk && m0 == n0 && M == N;
   uint16_t* planes = reinterpret_cast<uint16_t*>(lds_raw);
   if constexpr (MODE != GEMM_ANY) {
-    OperandBF<TM, MODE == GEMM_RAGGED> pa, pb;
-    pa.setup(baseA, g.sAm, g.sAk, M, K, m0);
-    pb.setup(baseB, g.sBn, g.sBk, N, K, n0);
-    if (kbeg < K) gemm_loop_bf<WB, A_BF16>(acc, pa, pb, planes, kbeg, K, tid, lane, wm, wn, !A_BF16 && same_ab);
+    if (kbeg < K) gemm_loops_bf<WB, MODE == GEMM_RAGGED, A_BF16>(acc, g, baseA, baseB, planes, m0, n0, kbeg, K, tid, lane, wm, wn, !A_BF16 && same_ab);
   } else {
     const int a_bf16 = g.a_bf16 == 2 ? src_is_bf16 : g.a_bf16;
     float (*As)[PITCH] = reinterpret_cast<float (*)[PITCH]>(lds_raw);
@@ -421,11 +440,8 @@ __global__ __launch_bounds__(256, MODE == GEMM_RAGGED ? 2 : 1) void k_gemm32(Dev
     const bool vec = opA.vec_ok && opB.vec_ok;
     if (kbeg >= K) {
     } else if (vec) {
-      OperandBF<TM> pa, pb;
-      pa.setup(baseA, g.sAm, g.sAk, M, K, m0);
-      pb.setup(baseB, g.sBn, g.sBk, N, K, n0);
-      if (a_bf16) gemm_loop_bf<WB, true>(acc, pa, pb, planes, kbeg, K, tid, lane, wm, wn, false);
-      else gemm_loop_bf<WB, false>(acc, pa, pb, planes, kbeg, K, tid, lane, wm, wn, same_ab);
+      if (a_bf16) gemm_loops_bf<WB, false, true>(acc, g, baseA, baseB, planes, m0, n0, kbeg, K, tid, lane, wm, wn, false);
+      else gemm_loops_bf<WB, false, false>(acc, g, baseA, baseB, planes, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab);
     } else if (a_bf16) {
       gemm_loop<WB, true>(acc, opA, opB, As, Bs, kbeg, K, tid, lane, wm, wn);
     } else {
@@ -580,10 +596,10 @@ __global__ __launch_bounds__(256, 2) void k_gemm_planes(DevCtx d, const GemmDesc
     asm volatile("" : "+v"(x), "+v"(y));          // nothing of this moves ahead of the step it stands in, where it would wait for the loads
     const bool okx = k < kend, oky = k + 4 < kend;                            // (K is a multiple of 4: whole vectors)
     uint32_t t0[3], t1[3], t2[3], t3[3];
-    OperandBF<128>::split3(okx ? x.x : 0u, okx ? x.y : 0u, t0);
-    OperandBF<128>::split3(okx ? x.z : 0u, okx ? x.w : 0u, t1);
-    OperandBF<128>::split3(oky ? y.x : 0u, oky ? y.y : 0u, t2);
-    OperandBF<128>::split3(oky ? y.z : 0u, oky ? y.w : 0u, t3);
+    OperandBF<128, false, false, true>::split3(okx ? x.x : 0u, okx ? x.y : 0u, t0);
+    OperandBF<128, false, false, true>::split3(okx ? x.z : 0u, okx ? x.w : 0u, t1);
+    OperandBF<128, false, false, true>::split3(oky ? y.x : 0u, oky ? y.y : 0u, t2);
+    OperandBF<128, false, false, true>::split3(oky ? y.z : 0u, oky ? y.w : 0u, t3);
 #pragma unroll
     for (int c = 0; c < 3; ++c) lds_planes[(buf * SLOTS + 4 * c) * 64 + aslot] = u32x4{t0[c], t1[c], t2[c], t3[c]};
   };
@@ -669,7 +685,7 @@ __global__ __launch_bounds__(256) void k_pack_planes(DevCtx d, const GemmDesc* _
     for (int e = 0; e < 8; ++e) x[e] = n < g.N && k + e < g.K ? __float_as_uint(B[(int64_t)(k + e) * g.sBk + n * g.sBn]) : 0u;
     uint32_t t[4][3];
 #pragma unroll
-    for (int h = 0; h < 4; ++h) OperandBF<128>::split3(x[2 * h], x[2 * h + 1], t[h]);
+    for (int h = 0; h < 4; ++h) OperandBF<128, false, false, true>::split3(x[2 * h], x[2 * h + 1], t[h]);
     *((GAS u32x4*)(p0 + off) + i) = u32x4{t[0][0], t[1][0], t[2][0], t[3][0]};
     *((GAS u32x4*)(p1 + off) + i) = u32x4{t[0][1], t[1][1], t[2][1], t[3][1]};
     *((GAS u32x4*)(p2 + off) + i) = u32x4{t[0][2], t[1][2], t[2][2], t[3][2]};
