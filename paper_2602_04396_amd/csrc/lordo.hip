@@ -52,13 +52,12 @@ struct Plan {
   size_t bytes = 0;
   int64_t lr_total = 0;             // elements of one flat low-rank array
   int64_t nchunks = 0;
-  int mb = 4;
   int up_waves = 4;                 // waves per workgroup of the up-projection (4: 64 x 64 wave tiles, 8: 32 x 64)
   int r_max = 0;                    // largest rank of any matrix
   int64_t rank_sq_sum = 0;          // sum of r^2 over the matrices
   int64_t frob_part = -1;           // per-chunk partial sums of ||Src||_F^2 (Rayleigh-Ritz option)
   int64_t jflags = -1;              // per-sweep "something rotated" flags of the multi-launch Jacobi solver
-  int down_pipe = 0;                // pipelined down-projection: rank blocks per wave (1: 128-rank tiles, 2: 256-rank), 0: plain kernel
+  int down_pipe = 0;                // down-projection: rank blocks of 32 per tile (8, 4, 2 or 1), 0: products in the grouped GEMM
   int rank_tile = 128;              // rank indices per down-projection tile
   bool g_once = true;               // every matrix has one rank tile of the down-projection: G is read exactly once
   int64_t colpart = -1, g_hi = -1, g_lo = -1;   // full-rank QHM column sums; error-feedback planes of g
@@ -727,17 +726,17 @@ void build_plan(const lordo_shape* shapes, int n, const lordo_hparams& hp, Plan&
   P.chunk_start_h[n] = chunks;
   P.nchunks = chunks;
   if (hp.rayleigh_ritz) { P.frob_part = A.take(sizeof(float) * (size_t)chunks); P.jflags = A.take(256); }
-  // rank blocks of 32 per down-projection tile: the pipelined kernel (bf16 G) always takes four and
-  // leaves the waves of absent blocks idle; the plain kernel is instantiated for 1, 2 and 4
   // (the pipelined kernel reads columns in pairs: a matrix of one column sends the set to the grouped GEMM, as fp32 gradients do)
   P.down_generic = hp.grad_dtype == LORDO_F32;
   for (int i = 0; i < n; ++i)
     if (!P.mat[i].tr && P.mat[i].q < 2) P.down_generic = true;
-  P.mb = 4;
-  // Down-projection launch shape: the pipelined kernel (rank tiles of 128, bf16 G, 256-column
-  // tiles) where it applies, else the plain kernel with 128-column tiles.
-  P.down_pipe = (P.mb == 4 && !P.down_generic) ? (rp_max >= 256 ? 2 : 1) : 0;
-  P.rank_tile = P.down_pipe ? 128 * P.down_pipe : 32 * P.mb;
+  // Rank blocks of 32 per down-projection tile, 256 columns wide: as many as the largest rank of the set has, up to 8.  At ranks up to 64
+  // the four-block tile left half of its waves or more without work and fetched absent blocks of Q; measured as whole steps on
+  // four / two blocks: 1 x (8192 x 28672), r = 64 486 -> 473 us, 125M set, r = 64 201 -> 197; on four / one: 1 x (8192 x 8192), r = 16
+  // 140 -> 135, 125M set, r = 32 178 -> 174, 1 x (640 x 640), r = 12 21.3 -> 19.4.  (More K slices, for the third workgroup per compute unit
+  // that the smaller tiles leave room for, gave 1 to 4 % less.)
+  P.down_pipe = P.down_generic ? 0 : rp_max >= 256 ? 8 : rp_max > 64 ? 4 : rp_max > 32 ? 2 : 1;
+  P.rank_tile = P.down_pipe ? 32 * P.down_pipe : 128;
   P.g_once = rp_max <= P.rank_tile;
   const int down_bn = P.down_pipe ? 256 : 128;
   P.up_waves = 4;
@@ -800,7 +799,7 @@ void build_plan(const lordo_shape* shapes, int n, const lordo_hparams& hp, Plan&
   // The 256-rank tiles also write what the full-rank QHM update and the error feedback need from that pass (column
   // sums of the denominators, operand planes of g); the 128-rank kernel has no registers to spare for them.
   const bool fuse_adam = P.down_pipe && P.nsplit == 1 && !hp.uplink_buffer && !P.any_tr &&
-                         (P.down_pipe == 2 || (hp.qhm_mode != 2 && !hp.error_feedback));
+                         (P.down_pipe == 8 || (hp.qhm_mode != 2 && !hp.error_feedback));
   P.adam_first = fuse_adam ? lr : 0;
   P.glow = A.take(sizeof(float) * lr * P.nsplit);
   P.u = A.take(sizeof(float) * lr);
@@ -1327,8 +1326,8 @@ int lordo_local_step(lordo_ctx* c, void* const* W, const void* const* G, double 
   for (int i = 0; i < c->n && g_tr; ++i)
     if (!P.mat[i].tr && ((P.mat[i].q & 7) != 0 || (reinterpret_cast<uintptr_t>(G[i]) & 15) != 0)) g_tr = false;
   if (!P.down_h.empty())
-    HIPCHK(launch_proj_down(c->dev, c->at<ProjTile>(P.down_tiles), (int)P.down_h.size(), P.mb, P.down_pipe, g_vec, g_tr, P.g_once, c->at<float>(P.glow),
-                            P.lr_total, (float)proj_scale, g_f32, ef ? (e_bf16 ? 3 : 1) : 0, &fuse, s));
+    HIPCHK(launch_proj_down(c->dev, c->at<ProjTile>(P.down_tiles), (int)P.down_h.size(), P.down_pipe, g_vec, g_tr, P.g_once, c->at<float>(P.glow),
+                            P.lr_total, (float)proj_scale, ef ? (e_bf16 ? 3 : 1) : 0, &fuse, s));
   if (P.any_tr || generic) {    // g^T = (s G) Q into the plain block zw[0], then into the blocked array the Adam kernel reads
     bool stream = P.tr_stream_shapes && !ef && !generic;
     if (ef) {                   // A = s G + E is formed in the residual buffer first (unless a refresh of the local variant has done it)
@@ -1459,8 +1458,8 @@ static int run_ops(lordo_ctx* c, const std::vector<Op>& ops, int32_t src_dtype, 
           for (int i = 0; i < 4; ++i) { a.grp_nsplit[i] = P.grp_nsplit[i]; a.grp_start[i] = P.grp_start[i]; }
           a.split_stride = P.lr_total;
           HIPCHK(launch_pack_y(c->dev, op.iarg, s));
-          HIPCHK(launch_proj_down(c->dev, c->at<ProjTile>(P.down_tiles), (int)P.down_h.size(), P.mb, P.down_pipe, true, proj_tr, P.g_once,
-                                  c->at<float>(P.glow), P.lr_total, 1.f, false, src_dtype == LORDO_F32 ? 2 : 0, nullptr, s));
+          HIPCHK(launch_proj_down(c->dev, c->at<ProjTile>(P.down_tiles), (int)P.down_h.size(), P.down_pipe, true, proj_tr, P.g_once,
+                                  c->at<float>(P.glow), P.lr_total, 1.f, src_dtype == LORDO_F32 ? 2 : 0, nullptr, s));
           HIPCHK(launch_glow_to_z(c->dev, c->at<float>(P.glow), 0, a, s));
           break;
         }

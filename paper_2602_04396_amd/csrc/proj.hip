@@ -198,7 +198,7 @@ __device__ __forceinline__ void add_residual(GStage<true>& out, const GStage<GF3
 }
 
 // ---------------------------------------------------------------------------------------
-// Down-projection, main path (rank tile of 128, bf16 G): 8 waves, output tile 128 rank indices x
+// Down-projection, main path (bf16 G), described at a rank tile of 128: 8 waves, output tile 128 rank indices x
 // 256 columns.  Wave w owns rank block w % 4 and the four column blocks of half w / 4.
 // Per stage of 32 rows of G: the G tile (32 x 256) is read once, transposed in registers and staged
 // in LDS in fragment order (wave w stages the 8-row group w / 2 of column half w % 2); the Q
@@ -293,10 +293,10 @@ __device__ __forceinline__ void store_colpart(const FusedAdam& f, const MatDev& 
   if (lane < 32) f.colpart[m.lr_off / 32 + ((int64_t)nbg * (m.rp / 32) + mbg) * 32 + lane] = total;
 }
 
-// 8 waves, 256-column tiles: wave w owns column half w / 4 (four column blocks) and RB rank blocks,
-// w % 4 + 4*rb: the tile spans 128*RB rank indices.  RB = 2 (ranks from 256 up) halves the number of
+// 8 waves, 256-column tiles of MB rank blocks (8, 4, 2 or 1: 32 MB rank indices).  MB = 4: wave w owns column half w / 4 (four
+// column blocks) and rank block w % 4.  MB = 8 (ranks from 256 up): rank blocks w % 4 and w % 4 + 4; this halves the number of
 // passes over G and the LDS reads per MFMA (each G fragment feeds two rank blocks); its 96 KiB of
-// LDS admit one workgroup per compute unit.
+// LDS admit one workgroup per compute unit.  MB = 2, 1 (ranks up to 64, 32): the waves go along the columns, two blocks each, or one.
 // VEC: q is even and every pair of columns 4-byte aligned; else pairs are read at the alignment of an element (q >= 2).
 // GONCE: one rank tile per column block, G is read once (streaming loads).
 // A tile marked `fuse` holds the whole contraction (no split-K): its epilogue applies Adam to its
@@ -308,7 +308,7 @@ __device__ __forceinline__ void store_colpart(const FusedAdam& f, const MatDev& 
 // EFM = 2: the projected matrix is an fp32 matrix alone (no G): the fp32 source of a subspace refresh, taken
 // from the caller's source table -- the product Z = Src^T Y of the power iteration has the shape of g = Q^T G.
 // EFM = 3: error feedback with the residual stored in bf16 (widened exactly; the sum is formed in fp32 as before).
-template <int RB, bool VEC, bool GONCE, int EFM>
+template <int MB, bool VEC, bool GONCE, int EFM>
 __global__ __launch_bounds__(512) void k_proj_down_pipe(DevCtx d, const ProjTile* __restrict__ tiles, float* __restrict__ glow,
                                                         int64_t split_stride, float grad_scale, FusedAdam fa) {
   constexpr bool EF = EFM != 0;                                // an fp32 operand is staged: hi and lo planes, three passes
@@ -316,7 +316,9 @@ __global__ __launch_bounds__(512) void k_proj_down_pipe(DevCtx d, const ProjTile
   constexpr bool E32 = EFM != 3;                               // storage type of the second operand (residual or source)
   constexpr uint32_t EES = E32 ? 4u : 2u;
   constexpr int BK = 32;
-  constexpr int NW = 8;
+  constexpr int RB = MB == 8 ? 2 : 1;                          // rank blocks per wave
+  constexpr int MW = MB / RB;                                  // waves along the ranks (4, 4, 2, 1), the others along the columns
+  constexpr int NC = MW;                                       // column blocks per wave: 8 over 8 / MW groups of waves
   const ProjTile t = tiles[blockIdx.x];
   if (t.mat < 0 || mat_skipped(d, t.mat)) return;
   const MatDev m = d.mats[t.mat];
@@ -324,22 +326,22 @@ __global__ __launch_bounds__(512) void k_proj_down_pipe(DevCtx d, const ProjTile
   const GAS u32x4* qt_lo = TO_GLOBAL(const u32x4, d.arena + m.qt_lo);
 
   constexpr int GSLOTS = 8 * 4 * 32;                           // (nblk, kgrp, n) 16-byte slots of one stage: 16 KiB
-  constexpr int ASLOTS = 4 * RB * 2 * 2 * 64;                  // (mblk, kstep, plane, lane): 16 KiB per 128 rank indices
-  extern __shared__ u32x4 lds_dyn[];                           // 2 stages of each: 64 KiB (RB = 1) or 96 KiB (RB = 2), + 32 KiB with EF
+  constexpr int ASLOTS = MB * 2 * 2 * 64;                      // (mblk, kstep, plane, lane): 4 KiB per 32 rank indices
+  extern __shared__ u32x4 lds_dyn[];                           // 2 stages of each: 96, 64, 48, 40 KiB, + 32 KiB with EF
   u32x4* gfrag = lds_dyn;
   u32x4* glo = lds_dyn + 2 * GSLOTS;                           // EF: lo plane of the staged sum
   u32x4* afrag = lds_dyn + (EF ? 4 : 2) * GSLOTS;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int mb = wave & 3, nh = wave >> 2;                     // compute role
+  const int mb = wave % MW, nh = wave / MW;                    // compute role
   const int kgrp = wave >> 1, half = wave & 1;                 // G staging role: 8-row group, column half
   const int rblocks = m.rp / 32;
   int mbg[RB];
   bool active[RB];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
-    mbg[rb] = t.m0 / 32 + mb + 4 * rb;
+    mbg[rb] = t.m0 / 32 + mb + MW * rb;
     active[rb] = mbg[rb] < rblocks;
   }
 
@@ -358,54 +360,54 @@ __global__ __launch_bounds__(512) void k_proj_down_pipe(DevCtx d, const ProjTile
                           : (EF ? make_rsrc(d.arena + m.err, (uint32_t)klim * erow_bytes) : rs);
   const GCol ge = g_columns<true>(col, t.n0 + 128 * half, m.q, EES);
 
-  // Q fragments of a stage: (mblk, kstep) pairs, both planes each; 8*RB pairs, RB per wave
+  // Q fragments of a stage: (mblk, kstep, plane), 4 * MB of them over eight waves (MB = 1: waves 0 to 3 bring in one each)
   const int64_t kgroups = m.pp / 8;
   const int kgmax = (int)kgroups - 2;
+  constexpr int QF = MB >= 2 ? MB / 2 : 1;
   auto issue_a = [&](int kr, int sbuf) {
+    if (MB == 1 && wave >= 4) return;
 #pragma unroll
-    for (int j = 0; j < RB; ++j) {
-      const int pair = wave * RB + j;                          // 0 .. 8*RB-1
-      const int fmb = pair >> 1, fks = pair & 1;
+    for (int j = 0; j < QF; ++j) {
+      const int frag = wave * QF + j;
+      const int fmb = frag >> 2, fks = (frag >> 1) & 1;
       const int fmbg = t.m0 / 32 + fmb < rblocks ? t.m0 / 32 + fmb : rblocks - 1;
       int kg = kr / 8 + 2 * fks;
       kg = kg < kgmax ? kg : kgmax;                            // a stage may reach past the padded height
       const int64_t src = ((int64_t)fmbg * kgroups + kg) * 32 + lane;
-      u32x4* dst = afrag + sbuf * ASLOTS + pair * 2 * 64;
-      dma16_async(qt_hi + src, dst);
-      dma16_async(qt_lo + src, dst + 64);
+      dma16_async((frag & 1 ? qt_lo : qt_hi) + src, afrag + sbuf * ASLOTS + frag * 64);
     }
   };
 
-  f32x16 acc[RB][4];
+  f32x16 acc[RB][NC];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < NC; ++a)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[rb][a][i] = 0.f;
 
   // Operand fragments of one k-step of 16: RB pairs of Q planes and the four G column blocks.
-  struct Frags { u32x4 ah[RB], al[RB], b[4], bl[EF ? 4 : 1]; };
+  struct Frags { u32x4 ah[RB], al[RB], b[NC], bl[EF ? NC : 1]; };
   auto load_frags = [&](Frags& f, int sbuf, int ks) {
     const u32x4* gb = gfrag + sbuf * GSLOTS;
     const u32x4* ab = afrag + sbuf * ASLOTS;
     if constexpr (EF) {
 #pragma unroll
-      for (int a = 0; a < 4; ++a) f.bl[a] = glo[sbuf * GSLOTS + ((4 * nh + a) * 4 + 2 * ks + (lane >> 5)) * 32 + (lane & 31)];
+      for (int a = 0; a < NC; ++a) f.bl[a] = glo[sbuf * GSLOTS + ((NC * nh + a) * 4 + 2 * ks + (lane >> 5)) * 32 + (lane & 31)];
     }
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-      f.ah[rb] = ab[(((mb + 4 * rb) * 2 + ks) * 2 + 0) * 64 + lane];
-      f.al[rb] = ab[(((mb + 4 * rb) * 2 + ks) * 2 + 1) * 64 + lane];
+      f.ah[rb] = ab[(((mb + MW * rb) * 2 + ks) * 2 + 0) * 64 + lane];
+      f.al[rb] = ab[(((mb + MW * rb) * 2 + ks) * 2 + 1) * 64 + lane];
     }
 #pragma unroll
-    for (int a = 0; a < 4; ++a) f.b[a] = gb[((4 * nh + a) * 4 + 2 * ks + (lane >> 5)) * 32 + (lane & 31)];
+    for (int a = 0; a < NC; ++a) f.b[a] = gb[((NC * nh + a) * 4 + 2 * ks + (lane >> 5)) * 32 + (lane & 31)];
   };
   auto mfma_frags = [&](const Frags& f) {
     // an absent second rank block (rank not a multiple of 256) is multiplied anyway: its Q fragments
     // repeat the last block and its accumulators are never stored; no branch splits the MFMA run
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < NC; ++a)
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
         acc[rb][a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf(f.ah[rb]), as_bf(f.b[a]), acc[rb][a], 0, 0, 0);
@@ -497,22 +499,22 @@ __global__ __launch_bounds__(512) void k_proj_down_pipe(DevCtx d, const ProjTile
   const bool fuse = t.fuse != 0 && fa.u != nullptr;            // uniform over the workgroup
   const int64_t rgroups = m.rp / 8;
   const float osc = EF ? 1.f : grad_scale;                     // with error feedback the scale went into the staged sum
-  // accumulator block idx = 4 rb + a: rank block mbg[rb], column block t.n0 / 32 + 4 nh + a
-  auto live = [&](int idx) { return active[idx >> 2] && t.n0 / 32 + 4 * nh + (idx & 3) < m.qp / 32; };
+  // accumulator block idx = NC rb + a: rank block mbg[rb], column block t.n0 / 32 + NC nh + a
+  auto live = [&](int idx) { return active[idx / NC] && t.n0 / 32 + NC * nh + idx % NC < m.qp / 32; };
   // offset of the lane's four consecutive rank indices of that block's column block, rank group 4*mbg + vq
   auto offset_of = [&](int idx, int vq) {
-    const int nbg = t.n0 / 32 + 4 * nh + (idx & 3);
-    return (((int64_t)nbg * rgroups + 4 * mbg[idx >> 2] + vq) * 32 + (lane & 31)) * 8 + 4 * (lane >> 5);
+    const int nbg = t.n0 / 32 + NC * nh + idx % NC;
+    return (((int64_t)nbg * rgroups + 4 * mbg[idx / NC] + vq) * 32 + (lane & 31)) * 8 + 4 * (lane >> 5);
   };
   if (!fuse) {
 #pragma unroll
-    for (int idx = 0; idx < 4 * RB; ++idx) {
+    for (int idx = 0; idx < NC * RB; ++idx) {
       if (!live(idx)) continue;
 #pragma unroll
       for (int vq = 0; vq < 4; ++vq) {
         f32x4 val;
-        val.x = osc * acc[idx >> 2][idx & 3][4 * vq];     val.y = osc * acc[idx >> 2][idx & 3][4 * vq + 1];
-        val.z = osc * acc[idx >> 2][idx & 3][4 * vq + 2]; val.w = osc * acc[idx >> 2][idx & 3][4 * vq + 3];
+        val.x = osc * acc[idx / NC][idx % NC][4 * vq];     val.y = osc * acc[idx / NC][idx % NC][4 * vq + 1];
+        val.z = osc * acc[idx / NC][idx % NC][4 * vq + 2]; val.w = osc * acc[idx / NC][idx % NC][4 * vq + 3];
         *reinterpret_cast<GAS f32x4*>(out + offset_of(idx, vq)) = val;
       }
     }
@@ -534,12 +536,12 @@ __global__ __launch_bounds__(512) void k_proj_down_pipe(DevCtx d, const ProjTile
   };
   if (PF) fetch(0, 0);
 #pragma unroll
-  for (int idx = 0; idx < 4 * RB; ++idx) {
+  for (int idx = 0; idx < NC * RB; ++idx) {
     if (!PF) fetch(idx, 0);
-    else if (idx + 1 < 4 * RB) fetch(idx + 1, (idx + 1) & 1);
+    else if (idx + 1 < NC * RB) fetch(idx + 1, (idx + 1) & 1);
     ISSUE_FENCE();
     if (!live(idx)) continue;
-    const int rb = idx >> 2, a = idx & 3;
+    const int rb = idx / NC, a = idx % NC;
     float dsum = 0.f;
 #pragma unroll
     for (int vq = 0; vq < 4; ++vq) {
@@ -551,7 +553,7 @@ __global__ __launch_bounds__(512) void k_proj_down_pipe(DevCtx d, const ProjTile
       dsum += adam4<RB == 2>(fa, base + o, val, uu[idx & PF][vq], vv[idx & PF][vq]);
     }
     if constexpr (RB == 2) {
-      if (fa.colpart) store_colpart(fa, m, t.n0 / 32 + 4 * nh + a, mbg[rb], lane, dsum);
+      if (fa.colpart) store_colpart(fa, m, t.n0 / 32 + NC * nh + a, mbg[rb], lane, dsum);
     }
   }
 }
@@ -771,64 +773,68 @@ static hipError_t launch_down_tr(dim3 grid, const DevCtx& d, const ProjTile* til
   return hipGetLastError();
 }
 
-// One instantiation of the pipelined kernel; its dynamic LDS (64 KiB for 128-rank tiles, 96 KiB for
-// 256-rank tiles, 32 KiB more with error feedback) is raised above the default limit at first use.
-template <int RB, bool VEC, bool GONCE, int EF>
+// One instantiation of the pipelined kernel; its dynamic LDS (per stage 16 KiB of G, or two planes of that, and 4 KiB per rank block)
+// is raised above the default limit at first use.
+template <int MB, bool VEC, bool GONCE, int EF>
 static hipError_t launch_pipe(dim3 grid, const DevCtx& d, const ProjTile* tiles, float* glow, int64_t split_stride,
                               float grad_scale, const FusedAdam& fa, hipStream_t s) {
-  constexpr int LDS_BYTES = (RB == 2 ? 98304 : 65536) + (EF != 0 ? 32768 : 0);
+  constexpr int LDS_BYTES = 2 * (16 + 4 * MB + (EF != 0 ? 16 : 0)) * 1024;
   static LdsRaised raised;
   if constexpr (LDS_BYTES > 65536)
-    if (hipError_t e = raise_lds(reinterpret_cast<const void*>(k_proj_down_pipe<RB, VEC, GONCE, EF>), LDS_BYTES, raised); e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_proj_down_pipe<RB, VEC, GONCE, EF>), grid, dim3(512), LDS_BYTES, s, d, tiles, glow, split_stride, grad_scale, fa);
+    if (hipError_t e = raise_lds(reinterpret_cast<const void*>(k_proj_down_pipe<MB, VEC, GONCE, EF>), LDS_BYTES, raised); e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_proj_down_pipe<MB, VEC, GONCE, EF>), grid, dim3(512), LDS_BYTES, s, d, tiles, glow, split_stride, grad_scale, fa);
   return hipGetLastError();
 }
-template <int RB, int EF>
+template <int MB, int EF>
 static hipError_t launch_pipe_vo(bool g_vec, bool g_once, dim3 grid, const DevCtx& d, const ProjTile* tiles, float* glow,
                                  int64_t split_stride, float grad_scale, const FusedAdam& fa, hipStream_t s) {
+  if (MB < 4 && !g_once) return hipErrorInvalidValue;            // (one rank tile by construction)
+  if (EF != 0 && !g_vec) return hipErrorInvalidValue;            // (error feedback and fp32 sources come with aligned pairs only)
   if constexpr (EF == 0) {
-    if (!g_vec) return g_once ? launch_pipe<RB, false, true, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s)
-                              : launch_pipe<RB, false, false, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+    if (!g_vec) {
+      if constexpr (MB >= 4)
+        if (!g_once) return launch_pipe<MB, false, false, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+      return launch_pipe<MB, false, true, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+    }
   }
-  if (!g_vec) return hipErrorInvalidValue;                       // (error feedback and fp32 sources come with aligned pairs only)
-  return g_once ? launch_pipe<RB, true, true, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s)
-                : launch_pipe<RB, true, false, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+  if constexpr (MB >= 4)
+    if (!g_once) return launch_pipe<MB, true, false, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+  return launch_pipe<MB, true, true, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s);
 }
-static hipError_t launch_pipe_select(int rb, bool g_vec, bool g_once, int ef, dim3 grid, const DevCtx& d, const ProjTile* tiles,
-                                     float* glow, int64_t split_stride, float grad_scale, const FusedAdam& fa, hipStream_t s) {
-#define LORDO_PIPE_RB(RBV)                                                                                               \
-  (ef == 3 ? launch_pipe_vo<RBV, 3>(g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s)                \
-   : ef == 2 ? launch_pipe_vo<RBV, 2>(g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s)              \
-   : ef == 1 ? launch_pipe_vo<RBV, 1>(g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s)              \
-             : launch_pipe_vo<RBV, 0>(g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s))
-  return rb == 2 ? LORDO_PIPE_RB(2) : LORDO_PIPE_RB(1);
-#undef LORDO_PIPE_RB
+template <int MB>
+static hipError_t launch_pipe_ef(int ef, bool g_vec, bool g_once, dim3 grid, const DevCtx& d, const ProjTile* tiles, float* glow,
+                                 int64_t split_stride, float grad_scale, const FusedAdam& fa, hipStream_t s) {
+  if (ef == 3) return launch_pipe_vo<MB, 3>(g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+  if (ef == 2) return launch_pipe_vo<MB, 2>(g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+  if (ef == 1) return launch_pipe_vo<MB, 1>(g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+  return launch_pipe_vo<MB, 0>(g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
 }
 
-hipError_t launch_proj_down(const DevCtx& d, const ProjTile* tiles, int ntiles, int mb, int pipe_rb, bool g_vec, bool g_tr, bool g_once, float* glow,
-                            int64_t split_stride, float grad_scale, bool g_is_f32, int ef, const DownFuse* fuse, hipStream_t s) {
+hipError_t launch_proj_down(const DevCtx& d, const ProjTile* tiles, int ntiles, int rank_blocks, bool g_vec, bool g_tr, bool g_once, float* glow,
+                            int64_t split_stride, float grad_scale, int ef, const DownFuse* fuse, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
-  dim3 grid(ntiles), block(256);
-  if (pipe_rb) {       // pipelined kernel: 128 * pipe_rb rank indices per tile
-    FusedAdam fa{};
-    if (fuse) {
-      fa.u = fuse->u; fa.v = fuse->v; fa.n_hi = fuse->n_hi; fa.n_lo = fuse->n_lo;
-      fa.b1 = fuse->a.b1; fa.omb1 = fuse->a.omb1; fa.b2 = fuse->a.b2; fa.omb2 = fuse->a.omb2;
-      fa.step = fuse->a.step; fa.eps = fuse->a.eps;
-      fa.qw = fuse->a.qw; fa.qg = fuse->a.qg;
-      fa.g_hi = fuse->a.g_hi; fa.g_lo = fuse->a.g_lo; fa.colpart = fuse->a.colpart;
-    }
-    // 256-rank tiles (ranks from 256 up, where the matrix cores bound the kernel): gradient by global-to-LDS loads,
-    // transposed while it is read from LDS -- 8 to 11 % faster there than staging through registers; with 128-rank
-    // tiles (memory-bound, two workgroups per compute unit) the register-staged kernel is as fast or faster
-    if (g_tr && ef == 0 && pipe_rb == 2)
-      return g_once ? launch_down_tr<2, true>(grid, d, tiles, glow, split_stride, grad_scale, fa, s)
-                    : launch_down_tr<2, false>(grid, d, tiles, glow, split_stride, grad_scale, fa, s);
-    return launch_pipe_select(pipe_rb, g_vec, g_once, ef, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+  dim3 grid(ntiles);
+  FusedAdam fa{};
+  if (fuse) {
+    fa.u = fuse->u; fa.v = fuse->v; fa.n_hi = fuse->n_hi; fa.n_lo = fuse->n_lo;
+    fa.b1 = fuse->a.b1; fa.omb1 = fuse->a.omb1; fa.b2 = fuse->a.b2; fa.omb2 = fuse->a.omb2;
+    fa.step = fuse->a.step; fa.eps = fuse->a.eps;
+    fa.qw = fuse->a.qw; fa.qg = fuse->a.qg;
+    fa.g_hi = fuse->a.g_hi; fa.g_lo = fuse->a.g_lo; fa.colpart = fuse->a.colpart;
   }
-  // fp32 gradients do not come here: their products run in the grouped GEMM with three-term operands
-  (void)mb; (void)g_is_f32; (void)block;
-  return hipErrorInvalidValue;
+  // 256-rank tiles (ranks from 256 up, where the matrix cores bound the kernel): gradient by global-to-LDS loads,
+  // transposed while it is read from LDS -- 8 to 11 % faster there than staging through registers; with 128-rank
+  // tiles (memory-bound, two workgroups per compute unit) the register-staged kernel is as fast or faster
+  if (g_tr && ef == 0 && rank_blocks == 8)
+    return g_once ? launch_down_tr<2, true>(grid, d, tiles, glow, split_stride, grad_scale, fa, s)
+                  : launch_down_tr<2, false>(grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+  switch (rank_blocks) {
+    case 8: return launch_pipe_ef<8>(ef, g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+    case 4: return launch_pipe_ef<4>(ef, g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+    case 2: return launch_pipe_ef<2>(ef, g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+    case 1: return launch_pipe_ef<1>(ef, g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+    default: return hipErrorInvalidValue;                        // (fp32 gradients run in the grouped GEMM)
+  }
 }
 
 // The last launch of a local step has one workgroup more than tiles, the first, which moves the step count on.  The test
