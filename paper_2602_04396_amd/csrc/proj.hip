@@ -698,25 +698,6 @@ __global__ __launch_bounds__(512) void k_proj_down_tr(DevCtx d, const ProjTile* 
   };
 
   const int nstages = (t.k1 - t.k0 + BK - 1) / BK;
-  // stages past the last one are loaded all the same (rows clamped, fragments clamped): the number of loads in
-  // flight is then the same in every iteration, which the explicit waits count on
-#pragma unroll
-  for (int s0 = 0; s0 < NS - 1; ++s0) issue_stage(s0, s0);
-  int sbuf = 0;
-  for (int s = 0; s < nstages; ++s) {
-    // at most NS - 2 younger stages outstanding: stage s has landed; barrier: visible to all, stage s-1 consumed by all
-    if constexpr ((NS - 2) * NDMA == 8) WAIT_VM_BARRIER(8);
-    else WAIT_VM_BARRIER(6);
-    static_assert((NS - 2) * NDMA == 8 || (NS - 2) * NDMA == 6, "wait count");
-    int nbuf = sbuf + NS - 1;
-    nbuf = nbuf >= NS ? nbuf - NS : nbuf;
-    issue_stage(s + NS - 1, nbuf);                              // into the buffer of stage s-1
-    ISSUE_FENCE();
-    compute(sbuf);
-    sbuf = sbuf + 1 == NS ? 0 : sbuf + 1;
-  }
-  WAIT_VM_BARRIER(0);             // the loads past the last stage must land before this workgroup's LDS is released
-
   const int64_t base = m.lr_off;
   GAS float* out = TO_GLOBAL(float, glow) + (int64_t)t.split * split_stride + base;
   const bool fuse = t.fuse != 0 && fa.u != nullptr;
@@ -727,9 +708,9 @@ __global__ __launch_bounds__(512) void k_proj_down_tr(DevCtx d, const ProjTile* 
     const int nbg = t.n0 / 32 + 4 * nh + (idx & 3);
     return (((int64_t)nbg * rgroups + 4 * mbg[idx >> 2] + vq) * 32 + (lane & 31)) * 8 + 4 * (lane >> 5);
   };
-  // fused Adam: the moments of the NEXT block are requested before this one is worked on, so that the epilogue of a
-  // tile exposes one memory latency and not one per block (this workgroup has the compute unit to itself: nothing
-  // else runs while it waits)
+  // fused Adam: the moments of the first block are requested ahead of the last stage, those of every further one before the one
+  // ahead of it is worked on, so that no block waits for a memory latency of its own (this workgroup has the compute unit to itself:
+  // nothing else runs while it waits)
   f32x4 uu[2][4], vv[2][4];
   auto fetch = [&](int idx, int buf) {
     if (!live(idx)) return;
@@ -740,7 +721,22 @@ __global__ __launch_bounds__(512) void k_proj_down_tr(DevCtx d, const ProjTile* 
       vv[buf][vq] = __builtin_nontemporal_load(TO_GLOBAL(const f32x4, fa.v + at));
     }
   };
+  static_assert(NS == 3 && NDMA == 6, "two stages in flight, wait count");
+  issue_stage(0, 0);
+  if (nstages > 1) issue_stage(1, 1);
+  int sbuf = 0;
+  for (int s = 0; s + 1 < nstages; ++s) {
+    // only stage s + 1 may be outstanding: stage s has landed; barrier: visible to all, stage s-1 consumed by all
+    WAIT_VM_BARRIER(6);
+    if (s + 2 < nstages) issue_stage(s + 2, sbuf == 0 ? 2 : sbuf - 1);      // into the buffer of stage s-1
+    ISSUE_FENCE();
+    compute(sbuf);
+    sbuf = sbuf + 1 == NS ? 0 : sbuf + 1;
+  }
+  WAIT_VM_BARRIER(0);
   if (fuse) fetch(0, 0);
+  ISSUE_FENCE();
+  if (nstages > 0) compute(sbuf);
 #pragma unroll
   for (int idx = 0; idx < 4 * RB; ++idx) {
     if (fuse && idx + 1 < 4 * RB) fetch(idx + 1, (idx + 1) & 1);
@@ -1243,8 +1239,10 @@ __global__ __launch_bounds__(64 * NW) void k_proj_up_dma(DevCtx d, const ProjTil
 // registers admit two workgroups per compute unit, so that the epilogue of one (read, update, write of its W tile)
 // runs under the contraction of the other.  Inside a wave the fragments of the next k-step are read from LDS into a
 // second register set while the matrix cores work on the current one; the registers then leave no room for W during
-// the contraction: its row blocks are requested when the contraction ends, three in flight (two when the epilogue
-// also reads a gradient tile: the full-rank QHM update, the residual of the error feedback).
+// the contraction: its row blocks are requested when the contraction ends, the first one ahead of the last products, three in
+// flight (two when the epilogue also reads a gradient tile: the full-rank QHM update, the residual of the error feedback).
+// Nothing is requested past the last k-step (repeating it for an even count of loads cost 19 % of the operand traffic at r = 256):
+// with the same in the down-projection 1B set, r = 256 4.00 -> 3.96 ms a step, its full-rank QHM form in bf16 7.11 -> 7.00 ms.
 // ---------------------------------------------------------------------------------------
 template <bool WBF, bool WITH_G, bool RAG = false>     // WITH_G: gradient-term epilogue (bf16 G): the full-rank QHM update, or the residual E as target; RAG: rows of the target at any alignment (plain update)
 __global__ __launch_bounds__(256) void k_proj_up_wide(DevCtx d, const ProjTile* __restrict__ tiles,
@@ -1291,7 +1289,6 @@ __global__ __launch_bounds__(256) void k_proj_up_wide(DevCtx d, const ProjTile* 
     fsrc[5] = nl + (int64_t)nbf * rgroups * 32 + lane;
   }
   auto issue_chunk = [&](int c, int s) {
-    c = c < nchunks ? c : nchunks - 1;                     // past the end the last k-step is loaded again: same count every iteration
     u32x4* base = frag + s * SLOTS * 64;
 #pragma unroll
     for (int j = 0; j < 2; ++j)
@@ -1355,14 +1352,18 @@ __global__ __launch_bounds__(256) void k_proj_up_wide(DevCtx d, const ProjTile* 
         acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf(f[8 + b]), as_bf(f[4 + a]), acc[a][b], 0, 0, 0);
       }
   };
-  // one k-step: on entry `cur` holds the fragments of k-step c; k-steps c+1 and c+2 are in flight
+  // one k-step: on entry `cur` holds the fragments of k-step c; k-steps c+1 and c+2 are in flight, c+3 is requested.  The last
+  // three request nothing more (the padded rank is a multiple of 32 and at least 256: an even number of k-steps, 16 or more)
   int sbuf = 0;                                              // ring buffer of k-step c
-  auto step = [&](const u32x4 (&cur)[12], u32x4 (&nxt)[12], int c) {
-    WAIT_VM_BARRIER(6);                                      // k-step c+1 has landed; every wave holds k-step c in registers
-    issue_chunk(c + 3, sbuf);                                // into the buffer of k-step c
+  auto advance_ring = [&](u32x4 (&nxt)[12]) {
     sbuf = sbuf == 2 ? 0 : sbuf + 1;
     read_frags(nxt, sbuf);
     ISSUE_FENCE();
+  };
+  auto step = [&](const u32x4 (&cur)[12], u32x4 (&nxt)[12], int c) {
+    WAIT_VM_BARRIER(6);                                      // k-step c+1 has landed; every wave holds k-step c in registers
+    issue_chunk(c + 3, sbuf);                                // into the buffer of k-step c
+    advance_ring(nxt);
     multiply(cur);
   };
   u32x4 fa[12], fb2[12];
@@ -1370,13 +1371,21 @@ __global__ __launch_bounds__(256) void k_proj_up_wide(DevCtx d, const ProjTile* 
   issue_chunk(2, 2);
   read_frags(fa, 0);
   ISSUE_FENCE();
-  for (int c = 0; c < nchunks; c += 2) {                     // (the padded rank is a multiple of 32: an even number of k-steps)
+  int c = 0;
+  for (; c + 4 < nchunks; c += 2) {
     step(fa, fb2, c);
     step(fb2, fa, c + 1);
   }
-  WAIT_VM_BARRIER(0);             // the repeated loads of the last k-step have landed, all waves are done reading fragments
-
-  if (mb0 >= mblocks || nb0 >= nblocks) return;
+  step(fa, fb2, c);
+  WAIT_VM_BARRIER(6);
+  advance_ring(fa);
+  multiply(fb2);
+  WAIT_VM_BARRIER(0);                                        // the last k-step has landed
+  advance_ring(fb2);
+  multiply(fa);
+  // all waves hold the last fragments in registers: the memory is free for staging.  The first rows of W are requested before the
+  // last products, in the registers of the fragments that are used up
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   float* T = reinterpret_cast<float*>(frag) + wave * 32 * TP;
   // gradient term: coef_g * G * c_j on the lane's four columns, c_j the column scale of the full-rank QHM update
   // (1 / mean over the rank of sqrt(v_hat) + eps, from the sums the Adam kernel left) or 1
@@ -1441,13 +1450,15 @@ __global__ __launch_bounds__(256) void k_proj_up_wide(DevCtx d, const ProjTile* 
       for (int j = 0; j < 8; ++j) gr.g[j] = __builtin_amdgcn_raw_buffer_load_b64(rg, gvoff, g_soff(a, j), STREAM);
     }
   };
-  // the fragment registers are free now: two further row blocks are requested at once, the last one as soon as
-  // the first has been combined, so that only one memory latency is left exposed per tile
+  // two further row blocks are requested at once, the last one as soon as the first has been combined
   // (fp32 target with a gradient tile: 48 registers per row block, two in flight keep the kernel at two waves per SIMD)
   constexpr bool THREE = !(WITH_G && !WBF);
   typename WA::raw_t wv0[8], wv1[8], wv2[THREE ? 8 : 1];
   GRows g0, g1, g2;
   fetch(0, wv0, g0);
+  ISSUE_FENCE();
+  multiply(fb2);
+  if (mb0 >= mblocks || nb0 >= nblocks) return;
   fetch(1, wv1, g1);
   if constexpr (THREE) {
     fetch(2, wv2, g2);
