@@ -190,10 +190,28 @@ struct ProgramBuilder {
     int ksplit = 1;
     if (small_out && tiles > 0 && tiles < 1024)
       ksplit = (int)std::min<int64_t>(P.part_slices, (1024 + tiles - 1) / tiles);     // never more slices than allocated
+    // Slices of an even length, but not shorter than kmin: a workgroup writes its whole tile for every slice (64 KiB, as much as 64 rows
+    // of 128 columns on either side are to read) and k_gemm_reduce reads it again.  192 rows always, longer ones up to 768 while the launch
+    // keeps four workgroups to five compute units.  Whole refreshes with kmin = 32 / 192 / 384 / 512 / 768 (us): 125M set, r = 128 1486 / 1398 /
+    // 1386 / 1417 / 1460; two blocks of it 646 / 641 / 681 / 714 / 780; 24 x (2048 x 2048), r = 64 793 / 798 / 810 / 823 / 842; 72 of 1024 .. 4096,
+    // r = 256 3909 / 3909 / 3823 / 3716 / 3733; four blocks of 7B, r = 128 4736 / 4748 / 4765 / 4697 / 4721, two of 2560 .. 8000, r = 400
+    // 5656 / 5641 / 5642 / 5638 / 5556.  (The initial projection keeps its slices, and so its bits.)
+    int kmin = 32;
+    if (ksplit > 1 && !initial) {
+      for (int f : {192, 256, 384, 512, 768}) {
+        int64_t wgs = 0;
+        for (const GemmDesc& g : made) {
+          const int tm = (g.M + op.tile - 1) / op.tile, tn = (g.N + op.tile - 1) / op.tile;
+          const int klen = std::max(f, ((g.K + ksplit - 1) / ksplit + 31) / 32 * 32);
+          wgs += (int64_t)(lower_only ? tm * (tm + 1) / 2 : tm * tn) * ((g.K + klen - 1) / klen);
+        }
+        if (f == 192 || wgs >= 205) kmin = f;
+      }
+    }
     op.desc_first = (int)P.desc_h.size();
     for (GemmDesc g : made) {
       int ks = ksplit;
-      int klen = ((g.K + ks - 1) / ks + 31) / 32 * 32;
+      int klen = std::max(kmin, ((g.K + ks - 1) / ks + 31) / 32 * 32);
       ks = (g.K + klen - 1) / klen;
       if (ks > 1) {
         g.ksplit = ks;
