@@ -76,6 +76,7 @@ struct GemmDesc {
   int64_t sAm, sAk, sBk, sBn;
   int32_t ldc, a_bf16, b_bf16;        // a_bf16: 0 fp32, 1 bf16, 2 = element type given at launch (refresh source)
   int32_t pad0;
+  int64_t diag;           // Gram matrix X^T X: its diagonal is summed in double on the side; ksplit x M partial sums at this offset (-1: not so)
   float alpha, beta;
   // split-K (ksplit > 1): slice s covers k in [s*klen, (s+1)*klen) and writes its raw M x N sum to
   // P + s*M*N; a reduction kernel then adds the slices in order and applies alpha, beta, C2
@@ -240,7 +241,7 @@ hipError_t launch_gram_shift(const DevCtx& d, float coef, bool store, hipStream_
 // exact diagonal of the Gram matrix of block `which` (0, 1: Y pair; 2, 3: zw[0], zw[1]) written over the one the GEMM left
 hipError_t launch_gram_diag(const DevCtx& d, int which, int rmax, int part_slices, hipStream_t s);
 hipError_t launch_mssv(const DevCtx& d, float* out, hipStream_t s);
-hipError_t launch_factor_diag(const DevCtx& d, int jb, int rmax, hipStream_t s);      // rmax: largest rank of the set
+hipError_t launch_factor_diag(const DevCtx& d, int jb, int rmax, float shift_coef, hipStream_t s);      // rmax: largest rank of the set; shift_coef: of the trace, on the diagonal
 hipError_t launch_potf2(const DevCtx& d, int jb, hipStream_t s);
 hipError_t launch_diag_inverses(const DevCtx& d, hipStream_t s);
 hipError_t launch_frob2(const DevCtx& d, const int64_t* chunk_start, int64_t nchunks, float* partial, bool src_f32, hipStream_t s);

@@ -7,13 +7,13 @@
 //   k_fold_grad       E <- E + s G, the projection source of the local variant (Alg. 2)
 //   k_pack_q / k_pack_block / k_split_planes   fp32 -> bf16 hi/lo operand planes in matrix-core order
 //   k_glow_to_z, k_lr_to_plain, k_plain_to_lr, k_lr_exchange, k_tr_exchange   between the operand layout of the low-rank state and plain buffers
-//   k_gram_shift, k_factor_diag   CholeskyQR: diagonal shift, Cholesky of a diagonal block and its inverse (k_potf2, k_diag_inverses: of the initial projection)
+//   k_factor_diag   CholeskyQR: Cholesky of a diagonal block with its shift, and its inverse (k_gram_shift, k_potf2, k_diag_inverses: of the initial projection)
 //   k_jacobi_svd      singular vectors of the Cholesky factor of the r x r Ritz matrix (Rayleigh-Ritz step: basis ordered as in Sec. 2's SVD projection)
 //   k_frob2_chunks / k_frob2_sum / k_stable_rank   squared Frobenius norm of the refresh source and its stable rank (Sec. 5.1)
 //   k_rot_pre / k_rot_post, k_mssv   elementwise parts of the moment rotation (Alg. 1 rotation lines); similarity diagnostic (Sec. 5.1)
 //   k_step_set        step count and bias corrections 1 - beta^t (Sec. 2) in device memory
 //   k_gauss_block     Gaussian start blocks of the range finder and of the random initial projection (Alg. 1 Require)
-//   k_gram_diag_part / k_gram_diag_sum   exact diagonal of the Gram matrices of CholeskyQR
+//   k_gram_diag_part / k_gram_diag_sum   exact diagonal of the Gram matrices of the initial projection
 //   k_bf16_to_f32 / k_f32_to_bf16   a bf16-stored residual through the fp32 state interface
 #include "common.h"
 
@@ -707,11 +707,8 @@ __global__ __launch_bounds__(256) void k_gram_shift(DevCtx d, float coef, int st
   if (store && m.ritz >= 0 && threadIdx.x == 0) reinterpret_cast<float*>(d.arena + m.ritz)[m.r + 2] = shift;
 }
 // Diagonal of the Gram matrix S = X^T X of a tall block X (rows x r, row-major), summed in double from the fp32
-// entries: S_kk = sum_i X_ik^2.  The grouped GEMM forms S from three-term bf16 operands; on the diagonal the product
-// of the two middle terms is a square, always positive and about 2^-18 of the entry, and in a long contraction it
-// falls below half an ulp of the running sum and is rounded away step after step: the diagonal came out 2e-6 to
-// 3e-6 too small at p >= 4096 and the columns of the orthonormalised block that much too long -- 7e-5 in
-// || Q^T Q - I ||_F at r = 512.  The diagonal carries the column norms, so it alone is recomputed exactly.
+// entries: S_kk = sum_i X_ik^2 (the reason stands at the DIAG loop of the grouped GEMM, which does this on its way; the passes here serve
+// the initial projection, whose bits stay as they are, and ranks below four, which run on the fp32 matrix cores).
 // Two stages, both in a fixed order: workgroup (64 columns, row chunk, matrix) sums its rows (4 row lanes x 64
 // columns, eight loads in flight per thread) into the split-K partial-sum buffer of the matrix, which the Gram
 // product has just released; one thread per column then adds the chunks and writes the diagonal entry.
@@ -1168,7 +1165,9 @@ __device__ __forceinline__ void mul_half(f32x4m (&acc)[4], LdsTile A, LdsTile B,
 // no more: 34 KiB let four workgroups share a compute unit where 102 KiB let one, which sets of more matrices than units need
 // (whole refresh of 1024 matrices of 256 x 256 at r = 16: 1536 -> 1419 us; of 2048 of 128 x 128 at r = 8: 2482 -> 2212 us).
 constexpr int FACTOR_LDS = 6 * HB * FPITCH * 4, FACTOR_LDS_HALF = 2 * HB * FPITCH * 4;
-__global__ __launch_bounds__(256) void k_factor_diag(DevCtx d, int jb) {
+// shift_coef != 0: shift_coef * trace(S) is added to the diagonal, which keeps the first factorisation positive definite in fp32.
+// The launch of the first block sums the trace and leaves the shift in the unused S(0, 1) for those of the others.
+__global__ __launch_bounds__(256) void k_factor_diag(DevCtx d, int jb, float shift_coef) {
   if (mat_skipped(d, blockIdx.x)) return;
   const MatDev& m = d.mats[blockIdx.x];
   const int o = jb * NB, r = m.r;
@@ -1191,6 +1190,12 @@ __global__ __launch_bounds__(256) void k_factor_diag(DevCtx d, int jb) {
   // Rows are read coalesced, PAD_PIVOT on the diagonal outside the block.  All loads are requested before the first is used (element 0 in the
   // place of what is not read): row by row, each waited for, they took 11 of the launch's 49 us.
   {
+    float* const S0 = reinterpret_cast<float*>(d.arena + m.gram);
+    float shift = 0.f, tr = 0.f;
+    if (shift_coef != 0.f) {                         // (uniform)
+      if (jb == 0) for (int i = tid; i < r; i += 256) tr += S0[(int64_t)i * r + i];
+      else shift = S0[1];
+    }
     float s11[HB / 4], s21[HB / 4], s22[HB / 4];
 #pragma unroll
     for (int i = 0; i < HB / 4; ++i) {
@@ -1201,14 +1206,26 @@ __global__ __launch_bounds__(256) void k_factor_diag(DevCtx d, int jb) {
       s22[i] = S[row + (rr < n2 && lane <= rr ? HB + lane : 0)];
     }
     asm volatile("" ::: "memory");                   // the loads stay ahead of the first use
+    if (shift_coef != 0.f && jb == 0) {
+      float* const red = &A1[0][0];
+      red[tid] = tr;
+      __syncthreads();
+      for (int k = 128; k > 0; k >>= 1) {
+        if (tid < k) red[tid] += red[tid + k];
+        __syncthreads();
+      }
+      shift = shift_coef * red[0];
+      __syncthreads();
+      if (r > NB && tid == 0) S0[1] = shift;
+    }
 #pragma unroll
     for (int i = 0; i < HB / 4; ++i) {
       const int rr = w + 4 * i;
-      const float diag = rr == lane ? PAD_PIVOT : 0.f;
-      A1[rr][lane] = rr < n1 && lane <= rr ? s11[i] : diag;
+      const float diag = rr == lane ? PAD_PIVOT : 0.f, add = rr == lane ? shift : 0.f;
+      A1[rr][lane] = rr < n1 && lane <= rr ? s11[i] + add : diag;
       if (n2 > 0) {
         P[rr][lane] = rr < n2 ? s21[i] : 0.f;
-        A2[rr][lane] = rr < n2 && lane <= rr ? s22[i] : diag;
+        A2[rr][lane] = rr < n2 && lane <= rr ? s22[i] + add : diag;
       }
     }
   }
@@ -1265,11 +1282,11 @@ __global__ __launch_bounds__(256) void k_factor_diag(DevCtx d, int jb) {
     }
   }
 }
-hipError_t launch_factor_diag(const DevCtx& d, int jb, int rmax, hipStream_t s) {
+hipError_t launch_factor_diag(const DevCtx& d, int jb, int rmax, float shift_coef, hipStream_t s) {
   static LdsRaised raised;
   const hipError_t e = raise_lds(reinterpret_cast<const void*>(k_factor_diag), FACTOR_LDS, raised);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_factor_diag, dim3(d.n), dim3(256), rmax - jb * NB > HB ? FACTOR_LDS : FACTOR_LDS_HALF, s, d, jb);
+  hipLaunchKernelGGL(k_factor_diag, dim3(d.n), dim3(256), rmax - jb * NB > HB ? FACTOR_LDS : FACTOR_LDS_HALF, s, d, jb, shift_coef);
   return hipGetLastError();
 }
 

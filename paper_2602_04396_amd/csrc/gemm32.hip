@@ -303,9 +303,18 @@ struct OperandBF {
 
 // same_ab (uniform): the tile of B is the tile of A (a diagonal tile of a Gram matrix X^T X): it is fetched and
 // split once and the B fragments are read from the planes of A.
-template <int WB, bool UA, bool A_BF16, bool A_KF, bool B_KF>
+// DIAG: such a tile also sums the squares of its columns in double, from the values as they pass through its registers, and leaves them
+// at g.diag (or, not split, as the diagonal of C).  The products of the two middle terms are dropped from the six: squares on the
+// diagonal, always positive and about 2^-18 of the entry; in a long contraction they fall below half an ulp of the running sum and
+// are rounded away step after step.  The diagonal came out 2e-6 to 3e-6 too small at p >= 4096 and the columns of the orthonormalised
+// block that much too long: 7e-5 in || Q^T Q - I ||_F at r = 512.  The diagonal carries the column norms, so it alone is summed exactly.
+// (As passes of their own, over X and over partial sums, with a launch for the diagonal shift, 24 us behind every Gram matrix of the
+// 125M set: its refresh 1897 -> 1796 us; four blocks of 7B 17.99 -> 17.39 ms, 1B synchronisation 26.19 -> 26.04 ms, two blocks of 125M
+// 641 -> 615 us.)
+template <int WB, bool UA, bool A_BF16, bool A_KF, bool B_KF, bool DIAG = false>
 __device__ __forceinline__ void gemm_loop_bf(f32x16 (&acc)[WB][WB], const GemmDesc& g, const char* baseA, const char* baseB,
-                                             uint16_t* lds, int m0, int n0, int kbeg, int K, int tid, int lane, int wm, int wn, bool same_ab) {
+                                             uint16_t* lds, int m0, int n0, int kbeg, int K, int tid, int lane, int wm, int wn, bool same_ab,
+                                             char* arena, int slice) {
   constexpr int TM = 64 * WB;
   typedef OperandBF<TM, UA, A_BF16, A_KF> OpA;
   typedef OperandBF<TM, UA, false, B_KF> OpB;
@@ -317,11 +326,21 @@ __device__ __forceinline__ void gemm_loop_bf(f32x16 (&acc)[WB][WB], const GemmDe
   constexpr int NA = A_BF16 ? 1 : 3;                           // planes of A; B always has three
   uint16_t* PA = lds;
   uint16_t* PB = (!A_BF16 && same_ab) ? lds : lds + NA * PLANE;
-  const bool own_b = A_BF16 || !same_ab;
+  const bool own_b = !DIAG && (A_BF16 || !same_ab);
+  double dsum[4] = {0.0, 0.0, 0.0, 0.0};                       // DIAG: of the thread's four columns over its rows
   auto step = [&](u32x4 (&ra)[OpA::NV], u32x4 (&rb)[OpB::NV], int k0) {
     __syncthreads();                           // previous tile fully consumed
     opA.stash(ra, PA, PLANE, k0, tid);
     if (own_b) opB.stash(rb, PB, PLANE, k0, tid);
+    if constexpr (DIAG) {
+#pragma unroll
+      for (int n = 0; n < OpA::NV; ++n)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const double x = (double)__uint_as_float(ra[n][e]);
+          dsum[e] = fma(x, x, dsum[e]);
+        }
+    }
     __syncthreads();
     opA.fetch(ra, k0 + 2 * TK);                // (past the end: the last vectors once more, so that every step has the same loads in flight)
     if (own_b) opB.fetch(rb, k0 + 2 * TK);
@@ -369,17 +388,42 @@ __device__ __forceinline__ void gemm_loop_bf(f32x16 (&acc)[WB][WB], const GemmDe
     step(ra1, rb1, k0 + TK);
   }
   if (k0 < K) step(ra0, rb0, k0);
+  if constexpr (DIAG) {
+    static_assert(!A_BF16 && !A_KF, "patches of four columns");
+    constexpr int GROUPS = 1024 / TM;                          // threads that share four columns, added in their order
+    double (*red)[TM] = reinterpret_cast<double (*)[TM]>(lds);
+    static_assert(sizeof(double) * GROUPS * TM <= sizeof(uint16_t) * 3 * PLANE, "partial sums must fit");
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[tid / (TM / 4)][opA.row(0, tid) + e] = dsum[e];
+    __syncthreads();
+    const int col = m0 + tid;
+    if (tid < TM && col < g.M) {
+      double sum = 0.0;
+#pragma unroll
+      for (int i = 0; i < GROUPS; ++i) sum += red[i][tid];
+      if (g.ksplit > 1) *((GAS double*)(arena + g.diag) + (int64_t)slice * g.M + col) = sum;
+      else *((GAS float*)(arena + g.C.off) + (int64_t)col * g.ldc + col) = (float)sum;
+    }
+  }
 }
 
 // The loop for the unit-stride directions of a problem's operands (uniform)
 template <int WB, bool UA, bool A_BF16>
 __device__ __forceinline__ void gemm_loops_bf(f32x16 (&acc)[WB][WB], const GemmDesc& g, const char* baseA, const char* baseB, uint16_t* lds,
-                                              int m0, int n0, int kbeg, int K, int tid, int lane, int wm, int wn, bool same_ab) {
+                                              int m0, int n0, int kbeg, int K, int tid, int lane, int wm, int wn, bool same_ab,
+                                             char* arena, int slice) {
   const bool akf = g.sAk == 1 && g.sAm != 1, bkf = g.sBk == 1 && g.sBn != 1;
-  if (akf && bkf) gemm_loop_bf<WB, UA, A_BF16, true, true>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab);
-  else if (akf) gemm_loop_bf<WB, UA, A_BF16, true, false>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab);
-  else if (bkf) gemm_loop_bf<WB, UA, A_BF16, false, true>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab);
-  else gemm_loop_bf<WB, UA, A_BF16, false, false>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab);
+  if constexpr (!A_BF16) {
+    if (same_ab && g.diag >= 0 && !akf && !bkf) {
+      gemm_loop_bf<WB, UA, false, false, false, true>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, true, arena, slice);
+      return;
+    }
+  }
+  if (akf && bkf) gemm_loop_bf<WB, UA, A_BF16, true, true>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab, arena, slice);
+  else if (akf) gemm_loop_bf<WB, UA, A_BF16, true, false>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab, arena, slice);
+  else if (bkf) gemm_loop_bf<WB, UA, A_BF16, false, true>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab, arena, slice);
+  else gemm_loop_bf<WB, UA, A_BF16, false, false>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab, arena, slice);
 }
 
 // 256 threads = 4 waves in a 2 x 2 grid; each wave WB x WB accumulator blocks of 32 x 32, so the
@@ -429,7 +473,7 @@ __global__ __launch_bounds__(256, MODE == GEMM_RAGGED ? 2 : 1) void k_gemm32(Dev
   const bool same_ab = g.A.off == g.B.off && g.A.ext == g.B.ext && g.sAm == g.sBn && g.sAk == g.sBk && m0 == n0 && M == N;
   uint16_t* planes = reinterpret_cast<uint16_t*>(lds_raw);
   if constexpr (MODE != GEMM_ANY) {
-    if (kbeg < K) gemm_loops_bf<WB, MODE == GEMM_RAGGED, A_BF16>(acc, g, baseA, baseB, planes, m0, n0, kbeg, K, tid, lane, wm, wn, !A_BF16 && same_ab);
+    if (kbeg < K) gemm_loops_bf<WB, MODE == GEMM_RAGGED, A_BF16>(acc, g, baseA, baseB, planes, m0, n0, kbeg, K, tid, lane, wm, wn, !A_BF16 && same_ab, d.arena, t.ks);
   } else {
     const int a_bf16 = g.a_bf16 == 2 ? src_is_bf16 : g.a_bf16;
     float (*As)[PITCH] = reinterpret_cast<float (*)[PITCH]>(lds_raw);
@@ -440,8 +484,8 @@ __global__ __launch_bounds__(256, MODE == GEMM_RAGGED ? 2 : 1) void k_gemm32(Dev
     const bool vec = opA.vec_ok && opB.vec_ok;
     if (kbeg >= K) {
     } else if (vec) {
-      if (a_bf16) gemm_loops_bf<WB, false, true>(acc, g, baseA, baseB, planes, m0, n0, kbeg, K, tid, lane, wm, wn, false);
-      else gemm_loops_bf<WB, false, false>(acc, g, baseA, baseB, planes, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab);
+      if (a_bf16) gemm_loops_bf<WB, false, true>(acc, g, baseA, baseB, planes, m0, n0, kbeg, K, tid, lane, wm, wn, false, d.arena, t.ks);
+      else gemm_loops_bf<WB, false, false>(acc, g, baseA, baseB, planes, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab, d.arena, t.ks);
     } else if (a_bf16) {
       gemm_loop<WB, true>(acc, opA, opB, As, Bs, kbeg, K, tid, lane, wm, wn);
     } else {
@@ -462,7 +506,7 @@ __global__ __launch_bounds__(256, MODE == GEMM_RAGGED ? 2 : 1) void k_gemm32(Dev
         int row = m0 + wm + 32 * a + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
         if (row < M && Pp) {
           Pp[(int64_t)row * N + col] = acc[a][b][v];
-        } else if (row < M) {
+        } else if (row < M && !(row == col && MODE != GEMM_ANY && g.diag >= 0)) {
           int64_t o = (int64_t)row * g.ldc + col;
           float val = g.alpha * alpha_mul * acc[a][b][v];
           if (g.beta != 0.f) val = fmaf(g.beta, C[o], val);
@@ -473,7 +517,8 @@ __global__ __launch_bounds__(256, MODE == GEMM_RAGGED ? 2 : 1) void k_gemm32(Dev
     }
 }
 
-// Sum of the split-K slices in slice order (deterministic), then alpha, beta and the optional square.
+// Sum of the split-K slices in slice order (deterministic), then alpha, beta and the optional square.  Of a Gram matrix the lower
+// triangle, which is all that is read, with the diagonal from its own sums.
 __global__ __launch_bounds__(256) void k_gemm_reduce(DevCtx d, const GemmDesc* __restrict__ descs) {
   const GemmDesc g = descs[blockIdx.y];
   if (g.ksplit <= 1 || mat_skipped(d, g.mat)) return;
@@ -482,6 +527,15 @@ __global__ __launch_bounds__(256) void k_gemm_reduce(DevCtx d, const GemmDesc* _
   float* C2 = g.C2.off >= 0 ? reinterpret_cast<float*>(const_cast<char*>(resolve(d, g.C2, g.mat))) : nullptr;
   const int64_t total = (int64_t)g.M * g.N;
   for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
+    const uint32_t row = (uint32_t)e / (uint32_t)g.N, col = (uint32_t)e - row * (uint32_t)g.N;      // (M N < 2^32: r x r products)
+    if (g.diag >= 0 && col >= row) {
+      if (col > row) continue;
+      const double* part = reinterpret_cast<const double*>(d.arena + g.diag);
+      double sum = 0.0;
+      for (int sl = 0; sl < g.ksplit; ++sl) sum += part[(int64_t)sl * g.M + row];
+      C[(int64_t)row * g.ldc + row] = (float)sum;
+      continue;
+    }
     float acc = 0.f;
     // eight loads in flight, added in slice order (one at a time, each waited for: 18 us at r = 128, 72 matrices, 15 slices)
     int sl = 0;
@@ -493,7 +547,6 @@ __global__ __launch_bounds__(256) void k_gemm_reduce(DevCtx d, const GemmDesc* _
       for (int i = 0; i < 8; ++i) acc += x[i];
     }
     for (; sl < g.ksplit; ++sl) acc += Pp[(int64_t)sl * total + e];
-    const uint32_t row = (uint32_t)e / (uint32_t)g.N, col = (uint32_t)e - row * (uint32_t)g.N;      // (M N < 2^32: r x r products)
     int64_t o = (int64_t)row * g.ldc + col;
     float val = g.alpha * acc;
     if (g.beta != 0.f) val = fmaf(g.beta, C[o], val);

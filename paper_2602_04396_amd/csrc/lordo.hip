@@ -38,7 +38,7 @@ struct Op {
   int a_bf16 = 0;                   // OP_GEMM: element type of A (as in GemmDesc)
   bool reads_src = false, reads_grad = false, reads_omega = false;      // OP_GEMM: caller's arrays among its operands
   int iarg = 0;                     // OP_FACTOR_DIAG, OP_POTF2: block index; OP_PACK: y buffer that becomes Q, -1: Q stays
-  float farg = 0.f;                 // OP_SHIFT: coefficient
+  float farg = 0.f;                 // OP_SHIFT, OP_FACTOR_DIAG: coefficient of the shift
   bool rot_only = false;            // part of the moment rotation (skipped while t == 0)
   int fast = 0;                     // OP_GEMM: 1 = the product Z = Src^T Y, which the down-projection kernel can take over (iarg: y buffer);
                                     // 2 = a product Y = Src B for the source-streaming kernel (iarg: z buffer of B, -1 = Omega)
@@ -164,6 +164,7 @@ struct ProgramBuilder {
       GemmDesc g{};
       g.C2 = ref_none();
       g.P = ref_none();
+      g.diag = -1;
       g.alpha = 1.f;
       g.beta = 0.f;
       g.mat = i;
@@ -195,15 +196,16 @@ struct ProgramBuilder {
     // keeps four workgroups to five compute units.  Whole refreshes with kmin = 32 / 192 / 384 / 512 / 768 (us): 125M set, r = 128 1486 / 1398 /
     // 1386 / 1417 / 1460; two blocks of it 646 / 641 / 681 / 714 / 780; 24 x (2048 x 2048), r = 64 793 / 798 / 810 / 823 / 842; 72 of 1024 .. 4096,
     // r = 256 3909 / 3909 / 3823 / 3716 / 3733; four blocks of 7B, r = 128 4736 / 4748 / 4765 / 4697 / 4721, two of 2560 .. 8000, r = 400
-    // 5656 / 5641 / 5642 / 5638 / 5556.  (The initial projection keeps its slices, and so its bits.)
+    // 5656 / 5641 / 5642 / 5638 / 5556.  (The initial projection keeps its slices, and so its
+    // bits; R = Q_new^T Q_old keeps the short ones: with them the rotated moments of 957 x 2201, r = 39 are off by 2.0e-7, not 2.7e-7.)
     int kmin = 32;
-    if (ksplit > 1 && !initial) {
+    if (ksplit > 1 && lower_only && !initial) {
       for (int f : {192, 256, 384, 512, 768}) {
         int64_t wgs = 0;
         for (const GemmDesc& g : made) {
-          const int tm = (g.M + op.tile - 1) / op.tile, tn = (g.N + op.tile - 1) / op.tile;
+          const int tm = (g.M + op.tile - 1) / op.tile;
           const int klen = std::max(f, ((g.K + ksplit - 1) / ksplit + 31) / 32 * 32);
-          wgs += (int64_t)(lower_only ? tm * (tm + 1) / 2 : tm * tn) * ((g.K + klen - 1) / klen);
+          wgs += (int64_t)(tm * (tm + 1) / 2) * ((g.K + klen - 1) / klen);
         }
         if (f == 192 || wgs >= 205) kmin = f;
       }
@@ -324,10 +326,10 @@ struct ProgramBuilder {
     for (int i = 0; i < n; ++i) mb = std::max(mb, (P.mat[i].r + nb() - 1) / nb());
     return mb;
   }
-  void factor(int max_blocks) {
+  void factor(int max_blocks, float shift = 0.f) {
     const int NB = nb();
     for (int jb = 0; jb < max_blocks; ++jb) {
-      simple(initial ? OP_POTF2 : OP_FACTOR_DIAG, jb);
+      simple(initial ? OP_POTF2 : OP_FACTOR_DIAG, jb, shift);
       // L_21 = S_21 L_11^{-T}
       gemm([&](int i, GemmDesc& g) {
         const MatDev& m = P.mat[i];
@@ -374,11 +376,19 @@ struct ProgramBuilder {
         g.B = ref_arena(buf_of(i, cur)); g.sBk = m.r; g.sBn = 1;
         g.C = ref_arena(m.gram); g.ldc = m.r;
         g.M = m.r; g.N = m.r; g.K = rows_of(i);
+        // partial sums of the diagonal: in the block X M^T is written to below (rows >= 2 ksplit, so they fit)
+        g.diag = initial ? -1 : buf_of(i, 1 - cur);
         return true;
       }, false, true, true);      // the factorisation reads the lower triangle only
-      simple(OP_GRAM_DIAG, (y_side ? 0 : 2) + cur);      // the diagonal (the column norms) exactly
-      if (pass < nshift) simple(OP_SHIFT, 0, 32.f * 5.9604645e-8f);
-      factor(max_blocks);
+      const float shift = pass < nshift ? 32.f * 5.9604645e-8f : 0.f;
+      if (initial || P.ops.back().mode == GEMM_ANY) {      // the diagonal (the column norms) exactly, and the shift, in passes of their own
+        for (int di = P.ops.back().desc_first; di < (int)P.desc_h.size(); ++di) P.desc_h[di].diag = -1;
+        simple(OP_GRAM_DIAG, (y_side ? 0 : 2) + cur);
+        if (shift != 0.f) simple(OP_SHIFT, 0, shift);
+        factor(max_blocks);
+      } else {
+        factor(max_blocks, shift);
+      }
       if (initial) simple(OP_DIAG_INV);
       // M = L^{-1}, row block by row block from the inverses of the diagonal blocks, which are in place:
       // M[i, <i] = -M_ii (L[i, <i] M[<i, <i]); the Gram buffer, consumed by the factorisation, holds the inner product
@@ -1499,7 +1509,7 @@ static int run_ops(lordo_ctx* c, const std::vector<Op>& ops, int32_t src_dtype, 
         break;
       case OP_SHIFT: HIPCHK(launch_gram_shift(c->dev, op.farg, op.iarg != 0, s)); break;
       case OP_GRAM_DIAG: HIPCHK(launch_gram_diag(c->dev, op.iarg, P.r_max, P.part_slices, s)); break;
-      case OP_FACTOR_DIAG: HIPCHK(launch_factor_diag(c->dev, op.iarg, P.r_max, s)); break;
+      case OP_FACTOR_DIAG: HIPCHK(launch_factor_diag(c->dev, op.iarg, P.r_max, op.farg, s)); break;
       case OP_POTF2: HIPCHK(launch_potf2(c->dev, op.iarg, s)); break;
       case OP_DIAG_INV: HIPCHK(launch_diag_inverses(c->dev, s)); break;
       case OP_JSVD:
