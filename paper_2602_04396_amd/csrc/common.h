@@ -254,15 +254,15 @@ hipError_t launch_y_from_ext(const DevCtx& d, hipStream_t s);
 hipError_t launch_pack_y(const DevCtx& d, int ybuf, hipStream_t s);
 hipError_t launch_pack_block(const DevCtx& d, int zbuf, uint16_t* p_hi, uint16_t* p_lo, hipStream_t s);
 hipError_t launch_src_times_block(const DevCtx& d, const ProjTile* tiles, int ntiles, const uint16_t* b_hi, const uint16_t* b_lo,
-                                  hipStream_t s);
+                                  hipStream_t s, float* glow = nullptr, float scale = 1.f);
 hipError_t launch_glow_to_z(const DevCtx& d, const float* glow, int zbuf, const AdamArgs& a, hipStream_t s);
 // state exchange with plain row-major buffers (one matrix)
 hipError_t launch_lr_to_plain(const DevCtx& d, int mat, const float* lr_arr, const uint16_t* n_hi, const uint16_t* n_lo,
                               float* dst, int nsplit, int64_t stride, hipStream_t s);
 hipError_t launch_plain_to_lr(const DevCtx& d, int mat, float* lr_arr, const float* src, hipStream_t s);
 hipError_t launch_lr_exchange(const DevCtx& d, float* lr_arr, bool to_plain, hipStream_t s);
-// right-projected matrices only: slice 0 of the blocked array g <- scale * (plain rows x r block in zw[0])
-hipError_t launch_tr_exchange(const DevCtx& d, float* glow, float scale, bool all, hipStream_t s);
+// slice 0 of the blocked array g <- plain rows x r block in zw[0], of the right-projected matrices or of all
+hipError_t launch_tr_exchange(const DevCtx& d, float* glow, bool all, hipStream_t s);
 // Gaussian block of every matrix from the counter-based generator: which = 0 into y[0] (p x r), 1 into zw[3] (q x r)
 hipError_t launch_gauss_block(const DevCtx& d, int which, uint64_t seed, uint32_t draw, hipStream_t s);
 

@@ -1809,10 +1809,9 @@ hipError_t launch_lr_exchange(const DevCtx& d, float* lr_arr, bool to_plain, hip
   return hipGetLastError();
 }
 
-// Right-projected matrices (m.tr): their down-projection leaves g^T as the plain q x r block zw[0] (q = rows of the caller's
-// matrix); the Adam kernel reads slice 0 of the blocked array g.  `scale` is the caller's gradient scale where the product
-// was formed from the raw gradient.
-__global__ __launch_bounds__(256) void k_tr_exchange(DevCtx d, float* glow, float scale, int all) {
+// Down-projections that ran in the grouped GEMM (fp32 gradients; right-projected matrices the streaming kernel does not take) leave g^T,
+// scaled, as the plain q x r block zw[0] (right projection: q = rows of the caller's matrix); the Adam kernel reads slice 0 of the blocked array g.
+__global__ __launch_bounds__(256) void k_tr_exchange(DevCtx d, float* glow, int all) {
   const int mat = blockIdx.y;
   const MatDev& m = d.mats[mat];
   if (!m.tr && !all) return;      // all: the product of every matrix was formed as a plain block (fp32 gradients)
@@ -1824,7 +1823,7 @@ __global__ __launch_bounds__(256) void k_tr_exchange(DevCtx d, float* glow, floa
   for (int64_t o = (int64_t)blockIdx.x * 256 + threadIdx.x; o < total; o += (int64_t)gridDim.x * 256) {
     const int64_t jb = o / per_jb, rem = o % per_jb;
     const int64_t j = jb * 32 + ((rem >> 3) & 31), i = (rem >> 8) * 8 + (rem & 7);      // column j of the low-rank state, rank index i
-    glow[m.lr_off + o] = (j < m.q && i < m.r) ? scale * plain[j * m.r + i] : 0.f;
+    glow[m.lr_off + o] = (j < m.q && i < m.r) ? plain[j * m.r + i] : 0.f;
   }
 }
 // ---------------------------------------------------------------------------------------
@@ -1876,8 +1875,8 @@ hipError_t launch_gauss_block(const DevCtx& d, int which, uint64_t seed, uint32_
   return hipGetLastError();
 }
 
-hipError_t launch_tr_exchange(const DevCtx& d, float* glow, float scale, bool all, hipStream_t s) {
-  hipLaunchKernelGGL(k_tr_exchange, dim3(64, d.n), dim3(256), 0, s, d, glow, scale, all ? 1 : 0);
+hipError_t launch_tr_exchange(const DevCtx& d, float* glow, bool all, hipStream_t s) {
+  hipLaunchKernelGGL(k_tr_exchange, dim3(64, d.n), dim3(256), 0, s, d, glow, all ? 1 : 0);
   return hipGetLastError();
 }
 

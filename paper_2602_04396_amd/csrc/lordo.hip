@@ -874,8 +874,7 @@ void build_plan(const lordo_shape* shapes, int n, const lordo_hparams& hp, Plan&
     // Shadow records: the caller's matrix W (rows x cols) as a left-projected problem.
     //   up-projection  W -= eta N^T Q^T: its A planes (row of W, rank) are the planes of N (column of the low-rank
     //     state = row of W, rank), its B planes (column of W, rank) the up-projection planes of Q (row of Q = column of W);
-    //   streaming product  g^T = G Q: its B planes (rank, column of W) are the down-projection planes of Q (rank, row of Q),
-    //     its result goes to zw[0] as the plain rows x r block.
+    //   streaming product  g^T = G Q: its B planes (rank, column of W) are the down-projection planes of Q (rank, row of Q).
     // The kernels add lr_off (in 2-byte elements) to the plane base pointers they are given: with the arena base as hi
     // pointer and arena + gap as lo pointer, lr_off = (offset of the hi plane) / 2 selects the planes of Q.
     P.mat_up = P.mat;
@@ -893,7 +892,7 @@ void build_plan(const lordo_shape* shapes, int n, const lordo_hparams& hp, Plan&
       up.lr_off = m.qa_hi / 2;
       up.qt_hi = m.lr_off;          // (unused by the up-projection otherwise) the matrix's place in the flat low-rank arrays: row scales of the full-rank QHM term
       stb.lr_off = m.qt_hi / 2;
-      stb.y[0] = m.zw[0];
+      stb.qa_hi = m.lr_off;         // (unused by that kernel otherwise) where its result goes in the flat array g
       P.mat_up[i] = up;
       P.mat_stb[i] = stb;
       if (hp.error_feedback) {
@@ -1356,7 +1355,7 @@ int lordo_local_step(lordo_ctx* c, void* const* W, const void* const* G, double 
   if (!P.down_h.empty())
     HIPCHK(launch_proj_down(c->dev, c->at<ProjTile>(P.down_tiles), (int)P.down_h.size(), P.down_pipe, g_vec, g_tr, P.g_once, c->at<float>(P.glow),
                             P.lr_total, (float)proj_scale, ef ? (e_bf16 ? 3 : 1) : 0, &fuse, s));
-  if (P.any_tr || generic) {    // g^T = (s G) Q into the plain block zw[0], then into the blocked array the Adam kernel reads
+  if (P.any_tr || generic) {    // g^T = (s G) Q: into the blocked array at once by the streaming kernel, by way of the plain block zw[0] by the grouped GEMM
     bool stream = P.tr_stream_shapes && !ef && !generic;
     if (ef) {                   // A = s G + E is formed in the residual buffer first (unless a refresh of the local variant has done it)
       if (!folded)
@@ -1372,12 +1371,12 @@ int lordo_local_step(lordo_ctx* c, void* const* W, const void* const* G, double 
       DevCtx dv = c->dev;
       dv.mats = c->at<MatDev>(P.mats_stb);
       dv.slot[EXT_SRC] = dv.slot[EXT_G];
-      HIPCHK(launch_src_times_block(dv, c->at<ProjTile>(P.ytile_tr), (int)P.ytile_tr_h.size(), planes_hi, planes_lo, s));
+      HIPCHK(launch_src_times_block(dv, c->at<ProjTile>(P.ytile_tr), (int)P.ytile_tr_h.size(), planes_hi, planes_lo, s, c->at<float>(P.glow), (float)grad_scale));
     } else if (!ef) {
       for (const Op& op : P.tr_down_ops)
         HIPCHK(run_gemm(c, op, 0, s, (float)grad_scale));
     }
-    HIPCHK(launch_tr_exchange(c->dev, c->at<float>(P.glow), stream ? (float)grad_scale : 1.f, generic, s));
+    if (!stream) HIPCHK(launch_tr_exchange(c->dev, c->at<float>(P.glow), generic, s));
   }
   c->prof.end(LORDO_K_DOWN, s);
   c->prof.begin(LORDO_K_ADAM, s);

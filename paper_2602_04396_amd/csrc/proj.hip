@@ -1556,9 +1556,13 @@ __device__ __forceinline__ void store_y_tile(const DevCtx& d, const MatDev& m, c
 // every iteration.  The epilogue is the row-order store of the up-projection kernel (per-wave LDS tile,
 // 16-byte stores along the rows of Y).
 // Needs q % 32 == 0, r % 4 == 0 and a 16-byte aligned source; rows past p are read from row p-1 and not stored.
+// glow != nullptr: g^T = scale * G Q of a right-projected matrix (its shadow record), whose accumulators are already in the blocked
+// layout of the low-rank state: four consecutive ranks of a column per lane, stored there at once, zeros in the padding.  By way of the plain
+// block and a launch that turned it, 125M set on the short side, r = 128: step 321 -> 303 us.
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_src_times_block(DevCtx d, const ProjTile* __restrict__ tiles,
-                                                         const uint16_t* __restrict__ b_hi, const uint16_t* __restrict__ b_lo) {
+                                                         const uint16_t* __restrict__ b_hi, const uint16_t* __restrict__ b_lo,
+                                                         float* __restrict__ glow, float scale) {
   const ProjTile t = tiles[blockIdx.x];
   if (t.mat < 0 || mat_skipped(d, t.mat)) return;
   const MatDev m = d.mats[t.mat];
@@ -1638,16 +1642,36 @@ __global__ __launch_bounds__(256) void k_src_times_block(DevCtx d, const ProjTil
   WAIT_VM_BARRIER(0);             // the repeated loads of the last chunk have landed and all waves are done reading
                                   // fragments: reuse the memory for staging
 
+  if (glow != nullptr) {          // (uniform) the gradient of a right-projected matrix: rows are columns of its low-rank state
+    const int64_t rgroups = m.rp / 8;
+    GAS float* out = TO_GLOBAL(float, glow) + m.qa_hi;     // (the shadow record keeps the matrix's place in the flat arrays there)
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const int rb = t.n0 / 32 + 2 * wn + a, nb = t.m0 / 32 + 2 * wm + b;
+        if (rb >= rblocks || nb >= m.pp / 32) continue;
+        const bool pad = 32 * nb + (lane & 31) >= p;
+#pragma unroll
+        for (int vq = 0; vq < 4; ++vq) {
+          f32x4 x;
+          x.x = scale * acc[a][b][4 * vq]; x.y = scale * acc[a][b][4 * vq + 1]; x.z = scale * acc[a][b][4 * vq + 2]; x.w = scale * acc[a][b][4 * vq + 3];
+          if (pad) x = f32x4{0.f, 0.f, 0.f, 0.f};
+          *reinterpret_cast<GAS f32x4*>(out + ((nb * rgroups + 4 * rb + vq) * 32 + (lane & 31)) * 8 + 4 * (lane >> 5)) = x;
+        }
+      }
+    return;
+  }
   store_y_tile(d, m, t, acc, reinterpret_cast<float*>(frag), wave, lane, wm, wn);
 }
 
 hipError_t launch_src_times_block(const DevCtx& d, const ProjTile* tiles, int ntiles, const uint16_t* b_hi, const uint16_t* b_lo,
-                                  hipStream_t s) {
+                                  hipStream_t s, float* glow, float scale) {
   if (ntiles <= 0) return hipSuccess;
   constexpr int LDS_BYTES = 3 * 24 * 1024;
   static LdsRaised raised;
   if (hipError_t e = raise_lds(reinterpret_cast<const void*>(k_src_times_block), LDS_BYTES, raised); e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_src_times_block, dim3(ntiles), dim3(256), LDS_BYTES, s, d, tiles, b_hi, b_lo);
+  hipLaunchKernelGGL(k_src_times_block, dim3(ntiles), dim3(256), LDS_BYTES, s, d, tiles, b_hi, b_lo, glow, scale);
   return hipGetLastError();
 }
 
