@@ -75,20 +75,20 @@ struct GemmDesc {
   int32_t M, N, K, mat;
   int64_t sAm, sAk, sBk, sBn;
   int32_t ldc, a_bf16, b_bf16;        // a_bf16: 0 fp32, 1 bf16, 2 = element type given at launch (refresh source)
-  int32_t pad0;
+  int32_t tri;            // tri = 1: B(k, n) = 0 for k > n (transposed lower-triangular factor): the contraction of a column tile ends at its last column
   int64_t diag;           // Gram matrix X^T X: its diagonal is summed in double on the side; ksplit x M partial sums at this offset (-1: not so)
   float alpha, beta;
   // split-K (ksplit > 1): slice s covers k in [s*klen, (s+1)*klen) and writes its raw M x N sum to
   // P + s*M*N; a reduction kernel then adds the slices in order and applies alpha, beta, C2
   int32_t ksplit, klen;
   OpRef P;
-  int32_t tri, pad_;      // tri = 1: B(k, n) = 0 for k > n (transposed lower-triangular factor): the contraction of a column tile ends at its last column
 };
 
 // How the operands of every problem of a launch can be read along their unit-stride direction:
 //   ALIGNED  whole 16-byte vectors (8-byte ones of a bf16 source): split into bf16 terms (see gemm32.hip);
 //   RAGGED   rows, ends or pointers at any element, at least four elements long: split into bf16 terms too;
-//   ANY      neither: such problems run on the fp32 matrix cores element by element, the aligned ones of the launch as in ALIGNED
+//   ANY      neither, or ragged ones whose sums keep the bits of the fp32 matrix cores (initial projection, steps with fp32 gradients):
+//            such problems run there, the aligned ones of the launch as in ALIGNED
 enum GemmMode : int32_t { GEMM_ALIGNED = 0, GEMM_RAGGED = 1, GEMM_ANY = 2 };
 
 struct GemmTile { int32_t desc; int16_t tm, tn; int16_t ks, pad; };

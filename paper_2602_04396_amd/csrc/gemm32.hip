@@ -27,14 +27,14 @@ __device__ __forceinline__ const char* resolve(const DevCtx& d, const OpRef& r, 
 
 // One operand of a workgroup tile: X(i, k), i < LIM (the M or N side), k < kend, at base + i*s_i + k*s_k.
 // The tile is TMN x TK; a thread fetches NV vectors of four elements along the unit-stride direction
-// (scalar accesses at ragged edges and for unaligned operands) and later writes them to LDS as
+// (scalar accesses where there are fewer than four) and later writes them to LDS as
 // S[k][i], the order the matrix-core operands are read in.
 template <int TMN, int NV>
 struct Operand {
   const char* base;
   int64_t s_i, s_k;
   int is_bf16, lim, kend, i0;
-  bool kfast, vec_ok;
+  bool kfast, vec_ok, four_ok;      // four_ok: unit stride over four elements at least, so that a vector can be read at any alignment
 
   __device__ __forceinline__ void setup(const char* b, int64_t si, int64_t sk, int bf, int lim_, int kend_, int i0_, int kbeg) {
     base = b; s_i = si; s_k = sk; is_bf16 = bf; lim = lim_; kend = kend_; i0 = i0_;
@@ -44,6 +44,7 @@ struct Operand {
     const uintptr_t align = is_bf16 ? 7 : 15;
     // whole vectors only: every vector then lies entirely inside or entirely outside the operand
     vec_ok = s_fast == 1 && (s_slow & 3) == 0 && (n_fast & 3) == 0 && (reinterpret_cast<uintptr_t>(b) & align) == 0 && (kbeg & 3) == 0;
+    four_ok = s_fast == 1 && n_fast >= 4;
   }
   __device__ __forceinline__ void coords(int v, int& ii, int& kk) const {
     if (kfast) { kk = (v % (TK / 4)) * 4; ii = v / (TK / 4); }
@@ -52,7 +53,8 @@ struct Operand {
   // Branch-free: an element outside the operand is read from element 0 (always valid) and replaced
   // by zero when the tile is written to LDS.  fetch_raw only issues the loads and leaves the loaded
   // bits untouched, so nothing waits for them until stash() runs one K step later.
-  template <bool BF16>
+  // V4: in vectors at the alignment of an element, those that would run over the end read further back (as OperandBF does)
+  template <bool BF16, bool V4>
   __device__ __forceinline__ void fetch_raw(u32x4 (&raw)[NV], int k0, int tid) const {
     const int64_t e_step = kfast ? s_k : s_i;                        // from one element of a vector to the next
     const int d_i = kfast ? 0 : 1, d_k = kfast ? 1 : 0;
@@ -61,6 +63,19 @@ struct Operand {
       int ii, kk;
       coords(tid + n * 256, ii, kk);
       const int gi = i0 + ii, gk = k0 + kk;
+      if constexpr (V4) {
+        const int li = kfast ? lim - 1 : lim - 4, lk = kfast ? kend - 4 : kend - 1;
+        const int64_t at = (int64_t)(gi < li ? gi : li) * s_i + (int64_t)(gk < lk ? gk : lk) * s_k;
+        typedef u32x2 half_t __attribute__((aligned(2)));
+        typedef u32x4 full_t __attribute__((aligned(4)));
+        if constexpr (BF16) {
+          const u32x2 w = *(const GAS half_t*)((const GAS char*)base + at * 2);
+          raw[n].x = w.x; raw[n].y = w.y;
+        } else {
+          raw[n] = *(const GAS full_t*)((const GAS char*)base + at * 4);
+        }
+        continue;
+      }
       const int64_t idx = (int64_t)gi * s_i + (int64_t)gk * s_k;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -72,7 +87,7 @@ struct Operand {
     }
   }
   // Converts the raw bits of the tile starting at k0, zeroes what lies outside the operand and writes S[k][i].
-  template <bool BF16>
+  template <bool BF16, bool V4>
   __device__ __forceinline__ void stash(const u32x4 (&raw)[NV], float (*S)[TMN + 4], int k0, int tid) const {
     const int d_i = kfast ? 0 : 1, d_k = kfast ? 1 : 0;
 #pragma unroll
@@ -81,8 +96,20 @@ struct Operand {
       coords(tid + n * 256, ii, kk);
       const int gi = i0 + ii, gk = k0 + kk;
       f32x4 r;
+      if constexpr (V4) {
+        const int over = kfast ? gk + 4 - kend : gi + 4 - lim;       // elements past the end, of a vector that starts inside
+        u32x4 x = raw[n];
+        if constexpr (BF16) x = u32x4{x.x << 16, x.x & 0xffff0000u, x.y << 16, x.y & 0xffff0000u};
+        if (over > 0 && over < 4) {
+          if (over & 1) x = u32x4{x.y, x.z, x.w, 0u};
+          if (over & 2) x = u32x4{x.z, x.w, 0u, 0u};
+        }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) r[e] = __uint_as_float(BF16 ? raw[n][e] << 16 : raw[n][e]);
+        for (int e = 0; e < 4; ++e) r[e] = __uint_as_float(x[e]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = __uint_as_float(BF16 ? raw[n][e] << 16 : raw[n][e]);
+      }
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         if (!(gi + e * d_i < lim && gk + e * d_k < kend)) r[e] = 0.f;
@@ -97,20 +124,20 @@ struct Operand {
 };
 
 // K loop of one workgroup tile on the fp32 matrix cores, specialised on the element type of A.
-template <int WB, bool A_BF16, int TM, int NV>
+template <int WB, bool A_BF16, bool V4, int TM, int NV>
 __device__ __forceinline__ void gemm_loop(f32x16 (&acc)[WB][WB], const Operand<TM, NV>& opA, const Operand<TM, NV>& opB,
                                           float (*As)[TM + 4], float (*Bs)[TM + 4], int kbeg, int K, int tid, int lane, int wm, int wn) {
   u32x4 ra[NV], rb[NV];
-  opA.template fetch_raw<A_BF16>(ra, kbeg, tid);
-  opB.template fetch_raw<false>(rb, kbeg, tid);
+  opA.template fetch_raw<A_BF16, V4>(ra, kbeg, tid);
+  opB.template fetch_raw<false, V4>(rb, kbeg, tid);
   for (int k0 = kbeg; k0 < K; k0 += TK) {
     __syncthreads();                           // previous tile fully consumed
-    opA.template stash<A_BF16>(ra, As, k0, tid);
-    opB.template stash<false>(rb, Bs, k0, tid);
+    opA.template stash<A_BF16, V4>(ra, As, k0, tid);
+    opB.template stash<false, V4>(rb, Bs, k0, tid);
     __syncthreads();
     if (k0 + TK < K) {
-      opA.template fetch_raw<A_BF16>(ra, k0 + TK, tid);
-      opB.template fetch_raw<false>(rb, k0 + TK, tid);
+      opA.template fetch_raw<A_BF16, V4>(ra, k0 + TK, tid);
+      opB.template fetch_raw<false, V4>(rb, k0 + TK, tid);
     }
     asm volatile("" ::: "memory");             // keep the loads above the arithmetic: they must be in flight during it
 #pragma unroll
@@ -432,7 +459,7 @@ __device__ __forceinline__ void gemm_loops_bf(f32x16 (&acc)[WB][WB], const GemmD
 // MODE (GemmMode; known on the host for a whole launch): how the operands of all its problems can be read.  One kernel that chose per tile
 // held six loops in the registers of the largest.  A_BF16 matters in the first two modes, src_is_bf16 in the third.
 template <int WB, int MODE, bool A_BF16>
-__global__ __launch_bounds__(256, MODE == GEMM_RAGGED ? 2 : 1) void k_gemm32(DevCtx d, const GemmDesc* __restrict__ descs,
+__global__ __launch_bounds__(256, MODE == GEMM_RAGGED ? 2 : MODE == GEMM_ANY && WB == 1 ? 4 : 1) void k_gemm32(DevCtx d, const GemmDesc* __restrict__ descs,
                                                 const GemmTile* __restrict__ tiles, int src_is_bf16, float alpha_mul, int sub_m, int sub_n) {
   constexpr int TM = 64 * WB, TN = 64 * WB;
   constexpr int PITCH = TM + 4;
@@ -486,10 +513,12 @@ __global__ __launch_bounds__(256, MODE == GEMM_RAGGED ? 2 : 1) void k_gemm32(Dev
     } else if (vec) {
       if (a_bf16) gemm_loops_bf<WB, false, true>(acc, g, baseA, baseB, planes, m0, n0, kbeg, K, tid, lane, wm, wn, false, d.arena, t.ks);
       else gemm_loops_bf<WB, false, false>(acc, g, baseA, baseB, planes, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab, d.arena, t.ks);
-    } else if (a_bf16) {
-      gemm_loop<WB, true>(acc, opA, opB, As, Bs, kbeg, K, tid, lane, wm, wn);
+    } else if (opA.four_ok && opB.four_ok) {
+      if (a_bf16) gemm_loop<WB, true, true>(acc, opA, opB, As, Bs, kbeg, K, tid, lane, wm, wn);
+      else gemm_loop<WB, false, true>(acc, opA, opB, As, Bs, kbeg, K, tid, lane, wm, wn);
     } else {
-      gemm_loop<WB, false>(acc, opA, opB, As, Bs, kbeg, K, tid, lane, wm, wn);
+      if (a_bf16) gemm_loop<WB, true, false>(acc, opA, opB, As, Bs, kbeg, K, tid, lane, wm, wn);
+      else gemm_loop<WB, false, false>(acc, opA, opB, As, Bs, kbeg, K, tid, lane, wm, wn);
     }
   }
 

@@ -172,9 +172,10 @@ struct ProgramBuilder {
       if (!make(i, g)) continue;
       if (g.M <= 0 || g.N <= 0 || g.K <= 0) continue;
       // every product of the program runs on the bf16 matrix cores with operands split into three terms (as exact as fp32);
-      // operands off the 16-byte grid too, but not in the initial projection, whose bits stay those of the fp32 matrix cores there
+      // operands off the 16-byte grid too, but not in the initial projection and in the steps with fp32 gradients, whose bits stay
+      // those of the fp32 matrix cores there (the sign of a first step's update turns on the last bit of a cancelled g)
       int mode = std::max(operand_mode(g.A, g.sAm, g.sAk, g.M, g.K, g.a_bf16 != 0), operand_mode(g.B, g.sBn, g.sBk, g.N, g.K, false));
-      if (initial && mode == GEMM_RAGGED) mode = GEMM_ANY;
+      if ((initial || exact_fp32) && mode == GEMM_RAGGED) mode = GEMM_ANY;
       op.mode = std::max(op.mode, mode);
       op.a_bf16 = g.a_bf16;
       if (g.B.ext == EXT_OMEGA) op.reads_omega = true;
@@ -319,6 +320,7 @@ struct ProgramBuilder {
   // Cholesky factor of the Gram matrix of every matrix, block column by block column (NB-wide: diagonal block by
   // k_factor_diag, two grouped GEMMs for the panel and the trailing update); the Gram buffer is consumed, the factor
   // goes to its own buffer, the inverses of the diagonal blocks to their places in that of the whole factor.
+  bool exact_fp32 = false;          // products of a step with fp32 gradients
   bool initial = false;             // the program of the initial projection: factored in blocks of 64 by the kernels that keep its bits
   int nb() const { return initial ? NB_INIT : NB; }
   int max_blocks_all() const {
@@ -540,6 +542,7 @@ struct ProgramBuilder {
     };
     std::vector<Op> keep;
     keep.swap(P.ops);
+    exact_fp32 = !g_bf16;
     gemm([&](int i, GemmDesc& g) {
       const MatDev& m = P.mat[i];
       if (!m.tr && !all_mats) return false;
@@ -562,6 +565,7 @@ struct ProgramBuilder {
       });
       P.tr_down_ef_ops.swap(P.ops);
     }
+    exact_fp32 = false;
     keep.swap(P.ops);
   }
 
