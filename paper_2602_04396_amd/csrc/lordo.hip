@@ -64,6 +64,8 @@ struct Plan {
   int64_t acc = -1;                 // up-link buffer: flat low-rank array, sum over the window of lr * N
   int64_t adam_first = 0;           // flat position from which the stand-alone Adam kernel runs (elements before it are fused)
   int nsplit = 1;                   // largest split-K factor of the down-projection
+  int nsplit_mul = 1;               // factor of all splits over those the order of the flat arrays goes by
+  bool fine_split = false;          // ... with slices below 256 rows
   std::vector<int> splits;          // split-K factor per matrix (1, 2, 4 or 8)
   int32_t grp_nsplit[4] = {1, 1, 1, 1};
   int64_t grp_start[4] = {0, INT64_MAX, INT64_MAX, INT64_MAX};
@@ -730,7 +732,7 @@ int validate(const lordo_shape* shapes, int32_t n, const lordo_hparams* hp) {
   return LORDO_OK;
 }
 
-void build_plan(const lordo_shape* shapes, int n, const lordo_hparams& hp, Plan& P) {
+void build_plan_as(const lordo_shape* shapes, int n, const lordo_hparams& hp, bool fine, Plan& P) {
   Alloc A;
   P.flag = A.take(256);
   P.step = A.take(256);
@@ -768,9 +770,9 @@ void build_plan(const lordo_shape* shapes, int n, const lordo_hparams& hp, Plan&
   // 140 -> 135, 125M set, r = 32 178 -> 174, 1 x (640 x 640), r = 12 21.3 -> 19.4.  (More K slices, for the third workgroup per compute unit
   // that the smaller tiles leave room for, gave 1 to 4 % less.)
   P.down_pipe = P.down_generic ? 0 : rp_max >= 256 ? 8 : rp_max > 64 ? 4 : rp_max > 32 ? 2 : 1;
-  P.rank_tile = P.down_pipe ? 32 * P.down_pipe : 128;
+  P.rank_tile = P.down_pipe ? 32 * P.down_pipe : rp_max >= 256 ? 256 : 128;
   P.g_once = rp_max <= P.rank_tile;
-  const int down_bn = P.down_pipe ? 256 : 128;
+  const int down_bn = 256;
   P.up_waves = 4;
 
   // Split-K of the down-projection.  With few output tiles (small models) the long contraction
@@ -782,12 +784,13 @@ void build_plan(const lordo_shape* shapes, int n, const lordo_hparams& hp, Plan&
     if (!P.mat[i].tr) tiles0 += (int64_t)((P.mat[i].qp + down_bn - 1) / down_bn) * ((P.mat[i].rp + P.rank_tile - 1) / P.rank_tile);
   P.splits.assign(n, 1);
   P.nsplit = 1;
-  if (tiles0 > 0 && tiles0 < 1536 && !P.down_generic) {
+  int64_t tiles = 0;                 // workgroups of the launch, if it is split
+  if (tiles0 > 0 && tiles0 < 1536 && hp.grad_dtype == LORDO_BF16) {
     // slices of about the shortest matrix's height; halved while the launch would still have fewer
     // than about 1.5 workgroups per compute unit (a single tall matrix, for instance)
     int chunk = std::max(256, pp_min);
     for (;;) {
-      int64_t tiles = 0;
+      tiles = 0;
       bool can_grow = false;
       P.nsplit = 1;
       for (int i = 0; i < n; ++i) {
@@ -804,6 +807,35 @@ void build_plan(const lordo_shape* shapes, int n, const lordo_hparams& hp, Plan&
       chunk = std::max(256, chunk / 2);
     }
   }
+  // The order of the matrices in the flat low-rank arrays, which lordo_sync_payload shows, goes by these factors; what follows changes
+  // the factors of all matrices alike.
+  const std::vector<int> order_by = P.splits;
+  auto rescale = [&](int mul) {
+    P.nsplit = 1;
+    for (int i = 0; i < n; ++i)
+      if (!P.mat[i].tr) P.nsplit = std::max(P.nsplit, P.splits[i] = std::min(8, order_by[i] * mul));
+  };
+  // `fine`: slices below 256 rows, down to about 128, where the launch leaves three compute units in four without work, or no matrix is
+  // split at all: 1 x (640 x 640), r = 12 19.5 -> 16.8 us a step, 12 x (384 x 384), r = 64 34 -> 19, 1 x (256 x 256), r = 16 29 -> 14 (with
+  // slices instead of the fused epilogue, which these few tiles have nothing to hide behind); elsewhere slices of 128 cost more than they
+  // give: one block of 125M, r = 128 41.7 -> 43.8.
+  if (P.down_generic) {
+    P.splits.assign(n, 1);
+    P.nsplit = 1;
+  } else if (fine && tiles > 0 && !P.any_tr) {       // (right-projected matrices have one slice, in the group of unsplit ones)
+    int mul = 1;
+    auto grows = [&] {
+      for (int i = 0; i < n; ++i)
+        if (!P.mat[i].tr && P.splits[i] < 8 && P.mat[i].pp / (2 * P.splits[i]) >= 128) return true;
+      return false;
+    };
+    while (mul < 8 && (tiles * mul < 64 || (tiles < 400 && P.nsplit == 1)) && grows()) {
+      mul *= 2;
+      rescale(mul);
+      P.nsplit_mul = mul;
+      P.fine_split = true;
+    }
+  }
   // flat low-rank layout: matrices ordered by split factor, so that the Adam kernel knows the
   // number of slices to sum from the flat position alone
   {
@@ -811,10 +843,10 @@ void build_plan(const lordo_shape* shapes, int n, const lordo_hparams& hp, Plan&
     for (int f = 1; f <= 8; f *= 2) {
       bool any = false;
       for (int i = 0; i < n; ++i) {
-        if (P.splits[i] != f) continue;
+        if (order_by[i] != f) continue;
         if (!any) {
           any = true;
-          P.grp_nsplit[g] = f;
+          P.grp_nsplit[g] = P.down_generic ? 1 : std::min(8, f * P.nsplit_mul);
           P.grp_start[g] = g == 0 ? 0 : lr;
         }
         P.mat[i].lr_off = lr;
@@ -1013,6 +1045,16 @@ void build_plan(const lordo_shape* shapes, int n, const lordo_hparams& hp, Plan&
   P.descs = A.take(sizeof(GemmDesc) * P.desc_h.size());
   P.gtiles = A.take(sizeof(GemmTile) * P.gtile_h.size());
   P.bytes = A.cur;
+}
+
+// Finer slices of the down-projection take a few per cent more workspace: a set that fits the static workspace (lordo_init_static) only
+// without them goes without.
+void build_plan(const lordo_shape* shapes, int n, const lordo_hparams& hp, Plan& P) {
+  build_plan_as(shapes, n, hp, true, P);
+  if (!P.fine_split || P.bytes <= (size_t)LORDO_STATIC_WORKSPACE_BYTES) return;
+  Plan coarse;
+  build_plan_as(shapes, n, hp, false, coarse);
+  if (coarse.bytes <= (size_t)LORDO_STATIC_WORKSPACE_BYTES) P = std::move(coarse);
 }
 
 }  // namespace
