@@ -52,7 +52,6 @@ struct Plan {
   size_t bytes = 0;
   int64_t lr_total = 0;             // elements of one flat low-rank array
   int64_t nchunks = 0;
-  int up_waves = 4;                 // waves per workgroup of the up-projection (4: 64 x 64 wave tiles, 8: 32 x 64)
   int r_max = 0;                    // largest rank of any matrix
   int64_t rank_sq_sum = 0;          // sum of r^2 over the matrices
   int64_t frob_part = -1;           // per-chunk partial sums of ||Src||_F^2 (Rayleigh-Ritz option)
@@ -773,7 +772,6 @@ void build_plan_as(const lordo_shape* shapes, int n, const lordo_hparams& hp, bo
   P.rank_tile = P.down_pipe ? 32 * P.down_pipe : rp_max >= 256 ? 256 : 128;
   P.g_once = rp_max <= P.rank_tile;
   const int down_bn = 256;
-  P.up_waves = 4;
 
   // Split-K of the down-projection.  With few output tiles (small models) the long contraction
   // over p is cut into slices of about the shortest matrix's height, so that every workgroup

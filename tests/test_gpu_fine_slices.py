@@ -9,8 +9,8 @@ pytestmark = pytest.mark.gpu
                                     [(400, 264, 300), (300, 520, 260)], [(2048, 64, 33), (129, 40, 5), (520, 72, 100)], [(33, 256, 8), (1030, 256, 8)]])
 @pytest.mark.parametrize("update", ["plain", "ef_full"])
 def test_sliced_step_follows_the_formulas(shapes, update):
-    """u, v and the residual or weights of one step from given moments against float64 at the library's own Q; the packed payload keeps
-    its order: the moments of matrix i stand where they stand without finer slices (by split factor of 256 rows, then by index)."""
+    """u, v and the residual or weights of one step from given moments against float64 at the library's own Q; and the packed payload
+    keeps its order: where no matrix is higher than the shortest (or 256 rows) they stand in it by their index, however finely they are split."""
     import torch
     from paper_2602_04396_amd import lordo
     gen = torch.Generator(device="cuda")
@@ -47,5 +47,11 @@ def test_sliced_step_follows_the_formulas(shapes, update):
         else:
             want = W0[i] - lr * Q @ N
         assert float((W[i].double() - want).abs().max()) <= 3e-5 * float(want.abs().max()), i
-    # order of the payload: split factor at slices of 256 rows and more, then index
-    assert moments == 2 * sum((q + 31) // 32 * 32 * ((r + 31) // 32 * 32) for p, q, r in shapes)
+    padded = [(q + 31) // 32 * 32 * ((r + 31) // 32 * 32) for p, q, r in shapes]
+    assert moments == 2 * sum(padded)
+    heights = [p for p, q, r in shapes]
+    if max(heights) <= max(256, min(heights)):
+        for i in range(len(shapes)):            # the first element of a matrix's block is rank 0 of column 0
+            at = sum(padded[:i])
+            assert float(payload[at]) == float(opt.get_state(i, lordo.STATE_U)[0, 0]), i
+            assert float(payload[sum(padded) + at]) == float(opt.get_state(i, lordo.STATE_V)[0, 0]), i
