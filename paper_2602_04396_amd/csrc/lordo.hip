@@ -83,7 +83,7 @@ struct Plan {
   std::vector<Op> init_ops;         // Q_0 from a caller-supplied block: copy, orthonormalise, pack
   std::vector<Op> gap_ops;          // estimate of sigma_{r+1} of a source (Rayleigh-Ritz option)
   bool any_tr = false;              // some matrix is projected on the right
-  bool down_generic = false;        // fp32 gradients, or a matrix of one column: the down-projection of EVERY matrix runs in the grouped GEMM (three-term operands)
+  bool down_generic = false;        // fp32 gradients: the down-projection of EVERY matrix runs in the grouped GEMM (three-term operands)
   std::vector<Op> tr_down_ops;      // their product g^T = G Q by the generic GEMM (fp32 gradients, shapes the streaming kernel does not take)
   // Right-projected matrices in the kernels of the left projection: the products of the step are those of the caller's
   // p x q matrix with the operand planes in exchanged roles (see build_plan), described by two shadow tables of MatDev.
@@ -759,10 +759,7 @@ void build_plan_as(const lordo_shape* shapes, int n, const lordo_hparams& hp, bo
   P.chunk_start_h[n] = chunks;
   P.nchunks = chunks;
   if (hp.rayleigh_ritz) { P.frob_part = A.take(sizeof(float) * (size_t)chunks); P.jflags = A.take(256); }
-  // (the pipelined kernel reads columns in pairs: a matrix of one column sends the set to the grouped GEMM, as fp32 gradients do)
   P.down_generic = hp.grad_dtype == LORDO_F32;
-  for (int i = 0; i < n; ++i)
-    if (!P.mat[i].tr && P.mat[i].q < 2) P.down_generic = true;
   // Rank blocks of 32 per down-projection tile, 256 columns wide: as many as the largest rank of the set has, up to 8.  At ranks up to 64
   // the four-block tile left half of its waves or more without work and fetched absent blocks of Q; measured as whole steps on
   // four / two blocks: 1 x (8192 x 28672), r = 64 486 -> 473 us, 125M set, r = 64 201 -> 197; on four / one: 1 x (8192 x 8192), r = 16
@@ -817,10 +814,7 @@ void build_plan_as(const lordo_shape* shapes, int n, const lordo_hparams& hp, bo
   // split at all: 1 x (640 x 640), r = 12 19.5 -> 16.8 us a step, 12 x (384 x 384), r = 64 34 -> 19, 1 x (256 x 256), r = 16 29 -> 14 (with
   // slices instead of the fused epilogue, which these few tiles have nothing to hide behind); elsewhere slices of 128 cost more than they
   // give: one block of 125M, r = 128 41.7 -> 43.8.
-  if (P.down_generic) {
-    P.splits.assign(n, 1);
-    P.nsplit = 1;
-  } else if (fine && tiles > 0 && !P.any_tr) {       // (right-projected matrices have one slice, in the group of unsplit ones)
+  if (fine && tiles > 0 && !P.any_tr) {       // (right-projected matrices have one slice, in the group of unsplit ones)
     int mul = 1;
     auto grows = [&] {
       for (int i = 0; i < n; ++i)
@@ -844,7 +838,7 @@ void build_plan_as(const lordo_shape* shapes, int n, const lordo_hparams& hp, bo
         if (order_by[i] != f) continue;
         if (!any) {
           any = true;
-          P.grp_nsplit[g] = P.down_generic ? 1 : std::min(8, f * P.nsplit_mul);
+          P.grp_nsplit[g] = std::min(8, f * P.nsplit_mul);
           P.grp_start[g] = g == 0 ? 0 : lr;
         }
         P.mat[i].lr_off = lr;

@@ -102,21 +102,22 @@ struct GStage {
 // Column handling of one lane, fixed for the whole kernel.  VEC: byte offset of its two columns inside a row (OOB if they
 // lie outside the matrix; q is even then).  Else rows start at any element: the pair is read at element alignment, and a lane whose
 // second column does not exist reads the pair one column further left, so that no access leaves the row; `shift` and `mask` put
-// its values in place when the stage goes to LDS.
+// its values in place when the stage goes to LDS.  A matrix of one column has no pairs: its elements are read one by one.
 struct GCol {
   uint32_t off0;
   uint32_t shift, mask;       // !VEC: of a packed bf16 pair
-  bool edge;                  // !VEC: this wave's columns reach past the last one (uniform)
+  bool edge, single;          // !VEC: this wave's columns reach past the last one; the matrix has one column (both uniform)
 };
 template <bool VEC>
 __device__ __forceinline__ GCol g_columns(int col, int wave_col0, int q, uint32_t es) {
   GCol gc;
   gc.off0 = col < q ? (uint32_t)col * es : OOB;
   gc.shift = 0u; gc.mask = 0xffffffffu;
-  gc.edge = false;
+  gc.edge = gc.single = false;
   if constexpr (!VEC) {
     gc.edge = wave_col0 + 128 > q;
-    if (col == q - 1) { gc.off0 -= es; gc.shift = 16u; gc.mask = 0xffffu; }
+    gc.single = q == 1;
+    if (col == q - 1) { gc.off0 -= gc.single ? 0u : es; gc.shift = gc.single ? 0u : 16u; gc.mask = 0xffffu; }
     if (col >= q) gc.mask = 0u;
   }
   return gc;
@@ -130,6 +131,13 @@ __device__ __forceinline__ GCol g_columns(int col, int wave_col0, int q, uint32_
 // stage before: the set above, 166 -> 113 us; 103 for 1024 and 2732 columns in aligned pairs.)
 template <bool GF32, int AUX, bool VEC>     // AUX: cache policy of the loads (STREAM where G is read once, 0 where rank tiles re-read it)
 __device__ __forceinline__ void load_gstage(GStage<GF32>& st, rsrc_t rs, const GAS char* base, uint32_t row_bytes, int krow, int rows, const GCol& gc) {
+  if constexpr (!VEC && !GF32) {
+    if (gc.single) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) st.x[i] = *(const GAS uint16_t*)(base + (uint32_t)(krow + i < rows ? krow + i : rows - 1) * row_bytes);
+      return;
+    }
+  }
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     if constexpr (!VEC && !GF32) {
@@ -297,7 +305,7 @@ __device__ __forceinline__ void store_colpart(const FusedAdam& f, const MatDev& 
 // column blocks) and rank block w % 4.  MB = 8 (ranks from 256 up): rank blocks w % 4 and w % 4 + 4; this halves the number of
 // passes over G and the LDS reads per MFMA (each G fragment feeds two rank blocks); its 96 KiB of
 // LDS admit one workgroup per compute unit.  MB = 2, 1 (ranks up to 64, 32): the waves go along the columns, two blocks each, or one.
-// VEC: q is even and every pair of columns 4-byte aligned; else pairs are read at the alignment of an element (q >= 2).
+// VEC: q is even and every pair of columns 4-byte aligned; else pairs are read at the alignment of an element.
 // GONCE: one rank tile per column block, G is read once (streaming loads).
 // A tile marked `fuse` holds the whole contraction (no split-K): its epilogue applies Adam to its
 // elements of the low-rank state instead of leaving that to a separate pass over g.

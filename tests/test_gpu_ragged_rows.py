@@ -146,3 +146,44 @@ def test_fp32_gradients_at_any_element(p, q, r, side, offset):
     g = Q.T @ (G[0].double().T if side else G[0].double())
     u = (1 - opt.hp.beta1) * g
     assert float((opt.get_state(0, lordo.STATE_U).double() - u).norm() / u.norm()) <= 2e-6       # fp32 products and sums over 300 terms
+
+
+# one element, one stage of rows and a bit, K slices, ranks of every tile of the down-projection
+@pytest.mark.parametrize("p, r", [(1, 1), (2, 2), (33, 20), (300, 130), (700, 40), (520, 300), (4096, 4)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_one_column_beside_a_wide_matrix(p, r, offset):
+    """A matrix of one column (a bias, a norm's scale) is read element by element and leaves the route of its neighbours alone: the
+    wide matrix has the bits it has beside a matrix of two columns, and the column follows the formulas."""
+    import torch
+    from paper_2602_04396_amd import lordo
+    got = []
+    for cols in (1, 2):
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(p + r)
+        wide = (max(p, 256), 515 if offset else 512, max(r, 4))
+        shapes = [wide, (p, cols, r)]
+        G = [_window(torch, wide[0], wide[1], torch.bfloat16, offset, gen)[1]]
+        W = [torch.randn(wide[0], wide[1], generator=gen, device="cuda")]
+        flat, w = _window(torch, p, cols, torch.float32, offset, gen)
+        G.append(_window(torch, p, cols, torch.bfloat16, offset, gen)[1])
+        before = flat.clone()
+        opt = lordo.Lordo(shapes, lordo.hparams(seed=7), W + [w], torch)
+        opt.init_projection()
+        opt.set_state(1, lordo.STATE_V, 1.0 + torch.rand(r, cols, generator=gen, device="cuda"))
+        v0 = opt.get_state(1, lordo.STATE_V).double()
+        opt.local_step(W + [w], G, 0.25)
+        opt.poll_status()
+        got.append((opt.get_state(0, lordo.STATE_U), opt.get_state(0, lordo.STATE_V), W[0]))
+        b1, b2, eps = opt.hp.beta1, opt.hp.beta2, opt.hp.eps
+        Q = opt.get_state(1, lordo.STATE_Q).double()
+        g = Q.T @ G[1].double()
+        u, v = (1 - b1) * g, b2 * v0 + (1 - b2) * g * g
+        # g: two-term planes of Q (2^-17) over fp32 sums
+        assert float((opt.get_state(1, lordo.STATE_U).double() - u).norm() / u.norm()) <= 2e-5
+        N = (u / (1 - b1)) / ((v / (1 - b2)).sqrt() + eps)
+        want = before[512 + offset:512 + offset + p * cols].view(p, cols).double() - 0.25 * Q @ N
+        assert float((w.double() - want).abs().max()) <= 3e-5 * float(want.abs().max())
+        flat[512 + offset:512 + offset + p * cols] = before[512 + offset:512 + offset + p * cols]
+        assert torch.equal(flat, before)
+    for one, two in zip(*got):
+        assert torch.equal(one, two)
