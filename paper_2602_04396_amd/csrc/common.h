@@ -143,10 +143,12 @@ struct UpArgs {
   int32_t w_bf16;         // the caller's W is bf16 storage (target W only; the plain update)
   StepDev* advance;       // last launch of a local step: its first workgroup moves the step count on and does nothing else (else null)
 };
-hipError_t launch_proj_up(const DevCtx& d, const ProjTile* tiles, int ntiles, bool vec, const uint16_t* b_hi,
+// How the rows of W can be accessed, over all matrices of a launch: as whole aligned quads of elements in every matrix, in none, or in some
+enum RowMode : int32_t { ROWS_WHOLE = 0, ROWS_RAGGED = 1, ROWS_MIXED = 2 };
+hipError_t launch_proj_up(const DevCtx& d, const ProjTile* tiles, int ntiles, RowMode rows, const uint16_t* b_hi,
                           const uint16_t* b_lo, const UpArgs& ua, hipStream_t s);
 // the same with 256 x 128 tiles (ranks from 256 up); `tiles` hold m0 in steps of 256
-hipError_t launch_proj_up_wide(const DevCtx& d, const ProjTile* tiles, int ntiles, bool vec, const uint16_t* b_hi, const uint16_t* b_lo,
+hipError_t launch_proj_up_wide(const DevCtx& d, const ProjTile* tiles, int ntiles, RowMode rows, const uint16_t* b_hi, const uint16_t* b_lo,
                                const UpArgs& ua, hipStream_t s);
 // gemm32.hip
 // alpha_mul scales every product of the launch (per-call coefficients); an entry of the table covers sub_m x sub_n tiles

@@ -1163,6 +1163,18 @@ struct lordo_ctx {
     dev.slot[table] = table * EXT_SLOTS + k;
     return LORDO_OK;
   }
+  // Rows of the left- (tr = 0) or right-projected (1) matrices of W in four-column accesses: the row length a multiple of four, the pointer of
+  // mask + 1 (a right-projected matrix: its p is the row length)
+  RowMode row_mode(void* const* W, uintptr_t mask, int tr) const {
+    int whole = 0, ragged = 0;
+    for (int i = 0; i < n; ++i) {
+      const MatDev& m = plan.mat[i];
+      if ((int)m.tr != tr) continue;
+      if (((tr ? m.p : m.q) & 3) == 0 && (reinterpret_cast<uintptr_t>(W[i]) & mask) == 0) ++whole;
+      else ++ragged;
+    }
+    return ragged == 0 ? ROWS_WHOLE : whole == 0 ? ROWS_RAGGED : ROWS_MIXED;
+  }
   // every pointer of the table in use is a multiple of mask + 1
   bool ext_aligned(int table, uintptr_t mask) const {
     for (const void* p : shadow[table][dev.slot[table] - table * EXT_SLOTS])
@@ -1364,13 +1376,10 @@ int lordo_local_step(lordo_ctx* c, void* const* W, const void* const* G, double 
     if (!P.mat[i].tr && ((P.mat[i].q & 1) != 0 || (reinterpret_cast<uintptr_t>(G[i]) & 3) != 0)) { g_vec = false; break; }
   const bool w_bf16 = c->hp.param_dtype == LORDO_BF16, e_bf16 = c->hp.err_dtype == LORDO_BF16;
   const uintptr_t w_mask = w_bf16 ? 7 : 15;     // four weights with one access: 16 bytes of fp32, 8 bytes of bf16
-  bool w_vec = true;            // four-column accesses to W need q % 4 == 0 and pointers aligned to them
-  for (int i = 0; i < c->n; ++i)
-    if (!P.mat[i].tr && ((P.mat[i].q & 3) != 0 || (reinterpret_cast<uintptr_t>(W[i]) & w_mask) != 0)) { w_vec = false; break; }
+  const RowMode w_rows = c->row_mode(W, w_mask, 0), w_rows_tr = c->row_mode(W, w_mask, 1);
+  const bool w_vec = w_rows == ROWS_WHOLE;
   if (qhm_full || ef) {         // the gradient-term epilogue reads four columns of G per lane
-    if (!w_vec) return LORDO_EINVAL;
-    for (int i = 0; i < c->n; ++i)
-      if (P.mat[i].tr && ((P.mat[i].p & 3) != 0 || (reinterpret_cast<uintptr_t>(W[i]) & w_mask) != 0)) return LORDO_EINVAL;
+    if (!w_vec || w_rows_tr != ROWS_WHOLE) return LORDO_EINVAL;
     for (int i = 0; i < c->n; ++i)
       if ((reinterpret_cast<uintptr_t>(G[i]) & (g_f32 ? 15 : 7)) != 0) return LORDO_EINVAL;
   }
@@ -1431,17 +1440,17 @@ int lordo_local_step(lordo_ctx* c, void* const* W, const void* const* G, double 
     ua.coef_acc = -1.f; ua.coef_g = (float)proj_scale; ua.target_err = 1; ua.colscale = 0; ua.colpart = nullptr;
     ua.w_bf16 = e_bf16 ? 1 : 0;         // element type of this launch's target: the residual
     if (!P.up_wide_h.empty() && w_vec && !g_f32)
-      HIPCHK(launch_proj_up_wide(c->dev, c->at<ProjTile>(P.up_wide_tiles), (int)P.up_wide_h.size(), w_vec, c->at<uint16_t>(P.g_hi),
+      HIPCHK(launch_proj_up_wide(c->dev, c->at<ProjTile>(P.up_wide_tiles), (int)P.up_wide_h.size(), w_rows, c->at<uint16_t>(P.g_hi),
                                  c->at<uint16_t>(P.g_lo), ua, s));
     else if (!P.up_h.empty())
-      HIPCHK(launch_proj_up(c->dev, c->at<ProjTile>(P.up_tiles), (int)P.up_h.size(), w_vec, c->at<uint16_t>(P.g_hi),
+      HIPCHK(launch_proj_up(c->dev, c->at<ProjTile>(P.up_tiles), (int)P.up_h.size(), w_rows, c->at<uint16_t>(P.g_hi),
                             c->at<uint16_t>(P.g_lo), ua, s));
     if (P.any_tr) {             // right-projected matrices: E already holds s G + E; E <- E - g^T Q^T on the shadow records (planes of g as A)
       UpArgs ue = ua;
       ue.coef_g = 0.f;
       DevCtx du = c->dev;
       du.mats = c->at<MatDev>(P.mats_up_ef);
-      HIPCHK(launch_proj_up(du, c->at<ProjTile>(P.up_tr_tiles), (int)P.up_tr_h.size(), true, reinterpret_cast<uint16_t*>(c->dev.arena),
+      HIPCHK(launch_proj_up(du, c->at<ProjTile>(P.up_tr_tiles), (int)P.up_tr_h.size(), ROWS_WHOLE, reinterpret_cast<uint16_t*>(c->dev.arena),
                             reinterpret_cast<uint16_t*>(c->dev.arena + P.tr_plane_gap), ue, s));
     }
   }
@@ -1457,21 +1466,18 @@ int lordo_local_step(lordo_ctx* c, void* const* W, const void* const* G, double 
   StepDev* const advance = c->at<StepDev>(P.step);             // t <- t + 1, with the last launch
   if (!P.any_tr) ua.advance = advance;
   if (!P.up_wide_h.empty() && !(qhm_full && g_f32))   // (the wide kernel's gradient-term epilogue reads bf16 gradients)
-    HIPCHK(launch_proj_up_wide(c->dev, c->at<ProjTile>(P.up_wide_tiles), (int)P.up_wide_h.size(), w_vec, c->at<uint16_t>(P.n_hi),
+    HIPCHK(launch_proj_up_wide(c->dev, c->at<ProjTile>(P.up_wide_tiles), (int)P.up_wide_h.size(), w_rows, c->at<uint16_t>(P.n_hi),
                                c->at<uint16_t>(P.n_lo), ua, s));
   else if (!P.up_h.empty())
-    HIPCHK(launch_proj_up(c->dev, c->at<ProjTile>(P.up_tiles), (int)P.up_h.size(), w_vec, c->at<uint16_t>(P.n_hi),
+    HIPCHK(launch_proj_up(c->dev, c->at<ProjTile>(P.up_tiles), (int)P.up_h.size(), w_rows, c->at<uint16_t>(P.n_hi),
                           c->at<uint16_t>(P.n_lo), ua, s));
   if (P.any_tr) {               // W <- W - eta N^T Q^T: the up-projection kernel on the shadow records (planes of N as A, of Q as B)
-    bool w_vec_tr = true;
-    for (int i = 0; i < c->n && w_vec_tr; ++i)
-      if (P.mat[i].tr && ((P.mat[i].p & 3) != 0 || (reinterpret_cast<uintptr_t>(W[i]) & w_mask) != 0)) w_vec_tr = false;
     DevCtx du = c->dev;
     du.mats = c->at<MatDev>(P.mats_up);
     UpArgs ut = ua;
     ut.advance = advance;
     if (qhm_full) ut.colscale = 2;      // the scale of the gradient term runs over the rows of W: the columns of the low-rank state
-    HIPCHK(launch_proj_up(du, c->at<ProjTile>(P.up_tr_tiles), (int)P.up_tr_h.size(), w_vec_tr, reinterpret_cast<uint16_t*>(c->dev.arena),
+    HIPCHK(launch_proj_up(du, c->at<ProjTile>(P.up_tr_tiles), (int)P.up_tr_h.size(), w_rows_tr, reinterpret_cast<uint16_t*>(c->dev.arena),
                           reinterpret_cast<uint16_t*>(c->dev.arena + P.tr_plane_gap), ut, s));
   }
   c->prof.end(LORDO_K_UP, s);
@@ -1788,19 +1794,18 @@ int lordo_outer_step_lowrank(lordo_ctx* c, void* const* W, const void* const* Av
     rc = c->set_ext(EXT_DIN, const_cast<void* const*>(reinterpret_cast<const void* const*>(AvgAcc)), s);
     if (rc != LORDO_OK) return rc;
   }
-  bool w_vec = true;            // rows of W of a multiple of 4 floats (a right-projected matrix: its p is the row length)
-  for (int i = 0; i < c->n; ++i)
-    if (((P.mat[i].tr ? P.mat[i].p : P.mat[i].q) & 3) != 0 || (reinterpret_cast<uintptr_t>(W[i]) & 15) != 0) { w_vec = false; break; }
+  const RowMode w_rows = c->row_mode(W, 15, 0), w_rows_tr = c->row_mode(W, 15, 1);
+  const bool w_vec = w_rows == ROWS_WHOLE && w_rows_tr == ROWS_WHOLE;
   // Delta = Q A through the up-projection kernel: the left-projected matrices, then the right-projected ones on their
   // shadow records (planes of A in the place of N as A operand, planes of Q as B operand)
   auto up_all = [&](const UpArgs& ua) -> hipError_t {
     hipError_t e = hipSuccess;
     if (!P.up_h.empty())
-      e = launch_proj_up(c->dev, c->at<ProjTile>(P.up_tiles), (int)P.up_h.size(), w_vec, c->at<uint16_t>(P.n_hi), c->at<uint16_t>(P.n_lo), ua, s);
+      e = launch_proj_up(c->dev, c->at<ProjTile>(P.up_tiles), (int)P.up_h.size(), w_rows, c->at<uint16_t>(P.n_hi), c->at<uint16_t>(P.n_lo), ua, s);
     if (e == hipSuccess && P.any_tr) {
       DevCtx du = c->dev;
       du.mats = c->at<MatDev>(P.mats_up);
-      e = launch_proj_up(du, c->at<ProjTile>(P.up_tr_tiles), (int)P.up_tr_h.size(), w_vec, reinterpret_cast<uint16_t*>(c->dev.arena),
+      e = launch_proj_up(du, c->at<ProjTile>(P.up_tr_tiles), (int)P.up_tr_h.size(), w_rows_tr, reinterpret_cast<uint16_t*>(c->dev.arena),
                          reinterpret_cast<uint16_t*>(c->dev.arena + P.tr_plane_gap), ua, s);
     }
     return e;

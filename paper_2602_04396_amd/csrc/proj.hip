@@ -886,7 +886,10 @@ template <> struct WAcc<true> {
 // Cacheable, not streaming: the rows' cache lines are shared with the wave and the tile beside, and a streaming line is fetched
 // again.  12 x (4 x 1023 x 1023, 1023 x 2731, 2731 x 1023), r = 100, fp32: 286 us with a kernel of 4-byte accesses, 268 with these
 // and streaming, 239 with streaming stores alone, 230 so (1.08 GB); 193 for 1024 and 2732 columns in whole vectors.
-template <bool WBF>
+// MIXED (ROWS_MIXED): a matrix whose rows are whole aligned quads (`whole`, uniform), beside one whose rows are not, is streamed as in a
+// set of its kind: step of the 125M set, r = 128, and twelve matrices of 768 x 2, 263 -> 236 us, and four of 768 x 771, 274 -> 250.
+// (Where no row is whole the tests alone cost 1 % of a step of the odd sizes above: those keep a kernel without them.)
+template <bool WBF, bool MIXED>
 struct Ragged {
   static constexpr uint32_t ES = WAcc<WBF>::ES;
   typedef typename WAcc<WBF>::raw_t raw_t;
@@ -895,14 +898,16 @@ struct Ragged {
   GAS char* base;
   uint32_t bytes, voff;      // size of the target; the lane's offset (OOB where its first column is outside)
   uint32_t ncol;             // edge: how many of the lane's four columns exist
-  bool edge;
+  bool edge, whole;
   __device__ __forceinline__ void setup(rsrc_t r_, const void* b, uint32_t n, uint32_t v, int lcol, int q, bool edge_) {
     r = r_; base = TO_GLOBAL(char, const_cast<void*>(b)); bytes = n; voff = v;
+    whole = MIXED && ((uint32_t)q & 3u) == 0u && ((uint32_t)reinterpret_cast<uintptr_t>(b) & (4u * ES - 1u)) == 0u;
     ncol = lcol + 4 <= q ? 4u : lcol < q ? (uint32_t)(q - lcol) : 0u;
     edge = edge_;
   }
   __device__ __forceinline__ uint32_t element(uint32_t i) const { return i < ncol ? voff + i * ES : OOB; }
   __device__ __forceinline__ raw_t load(uint32_t soff) const {
+    if (MIXED && whole) return WAcc<WBF>::load(r, voff, soff);
     if (edge) {
       uint32_t e[4];
 #pragma unroll
@@ -922,7 +927,9 @@ struct Ragged {
     }
   }
   __device__ __forceinline__ void store(f32x4 x, uint32_t soff) const {
-    if (edge) {
+    if (MIXED && whole) {
+      WAcc<WBF>::store(x, r, voff, soff);
+    } else if (edge) {
 #pragma unroll
       for (uint32_t i = 0; i < 4; ++i) {
         if constexpr (WBF) __builtin_amdgcn_raw_buffer_store_b16((short)pack_bf16_rne(x[i], 0.f), r, element(i), soff, 0);
@@ -964,12 +971,12 @@ struct Ragged {
 //   Delta = Q B stays in the accumulators, the tile that is read is the anchor, and the epilogue does
 //   b <- mu b + Delta;  x <- anchor - eta_s (Delta + mu b) (Nesterov), anchor - eta_s b (heavy ball) or anchor - eta_s Delta
 //   (no momentum);  W <- x, anchor <- x.
-template <int NW, int EPI, bool WBF, bool RAG = false>   // NW waves per workgroup: 4 (wave tile 64 x 64) or 8 (wave tile 32 x 64); EPI 0 plain, 1 gradient term, 2 outer step;
-                                       // WBF: the target (the caller's W, or the residual E) is stored in bf16; RAG: rows at any alignment (plain update)
+template <int NW, int EPI, bool WBF, RowMode ROWS = ROWS_WHOLE>   // NW waves per workgroup: 4 (wave tile 64 x 64) or 8 (wave tile 32 x 64); EPI 0 plain, 1 gradient term, 2 outer step;
+                                       // WBF: the target (the caller's W, or the residual E) is stored in bf16; ROWS: other than whole quads in the plain update only
 __global__ __launch_bounds__(64 * NW) void k_proj_up_dma(DevCtx d, const ProjTile* __restrict__ tiles,
                                                          const uint16_t* __restrict__ n_hi, const uint16_t* __restrict__ n_lo, UpArgs ua) {
   constexpr bool WITH_G = EPI == 1;
-  constexpr bool OUTER = EPI == 2;
+  constexpr bool OUTER = EPI == 2, RAG = ROWS != ROWS_WHOLE;
   static_assert(!WBF || EPI != 2, "bf16 targets: plain update and gradient-term epilogue");
   static_assert(!RAG || EPI == 0, "the other epilogues need rows of whole quads");
   typedef WAcc<WBF> WA;
@@ -1042,7 +1049,7 @@ __global__ __launch_bounds__(64 * NW) void k_proj_up_dma(DevCtx d, const ProjTil
   };
 
   const rsrc_t rg = WITH_G ? make_rsrc(ext_ptr(d, EXT_G, t.mat), (uint32_t)p * ((uint32_t)q * (ua.g_is_f32 ? 4u : 2u))) : rw;
-  Ragged<WBF> rag;
+  Ragged<WBF, ROWS == ROWS_MIXED> rag;
   if constexpr (RAG) rag.setup(rw, target, (uint32_t)p * row_bytes, voff, lcol, q, 32 * nb0 + 64 > q);
   if (advance_step(ua.advance)) return;
   issue_chunk(0, 0);
@@ -1252,9 +1259,10 @@ __global__ __launch_bounds__(64 * NW) void k_proj_up_dma(DevCtx d, const ProjTil
 // Nothing is requested past the last k-step (repeating it for an even count of loads cost 19 % of the operand traffic at r = 256):
 // with the same in the down-projection 1B set, r = 256 4.00 -> 3.96 ms a step, its full-rank QHM form in bf16 7.11 -> 7.00 ms.
 // ---------------------------------------------------------------------------------------
-template <bool WBF, bool WITH_G, bool RAG = false>     // WITH_G: gradient-term epilogue (bf16 G): the full-rank QHM update, or the residual E as target; RAG: rows of the target at any alignment (plain update)
+template <bool WBF, bool WITH_G, RowMode ROWS = ROWS_WHOLE>     // WITH_G: gradient-term epilogue (bf16 G): the full-rank QHM update, or the residual E as target; ROWS: other than whole quads in the plain update only
 __global__ __launch_bounds__(256) void k_proj_up_wide(DevCtx d, const ProjTile* __restrict__ tiles,
                                                       const uint16_t* __restrict__ n_hi, const uint16_t* __restrict__ n_lo, UpArgs ua) {
+  constexpr bool RAG = ROWS != ROWS_WHOLE;
   typedef WAcc<WBF> WA;
   constexpr uint32_t WES = WA::ES;
   const float lr = -ua.coef_acc;
@@ -1321,7 +1329,7 @@ __global__ __launch_bounds__(256) void k_proj_up_wide(DevCtx d, const ProjTile* 
 
   const rsrc_t rg = WITH_G ? make_rsrc(ext_ptr(d, EXT_G, t.mat), (uint32_t)p * ((uint32_t)q * 2u)) : rw;
   static_assert(!RAG || !WITH_G, "the gradient-term epilogue needs rows of whole quads");
-  Ragged<WBF> rag;
+  Ragged<WBF, ROWS == ROWS_MIXED> rag;
   if constexpr (RAG) rag.setup(rw, target, (uint32_t)p * row_bytes, voff, lcol, q, 32 * nb0 + 64 > q);
   if (advance_step(ua.advance)) return;
   issue_chunk(0, 0);
@@ -1490,21 +1498,23 @@ __global__ __launch_bounds__(256) void k_proj_up_wide(DevCtx d, const ProjTile* 
   }
 }
 
-hipError_t launch_proj_up_wide(const DevCtx& d, const ProjTile* tiles, int ntiles, bool vec, const uint16_t* b_hi, const uint16_t* b_lo,
+hipError_t launch_proj_up_wide(const DevCtx& d, const ProjTile* tiles, int ntiles, RowMode rows, const uint16_t* b_hi, const uint16_t* b_lo,
                                const UpArgs& ua, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
   constexpr int LDS_BYTES = 3 * 24 * 1024;
-  static LdsRaised raised[6];
-  const void* kernels[6] = {reinterpret_cast<const void*>(k_proj_up_wide<false, false>), reinterpret_cast<const void*>(k_proj_up_wide<true, false>),
+  static LdsRaised raised[8];
+  const void* kernels[8] = {reinterpret_cast<const void*>(k_proj_up_wide<false, false>), reinterpret_cast<const void*>(k_proj_up_wide<true, false>),
                             reinterpret_cast<const void*>(k_proj_up_wide<false, true>), reinterpret_cast<const void*>(k_proj_up_wide<true, true>),
-                            reinterpret_cast<const void*>(k_proj_up_wide<false, false, true>), reinterpret_cast<const void*>(k_proj_up_wide<true, false, true>)};
-  for (int k = 0; k < 6; ++k)
+                            reinterpret_cast<const void*>(k_proj_up_wide<false, false, ROWS_RAGGED>), reinterpret_cast<const void*>(k_proj_up_wide<true, false, ROWS_RAGGED>),
+                            reinterpret_cast<const void*>(k_proj_up_wide<false, false, ROWS_MIXED>), reinterpret_cast<const void*>(k_proj_up_wide<true, false, ROWS_MIXED>)};
+  for (int k = 0; k < 8; ++k)
     if (hipError_t e = raise_lds(kernels[k], LDS_BYTES, raised[k]); e != hipSuccess) return e;
   const bool with_g = ua.coef_g != 0.f || ua.target_err == 1;
-  if (with_g && (ua.g_is_f32 || !vec)) return hipErrorInvalidValue;      // the gradient-term epilogue here reads bf16 gradients, four columns at a time
+  if (with_g && (ua.g_is_f32 || rows != ROWS_WHOLE)) return hipErrorInvalidValue;      // the gradient-term epilogue here reads bf16 gradients, four columns at a time
   if (ua.target_err == 2 || ua.outer || ua.colscale == 2) return hipErrorInvalidValue;
 #define LORDO_WIDE(...) hipLaunchKernelGGL((k_proj_up_wide<__VA_ARGS__>), dim3(ntiles + (ua.advance ? 1 : 0)), dim3(256), LDS_BYTES, s, d, tiles, b_hi, b_lo, ua)
-  if (!vec) { if (ua.w_bf16) LORDO_WIDE(true, false, true); else LORDO_WIDE(false, false, true); }
+  if (rows == ROWS_MIXED) { if (ua.w_bf16) LORDO_WIDE(true, false, ROWS_MIXED); else LORDO_WIDE(false, false, ROWS_MIXED); }
+  else if (rows == ROWS_RAGGED) { if (ua.w_bf16) LORDO_WIDE(true, false, ROWS_RAGGED); else LORDO_WIDE(false, false, ROWS_RAGGED); }
   else if (ua.w_bf16) { if (with_g) LORDO_WIDE(true, true); else LORDO_WIDE(true, false); }
   else { if (with_g) LORDO_WIDE(false, true); else LORDO_WIDE(false, false); }
 #undef LORDO_WIDE
@@ -1683,25 +1693,28 @@ hipError_t launch_src_times_block(const DevCtx& d, const ProjTile* tiles, int nt
   return hipGetLastError();
 }
 
-hipError_t launch_proj_up(const DevCtx& d, const ProjTile* tiles, int ntiles, bool vec, const uint16_t* b_hi,
+hipError_t launch_proj_up(const DevCtx& d, const ProjTile* tiles, int ntiles, RowMode rows, const uint16_t* b_hi,
                           const uint16_t* b_lo, const UpArgs& ua, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
   dim3 grid(ntiles + (ua.advance ? 1 : 0)), block(256);
   const bool with_g = ua.coef_g != 0.f || ua.target_err == 1;
   const bool w_bf16 = ua.w_bf16 != 0 && ua.target_err != 2;     // element type of the target as the caller of this launch states it (the momentum is always fp32)
   if (ua.outer) {
-    if (!vec || w_bf16) return hipErrorInvalidValue;       // the outer-step epilogue exists for 16-byte row accesses of fp32 weights only
+    if (rows != ROWS_WHOLE || w_bf16) return hipErrorInvalidValue;       // the outer-step epilogue exists for 16-byte row accesses of fp32 weights only
     hipLaunchKernelGGL((k_proj_up_dma<4, 2, false>), grid, block, 0, s, d, tiles, b_hi, b_lo, ua);
   } else if (with_g) {
-    if (!vec) return hipErrorInvalidValue;                 // the gradient-term epilogue exists for four-column row accesses only
+    if (rows != ROWS_WHOLE) return hipErrorInvalidValue;                 // the gradient-term epilogue exists for four-column row accesses only
     if (w_bf16) hipLaunchKernelGGL((k_proj_up_dma<4, 1, true>), grid, block, 0, s, d, tiles, b_hi, b_lo, ua);
     else hipLaunchKernelGGL((k_proj_up_dma<4, 1, false>), grid, block, 0, s, d, tiles, b_hi, b_lo, ua);
-  } else if (vec) {
+  } else if (rows == ROWS_WHOLE) {
     if (w_bf16) hipLaunchKernelGGL((k_proj_up_dma<4, 0, true>), grid, block, 0, s, d, tiles, b_hi, b_lo, ua);
     else hipLaunchKernelGGL((k_proj_up_dma<4, 0, false>), grid, block, 0, s, d, tiles, b_hi, b_lo, ua);
+  } else if (rows == ROWS_RAGGED) {
+    if (w_bf16) hipLaunchKernelGGL((k_proj_up_dma<4, 0, true, ROWS_RAGGED>), grid, block, 0, s, d, tiles, b_hi, b_lo, ua);
+    else hipLaunchKernelGGL((k_proj_up_dma<4, 0, false, ROWS_RAGGED>), grid, block, 0, s, d, tiles, b_hi, b_lo, ua);
   } else {
-    if (w_bf16) hipLaunchKernelGGL((k_proj_up_dma<4, 0, true, true>), grid, block, 0, s, d, tiles, b_hi, b_lo, ua);
-    else hipLaunchKernelGGL((k_proj_up_dma<4, 0, false, true>), grid, block, 0, s, d, tiles, b_hi, b_lo, ua);
+    if (w_bf16) hipLaunchKernelGGL((k_proj_up_dma<4, 0, true, ROWS_MIXED>), grid, block, 0, s, d, tiles, b_hi, b_lo, ua);
+    else hipLaunchKernelGGL((k_proj_up_dma<4, 0, false, ROWS_MIXED>), grid, block, 0, s, d, tiles, b_hi, b_lo, ua);
   }
   return hipGetLastError();
 }

@@ -187,3 +187,38 @@ def test_one_column_beside_a_wide_matrix(p, r, offset):
         assert torch.equal(flat, before)
     for one, two in zip(*got):
         assert torch.equal(one, two)
+
+
+# plain update on 128-wide and on 256-wide tiles, last tiles of every size
+@pytest.mark.parametrize("r", [40, 128, 256])
+@pytest.mark.parametrize("store", ["f32", "bf16"])
+def test_whole_rows_beside_ragged_ones(r, store):
+    """Matrices of whole aligned quads beside others (streamed there): the same bits, and nothing outside, as with every array at an odd
+    element, where no row is whole."""
+    import torch
+    from paper_2602_04396_amd import lordo
+    wt = torch.bfloat16 if store == "bf16" else torch.float32
+    shapes = [(260, 512, r), (300, 259, r), (513, 68, r), (256, 4, r)]
+    results = []
+    for offset in (0, 1):
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(r)
+        bufs = [_window(torch, p, q, wt, offset, gen) for p, q, _ in shapes]
+        G = [torch.randn(p, q, generator=gen, device="cuda").bfloat16() for p, q, _ in shapes]
+        data = [torch.randn(p, q, generator=gen, device="cuda").to(wt) for p, q, _ in shapes]
+        for (_, view), x in zip(bufs, data):
+            view.copy_(x)
+        W = [view for _, view in bufs]
+        before = [flat.clone() for flat, _ in bufs]
+        opt = lordo.Lordo(shapes, lordo.hparams(seed=5, param_dtype=lordo.BF16 if store == "bf16" else lordo.F32), W, torch)
+        opt.init_projection()
+        for _ in range(2):
+            opt.local_step(W, G, 0.25)
+        opt.poll_status()
+        results.append([w.clone() for w in W])
+        for (flat, view), old, x in zip(bufs, before, data):
+            assert not torch.equal(view, x)
+            view.copy_(x)
+            assert torch.equal(flat, old)
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
