@@ -810,10 +810,14 @@ void build_plan_as(const lordo_shape* shapes, int n, const lordo_hparams& hp, bo
     for (int i = 0; i < n; ++i)
       if (!P.mat[i].tr) P.nsplit = std::max(P.nsplit, P.splits[i] = std::min(8, order_by[i] * mul));
   };
-  // `fine`: slices below 256 rows, down to about 128, where the launch leaves three compute units in four without work, or no matrix is
-  // split at all: 1 x (640 x 640), r = 12 19.5 -> 16.8 us a step, 12 x (384 x 384), r = 64 34 -> 19, 1 x (256 x 256), r = 16 29 -> 14 (with
-  // slices instead of the fused epilogue, which these few tiles have nothing to hide behind); elsewhere slices of 128 cost more than they
-  // give: one block of 125M, r = 128 41.7 -> 43.8.
+  // `fine`: slices below 256 rows, down to about 128, where the launch leaves three compute units in four without work, or half of them
+  // with no matrix split at all: 1 x (640 x 640), r = 12 19.5 -> 16.8 us a step, 12 x (384 x 384), r = 64 34 -> 19, 1 x (256 x 256), r = 16
+  // 29 -> 14 (with slices instead of the fused epilogue, which these few tiles have nothing to hide behind); elsewhere slices of 128 cost
+  // more than they give: one block of 125M, r = 128 41.7 -> 43.8.  Unsplit against split in two, one matrix of 256 .. 480 rows or
+  // many of 512 columns, T tiles: r = 64 .. 256 T = 64 0.74 .. 1.00 of the time, 96 0.83 .. 0.95, 128 0.92 .. 1.04, 160 1.01 .. 1.09, 192 1.04 .. 1.15,
+  // 256 1.08 .. 1.25, 384 1.07 .. 1.14 (past 128 two slices are more than one round of the 256 compute units, and g is written and read
+  // once more); r = 16, whose tiles are shorter, T = 64 0.92 .. 0.96, 80 0.96 .. 1.00, 96 0.98 .. 1.03, 128 0.99 .. 1.08.
+  const int half_idle = P.down_pipe == 1 ? 80 : 128;
   if (fine && tiles > 0 && !P.any_tr) {       // (right-projected matrices have one slice, in the group of unsplit ones)
     int mul = 1;
     auto grows = [&] {
@@ -821,7 +825,7 @@ void build_plan_as(const lordo_shape* shapes, int n, const lordo_hparams& hp, bo
         if (!P.mat[i].tr && P.splits[i] < 8 && P.mat[i].pp / (2 * P.splits[i]) >= 128) return true;
       return false;
     };
-    while (mul < 8 && (tiles * mul < 64 || (tiles < 400 && P.nsplit == 1)) && grows()) {
+    while (mul < 8 && (tiles * mul < 64 || (tiles <= half_idle && P.nsplit == 1)) && grows()) {
       mul *= 2;
       rescale(mul);
       P.nsplit_mul = mul;

@@ -76,6 +76,16 @@ def test_workspace_bytes_scales_and_validates(lib):
         assert e.value.code == lordo.EINVAL
 
 
+@pytest.mark.parametrize("shapes, slices", [([(256, 256 * 128, 64)], 2), ([(256, 256 * 128 + 1, 64)], 1), ([(480, 512, 200)] * 32, 2), ([(480, 512, 200)] * 33, 1),
+                                            ([(480, 512, 256)] * 64, 2), ([(480, 512, 256)] * 65, 1), ([(256, 256 * 80, 32)], 2), ([(256, 256 * 80 + 1, 32)], 1),
+                                            ([(224, 256, 64)], 1), ([(640, 640, 12)], 4)])
+def test_short_matrices_are_split_only_while_half_of_the_chip_is_idle(lib, shapes, slices):
+    """Slices of the down-projection's contraction, by the space for g: fp32 gradients are never split."""
+    g_slice = 4 * sum((q + 31) // 32 * 32 * ((r + 31) // 32 * 32) for p, q, r in shapes)
+    extra = lordo.workspace_bytes(shapes, lordo.hparams()) - lordo.workspace_bytes(shapes, lordo.hparams(grad_dtype=lordo.F32))
+    assert round(extra / g_slice) + 1 == slices
+
+
 def test_right_projection_validation(lib):
     hp = lordo.hparams()
     tall = lordo.workspace_bytes([(3072, 768, 128, 1)], hp)       # projection on the short side: Q 768 x 128, moments 128 x 3072

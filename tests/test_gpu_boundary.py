@@ -204,8 +204,12 @@ def test_recorded_local_step_counts_its_replays(torch, shape_set, update):
     residual launch and the gradient-term epilogue as well; the residual is compared too."""
     from paper_2602_04396_amd import lordo
     shapes = {"split_k": [(256, 384, 64), (130, 260, 128), (520, 392, 96)],
-              "fused_128_rank_tiles": [(256, 520, 192), (250, 388, 120)],          # no matrix taller than 256 rows: no split-K,
-              "fused_256_rank_tiles": [(256, 520, 256), (250, 388, 250)]}[shape_set]  # the moment update is in the epilogue
+              "fused_128_rank_tiles": [(224, 520, 192), (220, 388, 120)],          # too short for two slices of 128 rows; tiles for more than
+              "fused_256_rank_tiles": [(256, 33032, 256), (250, 388, 250)]}[shape_set]  # half of the compute units: the moment update is in the epilogue
+    # (fp32 gradients are never split: slices of g would be what a bf16 context needs beyond theirs)
+    g_slice = 4 * sum((q + 31) // 32 * 32 * ((r + 31) // 32 * 32) for p, q, r in shapes)
+    split = lordo.workspace_bytes(shapes, lordo.hparams()) - lordo.workspace_bytes(shapes, lordo.hparams(grad_dtype=lordo.F32)) > g_slice // 2
+    assert split == (shape_set == "split_k")
     n = len(shapes)
     W0 = _weights(shapes, 73)
     Q0 = [synth.orthonormal(np.random.default_rng(synth.seed_for(73, 700 + i)), p, r).astype(np.float32) for i, (p, q, r) in enumerate(shapes)]
