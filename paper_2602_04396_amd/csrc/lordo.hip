@@ -35,6 +35,7 @@ struct Op {
   int desc_first = 0, ndescs = 0;   // OP_GEMM: descriptors of this launch
   bool split = false;               // OP_GEMM: split-K launch, followed by the slice reduction
   int mode = GEMM_ALIGNED;          // OP_GEMM: the most general access any of its operands needs, caller's pointers taken as aligned
+  bool exact = false;               // OP_GEMM: operands off the grid of 16-byte vectors keep the bits of the fp32 matrix cores
   int a_bf16 = 0;                   // OP_GEMM: element type of A (as in GemmDesc)
   bool reads_src = false, reads_grad = false, reads_omega = false;      // OP_GEMM: caller's arrays among its operands
   int iarg = 0;                     // OP_FACTOR_DIAG, OP_POTF2: block index; OP_PACK: y buffer that becomes Q, -1: Q stays
@@ -176,7 +177,8 @@ struct ProgramBuilder {
       // operands off the 16-byte grid too, but not in the initial projection and in the steps with fp32 gradients, whose bits stay
       // those of the fp32 matrix cores there (the sign of a first step's update turns on the last bit of a cancelled g)
       int mode = std::max(operand_mode(g.A, g.sAm, g.sAk, g.M, g.K, g.a_bf16 != 0), operand_mode(g.B, g.sBn, g.sBk, g.N, g.K, false));
-      if ((initial || exact_fp32) && mode == GEMM_RAGGED) mode = GEMM_ANY;
+      op.exact = initial || exact_fp32;
+      if (op.exact && mode == GEMM_RAGGED) mode = GEMM_ANY;
       op.mode = std::max(op.mode, mode);
       op.a_bf16 = g.a_bf16;
       if (g.B.ext == EXT_OMEGA) op.reads_omega = true;
@@ -1331,7 +1333,7 @@ int lordo_init_static(lordo_ctx** out, const lordo_shape* shapes, int32_t n, con
 }
 
 // One launch of the grouped GEMM.  Pointers of the caller that are off the grid of 16-byte vectors (8-byte ones of bf16) send it to the
-// kernel for operands at any alignment.
+// kernel for operands at any alignment, or to the one that keeps such matrices, and no others, on the fp32 matrix cores.
 static hipError_t run_gemm(lordo_ctx* c, const Op& op, int32_t src_dtype, hipStream_t s, float alpha_mul = 1.f) {
   Plan& P = c->plan;
   const bool a_bf16 = op.a_bf16 == 2 ? src_dtype == LORDO_BF16 : op.a_bf16 != 0;
@@ -1339,7 +1341,7 @@ static hipError_t run_gemm(lordo_ctx* c, const Op& op, int32_t src_dtype, hipStr
   const uintptr_t mask = a_bf16 ? 7 : 15;
   if (mode == GEMM_ALIGNED && ((op.reads_src && !c->ext_aligned(EXT_SRC, mask)) || (op.reads_grad && !c->ext_aligned(EXT_G, mask)) ||
                                (op.reads_omega && !c->ext_aligned(EXT_OMEGA, 15))))
-    mode = GEMM_RAGGED;
+    mode = op.exact ? GEMM_ANY : GEMM_RAGGED;
   return launch_gemm32(c->dev, c->at<GemmDesc>(P.descs), c->at<GemmTile>(P.gtiles) + op.tile_first, op.ntiles, op.tile, mode, a_bf16, s, alpha_mul,
                        op.planes ? 128 / op.tile : 1, op.planes ? op.planes / op.tile : 1);
 }

@@ -222,3 +222,33 @@ def test_whole_rows_beside_ragged_ones(r, store):
             assert torch.equal(flat, old)
     for a, b in zip(*results):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("shape", [(128, 256, 64), (384, 132, 16), (260, 512, 130)])
+@pytest.mark.parametrize("side", [0, 1])
+@pytest.mark.parametrize("offset", [0, 1, 2])
+def test_fp32_gradients_of_an_aligned_shape_have_the_same_bits_beside_a_ragged_one(shape, side, offset):
+    """fp32 gradients whose rows are whole vectors, at any element: their step runs on the fp32 matrix cores where the pointer is off the
+    grid of 16-byte vectors, as that of ragged shapes does, whatever else the set holds; g against float64 at the library's own Q."""
+    import torch
+    from paper_2602_04396_amd import lordo
+    p, q, r = shape
+    got = []
+    for rest in ([], [(33, 65, 7, side)]):
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(p + q)
+        shapes = [(p, q, r, side)] + rest
+        G = [_window(torch, s[0], s[1], torch.float32, offset, gen)[1] for s in shapes]
+        W = [torch.zeros(s[0], s[1], device="cuda") for s in shapes]
+        opt = lordo.Lordo(shapes, lordo.hparams(seed=2, grad_dtype=lordo.F32), W, torch)
+        k = q if side else p
+        block, _ = torch.linalg.qr(torch.randn(k, r, generator=torch.Generator().manual_seed(1), dtype=torch.float64))
+        opt.set_state(0, lordo.STATE_Q, block.float().cuda().contiguous())
+        opt.local_step(W, G, 0.1)
+        opt.poll_status()
+        u = opt.get_state(0, lordo.STATE_U)
+        Q = opt.get_state(0, lordo.STATE_Q).double()
+        want = (1 - opt.hp.beta1) * (Q.T @ (G[0].double().T if side else G[0].double()))
+        assert float((u.double() - want).norm() / want.norm()) <= 2e-6       # fp32 products and sums over 500 terms
+        got.append(u)
+    assert torch.equal(got[0], got[1])
