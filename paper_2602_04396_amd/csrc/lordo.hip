@@ -818,8 +818,9 @@ void build_plan_as(const lordo_shape* shapes, int n, const lordo_hparams& hp, bo
   // more than they give: one block of 125M, r = 128 41.7 -> 43.8.  Unsplit against split in two, one matrix of 256 .. 480 rows or
   // many of 512 columns, T tiles: r = 64 .. 256 T = 64 0.74 .. 1.00 of the time, 96 0.83 .. 0.95, 128 0.92 .. 1.04, 160 1.01 .. 1.09, 192 1.04 .. 1.15,
   // 256 1.08 .. 1.25, 384 1.07 .. 1.14 (past 128 two slices are more than one round of the 256 compute units, and g is written and read
-  // once more); r = 16, whose tiles are shorter, T = 64 0.92 .. 0.96, 80 0.96 .. 1.00, 96 0.98 .. 1.03, 128 0.99 .. 1.08.
-  const int half_idle = P.down_pipe == 1 ? 80 : 128;
+  // once more); r = 16, whose tiles are shorter, T = 64 0.92 .. 0.96, 80 0.96 .. 1.00, 96 0.98 .. 1.03, 128 0.99 .. 1.08, and 0.90 at 84 tiles of
+  // 303 rows at odd elements.
+  const int half_idle = P.down_pipe == 1 ? 96 : 128;
   if (fine && tiles > 0 && !P.any_tr) {       // (right-projected matrices have one slice, in the group of unsplit ones)
     int mul = 1;
     auto grows = [&] {

@@ -77,7 +77,7 @@ def test_workspace_bytes_scales_and_validates(lib):
 
 
 @pytest.mark.parametrize("shapes, slices", [([(256, 256 * 128, 64)], 2), ([(256, 256 * 128 + 1, 64)], 1), ([(480, 512, 200)] * 32, 2), ([(480, 512, 200)] * 33, 1),
-                                            ([(480, 512, 256)] * 64, 2), ([(480, 512, 256)] * 65, 1), ([(256, 256 * 80, 32)], 2), ([(256, 256 * 80 + 1, 32)], 1),
+                                            ([(480, 512, 256)] * 64, 2), ([(480, 512, 256)] * 65, 1), ([(256, 256 * 96, 32)], 2), ([(256, 256 * 96 + 1, 32)], 1),
                                             ([(224, 256, 64)], 1), ([(640, 640, 12)], 4)])
 def test_short_matrices_are_split_only_while_half_of_the_chip_is_idle(lib, shapes, slices):
     """Slices of the down-projection's contraction, by the space for g: fp32 gradients are never split."""
