@@ -1472,7 +1472,12 @@ int lordo_local_step(lordo_ctx* c, void* const* W, const void* const* G, double 
   }
   StepDev* const advance = c->at<StepDev>(P.step);             // t <- t + 1, with the last launch
   if (!P.any_tr) ua.advance = advance;
-  if (!P.up_wide_h.empty() && !(qhm_full && g_f32))   // (the wide kernel's gradient-term epilogue reads bf16 gradients)
+  // Rows at any element: 256 x 128 tiles from three rounds of them on (two per compute unit).  Whole steps on 128 x 128 / 256 x 128 tiles,
+  // by the number of the latter (us): 2047 rows, r = 256, fp32 64 39.0 / 48.8, 128 42.7 / 52.2, 256 55.5 / 60.1, 512 87.3 / 91.1; r = 512 128 52.9 / 64.5,
+  // 512 142 / 146; r = 320, bf16 128 46.1 / 58.0, 512 107 / 113; 1024 of r = 256 138 / 142; 1800 of r = 300 359 / 360; 2048 of r = 1024 722 / 690; 6200 of
+  // r = 512 1320 / 1256; 9400 of r = 256 1250 / 1220.
+  const bool wide_rows = w_vec || P.up_wide_h.size() >= 1536;
+  if (!P.up_wide_h.empty() && wide_rows && !(qhm_full && g_f32))   // (the wide kernel's gradient-term epilogue reads bf16 gradients)
     HIPCHK(launch_proj_up_wide(c->dev, c->at<ProjTile>(P.up_wide_tiles), (int)P.up_wide_h.size(), w_rows, c->at<uint16_t>(P.n_hi),
                                c->at<uint16_t>(P.n_lo), ua, s));
   else if (!P.up_h.empty())

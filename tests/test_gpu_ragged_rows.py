@@ -252,3 +252,34 @@ def test_fp32_gradients_of_an_aligned_shape_have_the_same_bits_beside_a_ragged_o
         assert float((u.double() - want).norm() / want.norm()) <= 2e-6       # fp32 products and sums over 500 terms
         got.append(u)
     assert torch.equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("store", ["f32", "bf16"])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_many_wide_tiles_on_rows_at_any_element(store, offset):
+    """Enough tiles of 256 x 128 for the kernel that takes ranks from 256 up on them: one ragged matrix beside one of whole quads (offset 0), and
+    both ragged.  Weights against float64 at the library's own Q and N, nothing written outside."""
+    import torch
+    from paper_2602_04396_amd import lordo
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(offset)
+    wt = torch.bfloat16 if store == "bf16" else torch.float32
+    shapes = [(3050, 16385, 256), (520, 512, 300)]
+    bufs = [_window(torch, p, q, wt, offset, gen) for p, q, _ in shapes]
+    G = [torch.randn(p, q, generator=gen, device="cuda").bfloat16() for p, q, _ in shapes]
+    W = [view for _, view in bufs]
+    before = [flat.clone() for flat, _ in bufs]
+    opt = lordo.Lordo(shapes, lordo.hparams(seed=5, param_dtype=lordo.BF16 if store == "bf16" else lordo.F32), W, torch)
+    opt.init_projection()
+    lr = 0.25
+    opt.local_step(W, G, lr)
+    opt.poll_status()
+    for i, (p, q, r) in enumerate(shapes):
+        start = 512 + offset
+        old = before[i][start:start + p * q].view(p, q).double()
+        want = old - lr * opt.get_state(i, lordo.STATE_Q).double() @ opt.get_state(i, lordo.STATE_NUPD).double()
+        ulp = 0.0 if store == "f32" else 2.0 ** -8                # rounded once; ahead of it the planes' 2^-17 of Q N, and fp32 sums
+        assert float(((W[i].double() - want).abs() - ulp * want.abs()).max()) <= 3e-5 * float(want.abs().max()), i
+        got = bufs[i][0].clone()
+        got[start:start + p * q] = before[i][start:start + p * q]
+        assert torch.equal(got, before[i]), i
