@@ -86,33 +86,35 @@ struct Operand {
       }
     }
   }
-  // Converts the raw bits of the tile starting at k0, zeroes what lies outside the operand and writes S[k][i].
+  // Writes the tile starting at k0 to S[k][i], zeros past the end of k.  Rows past the last one stay what was read in their place: they
+  // end in elements of C that are not stored.
   template <bool BF16, bool V4>
   __device__ __forceinline__ void stash(const u32x4 (&raw)[NV], float (*S)[TMN + 4], int k0, int tid) const {
-    const int d_i = kfast ? 0 : 1, d_k = kfast ? 1 : 0;
+    if (k0 + TK > kend || (V4 && !kfast && i0 + TMN > lim)) put<BF16, V4, true>(raw, S, k0, tid);      // (uniform)
+    else put<BF16, V4, false>(raw, S, k0, tid);
+  }
+  template <bool BF16, bool V4, bool EDGE>
+  __device__ __forceinline__ void put(const u32x4 (&raw)[NV], float (*S)[TMN + 4], int k0, int tid) const {
+    const int d_k = kfast ? 1 : 0;
 #pragma unroll
     for (int n = 0; n < NV; ++n) {
       int ii, kk;
       coords(tid + n * 256, ii, kk);
       const int gi = i0 + ii, gk = k0 + kk;
-      f32x4 r;
+      u32x4 x = raw[n];
       if constexpr (V4) {
-        const int over = kfast ? gk + 4 - kend : gi + 4 - lim;       // elements past the end, of a vector that starts inside
-        u32x4 x = raw[n];
         if constexpr (BF16) x = u32x4{x.x << 16, x.x & 0xffff0000u, x.y << 16, x.y & 0xffff0000u};
-        if (over > 0 && over < 4) {
-          if (over & 1) x = u32x4{x.y, x.z, x.w, 0u};
-          if (over & 2) x = u32x4{x.z, x.w, 0u, 0u};
+        if constexpr (EDGE) {              // a vector that would run over the end was read further back
+          const int past = kfast ? gk + 4 - kend : gi + 4 - lim, over = past > 0 && past < 4 ? past : 0;
+          x = (over & 1) ? u32x4{x.y, x.z, x.w, 0u} : x;
+          x = (over & 2) ? u32x4{x.z, x.w, 0u, 0u} : x;
         }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) r[e] = __uint_as_float(x[e]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) r[e] = __uint_as_float(BF16 ? raw[n][e] << 16 : raw[n][e]);
+      } else if constexpr (BF16) {
+        x = u32x4{x.x << 16, x.y << 16, x.z << 16, x.w << 16};
       }
+      f32x4 r;
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (!(gi + e * d_i < lim && gk + e * d_k < kend)) r[e] = 0.f;
+      for (int e = 0; e < 4; ++e) r[e] = __uint_as_float(EDGE && gk + e * d_k >= kend ? 0u : x[e]);
       if (kfast) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) S[kk + e][ii] = r[e];
@@ -242,6 +244,8 @@ struct OperandBF {
       }
     }
   }
+  // Elements past the end of a vector that starts inside (at `at`, of `end`): so many it was read too far back
+  static __device__ __forceinline__ int past_end(int at, int end) { return at < end && at + 4 > end ? at + 4 - end : 0; }
   static __device__ __forceinline__ u32x4 shift_in(u32x4 x, int n) {
     if constexpr (BF16) {
       const uint64_t v = (((uint64_t)x.y << 32) | x.x) >> (16 * n);
@@ -278,15 +282,23 @@ struct OperandBF {
   }
   // P: the operand's planes (one for an exact bf16 operand, three for an fp32 one), `plane` elements apart
   __device__ __forceinline__ void stash(u32x4 (&raw)[NV], uint16_t* P, int plane, int k0, int tid) const {
-    if (i0 + TMN > lim || k0 + TK > kend) {           // (uniform) what lies outside becomes zero
+    // Rows past the last one stay what was read in their place: they end in elements of C that are not stored.  What lies past the end of
+    // k becomes zero.  (Uniform branches, selects inside them.  Zeros for the rows too, by lane branches in every K step of an edge tile:
+    // 48 x (5824 x 320 and 160 x 928), r = 136, fp32 gradients 850 us a step, 716 so.)
+    if constexpr (UA && !KF) {
+      if (i0 + TMN > lim) {
+#pragma unroll
+        for (int n = 0; n < NV; ++n) raw[n] = shift_in(raw[n], past_end(i0 + row(n, tid), lim));
+      }
+    }
+    if (k0 + TK > kend) {
 #pragma unroll
       for (int n = 0; n < NV; ++n) {
-        const int gi = i0 + row(n, tid), gk = k0 + kk0 + (KF ? 0 : n);
-        if constexpr (UA) {                           // how many elements of a vector that starts inside lie past the end
-          const int over = KF ? gk + 4 - kend : gi + 4 - lim;
-          if (over > 0 && over < 4) raw[n] = shift_in(raw[n], over);
-        }
-        if (!(gi < lim && gk < kend)) raw[n] = u32x4{0u, 0u, 0u, 0u};
+        const int k = k0 + kk0 + (KF ? 0 : n);
+        if constexpr (UA && KF) raw[n] = shift_in(raw[n], past_end(k, kend));
+        const uint32_t keep = k < kend ? 0xffffffffu : 0u;
+#pragma unroll
+        for (int e = 0; e < (BF16 ? 2 : 4); ++e) raw[n][e] &= keep;
       }
     }
     if constexpr (KF) {

@@ -283,3 +283,35 @@ def test_many_wide_tiles_on_rows_at_any_element(store, offset):
         got = bufs[i][0].clone()
         got[start:start + p * q] = before[i][start:start + p * q]
         assert torch.equal(got, before[i]), i
+
+
+@pytest.mark.parametrize("p, q, r", [(128, 200, 64), (130, 67, 33), (40, 3, 3), (96, 260, 5)])
+@pytest.mark.parametrize("side", [0, 1])
+@pytest.mark.parametrize("grad", ["f32", "bf16"])
+def test_an_infinity_stays_in_its_column(p, q, r, side, grad):
+    """Rows that an edge tile of the grouped GEMM reads in the place of absent ones end in no element that is stored: infinities in the
+    first and last element of G reach the moments of their own columns (rows, projected on the right) alone."""
+    import torch
+    from paper_2602_04396_amd import lordo
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(p + q)
+    if side:
+        p, q = q, p
+    G = torch.randn(p, q, generator=gen, device="cuda")
+    G[0, 0] = G[-1, -1] = float("inf")
+    G = G if grad == "f32" else G.bfloat16()
+    W = [torch.zeros(p, q, device="cuda")]
+    r = min(r, q if side else p)
+    opt = lordo.Lordo([(p, q, r, side)], lordo.hparams(seed=2, grad_dtype=lordo.F32 if grad == "f32" else lordo.BF16), W, torch)
+    opt.init_projection()
+    opt.local_step(W, [G], 0.1)
+    u = opt.get_state(0, lordo.STATE_U)
+    bad = ~torch.isfinite(u).all(0)
+    assert bad[0] and bad[-1] and int(bad.sum()) == 2
+    payload, moments = opt.sync_payload()
+    cols = p if side else q
+    v = payload[:moments // 2].view((cols + 31) // 32, -1, 32, 8)          # column block, rank group, column, rank
+    assert bool((v[-1, :, cols % 32:] == 0).all()) or cols % 32 == 0
+    if r % 32:
+        pad = v.permute(1, 3, 0, 2).reshape(-1, v.shape[0] * 32)[r:]          # ranks past the last one
+        assert bool(torch.isfinite(pad[:, 1:cols - 1]).all())
