@@ -195,15 +195,18 @@ struct ProgramBuilder {
     int ksplit = 1;
     if (small_out && tiles > 0 && tiles < 1024)
       ksplit = (int)std::min<int64_t>(P.part_slices, (1024 + tiles - 1) / tiles);     // never more slices than allocated
-    // Slices of an even length, but not shorter than kmin: a workgroup writes its whole tile for every slice (64 KiB, as much as 64 rows
-    // of 128 columns on either side are to read) and k_gemm_reduce reads it again.  192 rows always, longer ones up to 768 while the launch
-    // keeps four workgroups to five compute units.  Whole refreshes with kmin = 32 / 192 / 384 / 512 / 768 (us): 125M set, r = 128 1486 / 1398 /
-    // 1386 / 1417 / 1460; two blocks of it 646 / 641 / 681 / 714 / 780; 24 x (2048 x 2048), r = 64 793 / 798 / 810 / 823 / 842; 72 of 1024 .. 4096,
-    // r = 256 3909 / 3909 / 3823 / 3716 / 3733; four blocks of 7B, r = 128 4736 / 4748 / 4765 / 4697 / 4721, two of 2560 .. 8000, r = 400
-    // 5656 / 5641 / 5642 / 5638 / 5556.  (The initial projection keeps its slices, and so its
-    // bits; R = Q_new^T Q_old keeps the short ones: with them the rotated moments of 957 x 2201, r = 39 are off by 2.0e-7, not 2.7e-7.)
+    // Slices of an even length, and those of Gram matrices not shorter than kmin: a workgroup writes its whole tile for every slice (64 KiB,
+    // as much as 64 rows of 128 columns on either side are to read) and k_gemm_reduce reads it again.  192 rows always, longer ones up to 768
+    // while the launch keeps four workgroups to five compute units.  Whole refreshes from bf16 sources, one power iteration, with kmin =
+    // 32 / 192 / 256 / 384 / 512 / 768 and by the rule (us): 125M set, r = 128 1195 / 1133 / 1136 / 1116 / 1140 / 1169, 1118; two blocks of it 545 / 542 / 549 /
+    // 565 / 590 / 639, 542; 24 x (2048 x 2048), r = 64 523 / 522 / 514 / 525 / 532 / 545, 524; 24 x (1024 x 1024, 1024 x 4096, 4096 x 1024), r = 256
+    // 3729 / 3743 / 3724 / 3723 / 3677 / 3732, 3741; four blocks of 7B, r = 128 2918 / 2926 / 2924 / 2945 / 2914 / 2902, 2895; two of 2560 .. 8000,
+    // r = 400 3893 / 3896 / 3887 / 3896 / 3857 / 3765, 3766; 8 x (512 x 512), r = 128 384 / 393 / 403 / 425 / 443 / 443, 394.
+    // Ranks below four, on the fp32 matrix cores, keep the short ones: 24 x (1024 x 1024), r = 2 401 / 415 / 425 / 444 / 462 / 501, 11 x (256 x 608), r = 3
+    // 271 / 294 / 295 / 299 / 304 / 306.  So do the initial projection, for its bits, and R = Q_new^T Q_old: with long ones the rotated
+    // moments of 957 x 2201, r = 39 are off by 2.7e-7, not 2.0e-7.
     int kmin = 32;
-    if (ksplit > 1 && lower_only && !initial) {
+    if (ksplit > 1 && lower_only && !initial && op.mode < GEMM_ANY) {
       for (int f : {192, 256, 384, 512, 768}) {
         int64_t wgs = 0;
         for (const GemmDesc& g : made) {
