@@ -1674,7 +1674,7 @@ __global__ __launch_bounds__(256) void k_src_times_block(DevCtx d, const ProjTil
         for (int vq = 0; vq < 4; ++vq) {
           f32x4 x;
           x.x = scale * acc[a][b][4 * vq]; x.y = scale * acc[a][b][4 * vq + 1]; x.z = scale * acc[a][b][4 * vq + 2]; x.w = scale * acc[a][b][4 * vq + 3];
-          if (pad) x = f32x4{0.f, 0.f, 0.f, 0.f};
+          if (pad || 32 * rb + 8 * vq + 4 * (lane >> 5) >= m.r) x = f32x4{0.f, 0.f, 0.f, 0.f};      // (absent ranks: 0 * inf where G holds one)
           *reinterpret_cast<GAS f32x4*>(out + ((nb * rgroups + 4 * rb + vq) * 32 + (lane & 31)) * 8 + 4 * (lane >> 5)) = x;
         }
       }

@@ -174,3 +174,22 @@ def test_right_projection_local_variant(name):
             pair.local_step([g.draw(t) for g in gens], lr=1e-3, grad_scale=0.9, bf16=True)
             t += 1
         pair.compare_local(TOL)
+
+
+@pytest.mark.parametrize("shape", [(64, 96, 20, 1), (160, 64, 4, 1), (40, 160, 100, 1)])
+def test_padding_of_the_payload_stays_zero_beside_an_infinity(shape):
+    """The packed payload is padded with zeros (lordo_sync_payload), also where a gradient holds an infinity: the streaming kernel stores the
+    product of absent rank planes as zero, not as 0 * inf."""
+    import torch
+    from paper_2602_04396_amd import lordo
+    p, q, r, side = shape
+    G = torch.randn(p, q, generator=torch.Generator().manual_seed(p)).bfloat16().cuda()
+    G[p - 1, 3] = float("inf")
+    W = [torch.zeros(p, q, device="cuda")]
+    opt = lordo.Lordo([shape], lordo.hparams(seed=2), W, torch)
+    opt.init_projection()
+    opt.local_step(W, [G], 0.1)
+    payload, moments = opt.sync_payload()
+    u = payload[:moments // 2].view((p + 31) // 32, -1, 32, 8).permute(0, 2, 1, 3).reshape((p + 31) // 32 * 32, -1)      # state column, rank
+    assert not bool(torch.isfinite(u[p - 1, :r]).all()) and bool(torch.isfinite(u[:p - 1]).all())
+    assert bool((u[:, r:] == 0).all()) and bool((u[p:] == 0).all())
