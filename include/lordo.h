@@ -167,6 +167,8 @@ int lordo_init(lordo_ctx** out, const lordo_shape* shapes, int32_t n, const lord
  * LORDO_STATIC_WORKSPACE_BYTES per GPU, held from the first such call on a GPU until the process ends.  No device
  * memory is allocated or freed, here or in any later call on the context.
  *   shapes, n, hp, W, stream   as for lordo_init.
+ * (A set that fits into the array only without finer slices of its gradient products runs without them, here and after
+ * lordo_init alike; lordo_workspace_bytes is the size of that plan.)
  * Returns LORDO_ENOMEM (with the sizes on stderr) when lordo_workspace_bytes(shapes, n, hp) exceeds
  * LORDO_STATIC_WORKSPACE_BYTES, and LORDO_ESTATE while another context created by this call is alive on the current
  * GPU: every such context of a GPU uses the same array, so only one may exist at a time (lordo_destroy releases it);

@@ -1049,8 +1049,10 @@ void build_plan_as(const lordo_shape* shapes, int n, const lordo_hparams& hp, bo
   P.bytes = A.cur;
 }
 
-// Finer slices of the down-projection take a few per cent more workspace: a set that fits the static workspace (lordo_init_static) only
-// without them goes without.
+// Finer slices of the down-projection take more workspace, the array g once more for each doubling (15 % for 511 x 4096, r = 256, 28 % for
+// 12 x (1123 x 104), r = 5 .. 17).  A set that fits the static workspace (lordo_init_static) only without them goes without, in every context:
+// lordo_workspace_bytes, by which callers choose between the two, and the bits of a step must not depend on whose memory it is.  So
+// k x (384 x 384), r = 64 with k = 29 and 30 go without the finer slices of their neighbours (about 5 of 34 us a step).
 void build_plan(const lordo_shape* shapes, int n, const lordo_hparams& hp, Plan& P) {
   build_plan_as(shapes, n, hp, true, P);
   if (!P.fine_split || P.bytes <= (size_t)LORDO_STATIC_WORKSPACE_BYTES) return;

@@ -86,6 +86,18 @@ def test_short_matrices_are_split_only_while_half_of_the_chip_is_idle(lib, shape
     assert round(extra / g_slice) + 1 == slices
 
 
+def test_sets_around_the_size_of_the_static_workspace(lib):
+    """k x (384 x 384, r = 64): two slices of g fit up to k = 28, one still does at 29 and 30, and past that nothing does."""
+    g_slice = 4 * 384 * 64
+    sizes = {k: lordo.workspace_bytes([(384, 384, 64)] * k, lordo.hparams()) for k in range(26, 33)}
+    step = sizes[28] - sizes[27]
+    for k in range(26, 33):
+        assert (sizes[k] <= lordo.STATIC_WORKSPACE_BYTES) == (k <= 30), k
+        two = sizes[28] + (k - 28) * step
+        want = two - k * g_slice if k in (29, 30) else two
+        assert abs(sizes[k] - want) <= 16384, k              # (tables)
+
+
 def test_right_projection_validation(lib):
     hp = lordo.hparams()
     tall = lordo.workspace_bytes([(3072, 768, 128, 1)], hp)       # projection on the short side: Q 768 x 128, moments 128 x 3072

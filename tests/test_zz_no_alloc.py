@@ -73,3 +73,26 @@ def test_static_workspace_context_matches_the_arena_context_twice_in_a_row():
     # after the refusal and the releases above the array is free again
     opt = lordo.Lordo(second, lordo.hparams(), [torch.zeros(128, 96, device="cuda")], torch, static_workspace=True)
     opt.close()
+
+
+def test_a_set_that_fits_only_with_one_slice_is_the_same_in_both_contexts():
+    """30 x (384 x 384, r = 64) exceeds the array with two slices of g and fits with one: both contexts go without the finer slices."""
+    import torch
+    from paper_2602_04396_amd import lordo
+    shapes = [(384, 384, 64)] * 30
+    assert lordo.workspace_bytes(shapes, lordo.hparams()) <= lordo.STATIC_WORKSPACE_BYTES
+    states = []
+    for static in (False, True):
+        W = [torch.zeros(384, 384, device="cuda") for _ in shapes]
+        gen = torch.Generator(device="cuda").manual_seed(3)
+        G = [torch.randn(384, 384, generator=gen, device="cuda").bfloat16() for _ in shapes]
+        opt = lordo.Lordo(shapes, lordo.hparams(seed=5), W, torch, static_workspace=static)
+        opt.init_projection()
+        opt.local_step(W, G, 0.1)
+        opt.refresh_subspace(G)
+        opt.local_step(W, G, 0.1)
+        opt.poll_status()
+        states.append(W + [opt.get_state(i, lordo.STATE_U).clone() for i in (0, 29)])
+        opt.close()
+    for a, b in zip(*states):
+        assert torch.equal(a, b)
