@@ -4,7 +4,8 @@
 // workgroup to (problem, tile, K slice).  Operands are addressed by element strides, so any transpose
 // and the bf16 gradient type are handled by the loader; accumulation is fp32.  Arithmetic: operands are read in vectors of four
 // elements, aligned or not (GemmMode), split into bf16 terms (three per fp32 operand: as exact as fp32) and multiplied on
-// v_mfma_f32_32x32x16_bf16; operands too short for a vector, and unaligned ones of the initial projection, run on the fp32 matrix cores
+// v_mfma_f32_32x32x16_bf16; operands too short for a vector, and unaligned ones of the initial projection and of steps with fp32
+// gradients, whose bits stay, run on the fp32 matrix cores
 // (v_mfma_f32_32x32x2_f32).  k_gemm_planes is the kernel for products of a tall fp32 matrix with a block that many row tiles
 // share: the same arithmetic with the block split once (k_pack_planes).
 #include "common.h"
@@ -447,21 +448,27 @@ __device__ __forceinline__ void gemm_loop_bf(f32x16 (&acc)[WB][WB], const GemmDe
   }
 }
 
-// The loop for the unit-stride directions of a problem's operands (uniform)
-template <int WB, bool UA, bool A_BF16>
+// The loop for the unit-stride directions of a problem's operands (uniform).  A bf16 A is a source or a gradient, whose B (start block, Y, Z, Q)
+// is never contiguous in k.  WITH_DIAG: problems may carry g.diag.
+template <int WB, bool UA, bool A_BF16, bool WITH_DIAG>
 __device__ __forceinline__ void gemm_loops_bf(f32x16 (&acc)[WB][WB], const GemmDesc& g, const char* baseA, const char* baseB, uint16_t* lds,
                                               int m0, int n0, int kbeg, int K, int tid, int lane, int wm, int wn, bool same_ab,
                                              char* arena, int slice) {
   const bool akf = g.sAk == 1 && g.sAm != 1, bkf = g.sBk == 1 && g.sBn != 1;
-  if constexpr (!A_BF16) {
+  if constexpr (!A_BF16 && WITH_DIAG) {
     if (same_ab && g.diag >= 0 && !akf && !bkf) {
       gemm_loop_bf<WB, UA, false, false, false, true>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, true, arena, slice);
       return;
     }
   }
-  if (akf && bkf) gemm_loop_bf<WB, UA, A_BF16, true, true>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab, arena, slice);
-  else if (akf) gemm_loop_bf<WB, UA, A_BF16, true, false>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab, arena, slice);
-  else if (bkf) gemm_loop_bf<WB, UA, A_BF16, false, true>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab, arena, slice);
+  if constexpr (!A_BF16) {
+    if (bkf) {
+      if (akf) gemm_loop_bf<WB, UA, A_BF16, true, true>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab, arena, slice);
+      else gemm_loop_bf<WB, UA, A_BF16, false, true>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab, arena, slice);
+      return;
+    }
+  }
+  if (akf) gemm_loop_bf<WB, UA, A_BF16, true, false>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab, arena, slice);
   else gemm_loop_bf<WB, UA, A_BF16, false, false>(acc, g, baseA, baseB, lds, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab, arena, slice);
 }
 
@@ -512,7 +519,7 @@ __global__ __launch_bounds__(256, MODE == GEMM_RAGGED ? 2 : MODE == GEMM_ANY && 
   const bool same_ab = g.A.off == g.B.off && g.A.ext == g.B.ext && g.sAm == g.sBn && g.sAk == g.sBk && m0 == n0 && M == N;
   uint16_t* planes = reinterpret_cast<uint16_t*>(lds_raw);
   if constexpr (MODE != GEMM_ANY) {
-    if (kbeg < K) gemm_loops_bf<WB, MODE == GEMM_RAGGED, A_BF16>(acc, g, baseA, baseB, planes, m0, n0, kbeg, K, tid, lane, wm, wn, !A_BF16 && same_ab, d.arena, t.ks);
+    if (kbeg < K) gemm_loops_bf<WB, MODE == GEMM_RAGGED, A_BF16, true>(acc, g, baseA, baseB, planes, m0, n0, kbeg, K, tid, lane, wm, wn, !A_BF16 && same_ab, d.arena, t.ks);
   } else {
     const int a_bf16 = g.a_bf16 == 2 ? src_is_bf16 : g.a_bf16;
     float (*As)[PITCH] = reinterpret_cast<float (*)[PITCH]>(lds_raw);
@@ -523,8 +530,8 @@ __global__ __launch_bounds__(256, MODE == GEMM_RAGGED ? 2 : MODE == GEMM_ANY && 
     const bool vec = opA.vec_ok && opB.vec_ok;
     if (kbeg >= K) {
     } else if (vec) {
-      if (a_bf16) gemm_loops_bf<WB, false, true>(acc, g, baseA, baseB, planes, m0, n0, kbeg, K, tid, lane, wm, wn, false, d.arena, t.ks);
-      else gemm_loops_bf<WB, false, false>(acc, g, baseA, baseB, planes, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab, d.arena, t.ks);
+      if (a_bf16) gemm_loops_bf<WB, false, true, false>(acc, g, baseA, baseB, planes, m0, n0, kbeg, K, tid, lane, wm, wn, false, d.arena, t.ks);
+      else gemm_loops_bf<WB, false, false, false>(acc, g, baseA, baseB, planes, m0, n0, kbeg, K, tid, lane, wm, wn, same_ab, d.arena, t.ks);
     } else if (opA.four_ok && opB.four_ok) {
       if (a_bf16) gemm_loop<WB, true, true>(acc, opA, opB, As, Bs, kbeg, K, tid, lane, wm, wn);
       else gemm_loop<WB, false, true>(acc, opA, opB, As, Bs, kbeg, K, tid, lane, wm, wn);
