@@ -7,13 +7,14 @@
 //   k_fold_grad       E <- E + s G, the projection source of the local variant (Alg. 2)
 //   k_pack_q / k_pack_block / k_split_planes   fp32 -> bf16 hi/lo operand planes in matrix-core order
 //   k_glow_to_z, k_lr_to_plain, k_plain_to_lr, k_lr_exchange, k_tr_exchange   between the operand layout of the low-rank state and plain buffers
-//   k_factor_diag   CholeskyQR: Cholesky of a diagonal block with its shift, and its inverse (k_gram_shift, k_potf2, k_diag_inverses: of the initial projection)
+//   k_factor_diag   CholeskyQR: Cholesky of a diagonal block with its shift, and its inverse (k_potf2, k_diag_inverses: of the initial projection)
+//   k_gram_shift      the shift in a pass of its own: initial projection, ranks below four, the Ritz matrix
 //   k_jacobi_svd      singular vectors of the Cholesky factor of the r x r Ritz matrix (Rayleigh-Ritz step: basis ordered as in Sec. 2's SVD projection)
 //   k_frob2_chunks / k_frob2_sum / k_stable_rank   squared Frobenius norm of the refresh source and its stable rank (Sec. 5.1)
 //   k_rot_pre / k_rot_post, k_mssv   elementwise parts of the moment rotation (Alg. 1 rotation lines); similarity diagnostic (Sec. 5.1)
 //   k_step_set        step count and bias corrections 1 - beta^t (Sec. 2) in device memory
 //   k_gauss_block     Gaussian start blocks of the range finder and of the random initial projection (Alg. 1 Require)
-//   k_gram_diag_part / k_gram_diag_sum   exact diagonal of the Gram matrices of the initial projection
+//   k_gram_diag_part / k_gram_diag_sum   exact diagonal of the Gram matrices of the initial projection and of ranks below four
 //   k_bf16_to_f32 / k_f32_to_bf16   a bf16-stored residual through the fp32 state interface
 #include "common.h"
 

@@ -349,7 +349,7 @@ struct OperandBF {
 // are rounded away step after step.  The diagonal came out 2e-6 to 3e-6 too small at p >= 4096 and the columns of the orthonormalised
 // block that much too long: 7e-5 in || Q^T Q - I ||_F at r = 512.  The diagonal carries the column norms, so it alone is summed exactly.
 // (As passes of their own, over X and over partial sums, with a launch for the diagonal shift, 24 us behind every Gram matrix of the
-// 125M set: its refresh 1897 -> 1796 us; four blocks of 7B 17.99 -> 17.39 ms, 1B synchronisation 26.19 -> 26.04 ms, two blocks of 125M
+// 125M set: its refresh 1897 -> 1796 us; four blocks of 7B 17.99 -> 17.39 ms, two blocks of 125M
 // 641 -> 615 us.)
 template <int WB, bool UA, bool A_BF16, bool A_KF, bool B_KF, bool DIAG = false>
 __device__ __forceinline__ void gemm_loop_bf(f32x16 (&acc)[WB][WB], const GemmDesc& g, const char* baseA, const char* baseB,

@@ -767,7 +767,7 @@ void build_plan_as(const lordo_shape* shapes, int n, const lordo_hparams& hp, bo
   P.down_generic = hp.grad_dtype == LORDO_F32;
   // Rank blocks of 32 per down-projection tile, 256 columns wide: as many as the largest rank of the set has, up to 8.  At ranks up to 64
   // the four-block tile left half of its waves or more without work and fetched absent blocks of Q; measured as whole steps on
-  // four / two blocks: 1 x (8192 x 28672), r = 64 486 -> 473 us, 125M set, r = 64 201 -> 197; on four / one: 1 x (8192 x 8192), r = 16
+  // four / two blocks: 1 x (8192 x 28672), r = 64 486 -> 473 us (two runs differ by up to 5 % there), 125M set, r = 64 201 -> 197; on four / one: 1 x (8192 x 8192), r = 16
   // 140 -> 135, 125M set, r = 32 178 -> 174, 1 x (640 x 640), r = 12 21.3 -> 19.4.  (More K slices, for the third workgroup per compute unit
   // that the smaller tiles leave room for, gave 1 to 4 % less.)
   P.down_pipe = P.down_generic ? 0 : rp_max >= 256 ? 8 : rp_max > 64 ? 4 : rp_max > 32 ? 2 : 1;

@@ -128,7 +128,7 @@ __device__ __forceinline__ GCol g_columns(int col, int wave_col0, int q, uint32_
 // at the end of the resource, so every lane of that access is out of range and reads zero.
 // A bf16 matrix with rows at odd elements is read with 4-byte global accesses at 2-byte alignment, rows clamped to the last one,
 // lanes outside the matrix to its first column: fix_gstage() turns what they fetch into zeros.  (Sixteen 2-byte accesses per
-// stage before: the set above, 166 -> 113 us; 103 for 1024 and 2732 columns in aligned pairs.)
+// stage before: 12 x (4 x 1023 x 1023, 1023 x 2731, 2731 x 1023), r = 100, 166 -> 113 us; 103 for 1024 and 2732 columns in aligned pairs.)
 template <bool GF32, int AUX, bool VEC>     // AUX: cache policy of the loads (STREAM where G is read once, 0 where rank tiles re-read it)
 __device__ __forceinline__ void load_gstage(GStage<GF32>& st, rsrc_t rs, const GAS char* base, uint32_t row_bytes, int krow, int rows, const GCol& gc) {
   if constexpr (!VEC && !GF32) {
@@ -1256,8 +1256,9 @@ __global__ __launch_bounds__(64 * NW) void k_proj_up_dma(DevCtx d, const ProjTil
 // second register set while the matrix cores work on the current one; the registers then leave no room for W during
 // the contraction: its row blocks are requested when the contraction ends, the first one ahead of the last products, three in
 // flight (two when the epilogue also reads a gradient tile: the full-rank QHM update, the residual of the error feedback).
-// Nothing is requested past the last k-step (repeating it for an even count of loads cost 19 % of the operand traffic at r = 256):
-// with the same in the down-projection 1B set, r = 256 4.00 -> 3.96 ms a step, its full-rank QHM form in bf16 7.11 -> 7.00 ms.
+// Nothing is requested past the last k-step (repeating it for an even count of loads cost 19 % of the operand traffic at r = 256).
+// Both, and the same in the transposing down-projection with its first moments ahead of the last stage, together: 1B set, r = 256
+// 4.00 -> 3.96 ms a step, its full-rank QHM form in bf16 7.11 -> 7.00 ms (1 to 1.5 %, the scatter of two runs being up to 1 %).
 // ---------------------------------------------------------------------------------------
 template <bool WBF, bool WITH_G, RowMode ROWS = ROWS_WHOLE>     // WITH_G: gradient-term epilogue (bf16 G): the full-rank QHM update, or the residual E as target; ROWS: other than whole quads in the plain update only
 __global__ __launch_bounds__(256) void k_proj_up_wide(DevCtx d, const ProjTile* __restrict__ tiles,
