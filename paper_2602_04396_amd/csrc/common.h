@@ -89,6 +89,8 @@ struct GemmDesc {
 //   RAGGED   rows, ends or pointers at any element, at least four elements long: split into bf16 terms too;
 //   ANY      neither, or ragged ones whose sums keep the bits of the fp32 matrix cores (initial projection, steps with fp32 gradients):
 //            such problems run there, the aligned ones of the launch as in ALIGNED
+// The mode of a launch is that of its most general problem: beside a rank or side below four, ragged problems run on the fp32 matrix cores
+// too (both are as exact as fp32, their bits differ).
 enum GemmMode : int32_t { GEMM_ALIGNED = 0, GEMM_RAGGED = 1, GEMM_ANY = 2 };
 
 struct GemmTile { int32_t desc; int16_t tm, tn; int16_t ks, pad; };

@@ -14,6 +14,15 @@ from oracle import lordo_oracle as orc
 from paper_2602_04396_amd import synth
 
 
+def down_slices(shapes):
+    """Slices of the down-projection's contraction that the library's plan holds for bf16 gradients (1: the moment update rides in the
+    epilogue of that launch), by the space for g: fp32 gradients are never split."""
+    from paper_2602_04396_amd import lordo
+    g_slice = 4 * sum((sh[1] + 31) // 32 * 32 * ((sh[2] + 31) // 32 * 32) for sh in shapes)
+    extra = lordo.workspace_bytes(shapes, lordo.hparams()) - lordo.workspace_bytes(shapes, lordo.hparams(grad_dtype=lordo.F32))
+    return round(extra / g_slice) + 1
+
+
 def rel_l2(a, b):
     a = np.asarray(a, dtype=np.float64)
     b = np.asarray(b, dtype=np.float64)

@@ -7,6 +7,7 @@ import re
 import pytest
 
 from paper_2602_04396_amd import lordo, synth
+from tests.harness import down_slices
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -80,10 +81,8 @@ def test_workspace_bytes_scales_and_validates(lib):
                                             ([(480, 512, 256)] * 64, 2), ([(480, 512, 256)] * 65, 1), ([(256, 256 * 96, 32)], 2), ([(256, 256 * 96 + 1, 32)], 1),
                                             ([(224, 256, 64)], 1), ([(640, 640, 12)], 4)])
 def test_short_matrices_are_split_only_while_half_of_the_chip_is_idle(lib, shapes, slices):
-    """Slices of the down-projection's contraction, by the space for g: fp32 gradients are never split."""
-    g_slice = 4 * sum((q + 31) // 32 * 32 * ((r + 31) // 32 * 32) for p, q, r in shapes)
-    extra = lordo.workspace_bytes(shapes, lordo.hparams()) - lordo.workspace_bytes(shapes, lordo.hparams(grad_dtype=lordo.F32))
-    assert round(extra / g_slice) + 1 == slices
+    """Past that, two slices are more than one round of the compute units."""
+    assert down_slices(shapes) == slices
 
 
 def test_sets_around_the_size_of_the_static_workspace(lib):

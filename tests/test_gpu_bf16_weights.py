@@ -8,7 +8,7 @@ import pytest
 
 from oracle import lordo_oracle as orc
 from paper_2602_04396_amd import synth
-from tests.harness import rel_l2
+from tests.harness import down_slices, rel_l2
 
 pytestmark = pytest.mark.gpu
 
@@ -134,7 +134,8 @@ def test_bf16_residual_local_steps(variant):
     from paper_2602_04396_amd import lordo
     shapes = [(520, 392, 256), (300, 260, 288)] if variant.endswith("wide") else [(256, 384, 64), (130, 260, 128), (520, 392, 96)]
     if variant.endswith("one_slice"):       # no split-K: moment update, column sums and planes of g in the down-projection's epilogue
-        shapes = [(256, 520, 230), (250, 388, 225)]
+        shapes = [(256, 520, 230), (250, 388, 225)] + [(240, 8, 225)] * 124       # (tiles for more than half of the compute units)
+        assert down_slices(shapes) == 1
     w_bf16 = "bf16_weights" in variant
     qhm = "full" if variant.startswith("global") else ("low" if variant.startswith("lowqhm") else "none")
     kw = dict(error_feedback=True, omega=0.8 if qhm != "none" else 1.0)

@@ -8,7 +8,7 @@ import pytest
 
 from oracle import lordo_oracle as orc
 from paper_2602_04396_amd import synth
-from tests.harness import Pair, projector_distance, rel_l2
+from tests.harness import Pair, down_slices, projector_distance, rel_l2
 
 pytestmark = pytest.mark.gpu
 
@@ -173,7 +173,8 @@ def test_local_steps_ranks_from_256_up_gradient_term(torch, variant, shape_set):
     shapes = [(520, 392, 256), (300, 260, 257), (257, 132, 256), (1100, 644, 320), (256, 128, 256)]
     if shape_set == "one_slice":      # no matrix taller than 256 rows: no split-K, so the moment update -- with the column sums of the
         shapes = [(256, 520, 256), (256, 388, 250), (250, 132, 250)]      # full-rank QHM scale and the operand planes of g -- runs
-                                                                          # in the epilogue of the down-projection
+        shapes += [(240, 8, 230)] * 124                                   # in the epilogue of the down-projection (with tiles for more
+        assert down_slices(shapes) == 1                                   # than half of the compute units: fewer are split in two)
     bf16 = variant != "global_fp32_grads"
     qhm = "none" if variant == "ef" else "full"
     ef = variant != "full_qhm"

@@ -315,3 +315,40 @@ def test_an_infinity_stays_in_its_column(p, q, r, side, grad):
     if r % 32:
         pad = v.permute(1, 3, 0, 2).reshape(-1, v.shape[0] * 32)[r:]          # ranks past the last one
         assert bool(torch.isfinite(pad[:, 1:cols - 1]).all())
+
+
+@pytest.mark.parametrize("source", ["bf16", "fp32"])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_refresh_of_a_set_of_every_kind(source, offset):
+    """Aligned, ragged and too-short operands in one launch (ranks and sides below four beside large matrices): every basis is orthonormal,
+    spans its source's columns, and the moments are those of before, rotated."""
+    import torch
+    from paper_2602_04396_amd import lordo
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(offset)
+    shapes = [(256, 320, 64), (389, 515, 131), (130, 97, 2), (300, 3, 3), (96, 1, 1), (68, 256, 3), (257, 129, 66)]
+    W = [torch.randn(p, q, generator=gen, device="cuda") for p, q, r in shapes]
+    opt = lordo.Lordo(shapes, lordo.hparams(power_iters=1, seed=3), W, torch)
+    opt.init_projection()
+    for _ in range(2):
+        opt.local_step(W, [torch.randn(p, q, generator=gen, device="cuda").bfloat16() for p, q, r in shapes], 0.5)
+    q_old = [opt.get_state(i, lordo.STATE_Q).double() for i in range(len(shapes))]
+    u_old = [opt.get_state(i, lordo.STATE_U).double() for i in range(len(shapes))]
+    dt = torch.bfloat16 if source == "bf16" else torch.float32
+    src, om, U = [], [], []
+    for p, q, r in shapes:
+        a, _ = torch.linalg.qr(torch.randn(p, r, generator=gen, device="cuda", dtype=torch.float64))
+        b, _ = torch.linalg.qr(torch.randn(q, r, generator=gen, device="cuda", dtype=torch.float64))
+        src.append(_window(torch, p, q, dt, offset, gen)[1])
+        src[-1].copy_(100.0 * a @ b.T)
+        om.append(_window(torch, q, r, torch.float32, offset, gen)[1])
+        U.append(a)
+    opt.refresh_subspace(src, om)
+    opt.poll_status()
+    for i, (p, q, r) in enumerate(shapes):
+        Q = opt.get_state(i, lordo.STATE_Q).double()
+        assert float((Q.T @ Q - torch.eye(r, device="cuda", dtype=torch.float64)).norm()) <= 1e-4, i      # CholeskyQR2 in fp32
+        if source == "fp32":      # (a bf16 source has rounding noise: its trailing directions depend on the start block)
+            assert float((U[i] - Q @ (Q.T @ U[i])).norm()) / r ** 0.5 <= 5e-5, i
+        want = (Q.T @ q_old[i]) @ u_old[i]
+        assert float((opt.get_state(i, lordo.STATE_U).double() - want).norm() / want.norm()) <= 1e-5, i   # fp32 sums over p and r
