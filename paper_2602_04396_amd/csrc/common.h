@@ -127,7 +127,9 @@ constexpr int NB_INIT = 64;       // ... of the initial projection
 // ---------------------------------------------------------------------------------------
 // proj.hip
 struct DownFuse;     // below: state arrays and coefficients of the Adam update fused into the down-projection
-hipError_t launch_proj_down(const DevCtx& d, const ProjTile* tiles, int ntiles, int rank_blocks, bool g_vec, bool g_tr, bool g_once, float* glow,
+// How the rows of a bf16 G can be read, over all left-projected matrices: in aligned pairs of columns; at any element; so, and one of a single column
+enum GRows : int32_t { G_PAIRS = 0, G_ELEMENTS = 1, G_ONE_COLUMN = 2 };
+hipError_t launch_proj_down(const DevCtx& d, const ProjTile* tiles, int ntiles, int rank_blocks, GRows g_rows, bool g_tr, bool g_once, float* glow,
                             int64_t split_stride, float grad_scale, int ef, const DownFuse* fuse, hipStream_t s);
 // Epilogue of the up-projection: target <- target + coef_acc * (Q B) + coef_g * G * c_j
 struct UpArgs {

@@ -1383,9 +1383,9 @@ int lordo_local_step(lordo_ctx* c, void* const* W, const void* const* G, double 
   a.acc = c->hp.uplink_buffer ? c->at<float>(P.acc) : nullptr;
   a.lr = (float)lr;
   const bool g_f32 = c->hp.grad_dtype == LORDO_F32;
-  bool g_vec = true;            // 4-byte accesses to a bf16 G need an even q and 4-byte aligned pointers
-  for (int i = 0; i < c->n; ++i)      // (right-projected matrices do not pass through the projection kernels)
-    if (!P.mat[i].tr && ((P.mat[i].q & 1) != 0 || (reinterpret_cast<uintptr_t>(G[i]) & 3) != 0)) { g_vec = false; break; }
+  GRows g_rows = G_PAIRS;       // 4-byte accesses to a bf16 G need an even q and 4-byte aligned pointers
+  for (int i = 0; i < c->n && g_rows != G_ONE_COLUMN; ++i)      // (right-projected matrices do not pass through the projection kernels)
+    if (!P.mat[i].tr && ((P.mat[i].q & 1) != 0 || (reinterpret_cast<uintptr_t>(G[i]) & 3) != 0)) g_rows = P.mat[i].q == 1 ? G_ONE_COLUMN : G_ELEMENTS;
   const bool w_bf16 = c->hp.param_dtype == LORDO_BF16, e_bf16 = c->hp.err_dtype == LORDO_BF16;
   const uintptr_t w_mask = w_bf16 ? 7 : 15;     // four weights with one access: 16 bytes of fp32, 8 bytes of bf16
   const RowMode w_rows = c->row_mode(W, w_mask, 0), w_rows_tr = c->row_mode(W, w_mask, 1);
@@ -1412,7 +1412,7 @@ int lordo_local_step(lordo_ctx* c, void* const* W, const void* const* G, double 
   for (int i = 0; i < c->n && g_tr; ++i)
     if (!P.mat[i].tr && ((P.mat[i].q & 7) != 0 || (reinterpret_cast<uintptr_t>(G[i]) & 15) != 0)) g_tr = false;
   if (!P.down_h.empty())
-    HIPCHK(launch_proj_down(c->dev, c->at<ProjTile>(P.down_tiles), (int)P.down_h.size(), P.down_pipe, g_vec, g_tr, P.g_once, c->at<float>(P.glow),
+    HIPCHK(launch_proj_down(c->dev, c->at<ProjTile>(P.down_tiles), (int)P.down_h.size(), P.down_pipe, g_rows, g_tr, P.g_once, c->at<float>(P.glow),
                             P.lr_total, (float)proj_scale, ef ? (e_bf16 ? 3 : 1) : 0, &fuse, s));
   if (P.any_tr || generic) {    // g^T = (s G) Q: into the blocked array at once by the streaming kernel, by way of the plain block zw[0] by the grouped GEMM
     bool stream = P.tr_stream_shapes && !ef && !generic;
@@ -1546,7 +1546,7 @@ static int run_ops(lordo_ctx* c, const std::vector<Op>& ops, int32_t src_dtype, 
           for (int i = 0; i < 4; ++i) { a.grp_nsplit[i] = P.grp_nsplit[i]; a.grp_start[i] = P.grp_start[i]; }
           a.split_stride = P.lr_total;
           HIPCHK(launch_pack_y(c->dev, op.iarg, s));
-          HIPCHK(launch_proj_down(c->dev, c->at<ProjTile>(P.down_tiles), (int)P.down_h.size(), P.down_pipe, true, proj_tr, P.g_once,
+          HIPCHK(launch_proj_down(c->dev, c->at<ProjTile>(P.down_tiles), (int)P.down_h.size(), P.down_pipe, G_PAIRS, proj_tr, P.g_once,
                                   c->at<float>(P.glow), P.lr_total, 1.f, src_dtype == LORDO_F32 ? 2 : 0, nullptr, s));
           HIPCHK(launch_glow_to_z(c->dev, c->at<float>(P.glow), 0, a, s));
           break;

@@ -129,9 +129,9 @@ __device__ __forceinline__ GCol g_columns(int col, int wave_col0, int q, uint32_
 // A bf16 matrix with rows at odd elements is read with 4-byte global accesses at 2-byte alignment, rows clamped to the last one,
 // lanes outside the matrix to its first column: fix_gstage() turns what they fetch into zeros.  (Sixteen 2-byte accesses per
 // stage before: 12 x (4 x 1023 x 1023, 1023 x 2731, 2731 x 1023), r = 100, 166 -> 113 us; 103 for 1024 and 2732 columns in aligned pairs.)
-template <bool GF32, int AUX, bool VEC>     // AUX: cache policy of the loads (STREAM where G is read once, 0 where rank tiles re-read it)
+template <bool GF32, int AUX, bool VEC, bool ONE = false>     // AUX: cache policy of the loads (STREAM where G is read once, 0 where rank tiles re-read it); ONE: see k_proj_down_pipe
 __device__ __forceinline__ void load_gstage(GStage<GF32>& st, rsrc_t rs, const GAS char* base, uint32_t row_bytes, int krow, int rows, const GCol& gc) {
-  if constexpr (!VEC && !GF32) {
+  if constexpr (ONE) {
     if (gc.single) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) st.x[i] = *(const GAS uint16_t*)(base + (uint32_t)(krow + i < rows ? krow + i : rows - 1) * row_bytes);
@@ -305,7 +305,8 @@ __device__ __forceinline__ void store_colpart(const FusedAdam& f, const MatDev& 
 // column blocks) and rank block w % 4.  MB = 8 (ranks from 256 up): rank blocks w % 4 and w % 4 + 4; this halves the number of
 // passes over G and the LDS reads per MFMA (each G fragment feeds two rank blocks); its 96 KiB of
 // LDS admit one workgroup per compute unit.  MB = 2, 1 (ranks up to 64, 32): the waves go along the columns, two blocks each, or one.
-// VEC: q is even and every pair of columns 4-byte aligned; else pairs are read at the alignment of an element.
+// VEC: q is even and every pair of columns 4-byte aligned; else pairs are read at the alignment of an element.  ONE: not VEC, and some matrix of
+// the set has one column (the uniform test of it in every stage costs the others 0.3 % of a step).
 // GONCE: one rank tile per column block, G is read once (streaming loads).
 // A tile marked `fuse` holds the whole contraction (no split-K): its epilogue applies Adam to its
 // elements of the low-rank state instead of leaving that to a separate pass over g.
@@ -316,7 +317,7 @@ __device__ __forceinline__ void store_colpart(const FusedAdam& f, const MatDev& 
 // EFM = 2: the projected matrix is an fp32 matrix alone (no G): the fp32 source of a subspace refresh, taken
 // from the caller's source table -- the product Z = Src^T Y of the power iteration has the shape of g = Q^T G.
 // EFM = 3: error feedback with the residual stored in bf16 (widened exactly; the sum is formed in fp32 as before).
-template <int MB, bool VEC, bool GONCE, int EFM>
+template <int MB, bool VEC, bool GONCE, int EFM, bool ONE = false>
 __global__ __launch_bounds__(512) void k_proj_down_pipe(DevCtx d, const ProjTile* __restrict__ tiles, float* __restrict__ glow,
                                                         int64_t split_stride, float grad_scale, FusedAdam fa) {
   constexpr bool EF = EFM != 0;                                // an fp32 operand is staged: hi and lo planes, three passes
@@ -360,6 +361,7 @@ __global__ __launch_bounds__(512) void k_proj_down_pipe(DevCtx d, const ProjTile
   const rsrc_t rs = make_rsrc(Gbase, (uint32_t)klim * row_bytes);
   const int col = t.n0 + 128 * half + 2 * lane;
   const GCol gc = g_columns<VEC>(col, t.n0 + 128 * half, m.q, 2u);
+  static_assert(!ONE || !VEC, "pairs have two columns");
   static_assert(VEC || EFM == 0, "fp32 operands are read in aligned pairs");
   const int wslot = ((4 * half + (lane >> 4)) * 4 + kgrp) * 32 + 2 * (lane & 15);
   // residual E: fp32 p x q in the arena, same rows and columns (8-byte accesses)
@@ -471,9 +473,9 @@ __global__ __launch_bounds__(512) void k_proj_down_pipe(DevCtx d, const ProjTile
     }
   };
   issue_a(t.k0, 0);
-  if constexpr (!SRC32) load_gstage<false, GAUX, VEC>(st0, rs, gbytes, row_bytes, krow0, klim, gc);                  // stage 0
+  if constexpr (!SRC32) load_gstage<false, GAUX, VEC, ONE>(st0, rs, gbytes, row_bytes, krow0, klim, gc);                  // stage 0
   if constexpr (EF) load_gstage<E32, GAUX, true>(se0, re, nullptr, erow_bytes, krow0, klim, ge);
-  if constexpr (!SRC32) load_gstage<false, GAUX, VEC>(st1, rs, gbytes, row_bytes, krow0 + BK, klim, gc);             // stage 1
+  if constexpr (!SRC32) load_gstage<false, GAUX, VEC, ONE>(st1, rs, gbytes, row_bytes, krow0 + BK, klim, gc);             // stage 1
   if constexpr (EF) load_gstage<E32, GAUX, true>(se1, re, nullptr, erow_bytes, krow0 + BK, klim, ge);
   stage_out(st0, se0, krow0, 0);
   wait_one_stage();
@@ -483,7 +485,7 @@ __global__ __launch_bounds__(512) void k_proj_down_pipe(DevCtx d, const ProjTile
   {                                                                                               \
     const int kr = t.k0 + (S) * BK;                                                               \
     if ((S) + 1 < nstages) issue_a(kr + BK, ((S) + 1) & 1);                                       \
-    if constexpr (!SRC32) load_gstage<false, GAUX, VEC>(LOAD, rs, gbytes, row_bytes, krow0 + ((S) + 2) * BK, klim, gc); \
+    if constexpr (!SRC32) load_gstage<false, GAUX, VEC, ONE>(LOAD, rs, gbytes, row_bytes, krow0 + ((S) + 2) * BK, klim, gc); \
     if constexpr (EF) load_gstage<E32, GAUX, true>(LOADE, re, nullptr, erow_bytes, krow0 + ((S) + 2) * BK, klim, ge); \
     ISSUE_FENCE();                                                                                \
     compute((S) & 1);                                                                             \
@@ -779,26 +781,29 @@ static hipError_t launch_down_tr(dim3 grid, const DevCtx& d, const ProjTile* til
 
 // One instantiation of the pipelined kernel; its dynamic LDS (per stage 16 KiB of G, or two planes of that, and 4 KiB per rank block)
 // is raised above the default limit at first use.
-template <int MB, bool VEC, bool GONCE, int EF>
+template <int MB, bool VEC, bool GONCE, int EF, bool ONE = false>
 static hipError_t launch_pipe(dim3 grid, const DevCtx& d, const ProjTile* tiles, float* glow, int64_t split_stride,
                               float grad_scale, const FusedAdam& fa, hipStream_t s) {
   constexpr int LDS_BYTES = 2 * (16 + 4 * MB + (EF != 0 ? 16 : 0)) * 1024;
   static LdsRaised raised;
   if constexpr (LDS_BYTES > 65536)
-    if (hipError_t e = raise_lds(reinterpret_cast<const void*>(k_proj_down_pipe<MB, VEC, GONCE, EF>), LDS_BYTES, raised); e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_proj_down_pipe<MB, VEC, GONCE, EF>), grid, dim3(512), LDS_BYTES, s, d, tiles, glow, split_stride, grad_scale, fa);
+    if (hipError_t e = raise_lds(reinterpret_cast<const void*>(k_proj_down_pipe<MB, VEC, GONCE, EF, ONE>), LDS_BYTES, raised); e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_proj_down_pipe<MB, VEC, GONCE, EF, ONE>), grid, dim3(512), LDS_BYTES, s, d, tiles, glow, split_stride, grad_scale, fa);
   return hipGetLastError();
 }
 template <int MB, int EF>
-static hipError_t launch_pipe_vo(bool g_vec, bool g_once, dim3 grid, const DevCtx& d, const ProjTile* tiles, float* glow,
+static hipError_t launch_pipe_vo(GRows g_rows, bool g_once, dim3 grid, const DevCtx& d, const ProjTile* tiles, float* glow,
                                  int64_t split_stride, float grad_scale, const FusedAdam& fa, hipStream_t s) {
   if (MB < 4 && !g_once) return hipErrorInvalidValue;            // (one rank tile by construction)
-  if (EF != 0 && !g_vec) return hipErrorInvalidValue;            // (error feedback and fp32 sources come with aligned pairs only)
+  if (EF != 0 && g_rows != G_PAIRS) return hipErrorInvalidValue;            // (error feedback and fp32 sources come with aligned pairs only)
   if constexpr (EF == 0) {
-    if (!g_vec) {
+    if (g_rows != G_PAIRS) {
+      const bool one = g_rows == G_ONE_COLUMN;
       if constexpr (MB >= 4)
-        if (!g_once) return launch_pipe<MB, false, false, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s);
-      return launch_pipe<MB, false, true, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+        if (!g_once) return one ? launch_pipe<MB, false, false, EF, true>(grid, d, tiles, glow, split_stride, grad_scale, fa, s)
+                                : launch_pipe<MB, false, false, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+      return one ? launch_pipe<MB, false, true, EF, true>(grid, d, tiles, glow, split_stride, grad_scale, fa, s)
+                 : launch_pipe<MB, false, true, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s);
     }
   }
   if constexpr (MB >= 4)
@@ -806,15 +811,15 @@ static hipError_t launch_pipe_vo(bool g_vec, bool g_once, dim3 grid, const DevCt
   return launch_pipe<MB, true, true, EF>(grid, d, tiles, glow, split_stride, grad_scale, fa, s);
 }
 template <int MB>
-static hipError_t launch_pipe_ef(int ef, bool g_vec, bool g_once, dim3 grid, const DevCtx& d, const ProjTile* tiles, float* glow,
+static hipError_t launch_pipe_ef(int ef, GRows g_rows, bool g_once, dim3 grid, const DevCtx& d, const ProjTile* tiles, float* glow,
                                  int64_t split_stride, float grad_scale, const FusedAdam& fa, hipStream_t s) {
-  if (ef == 3) return launch_pipe_vo<MB, 3>(g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
-  if (ef == 2) return launch_pipe_vo<MB, 2>(g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
-  if (ef == 1) return launch_pipe_vo<MB, 1>(g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
-  return launch_pipe_vo<MB, 0>(g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+  if (ef == 3) return launch_pipe_vo<MB, 3>(g_rows, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+  if (ef == 2) return launch_pipe_vo<MB, 2>(g_rows, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+  if (ef == 1) return launch_pipe_vo<MB, 1>(g_rows, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+  return launch_pipe_vo<MB, 0>(g_rows, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
 }
 
-hipError_t launch_proj_down(const DevCtx& d, const ProjTile* tiles, int ntiles, int rank_blocks, bool g_vec, bool g_tr, bool g_once, float* glow,
+hipError_t launch_proj_down(const DevCtx& d, const ProjTile* tiles, int ntiles, int rank_blocks, GRows g_rows, bool g_tr, bool g_once, float* glow,
                             int64_t split_stride, float grad_scale, int ef, const DownFuse* fuse, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
   dim3 grid(ntiles);
@@ -833,10 +838,10 @@ hipError_t launch_proj_down(const DevCtx& d, const ProjTile* tiles, int ntiles, 
     return g_once ? launch_down_tr<2, true>(grid, d, tiles, glow, split_stride, grad_scale, fa, s)
                   : launch_down_tr<2, false>(grid, d, tiles, glow, split_stride, grad_scale, fa, s);
   switch (rank_blocks) {
-    case 8: return launch_pipe_ef<8>(ef, g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
-    case 4: return launch_pipe_ef<4>(ef, g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
-    case 2: return launch_pipe_ef<2>(ef, g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
-    case 1: return launch_pipe_ef<1>(ef, g_vec, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+    case 8: return launch_pipe_ef<8>(ef, g_rows, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+    case 4: return launch_pipe_ef<4>(ef, g_rows, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+    case 2: return launch_pipe_ef<2>(ef, g_rows, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
+    case 1: return launch_pipe_ef<1>(ef, g_rows, g_once, grid, d, tiles, glow, split_stride, grad_scale, fa, s);
     default: return hipErrorInvalidValue;                        // (fp32 gradients run in the grouped GEMM)
   }
 }
