@@ -202,16 +202,17 @@ struct ProgramBuilder {
     // 565 / 590 / 639, 542; 24 x (2048 x 2048), r = 64 523 / 522 / 514 / 525 / 532 / 545, 524; 24 x (1024 x 1024, 1024 x 4096, 4096 x 1024), r = 256
     // 3729 / 3743 / 3724 / 3723 / 3677 / 3732, 3741; four blocks of 7B, r = 128 2918 / 2926 / 2924 / 2945 / 2914 / 2902, 2895; two of 2560 .. 8000,
     // r = 400 3893 / 3896 / 3887 / 3896 / 3857 / 3765, 3766; 8 x (512 x 512), r = 128 384 / 393 / 403 / 425 / 443 / 443, 394.
-    // Ranks below four, on the fp32 matrix cores, keep the short ones: 24 x (1024 x 1024), r = 2 401 / 415 / 425 / 444 / 462 / 501, 11 x (256 x 608), r = 3
+    // Problems of ranks below four, on the fp32 matrix cores, keep the short ones: 24 x (1024 x 1024), r = 2 401 / 415 / 425 / 444 / 462 / 501, 11 x (256 x 608), r = 3
     // 271 / 294 / 295 / 299 / 304 / 306.  So do the initial projection, for its bits, and R = Q_new^T Q_old: with long ones the rotated
     // moments of 957 x 2201, r = 39 are off by 2.7e-7, not 2.0e-7.
     int kmin = 32;
-    if (ksplit > 1 && lower_only && !initial && op.mode < GEMM_ANY) {
+    auto min_len = [&](const GemmDesc& g) { return g.N < 4 ? 32 : kmin; };
+    if (ksplit > 1 && lower_only && !initial) {
       for (int f : {192, 256, 384, 512, 768}) {
         int64_t wgs = 0;
         for (const GemmDesc& g : made) {
           const int tm = (g.M + op.tile - 1) / op.tile;
-          const int klen = std::max(f, ((g.K + ksplit - 1) / ksplit + 31) / 32 * 32);
+          const int klen = std::max(g.N < 4 ? 32 : f, ((g.K + ksplit - 1) / ksplit + 31) / 32 * 32);
           wgs += (int64_t)(tm * (tm + 1) / 2) * ((g.K + klen - 1) / klen);
         }
         if (f == 192 || wgs >= 205) kmin = f;
@@ -220,7 +221,7 @@ struct ProgramBuilder {
     op.desc_first = (int)P.desc_h.size();
     for (GemmDesc g : made) {
       int ks = ksplit;
-      int klen = std::max(kmin, ((g.K + ks - 1) / ks + 31) / 32 * 32);
+      int klen = std::max(min_len(g), ((g.K + ks - 1) / ks + 31) / 32 * 32);
       ks = (g.K + klen - 1) / klen;
       if (ks > 1) {
         g.ksplit = ks;
